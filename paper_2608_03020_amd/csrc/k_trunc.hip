@@ -1245,20 +1245,70 @@ __global__ __launch_bounds__(kT) void k_trunc_apply(int64_t d, int64_t kp, int64
   }
 }
 
-// out[i][j] = sum_c L(i, c) R(c, j) with general strides (fp64 accumulation).
-__global__ void k_lowrank_product(int64_t rows, int64_t cols, int64_t kk, const float* __restrict__ L,
-                                  int64_t l_bstride, int64_t l_si, int64_t l_sc, const float* __restrict__ R,
-                                  int64_t r_bstride, int64_t r_group, int64_t r_sc, int64_t r_sj,
-                                  float* __restrict__ out, int64_t out_bstride) {
+// out[i][j] = sum_c L(i, c) R(c, j) with general strides, products and sums in fp64 (on the
+// fp64 matrix cores), rounded to float once.  A workgroup takes 64 rows x 256 columns, a wave
+// 64 x 64 of them as 4 x 4 blocks of 16 x 16.  Block q of a wave's columns holds the columns
+// j0 + 4 (lane % 16) + q, so that a lane's four results of a row are consecutive columns and
+// leave in one 16-byte store (V4: cols % 4 == 0 and 16-byte aligned output rows); the factors
+// are small and come from cache.  Bound by the write of the output: 28 x 1536 x 1536 with
+// kk = 16 (264 MB) took 1812 us with one thread per entry, each reading 2 kk scalars through
+// the cache; now the whole truncation with that product takes 305 us (1948 before).
+constexpr int kLPR = 64, kLPC = 256;  // rows and columns per workgroup
+template <bool V4>
+__global__ __launch_bounds__(256) void k_lowrank_product(int64_t rows, int64_t cols, int64_t kk,
+                                                         const float* __restrict__ L, int64_t l_bstride, int64_t l_si,
+                                                         int64_t l_sc, const float* __restrict__ R, int64_t r_bstride,
+                                                         int64_t r_group, int64_t r_sc, int64_t r_sj,
+                                                         float* __restrict__ out, int64_t out_bstride) {
   const int64_t mi = blockIdx.z;
-  const int64_t i = blockIdx.y;
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= cols) return;
-  const float* Lm = L + mi * l_bstride + i * l_si;
-  const float* Rm = R + (mi / r_group) * r_bstride + j * r_sj;
-  double s = 0.0;
-  for (int64_t c = 0; c < kk; ++c) s += (double)Lm[c * l_sc] * (double)Rm[c * r_sc];
-  out[mi * out_bstride + i * cols + j] = (float)s;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  const int64_t i0 = (int64_t)blockIdx.y * kLPR, j0 = (int64_t)blockIdx.x * kLPC + 64 * wid;
+  if (j0 >= cols) return;
+  const float* Lm = L + mi * l_bstride;
+  const float* Rm = R + (mi / r_group) * r_bstride;
+  int64_t li_off[4], rj_off[4];  // entries past the edge read the last row or column: never stored
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int64_t i = i0 + 16 * q + li, j = j0 + 4 * li + q;
+    li_off[q] = (i < rows ? i : rows - 1) * l_si;
+    rj_off[q] = (j < cols ? j : cols - 1) * r_sj;
+  }
+  f64x4_t acc[4][4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[a][q] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  for (int64_t c0 = 0; c0 < kk; c0 += 4) {
+    const int64_t c = c0 + lk;
+    const bool ok = c < kk;
+    double fa[4], fb[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float x = Lm[li_off[q] + (ok ? c : 0) * l_sc], y = Rm[rj_off[q] + (ok ? c : 0) * r_sc];
+      fa[q] = ok ? (double)x : 0.0;
+      fb[q] = ok ? (double)y : 0.0;
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[a][q] = mfma_f64(fa[a], fb[q], acc[a][q]);
+  }
+  float* O = out + mi * out_bstride;
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t i = i0 + 16 * a + lk + 4 * r, j = j0 + 4 * li;
+      if (i >= rows || j >= cols) continue;
+      float* dst = O + i * cols + j;
+      if (V4) {
+        *(float4*)dst = make_float4((float)acc[a][0][r], (float)acc[a][1][r], (float)acc[a][2][r], (float)acc[a][3][r]);
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (j + q < cols) dst[q] = (float)acc[a][q][r];
+      }
+    }
 }
 
 __global__ void k_fill_zero(int32_t* p, int64_t cnt) {
@@ -1388,14 +1438,25 @@ __global__ __launch_bounds__(kTCC) void k_trunc_complete(int64_t d, int64_t r_a,
 
 }  // namespace
 
+static hipError_t lowrank_product(hipStream_t s, int64_t nmat, int64_t rows, int64_t cols, int64_t kk, const float* L,
+                                  int64_t l_bstride, int64_t l_si, int64_t l_sc, const float* R, int64_t r_bstride,
+                                  int64_t r_group, int64_t r_sc, int64_t r_sj, float* out, int64_t out_bstride) {
+  const dim3 grid((unsigned)((cols + kLPC - 1) / kLPC), (unsigned)((rows + kLPR - 1) / kLPR), (unsigned)nmat);
+  if (cols % 4 == 0 && out_bstride % 4 == 0 && ((uintptr_t)out & 15) == 0)
+    k_lowrank_product<true><<<grid, 256, 0, s>>>(rows, cols, kk, L, l_bstride, l_si, l_sc, R, r_bstride, r_group, r_sc,
+                                                 r_sj, out, out_bstride);
+  else
+    k_lowrank_product<false><<<grid, 256, 0, s>>>(rows, cols, kk, L, l_bstride, l_si, l_sc, R, r_bstride, r_group, r_sc,
+                                                  r_sj, out, out_bstride);
+  return hipGetLastError();
+}
+
 hipError_t launch_lowrank_product(hipStream_t s, int64_t nmat, int64_t rows, int64_t cols, int64_t kk,
                                   const float* L, int64_t l_bstride, int64_t l_ld, const float* R,
                                   int64_t r_bstride, int64_t r_group, int64_t r_ld, float* out,
                                   int64_t out_bstride) {
-  dim3 grid((unsigned)((cols + 255) / 256), (unsigned)rows, (unsigned)nmat);
-  k_lowrank_product<<<grid, 256, 0, s>>>(rows, cols, kk, L, l_bstride, l_ld, 1, R, r_bstride, r_group, r_ld, 1, out,
-                                         out_bstride);
-  return hipGetLastError();
+  return lowrank_product(s, nmat, rows, cols, kk, L, l_bstride, l_ld, 1, R, r_bstride, r_group, r_ld, 1, out,
+                         out_bstride);
 }
 
 int trunc_splits(int64_t d) {
@@ -1444,10 +1505,8 @@ hipError_t launch_lowrank_truncate(const TruncArgs& a) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !a.w_dense_out) return e;
   // W_r[i][j] = sum_a a_out[a][i] b_out[j][a]
-  dim3 grid((unsigned)((a.d + 255) / 256), (unsigned)a.d, (unsigned)a.nm);
-  k_lowrank_product<<<grid, 256, 0, a.stream>>>(a.d, a.d, a.r_a, a.a_out, a.a_bstride, 1, a.d, a.b_out, a.b_bstride,
-                                                1, 1, a.r_a, a.w_dense_out, a.w_bstride);
-  return hipGetLastError();
+  return lowrank_product(a.stream, a.nm, a.d, a.d, a.r_a, a.a_out, a.a_bstride, 1, a.d, a.b_out, a.b_bstride, 1, 1, a.r_a,
+                         a.w_dense_out, a.w_bstride);
 }
 
 // ------------------------------------------------------------------ projected form (Eqs. 6-9)
