@@ -138,10 +138,11 @@ struct XStage {
 
 // ------------------------------------------------------------------ S += X^T X (bf16)
 
+// Register-staged form, for weighted blocks of X past 2 GB only (see launch_accumulate_stats):
 // BM x BM tiles of S on or above the diagonal; WGM x WGN waves, each owning a
-// (BM/WGM) x (BM/WGN) block of 32 x 32 MFMA tiles.
-// WT: statistic weights from `wpad` (zero past n, readable up to the next multiple of kBK).
-template <int BM, int WGM, int WGN, bool WT>
+// (BM/WGM) x (BM/WGN) block of 32 x 32 MFMA tiles.  Statistic weights from `wpad` (zero
+// past n, readable up to the next multiple of kBK).
+template <int BM, int WGM, int WGN>
 __global__ __launch_bounds__(64 * WGM * WGN) void k_gram_bf16(int64_t n, int64_t d,
                                                              const uint16_t* __restrict__ Xall, int64_t ldx,
                                                              int64_t x_bstride, float* __restrict__ Sall,
@@ -199,21 +200,18 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gram_bf16(int64_t n, int64_t
         bf16x8_t fb[NBN], fl[NBN];
 #pragma unroll
         for (int q = 0; q < NBN; ++q) fb[q] = frag32_tr(tB, LDT, wj * WN + 32 * q, ks, lane);
-        if (WT) {
-          const float* wl = wpad + (int64_t)kt * kBK + ks + 8 * (lane >> 5);
-          const float4 w0 = *(const float4*)wl, w1 = *(const float4*)(wl + 4);
-          const float wv[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+        const float* wl = wpad + (int64_t)kt * kBK + ks + 8 * (lane >> 5);
+        const float4 w0 = *(const float4*)wl, w1 = *(const float4*)(wl + 4);
+        const float wv[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
 #pragma unroll
-          for (int q = 0; q < NBN; ++q) weight_split(fb[q], wv, fb[q], fl[q]);
-        }
+        for (int q = 0; q < NBN; ++q) weight_split(fb[q], wv, fb[q], fl[q]);
 #pragma unroll
         for (int m = 0; m < NBM; ++m) {
           const bf16x8_t fa = frag32_tr(tA, LDT, wi * WM + 32 * m, ks, lane);
 #pragma unroll
           for (int q = 0; q < NBN; ++q) acc[m][q] = mfma32(fa, fb[q], acc[m][q]);
-          if (WT)
 #pragma unroll
-            for (int q = 0; q < NBN; ++q) acc[m][q] = mfma32(fa, fl[q], acc[m][q]);
+          for (int q = 0; q < NBN; ++q) acc[m][q] = mfma32(fa, fl[q], acc[m][q]);
         }
       }
     }
@@ -264,7 +262,18 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gram_bf16(int64_t n, int64_t
 // XOR swizzle of the 16-byte chunks instead of padding: chunk c of row r sits at
 // c ^ 4(r & 3), so the four rows x four chunks that half a wave reads in one LDS
 // cycle land on 16 distinct chunk positions (all 64 banks).  Rows past n and columns past d are read from a zeroed 16-byte area of the
-// workspace.  Requires d % 8 == 0.
+// workspace.  With d % 8 != 0 the last chunk of a row holds up to seven columns past d: the
+// row's padding (ldx is a multiple of 8; X is 16-byte aligned, so a chunk that starts inside
+// the row lies within one aligned 16-byte granule also in the last row).  Their values, NaN
+// included, reach only entries of S and Kraw in rows or columns past d, which are not written.
+//
+// Every width takes this kernel: the register-staged 128 x 128 tiles that widths below 1024
+// once took, and the 256 x 256 ones of d % 8 != 0, with the cross statistic in a launch of
+// its own, lost at every size measured (us per call, before -> now, d x blocks x tokens):
+// 128 x 24 x 2048 120 -> 57, 256 x 200 x 2048 340 -> 92, 512 x 4 x 2048 164 -> 58,
+// 896 x 1 x 512 43 -> 31, 896 x 24 x 8192 1218 -> 223, 1100 x 12 x 2999 519 -> 90; weighted
+// 248 x 32 x 3705 874 -> 216 (the staging waited for every stage's loads; here three are in
+// flight).
 constexpr int kDLStages = 4;
 constexpr int kDLRowBytes = 512;
 
@@ -804,10 +813,6 @@ __global__ void k_stats_finalize(int64_t n, int64_t d, int64_t k, int ntile, con
 
 }  // namespace
 
-__global__ void k_zero_bytes(uint32_t* p, int cnt) {
-  if ((int)threadIdx.x < cnt) p[threadIdx.x] = 0u;
-}
-
 // Yhl[b][t] = [bf16(y) | bf16(y - bf16(y)) | 0] (w2p columns, w2p % 8 == 0) from the float
 // targets, and the 256 zero bytes at the head of the workspace.  One thread per 8 columns of a
 // row (one 16-byte store); IT is the index type (32-bit while n w2p / 8 fits).
@@ -956,37 +961,30 @@ hipError_t launch_accumulate_stats(const StatsArgs& a) {
     const int64_t npad = weights_pad(a.n);
     k_pad_weights<<<(unsigned)((npad + 255) / 256), 256, 0, a.stream>>>(a.n, npad, a.a_w, wpad);
   }
-  // Tile size: 256 x 256 when the matrix is wide enough to fill the GPU with such tiles.
-  const bool big = a.d >= 1024;
-  const int BM = big ? 256 : 128;
+  constexpr int BM = 256;
   const int T = (int)((a.d + BM - 1) / BM);
-  dim3 grid((unsigned)(T * (T + 1) / 2), (unsigned)a.nb);
   const int64_t w2 = 2 * a.k, w2p = (w2 + 7) / 8 * 8;
   // buffer-path copies when a block's X (and its split targets) fit 31-bit byte offsets
   const bool buf = (a.n * a.ldx * 2) < ((int64_t)1 << 31);
   // direct-to-LDS kernel; with weights only on the buffer path (the global-address
   // variant runs out of scalar registers with the weights, so blocks of X over 2 GB
   // take the register-staged kernel when weighted)
-  const bool dl = big && (a.d % 8) == 0 && (buf || !wt);
-  const bool fused = dl && w2p <= 64;
+  const bool dl = buf || !wt;
+  const bool fused = w2p <= 64;
   // wider split targets: cross tiles in the same launch (one per row panel of each block)
-  const bool ctiles = dl && !fused;
+  const bool ctiles = !fused;
   if (dl) {
-    if (fused || ctiles) {
-      const bool v8 = a.k % 8 == 0 && a.y_bstride % 8 == 0 && ((uintptr_t)a.y & 31) == 0;
-      const int64_t groups = v8 ? a.n * (a.k / 8) : a.n * (w2p / 8);
-      dim3 gy((unsigned)((groups + 255) / 256), (unsigned)a.nb);
-      if (v8 && groups < ((int64_t)1 << 31))
-        k_split_y8<uint32_t><<<gy, 256, 0, a.stream>>>(a.n, a.k, a.y, a.y_bstride, Yhl, (uint32_t*)a.ws);
-      else if (v8)
-        k_split_y8<int64_t><<<gy, 256, 0, a.stream>>>(a.n, a.k, a.y, a.y_bstride, Yhl, (uint32_t*)a.ws);
-      else if (groups < ((int64_t)1 << 31))
-        k_split_y<uint32_t><<<gy, 256, 0, a.stream>>>(a.n, a.k, w2p, a.y, a.y_bstride, Yhl, (uint32_t*)a.ws);
-      else
-        k_split_y<int64_t><<<gy, 256, 0, a.stream>>>(a.n, a.k, w2p, a.y, a.y_bstride, Yhl, (uint32_t*)a.ws);
-    } else {
-      k_zero_bytes<<<1, 64, 0, a.stream>>>((uint32_t*)a.ws, 64);
-    }
+    const bool v8 = a.k % 8 == 0 && a.y_bstride % 8 == 0 && ((uintptr_t)a.y & 31) == 0;
+    const int64_t groups = v8 ? a.n * (a.k / 8) : a.n * (w2p / 8);
+    dim3 gy((unsigned)((groups + 255) / 256), (unsigned)a.nb);
+    if (v8 && groups < ((int64_t)1 << 31))
+      k_split_y8<uint32_t><<<gy, 256, 0, a.stream>>>(a.n, a.k, a.y, a.y_bstride, Yhl, (uint32_t*)a.ws);
+    else if (v8)
+      k_split_y8<int64_t><<<gy, 256, 0, a.stream>>>(a.n, a.k, a.y, a.y_bstride, Yhl, (uint32_t*)a.ws);
+    else if (groups < ((int64_t)1 << 31))
+      k_split_y<uint32_t><<<gy, 256, 0, a.stream>>>(a.n, a.k, w2p, a.y, a.y_bstride, Yhl, (uint32_t*)a.ws);
+    else
+      k_split_y<int64_t><<<gy, 256, 0, a.stream>>>(a.n, a.k, w2p, a.y, a.y_bstride, Yhl, (uint32_t*)a.ws);
     // one-dimensional grid (the XCD-aware order spans the blocks), in chunks of blocks
     // small enough that the grid stays far below the launch limits
     const int64_t ntile = (int64_t)T * (T + 1) / 2;
@@ -994,34 +992,22 @@ hipError_t launch_accumulate_stats(const StatsArgs& a) {
     const int64_t chunk = std::max<int64_t>(1, ((int64_t)1 << 22) / (ntile + ncross));
     for (int64_t b0 = 0; b0 < a.nb; b0 += chunk) {
       const int64_t nbc = std::min<int64_t>(chunk, a.nb - b0);
-      const bool use_buf = buf;
-      const uint16_t* yf = (fused || ctiles) ? Yhl : nullptr;
-      if (use_buf && wt)
-        launch_gram_dl<true, true>(a, ntile, b0, nbc, zero16, diag_part, yf, w2, w2p, Kraw, wpad, ncross);
-      else if (use_buf)
-        launch_gram_dl<true, false>(a, ntile, b0, nbc, zero16, diag_part, yf, w2, w2p, Kraw, nullptr, ncross);
+      if (buf && wt)
+        launch_gram_dl<true, true>(a, ntile, b0, nbc, zero16, diag_part, Yhl, w2, w2p, Kraw, wpad, ncross);
+      else if (buf)
+        launch_gram_dl<true, false>(a, ntile, b0, nbc, zero16, diag_part, Yhl, w2, w2p, Kraw, nullptr, ncross);
       else
-        launch_gram_dl<false, false>(a, ntile, b0, nbc, zero16, diag_part, yf, w2, w2p, Kraw, nullptr, ncross);
+        launch_gram_dl<false, false>(a, ntile, b0, nbc, zero16, diag_part, Yhl, w2, w2p, Kraw, nullptr, ncross);
     }
-  } else if (big) {
-    if (wt)
-      k_gram_bf16<256, 2, 4, true><<<grid, 512, 0, a.stream>>>(a.n, a.d, X, a.ldx, a.x_bstride, (float*)a.S,
-                                                               a.s_bstride, diag_part, wpad, a.overwrite ? 0 : 1);
-    else
-      k_gram_bf16<256, 2, 4, false><<<grid, 512, 0, a.stream>>>(a.n, a.d, X, a.ldx, a.x_bstride, (float*)a.S,
-                                                                a.s_bstride, diag_part, nullptr, a.overwrite ? 0 : 1);
   } else {
-    if (wt)
-      k_gram_bf16<128, 2, 2, true><<<grid, 256, 0, a.stream>>>(a.n, a.d, X, a.ldx, a.x_bstride, (float*)a.S,
-                                                               a.s_bstride, diag_part, wpad, a.overwrite ? 0 : 1);
-    else
-      k_gram_bf16<128, 2, 2, false><<<grid, 256, 0, a.stream>>>(a.n, a.d, X, a.ldx, a.x_bstride, (float*)a.S,
-                                                                a.s_bstride, diag_part, nullptr, a.overwrite ? 0 : 1);
+    const dim3 grid((unsigned)(T * (T + 1) / 2), (unsigned)a.nb);
+    k_gram_bf16<BM, 2, 4><<<grid, 512, 0, a.stream>>>(a.n, a.d, X, a.ldx, a.x_bstride, (float*)a.S, a.s_bstride,
+                                                      diag_part, wpad, a.overwrite ? 0 : 1);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   dim3 gc((unsigned)((a.d + 255) / 256), (unsigned)a.nb);
-  if (!fused && !ctiles) {  // the cross statistic in a launch of its own
+  if (!dl) {  // the cross statistic in a launch of its own
     if (w2 <= 32)
       k_cross_bf16<32><<<gc, kThreads, 0, a.stream>>>(a.n, a.d, a.k, X, a.ldx, a.x_bstride, a.y, a.y_bstride, Kraw,
                                                        a.a_w);

@@ -1,0 +1,69 @@
+"""Kernels at the sizes where their tiles, remainders and dispatch rules meet, through the
+C ABI against float64."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from gpu_helpers import log, rel
+
+pytestmark = pytest.mark.gpu
+
+
+# widths and ranks on both sides of the 64 x 256 workgroup tile, the 16-byte stores and the
+# matrix cores' four-deep steps; sums of at most 64 exact products in float64, rounded once to
+# float: 2^-24 of each entry
+@pytest.mark.parametrize("d,kp,r", [(5, 3, 2), (63, 8, 5), (64, 16, 16), (257, 24, 7), (260, 64, 64), (1031, 12, 12)])
+def test_dense_truncation_product_edges(d, kp, r):
+    import torch
+    from paper_2608_03020_amd import loca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    nm = 3
+    m = torch.randn((nm, d, kp), generator=g, device="cuda") * 0.8 ** torch.arange(kp, device="cuda")
+    b = torch.randn((nm, kp, d), generator=g, device="cuda")
+    kw = dict(dtype=torch.float32, device="cuda")
+    a_o, b_o = torch.full((nm, r, d), float("nan"), **kw), torch.full((nm, d, r), float("nan"), **kw)
+    sig, W = torch.empty((nm, kp), **kw), torch.full((nm, d, d), float("nan"), **kw)
+    info = torch.zeros(nm, dtype=torch.int32, device="cuda")
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_LOWRANK_TRUNCATE, nm, 0, d, kp, r_a=r))
+    log("dense truncation product", d, kp, r)
+    loca.loca_lowrank_truncate(m, b, r, a_o, b_o, sig, info, ws, w_dense_out=W)
+    ref = np.einsum("bri,bjr->bij", a_o.double().cpu().numpy(), b_o.double().cpu().numpy())
+    assert np.max(np.abs(W.double().cpu().numpy() - ref) - 2.0 ** -23 * np.abs(ref)) <= 1e-30
+
+
+# every width takes the direct-to-LDS kernel: below one tile, its edges, ragged last chunks with
+# NaN in the rows' padding (read, never used), fused (2k <= 64) and cross-tile targets, weights.
+# S: float32 sums of exact products, error at most n 2^-24 sum|x_i x_j| and far below 1e-5 of S
+# in practice; K: two bf16 parts of Y (2^-16) on top
+@pytest.mark.parametrize("d,n,k,w", [(1, 40, 4, 0), (7, 33, 3, 1), (64, 500, 8, 0), (255, 100, 40, 0), (256, 257, 32, 1),
+                                     (260, 64, 64, 1), (517, 300, 16, 0), (896, 1, 12, 0), (1030, 95, 128, 0)])
+def test_statistics_at_every_width(d, n, k, w):
+    import torch
+    from paper_2608_03020_amd import loca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(100 * d + n)
+    nb, ld = 3, -(-d // 8) * 8
+    buf = torch.full((nb, n, ld), float("nan"), dtype=torch.bfloat16, device="cuda")
+    buf[:, :, :d] = torch.randn((nb, n, d), generator=g, device="cuda")
+    x = buf[:, :, :d]
+    y = torch.randn((nb, n, k), generator=g, device="cuda")
+    a = torch.rand(n, generator=g, device="cuda") if w else None
+    mb = loca.new_mb(nb)
+    mb[:, 0] = 7.0
+    S = torch.full((nb, d, d), float("nan"), dtype=torch.float32, device="cuda")
+    K = torch.full((nb, d, k), float("nan"), dtype=torch.float32, device="cuda")
+    info = torch.zeros(nb, dtype=torch.int32, device="cuda")
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_ACCUMULATE_STATS, nb, n, d, k))
+    log("statistics at width", d, n, k, w)
+    loca.loca_accumulate_stats(x, y, 0.5, mb, S, K, ws, a_w=a, dev_info=info, overwrite=True)
+    X, Y = x.double().cpu().numpy(), y.double().cpu().numpy()
+    aw = a.double().cpu().numpy()[None, :, None] if w else 1.0
+    iu = np.triu_indices(d)
+    assert info.eq(0).all()
+    for b in range(nb):
+        ref = X[b].T @ ((aw * X)[b] if w else X[b])
+        assert rel(S[b].cpu().numpy()[iu], ref[iu]) < 1e-5
+        eta = 0.5 * np.sqrt(((aw * X * X)[b] if w else X[b] ** 2).sum() / 7.0)
+        assert rel(K[b].cpu().numpy(), -eta * X[b].T @ ((aw * Y)[b] if w else Y[b])) < 1e-5
