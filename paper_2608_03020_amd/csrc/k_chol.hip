@@ -22,6 +22,7 @@
 #include "loca_bf16.h"
 
 #include <functional>
+#include <utility>
 #include <vector>
 
 namespace loca {
@@ -291,316 +292,188 @@ LOCA_DEV void tile_mma(const T* sP, const T* sQ, int ld, int K, int wi, int wj, 
 
 // ------------------------------------------------------------------ diagonal block: factor and invert
 
-// One workgroup per matrix factors the P x P diagonal block, A11 = U11^T U11, and
-// inverts U11.  The block lives in registers: thread (ty, tx) of a 16 x 16 grid owns
-// the entries (ty + 16 i, tx + 16 k).  Step j of the factorization needs only row j,
-// which its owners publish to a double-buffered LDS row, so each step costs one
-// barrier.  The inverse X = U11^{-1} is built bottom-up the same way (row i of X is
-// final once rows > i have been applied).  X replaces the diagonal block of F (strict
-// lower part zeroed): the row panel and the back substitution apply it as a product.
+// One workgroup per matrix factors the P x P diagonal block, A11 = U11^T U11, and inverts
+// U11; X = U11^{-1} replaces the diagonal block of F (strict lower part zeroed), for the row
+// panel and the back substitution apply it as a product.  The kernel is a serial chain on
+// every panel's critical path, so it is built to make that chain short.
+//
+// The block is worked on as NB x NB blocks of 16 in LDS.  Eliminating the rows of [A | I]
+// gives L^{-1} [A | I] = [U | E], E = U11^{-T}, so the inverse grows along with the factor: U
+// takes the blocks right of the diagonal, E those left of it (E_rs starts as zero), and step q is
+//   factor:    one wave factors A_qq and forms E_qq (chol_inv16),
+//   row panel: block (q, s) <- E_qq block (q, s) for every s != q, one wave each; for s < q
+//              that is the final E_qs, whose transpose goes straight to F,
+//   update:    block (r, s) -= U_qr^T block (q, s) for r > q and s <= q or s >= r; wave 0 only
+//              takes (q + 1, q + 1) and goes on to factor it while the others finish,
+// the products on the 16x16x4 matrix cores (fp32, or fp64 for fp64 statistics).  Entries past
+// the matrix (a ragged last block) are an identity extension.
+//
+// 128 x 128 in fp32, one matrix: 49.8 us blocked by 32 (a column of a block waited for an LDS
+// round trip, and the inverse was assembled at the end); 64 x 64 in fp64: 68.6 us with one
+// column of the whole block per step (two barriers and an fp64 square root and division each).
+template <typename T> struct Dg;
+template <> struct Dg<float> {
+  typedef f32x4_t acc_t;
+  static constexpr int LD_PAD = 20;  // row length = P + 20: operand reads of either kind fall on distinct banks
+  static LOCA_DEV acc_t mma(float a, float b, acc_t c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+  static LOCA_DEV int row(int lane, int r) { return 4 * (lane >> 4) + r; }
+  static LOCA_DEV float rsq(float v) { return __builtin_amdgcn_rsqf(v); }  // about 1 ulp
+  template <int CTRL> static LOCA_DEV float dpp(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+  }
+};
+template <> struct Dg<double> {
+  typedef f64x4_t acc_t;
+  static constexpr int LD_PAD = 18;
+  static LOCA_DEV acc_t mma(double a, double b, acc_t c) { return mfma_f64(a, b, c); }
+  static LOCA_DEV int row(int lane, int r) { return (lane >> 4) + 4 * r; }
+  // the hardware estimate and two Newton steps: y <- y + y (1 - v y^2) / 2
+  static LOCA_DEV double rsq(double v) {
+    double y = __builtin_amdgcn_rsq(v);
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+      const double h = 0.5 * y, g = v * y;
+      y = fma(fma(-g, h, 0.5), y, y);
+    }
+    return y;
+  }
+  template <int CTRL> static LOCA_DEV double dpp(double v) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+  }
+};
+// lane I of each row of 16 lanes to all 16 (DPP row_newbcast)
+template <int I, typename T>
+LOCA_DEV T bcast16(T v) { return Dg<T>::template dpp<0x150 + I>(v); }
+
+// Step J of the elimination of a 16 x 16 block: lane c (mod 16) holds column c of A in a[] and
+// of E in e[].  The multipliers U[J][I] come from lane I by a DPP broadcast, so a step has no
+// memory access; row J + 1 is updated first, since the next pivot waits for it.
+template <int J, typename T, int... K>
+LOCA_DEV void elim_rows(T (&a)[16], T (&e)[16], T uc, T nuc, T ec, std::integer_sequence<int, K...>) {
+  auto row = [&](auto ic) {
+    constexpr int I = J + 1 + decltype(ic)::value;
+    const T m = bcast16<I>(nuc);
+    a[I] = fma(m, uc, a[I]);
+    e[I] = fma(m, ec, e[I]);
+  };
+  (row(std::integral_constant<int, K>{}), ...);
+}
+template <int J, typename T>
+LOCA_DEV void elim_step(T (&a)[16], T (&e)[16], int& bad) {
+  const T piv = bcast16<J>(a[J]);
+  bad = (!(piv > (T)0) && bad == 16) ? J : bad;
+  const T inv = Dg<T>::rsq(piv);
+  const T uc = a[J] * inv, ec = e[J] * inv;
+  e[J] = ec;
+  elim_rows<J>(a, e, uc, -uc, ec, std::make_integer_sequence<int, 15 - J>{});
+}
+template <typename T, int... J>
+LOCA_DEV void elim_all(T (&a)[16], T (&e)[16], int& bad, std::integer_sequence<int, J...>) {
+  (elim_step<J>(a, e, bad), ...);
+}
+
+// One wave: A (16 x 16 at B, row stride ld; upper part used) = U^T U, E = U^{-T} over it (zero
+// above its diagonal).  X = E^T to rows of the output (row stride ldx; rows and columns < valid).
+// The first non-positive pivot among the first `valid` is reported (1-based, offset base).
 template <typename T>
-__global__ __launch_bounds__(kT) void k_diag_block(int64_t d, int64_t p, T* __restrict__ Fall,
-                                                   int32_t* __restrict__ dev_info) {
-  constexpr int P = Mf<T>::P, NI = P / 16;
-  __shared__ T rowbuf[2][P];
-  __shared__ T sU[P][P + 1];
+LOCA_DEV void chol_inv16(T* B, int ld, T* X, int64_t ldx, int lane, int valid, int64_t base, int32_t* info) {
+  const int c = lane & 15;
+  T a[16], e[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) a[r] = B[r * ld + c];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) e[r] = r == c ? (T)1 : (T)0;
+  int bad = 16;
+  elim_all(a, e, bad, std::make_integer_sequence<int, 16>{});
+  if (bad < 16 && bad < valid && lane == 0) atomicCAS(info, 0, (int32_t)(base + bad + 1));
+  if (lane < 16) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) B[r * ld + c] = e[r];
+    if (c < valid)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (r < valid) X[c * ldx + r] = e[r];
+  }
+}
+
+// acc += Aop Bop for one 16 x 16 block with K = 16 from LDS: Aop[i][k] = Am[i ld + k], or
+// Am[k ld + i] (TA); Bop[k][j] = Bm[k ld + j].
+template <typename T, bool TA>
+LOCA_DEV void mm16(typename Dg<T>::acc_t& acc, const T* Am, const T* Bm, int ld, int lane) {
+  const int i = lane & 15, kq = lane >> 4;
+#pragma unroll
+  for (int s = 0; s < 16; s += 4) {
+    const int k = s + kq;
+    acc = Dg<T>::mma(TA ? Am[k * ld + i] : Am[i * ld + k], Bm[k * ld + i], acc);
+  }
+}
+
+template <typename T, int P>
+__global__ __launch_bounds__(4 * P) void k_diag_inv(int64_t d, int64_t p, T* __restrict__ Fall,
+                                                    int32_t* __restrict__ dev_info) {
+  constexpr int NB = P / 16, LD = P + Dg<T>::LD_PAD, NT = 4 * P, NW = NT / 64;
+  static_assert(NW == NB, "one wave per block of a row panel");
+  __shared__ __attribute__((aligned(16))) T sA[P * LD];
   const int64_t mi = blockIdx.x;
-  T* F = Fall + mi * d * d;
-  const T* A0 = F + p * d + p;
+  T* F = Fall + mi * d * d + p * d + p;  // the diagonal block
   const int pw = (int)((d - p) < P ? (d - p) : P);
-  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-  T a[NI][NI];
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15;
+  {  // the upper part to LDS, all loads issued before the first use; zero below the diagonal
+    constexpr int NE = P * P / NT;
+    T v[NE];
 #pragma unroll
-  for (int i = 0; i < NI; ++i)
-#pragma unroll
-    for (int k = 0; k < NI; ++k) {
-      const int r = ty + 16 * i, c = tx + 16 * k;
-      a[i][k] = ld_or_zero(A0, (int64_t)r * d + c, r < pw && c < pw && c >= r);
+    for (int u = 0; u < NE; ++u) {
+      const int e = tid + NT * u, r = e / P, c = e % P;
+      v[u] = ld_or_zero(F, (int64_t)r * d + c, c >= r && c < pw);
     }
-  if (ty == 0)
 #pragma unroll
-    for (int k = 0; k < NI; ++k) rowbuf[0][tx + 16 * k] = a[0][k];
-  for (int j = 0; j < pw; ++j) {
-    __syncthreads();
-    const T* rb = rowbuf[j & 1];
-    const T piv = rb[j];
-    if (!(piv > (T)0) && tid == 0) atomicCAS(&dev_info[mi], 0, (int32_t)(p + j + 1));
-    const T ujj = sqrt(piv);
-    const T inv = (T)1 / ujj;
-    T ur[NI], uc[NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) ur[i] = rb[ty + 16 * i] * inv;
-#pragma unroll
-    for (int k = 0; k < NI; ++k) uc[k] = rb[tx + 16 * k] * inv;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int r = ty + 16 * i;
-      if (r == j) {  // owners of row j: final row of U
-#pragma unroll
-        for (int k = 0; k < NI; ++k) {
-          const int c = tx + 16 * k;
-          if (c >= j && c < pw) a[i][k] = (c == j) ? ujj : uc[k];
-        }
-      } else if (r > j && r < pw) {
-#pragma unroll
-        for (int k = 0; k < NI; ++k) {
-          const int c = tx + 16 * k;
-          if (c >= r && c < pw) a[i][k] -= ur[i] * uc[k];
-        }
-      }
-    }
-    if (j + 1 < pw) {
-#pragma unroll
-      for (int i = 0; i < NI; ++i)
-        if (ty + 16 * i == j + 1)
-#pragma unroll
-          for (int k = 0; k < NI; ++k) rowbuf[(j + 1) & 1][tx + 16 * k] = a[i][k];
+    for (int u = 0; u < NE; ++u) {
+      const int e = tid + NT * u, r = e / P, c = e % P;
+      sA[r * LD + c] = r == c && r >= pw ? (T)1 : v[u];
+      if (c < r && r < pw) F[(int64_t)r * d + c] = (T)0;
     }
   }
-  // U to LDS (column reads below), then X = U^{-1} bottom-up in registers (t = partial sums, then X)
-#pragma unroll
-  for (int i = 0; i < NI; ++i)
-#pragma unroll
-    for (int k = 0; k < NI; ++k) sU[ty + 16 * i][tx + 16 * k] = a[i][k];
   __syncthreads();
-  T t[NI][NI];
+  auto blk = [&](int r, int s) { return sA + 16 * r * LD + 16 * s; };
+  auto update = [&](int q, int r, int s) {  // block (r, s) -= U_qr^T block (q, s)
+    typename Dg<T>::acc_t acc = {};
+    mm16<T, true>(acc, blk(q, r), blk(q, s), LD, lane);
+    T* B = blk(r, s);
 #pragma unroll
-  for (int i = 0; i < NI; ++i)
-#pragma unroll
-    for (int k = 0; k < NI; ++k) t[i][k] = (T)0;
-  {
-    const int last = pw - 1;
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-      if (ty + 16 * i == last)
-#pragma unroll
-        for (int k = 0; k < NI; ++k) {
-          const int c = tx + 16 * k;
-          const T x = (c == last) ? (T)1 / sU[last][last] : (T)0;
-          t[i][k] = x;
-          rowbuf[last & 1][c] = x;
-        }
-  }
-  for (int i0 = pw - 1; i0 >= 0; --i0) {
+    for (int e = 0; e < 4; ++e) B[Dg<T>::row(lane, e) * LD + li] -= acc[e];
+  };
+  for (int q = 0; q < NB; ++q) {
+    if (wid == 0) chol_inv16<T>(blk(q, q), LD, F + (int64_t)16 * q * d + 16 * q, d, lane, pw - 16 * q, p + 16 * q, dev_info + mi);
     __syncthreads();
-    const T* xb = rowbuf[i0 & 1];
-    T xc[NI];
+    if (wid != q) {
+      typename Dg<T>::acc_t acc = {};
+      mm16<T, false>(acc, blk(q, q), blk(q, wid), LD, lane);
+      T* B = blk(q, wid);
 #pragma unroll
-    for (int k = 0; k < NI; ++k) xc[k] = xb[tx + 16 * k];
+      for (int e = 0; e < 4; ++e) B[Dg<T>::row(lane, e) * LD + li] = acc[e];
+      if (wid < q) {  // E_qs is final: X's block (s, q) is its transpose
+        const int xr = 16 * wid + li;  // < pw: below a full block
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int r = ty + 16 * i;
-      if (r < i0) {
-        const T uri = sU[r][i0];
-#pragma unroll
-        for (int k = 0; k < NI; ++k) t[i][k] += uri * xc[k];
+        for (int e = 0; e < 4; ++e) {
+          const int xc = 16 * q + Dg<T>::row(lane, e);
+          if (xc < pw) F[(int64_t)xr * d + xc] = acc[e];
+        }
       }
     }
-    const int nr = i0 - 1;  // row finalized in this step
-    if (nr >= 0) {
-      const T inv = (T)1 / sU[nr][nr];
-#pragma unroll
-      for (int i = 0; i < NI; ++i)
-        if (ty + 16 * i == nr)
-#pragma unroll
-          for (int k = 0; k < NI; ++k) {
-            const int c = tx + 16 * k;
-            const T x = (c >= nr && c < pw) ? ((c == nr ? (T)1 : (T)0) - t[i][k]) * inv : (T)0;
-            t[i][k] = x;
-            rowbuf[nr & 1][c] = x;
-          }
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < NI; ++i)
-#pragma unroll
-    for (int k = 0; k < NI; ++k) {
-      const int r = ty + 16 * i, c = tx + 16 * k;
-      if (r < pw && c < pw) F[(p + r) * d + p + c] = (c >= r) ? t[i][k] : (T)0;
-    }
-}
-
-// ------------------------------------------------------------------ diagonal block, float, blocked by 32
-
-// acc += Aop Bop for one 32 x 32 block with K = 32 from LDS (fp32 MFMA 32x32x2, 16 steps):
-// Aop[i][k] = Am[i * lda + k] (a_rows) or Am[k * lda + i]; Bop[k][j] = Bm[k * ldb + j].
-LOCA_DEV void mm32(f32x16_t& acc, const float* Am, int lda, bool a_rows, const float* Bm, int ldb, int lane) {
-  const int i = lane & 31, kh = lane >> 5;
-#pragma unroll
-  for (int s2 = 0; s2 < 32; s2 += 2) {
-    const int k = s2 + kh;
-    const float av = a_rows ? Am[i * lda + k] : Am[k * lda + i];
-    acc = mfma_f32x2(av, Bm[k * ldb + i], acc);
-  }
-}
-LOCA_DEV void zero16(f32x16_t& acc) {
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-}
-
-// One wave factors the 32 x 32 block B (upper part used) as U^T U, writes U over B (zero
-// below the diagonal) and X = U^{-1} to Xo.  Lane c < 32 holds column c (rows 0..31);
-// lanes 32..63 mirror lanes 0..31 and write nothing.  Step j of the factorization takes
-// the pivot from lane j (v_readlane; lane j forms it in step j - 1 from its own values,
-// so that the pivot does not wait for the row's round trip through LDS) and writes row j of
-// U, U[j][c] from lane c, straight to its place in B; the update A[i][c] -= U[j][i] U[j][c]
-// then reads that row back from LDS (one broadcast read per entry instead of a cross-lane
-// read each).  The inverse is
-// built bottom-up the same way, lane c finishing column c of X with row i of U read from
-// B.  A wave's LDS accesses complete in order, so each read sees the row just written.
-// 1/sqrt of the pivot and the reciprocals are the hardware ones (about 1 ulp).  The first
-// non-positive pivot among the first `valid` is reported (1-based, offset base).
-LOCA_DEV float lane_val(float v, int l) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-LOCA_DEV void chol_inv32(float* B, int ld, float* Xo, int ldx, int lane, int valid, int64_t base, int32_t* info) {
-  const int c = lane & 31;
-  const bool wr = lane < 32;
-  float a[32];
-#pragma unroll
-  for (int r = 0; r < 32; ++r) a[r] = B[r * ld + c];
-  float piv = lane_val(a[0], 0);
-  int bad = 32;  // the first non-positive pivot (wave-uniform), reported after the loop
-#pragma unroll
-  for (int j = 0; j < 32; ++j) {
-    if (!(piv > 0.f) && j < valid && bad == 32) bad = j;
-    const float inv = __builtin_amdgcn_rsqf(piv);
-    const float ujj = piv * inv;
-    const float uc = c > j ? a[j] * inv : (c == j ? ujj : 0.f);  // U[j][c]
-    a[j] = uc;
-    // the next pivot from lane j + 1's own values (U[j][j + 1] is its uc), ahead of the
-    // row's round trip through LDS; the same fused operation as its update below
-    if (j < 31) piv = lane_val(fmaf(-uc, uc, a[j + 1]), j + 1);
-    if (wr) B[j * ld + c] = uc;
-#pragma unroll
-    for (int i = j + 1; i < 32; ++i) a[i] = fmaf(-B[j * ld + i], uc, a[i]);  // A[i][c] -= U[j][i] U[j][c]
-  }
-  if (bad < 32 && lane == 0) atomicCAS(info, 0, (int32_t)(base + bad + 1));
-  float x[32];
-#pragma unroll
-  for (int i = 31; i >= 0; --i) {
-    float part[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k = i + 1; k < 32; ++k) part[k & 3] += B[i * ld + k] * x[k];  // U[i][k] x[k]
-    const float tot = (part[0] + part[1]) + (part[2] + part[3]);
-    x[i] = c >= i ? ((c == i ? 1.f : 0.f) - tot) * __builtin_amdgcn_rcpf(B[i * ld + i]) : 0.f;
-  }
-  if (wr) {
-#pragma unroll
-    for (int r = 0; r < 32; ++r) Xo[r * ldx + c] = x[r];
-  }
-}
-
-// Factor and invert the P x P (P = 128) diagonal block of F at p, blocked by 32: per
-// 32-column block q, one wave factors and inverts the block (chol_inv32), the waves form
-// its row panel U_qr = X_qq^T A_qr and the update A_rs -= U_qr^T U_qs with MFMA; the
-// inverse of the whole block is then assembled column by column (wave s):
-// X_rs = -X_rr sum_{r < t <= s} U_rt X_ts.  Entries past the matrix (a ragged last block)
-// are an identity extension.  Output as for k_diag_block: X over the diagonal block, zero
-// strictly below its diagonal.
-__global__ __launch_bounds__(kT) void k_diag_f32(int64_t d, int64_t p, float* __restrict__ Fall,
-                                                 int32_t* __restrict__ dev_info) {
-  constexpr int P = 128, LD = 132;
-  __shared__ __attribute__((aligned(16))) float sA[P * LD];
-  __shared__ __attribute__((aligned(16))) float sX[P * LD];
-  __shared__ __attribute__((aligned(16))) float sT[3][32 * 36];
-  const int64_t mi = blockIdx.x;
-  float* F = Fall + mi * d * d;
-  const float* A0 = F + p * d + p;
-  const int pw = (int)((d - p) < P ? (d - p) : P);
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  // the block in 16 four-column chunks per thread, all loads issued before the first use
-  // (16-byte loads when the rows are 16-byte aligned and the chunk lies inside the block)
-  {
-    constexpr int NCH = P * P / 4 / kT;
-    float4 v[NCH];
-    if ((d & 3) == 0 && pw == P) {  // a whole block with 16-byte aligned rows
-#pragma unroll
-      for (int u = 0; u < NCH; ++u) {
-        const int e = tid + kT * u, r = e >> 5, c = 4 * (e & 31);
-        v[u] = *(const float4*)(A0 + (int64_t)r * d + c);
-      }
+    if (q == NB - 1) break;
+    __syncthreads();
+    if (wid == 0) {
+      update(q, q + 1, q + 1);
+      wave_lds_sync();
     } else {
-#pragma unroll
-      for (int u = 0; u < NCH; ++u) {
-        const int e = tid + kT * u, r = e >> 5, c = 4 * (e & 31);
-        const int64_t o = (int64_t)r * d + c;
-        v[u].x = ld_or_zero(A0, o, r < pw && c < pw);
-        v[u].y = ld_or_zero(A0, o + 1, r < pw && c + 1 < pw);
-        v[u].z = ld_or_zero(A0, o + 2, r < pw && c + 2 < pw);
-        v[u].w = ld_or_zero(A0, o + 3, r < pw && c + 3 < pw);
+      for (int u = wid - 1; u < (NB - 1 - q) * NB; u += NW - 1) {
+        const int r = q + 1 + u / NB, s = u % NB;
+        if ((s > q && s < r) || (r == q + 1 && s == r)) continue;
+        update(q, r, s);
       }
-    }
-#pragma unroll
-    for (int u = 0; u < NCH; ++u) {
-      const int e = tid + kT * u, r = e >> 5, c = 4 * (e & 31);
-      const float in4[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-      float o4[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int cc = c + t;
-        const bool in = r < pw && cc < pw;
-        o4[t] = in ? (cc >= r ? in4[t] : 0.f) : (r == cc ? 1.f : 0.f);
-      }
-      *(float4*)&sA[r * LD + c] = make_float4(o4[0], o4[1], o4[2], o4[3]);
-      *(float4*)&sX[r * LD + c] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  }
-  __syncthreads();
-  for (int q = 0; q < 4; ++q) {
-    const int c0 = 32 * q;
-    if (wid == 0) chol_inv32(sA + c0 * LD + c0, LD, sX + c0 * LD + c0, LD, lane, pw - c0, p + c0, dev_info + mi);
-    __syncthreads();
-    const int nr = 3 - q;
-    if (wid < nr) {  // row panel block r: U_qr = X_qq^T A_qr
-      const int r = q + 1 + wid;
-      f32x16_t acc;
-      zero16(acc);
-      mm32(acc, sX + c0 * LD + c0, LD, false, sA + c0 * LD + 32 * r, LD, lane);
-#pragma unroll
-      for (int e = 0; e < 16; ++e) sA[(c0 + mfma32_row(lane, e)) * LD + 32 * r + (lane & 31)] = acc[e];
-    }
-    __syncthreads();
-    for (int u = wid; u < nr * (nr + 1) / 2; u += 4) {  // trailing block (r, s), q < r <= s
-      int r = q + 1, rem = u;
-      while (rem >= 4 - r) { rem -= 4 - r; ++r; }
-      const int s2 = r + rem;
-      f32x16_t acc;
-      zero16(acc);
-      mm32(acc, sA + c0 * LD + 32 * r, LD, false, sA + c0 * LD + 32 * s2, LD, lane);
-#pragma unroll
-      for (int e = 0; e < 16; ++e) sA[(32 * r + mfma32_row(lane, e)) * LD + 32 * s2 + (lane & 31)] -= acc[e];
-    }
-    __syncthreads();
-  }
-  if (wid >= 1) {  // column s = wid of the inverse
-    const int s2 = wid;
-    float* T = sT[wid - 1];
-    for (int r = s2 - 1; r >= 0; --r) {
-      f32x16_t acc;
-      zero16(acc);
-      for (int t = r + 1; t <= s2; ++t) mm32(acc, sA + 32 * r * LD + 32 * t, LD, true, sX + 32 * t * LD + 32 * s2, LD, lane);
-#pragma unroll
-      for (int e = 0; e < 16; ++e) T[mfma32_row(lane, e) * 36 + (lane & 31)] = acc[e];
-      zero16(acc);
-      mm32(acc, sX + 32 * r * LD + 32 * r, LD, true, T, 36, lane);
-#pragma unroll
-      for (int e = 0; e < 16; ++e) sX[(32 * r + mfma32_row(lane, e)) * LD + 32 * s2 + (lane & 31)] = -acc[e];
-    }
-  }
-  __syncthreads();
-  for (int e = tid; e < P * P / 4; e += kT) {
-    const int r = e >> 5, c = 4 * (e & 31);
-    if (r >= pw) continue;
-    const float4 x = *(const float4*)&sX[r * LD + c];
-    const float x4[4] = {c >= r ? x.x : 0.f, c + 1 >= r ? x.y : 0.f, c + 2 >= r ? x.z : 0.f, c + 3 >= r ? x.w : 0.f};
-    float* dst = F + (p + r) * d + p + c;
-    if ((d & 3) == 0 && c + 4 <= pw) {
-      *(float4*)dst = make_float4(x4[0], x4[1], x4[2], x4[3]);
-    } else {
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        if (c + t < pw) dst[t] = x4[t];
     }
   }
 }
@@ -1505,8 +1378,7 @@ hipError_t run_group(const SolveArgs& a, int64_t b0, int64_t nbg, hipStream_t st
       const bool rec = after_diag && pp == 0;
       if (rec && emit.ops) emit.stagger_at = (int)emit.ops->size();
       e = emit([=]() {
-        if constexpr (sizeof(T) == 4) k_diag_f32<<<(unsigned)nm, kT, 0, st>>>(d, pp, (float*)F, info);
-        else if (!reuse) k_diag_block<T><<<(unsigned)nm, kT, 0, st>>>(d, pp, F, info);
+        if (!reuse) k_diag_inv<T, P><<<(unsigned)nm, 4 * P, 0, st>>>(d, pp, F, info);
         const hipError_t er = hipGetLastError();
         if (er != hipSuccess || !rec) return er;
         return hipEventRecord(after_diag, st);

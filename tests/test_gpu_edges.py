@@ -67,3 +67,35 @@ def test_statistics_at_every_width(d, n, k, w):
         assert rel(S[b].cpu().numpy()[iu], ref[iu]) < 1e-5
         eta = 0.5 * np.sqrt(((aw * X * X)[b] if w else X[b] ** 2).sum() / 7.0)
         assert rel(K[b].cpu().numpy(), -eta * X[b].T @ ((aw * Y)[b] if w else Y[b])) < 1e-5
+
+
+# widths at the edges of the 16-wide blocks, the 64- and 128-wide panels and the 512-wide
+# super-panels.  S from 4 d Gaussian rows: the equilibrated matrix's condition number is about
+# (1 + 1/2)^2 / (1 - 1/2)^2 = 9; a backward stable solve errs by a small multiple of
+# 9 sqrt(d) 2^-24 (fp32, 1.3e-5 at d = 530) or 9 sqrt(d) 2^-53, then the float output's 2^-24
+@pytest.mark.parametrize("acc", ["f32", "f64"])
+@pytest.mark.parametrize("d", [1, 15, 16, 17, 63, 64, 65, 100, 127, 128, 129, 144, 260, 530])
+def test_ridge_solve_block_edges(d, acc):
+    import torch
+    from paper_2608_03020_amd import loca
+    g = np.random.default_rng(d)
+    nb, k, lams = 2, 5, [1e-2, 1.0]
+    dt = torch.float32 if acc == "f32" else torch.float64
+    X = g.standard_normal((nb, 4 * d + 4, d))
+    S = torch.from_numpy(X.transpose(0, 2, 1) @ X).to("cuda", dt)
+    K = torch.from_numpy(g.standard_normal((nb, d, k))).to("cuda", dt)
+    M = torch.full((nb, len(lams), d, k), float("nan"), dtype=torch.float32, device="cuda")
+    info = torch.full((nb * len(lams),), 77, dtype=torch.int32, device="cuda")
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_RIDGE_SOLVE, nb, 0, d, k, n_lambda=len(lams),
+                                                  acc=loca.LOCA_F32 if acc == "f32" else loca.LOCA_F64))
+    ws.fill_(255)
+    ref_s = torch.triu(S).double().cpu().numpy()
+    ref_s = ref_s + np.triu(ref_s, 1).transpose(0, 2, 1)
+    S += torch.tril(torch.full_like(S, float("nan")), -1)  # never read
+    log("ridge solve", d, acc)
+    loca.loca_ridge_solve(S, K, lams, M, info, ws)
+    assert info.eq(0).all()
+    for b in range(nb):
+        for i, lam in enumerate(lams):
+            ref = np.linalg.solve(ref_s[b] + lam * np.eye(d), K[b].double().cpu().numpy())
+            assert rel(M[b, i].cpu().numpy(), ref) < (9 * np.sqrt(d) * 2.0 ** -24 if acc == "f32" else 0) + 2.0 ** -23
