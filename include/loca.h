@@ -33,8 +33,8 @@
  *     The library never synchronises and never allocates device memory.
  *     Scratch memory comes from the caller's `ws`, at least
  *     loca_workspace_size(...) bytes, 256-byte aligned.
- *   - State kept by the library: loca_ridge_solve creates, on its first call
- *     on a device, two internal streams and a few events of that device, and
+ *   - State kept by the library: loca_ridge_solve creates, on its first large call
+ *     on a device, an internal stream and a few events of that device, and
  *     keeps them until the process ends; creating them and every submission
  *     that uses them run under a per-device mutex.  loca_error_targets_noalloc
  *     uses a fixed device array instead of a workspace (see there).
@@ -232,12 +232,12 @@ loca_status loca_accumulate_stats(loca_stream_t stream, int64_t nb, int64_t n, i
  * dev_info : nb * n_lambda int32; 0, or the 1-based index of a non-positive
  *            pivot (LAPACK potrf convention; a NaN pivot counts as non-positive).
  * Limits: r_prev + k <= 128, n_lambda <= 8, nb * n_lambda <= 65535, d <= 65535.
- * With two or more blocks the blocks are split into up to three groups: the first
- * runs on the caller's stream, the others on two internal streams the library
- * creates on its first call on the device.  The internal streams wait for the
- * caller's stream at entry and the caller's stream waits for them at the end, so
- * the call stays ordered on the caller's stream; calls from several host threads
- * are serialised on the internal streams (see the conventions above).
+ * A large call's blocks are split into two groups: the first runs on the caller's
+ * stream, the other on an internal stream the library creates on its first such call
+ * on the device.  The internal stream waits for the caller's stream at entry and the
+ * caller's stream waits for it at the end, so the call stays ordered on the caller's
+ * stream; calls from several host threads are serialised on the internal stream (see
+ * the conventions above).
  * ------------------------------------------------------------------------- */
 loca_status loca_ridge_solve(loca_stream_t stream, int64_t nb, int64_t d, int64_t k, const void* S,
                              const void* K, loca_dtype acc, int64_t s_bstride, int64_t k_bstride,

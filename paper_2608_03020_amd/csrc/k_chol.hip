@@ -5,11 +5,11 @@
 // solved for every (block, lam) pair of a call in one batched pass:
 //   1. Jacobi equilibration  A^ = D (S + lam I) D,  D = diag(S + lam I)^{-1/2};
 //   2. right-looking blocked Cholesky A^ = U^T U (U upper, row-major) with
-//      P-wide panels (P = 128 in fp32, 64 in fp64).  Per panel, three launches
-//      batched over all matrices: the diagonal block is factored and inverted
-//      in LDS by one workgroup per matrix; the row panel U12 = U11^{-T} A12 is
-//      a matrix-core product with that inverse; the trailing matrix takes the
-//      symmetric rank-P update A22 -= U12^T U12.  The right-hand sides ride
+//      P-wide panels (P = 128 in fp32, 64 in fp64), four to a super-panel.  Per panel,
+//      launches batched over all matrices: the diagonal block is factored and inverted
+//      in LDS by one workgroup per matrix; the row panel takes the update by the
+//      super-panel's earlier panels and U12 = U11^{-T} A12, matrix-core products; per
+//      super-panel the trailing matrix takes the symmetric update A22 -= U12^T U12.  The right-hand sides ride
 //      along as extra columns of the row panel and the update, so the forward
 //      substitution costs nothing extra.  Products use MFMA (fp32 32x32x2, or
 //      fp64 16x16x4 for fp64 statistics);
@@ -290,6 +290,265 @@ LOCA_DEV void tile_mma(const T* sP, const T* sQ, int ld, int K, int wi, int wj, 
   }
 }
 
+// ------------------------------------------------------------------ fp32 panels on bf16 matrix cores
+
+// A float a is carried as three bfloat16 parts, h = bf16(a), m = bf16(a - h),
+// l = bf16(a - h - m) (each difference is exact in float), which hold a to about 2^-27
+// relative.  The product of two split values keeps the six terms of order 2^-16 and
+// larger (h*h, h*m, m*h, h*l, l*h, m*m) and drops m*l, l*m, l*l (order 2^-24 and
+// below), so a product has float-class error while running on bf16 MFMA, which
+// retires sixteen times the flops of the fp32 MFMA per cycle.
+// The split is split3_pair (loca_bf16.h): hardware conversions, two values at a time.
+// The kept terms, smallest first:
+constexpr int kX6A[6] = {2, 0, 1, 1, 0, 0}, kX6B[6] = {0, 2, 1, 0, 1, 0};
+
+LOCA_DEV float4 ld4_or_zero(const float* base, int64_t idx, bool ok) {
+  const float4 v = *(const float4*)(base + (ok ? idx : 0));
+  return ok ? v : make_float4(0.f, 0.f, 0.f, 0.f);
+}
+LOCA_DEV float4 ld4_or_zero_ro(const float* __restrict__ base, int64_t idx, bool ok) { return ld4_or_zero(base, idx, ok); }
+
+// The first operand of a panel's products: stages of 16 rows x the panel's 128 columns of F,
+// one 16-byte load (V4: d % 4 == 0) per four values, split once by the workgroup into three
+// bf16 planes [16][kPanelLD] (the four rows a half-wave's transpose read takes start 64 bytes
+// apart modulo 256: conflict-free).
+constexpr int kPanelLD = 160, kPanelPlane = 16 * kPanelLD;
+// The load takes the nearest element inside the matrix and panel_mask zeroes what lay outside,
+// when the value is used: a load under a condition would be waited for where it is issued.
+template <bool V4>
+LOCA_DEV float4 panel_load(const float* F, int64_t d, int64_t row, int64_t col) {
+  const float* r = F + (row < d ? row : d - 1) * d;
+  if (V4) return *(const float4*)(r + (col < d ? col : d - 4));
+  float4 v;
+  v.x = r[col < d ? col : d - 1];
+  v.y = r[col + 1 < d ? col + 1 : d - 1];
+  v.z = r[col + 2 < d ? col + 2 : d - 1];
+  v.w = r[col + 3 < d ? col + 3 : d - 1];
+  return v;
+}
+LOCA_DEV float4 panel_mask(float4 v, int64_t d, int64_t row, int64_t col) {
+  const bool ok = row < d;
+  v.x = ok && col < d ? v.x : 0.f;
+  v.y = ok && col + 1 < d ? v.y : 0.f;
+  v.z = ok && col + 2 < d ? v.z : 0.f;
+  v.w = ok && col + 3 < d ? v.w : 0.f;
+  return v;
+}
+LOCA_DEV void panel_put(uint16_t* planes, int kk, int c4, const float4& v) {
+  uint32_t h[2], m[2], l[2];
+  split3_pair(v.x, v.y, h[0], m[0], l[0]);
+  split3_pair(v.z, v.w, h[1], m[1], l[1]);
+  const int o = kk * kPanelLD + c4;
+  *(uint2*)(planes + o) = make_uint2(h[0], h[1]);
+  *(uint2*)(planes + kPanelPlane + o) = make_uint2(m[0], m[1]);
+  *(uint2*)(planes + 2 * kPanelPlane + o) = make_uint2(l[0], l[1]);
+}
+
+// As frag32_tr on the 16 rows of a stage, in the row order of a lane's own MFMA results: the
+// operand of lane l is the rows 8 (e / 4) + 4 (l / 32) + e % 4, e = 0..7, of column c0 + l % 32.
+LOCA_DEV bf16x8_t frag32_tr_own(const uint16_t* tile, int ld, int c0, int lane) {
+  const int g = lane >> 4, w = lane & 15;
+  const uint16_t* q = tile + (4 * (g >> 1) + (w >> 2)) * ld + c0 + 16 * (g & 1) + 4 * (w & 3);
+  const s16x4_t lo = lds_read_tr16(q), hi = lds_read_tr16(q + 8 * ld);
+  typedef short s16x8_t __attribute__((ext_vector_type(8)));
+  const s16x8_t v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  return __builtin_bit_cast(bf16x8_t, v);
+}
+
+// The diagonal block's own strip update, eight waves: the ten 32 x 32 blocks on or above the
+// diagonal of sum_kk F[kk][p + i] F[kk][p + j], rows kk in [k0, p), subtracted from sA.
+template <bool V4, int LDA>
+LOCA_DEV void diag_strip_update(const float* F, int64_t d, int64_t k0, int64_t p, uint16_t (&sP)[2][3 * kPanelPlane],
+                                float* sA, int tid, int lane, int wid) {
+  constexpr int D = 4;
+  const int ns = (int)((p - k0) / 16);  // a multiple of 8
+  const int kk = tid >> 5, c4 = 4 * (tid & 31);
+  int bi[2], bj[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int u = wid + 8 * t < 10 ? wid + 8 * t : wid;
+    bi[t] = u < 4 ? 0 : (u < 7 ? 1 : (u < 9 ? 2 : 3));
+    bj[t] = u < 4 ? u : (u < 7 ? u - 3 : (u < 9 ? u - 5 : 3));
+  }
+  const int nt = wid < 2 ? 2 : 1;
+  f32x16_t acc[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+  float4 rp[D];
+#pragma unroll
+  for (int u = 0; u < D; ++u) rp[u] = panel_load<V4>(F, d, k0 + 16 * u + kk, p + c4);
+  panel_put(sP[0], kk, c4, panel_mask(rp[0], d, k0, p + c4));
+  __syncthreads();
+  for (int s0 = 0; s0 < ns; s0 += D) {
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      const int s = s0 + u, cur = u & 1;
+      rp[u] = panel_load<V4>(F, d, k0 + 16 * (s + D) + kk, p + c4);  // past the last stage: not used
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        if (t >= nt) continue;
+        bf16x8_t fa[3], fb[3];
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+          fa[x] = frag32_tr(sP[cur] + x * kPanelPlane, kPanelLD, 32 * bi[t], 0, lane);
+          fb[x] = frag32_tr(sP[cur] + x * kPanelPlane, kPanelLD, 32 * bj[t], 0, lane);
+        }
+#pragma unroll
+        for (int x = 0; x < 6; ++x) acc[t] = mfma32(fa[kX6A[x]], fb[kX6B[x]], acc[t]);
+      }
+      panel_put(sP[cur ^ 1], kk, c4, panel_mask(rp[(u + 1) % D], d, k0, p + c4));
+      __syncthreads();
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    if (t >= nt) continue;
+    float* B = sA + 32 * bi[t] * LDA + 32 * bj[t] + (lane & 31);
+    // the 16 x 16 block below the diagonal of a diagonal 32 x 32 one holds E's zeros
+    const bool low = bi[t] == bj[t] && (lane & 31) < 16;
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (!(low && r >= 8)) B[mfma32_row(lane, r) * LDA] -= acc[t][r];
+  }
+}
+
+// The rows [p, p + 128) of a panel right of its diagonal block, and of the right-hand sides:
+//   A12 -= sum over kk in [k0, p) of F[kk][p + i] F[kk][j]   (the super-panel's earlier panels)
+//   U12  = X^T A12,                                           X = U11^{-1} in the diagonal block.
+// A wave owns 32 columns of all 128 rows (column block cb: the first nF in F, then R's), so the
+// updated A12 is already, in the registers where the matrix cores left it, the second operand of
+// the product with X: rows 16 c + 8 (e / 4) + 4 h + e % 4 of lane half h are one step's eight
+// values, the first operand (X's rows, read in the same order) being staged as one more run of
+// stages after the update's.  The second operand of the update is loaded by its owner straight
+// into the matrix cores' layout (32 lanes on consecutive columns).  So a panel's rows cross HBM
+// once in each direction where the update and the product, in a launch each, crossed it twice.
+// NWV waves per workgroup share the staged operand: fewer when the launch leaves compute units
+// idle (the rule and its figures stand at the launch).
+template <int NWV, bool V4>
+__global__ __launch_bounds__(64 * NWV) void k_panel_f32(int64_t d, int64_t k0, int64_t p, float* __restrict__ Fall,
+                                                        float* __restrict__ Rall, int64_t m, int nF) {
+  constexpr int NT = 64 * NWV, P = 128, QP = 512 / NT, D = 4;
+  __shared__ __attribute__((aligned(16))) uint16_t sP[2][3 * kPanelPlane];
+  const int64_t mi = blockIdx.y;
+  float* F = Fall + mi * d * d;
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5;
+  const int cb = (int)blockIdx.x * NWV + wid;
+  const bool inF = cb < nF;
+  float* B = inF ? F : Rall + mi * d * m;
+  const int64_t ldb = inF ? d : m, c0 = inF ? p + P + 32 * (int64_t)cb : 32 * (int64_t)(cb - nF);
+  const int64_t col = c0 + (lane & 31);
+  const bool cok = col < ldb;  // false in the waves that the last workgroup has to spare
+  const int pw = (int)((d - p) < P ? (d - p) : P);
+  const int nk1 = (int)((p - k0) / 16), ns = nk1 + P / 16;  // nk1: a multiple of 8
+
+  float4 rp[D][QP];
+  auto load_p = [&](int slot, int s) {
+#pragma unroll
+    for (int q = 0; q < QP; ++q) {
+      const int c = tid + NT * q;
+      rp[slot][q] = panel_load<V4>(F, d, k0 + 16 * s + (c >> 5), p + 4 * (c & 31));
+    }
+  };
+  auto put_p = [&](int buf, int slot, int s) {
+#pragma unroll
+    for (int q = 0; q < QP; ++q) {
+      const int c = tid + NT * q, kk = c >> 5, c4 = 4 * (c & 31);
+      panel_put(sP[buf], kk, c4, panel_mask(rp[slot][q], d, k0 + 16 * s + kk, p + c4));
+    }
+  };
+  float rb[D][8];  // rows 8 h + e of a stage (columns past the edge read column 0: never stored)
+  const uint32_t boff = (uint32_t)(4 * (8 * h * ldb + (cok ? col : 0)));
+  auto load_b = [&](int slot, int s) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      rb[slot][e] = *(const float*)((const char*)(B + (k0 + 16 * (int64_t)s + e) * ldb) + boff);
+  };
+  auto split_b = [&](const float (&v)[8], bf16x8_t (&f)[3]) {
+    uint32_t x[3][4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) split3_pair(v[2 * e], v[2 * e + 1], x[0][e], x[1][e], x[2][e]);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) f[t] = __builtin_bit_cast(bf16x8_t, make_uint4(x[t][0], x[t][1], x[t][2], x[t][3]));
+  };
+
+#pragma unroll
+  for (int u = 0; u < D; ++u) load_p(u, u);
+  f32x16_t acc[4], old[4];  // the update's sum, then A12 less it; A12
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int row = 32 * a + mfma32_row(lane, r);
+      old[a][r] = B[(p + (row < pw ? row : 0)) * ldb + (cok ? col : 0)];  // rows past pw meet X's zero rows
+      acc[a][r] = 0.f;
+    }
+  if (nk1 > 0)
+#pragma unroll
+    for (int u = 0; u < D; ++u) load_b(u, u);
+  put_p(0, 0, 0);
+  __syncthreads();
+  for (int s0 = 0; s0 < nk1; s0 += D) {
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      const int s = s0 + u, cur = u & 1;
+      load_p(u, s + D);
+      bf16x8_t fb[3], fa[3][4];
+      split_b(rb[u], fb);
+      load_b(u, s + D < nk1 ? s + D : nk1 - 1);
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int a = 0; a < 4; ++a) fa[t][a] = frag32_tr(sP[cur] + t * kPanelPlane, kPanelLD, 32 * a, 0, lane);
+#pragma unroll
+      for (int t = 0; t < 6; ++t)
+#pragma unroll
+        for (int a = 0; a < 4; ++a) acc[a] = mfma32(fa[kX6A[t]][a], fb[kX6B[t]], acc[a]);
+      put_p(cur ^ 1, (u + 1) % D, s + 1);
+      __syncthreads();
+    }
+  }
+  f32x16_t out[4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      acc[a][r] = old[a][r] - acc[a][r];
+      out[a][r] = 0.f;
+    }
+  // X's rows 16 c ..: zero left of the diagonal, so 32-row blocks of the output above row 16 c take nothing
+#pragma unroll
+  for (int c = 0; c < P / 16; ++c) {
+    const int u = c % D, cur = c & 1;
+    if (c + D < P / 16) load_p(u, nk1 + c + D);
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = acc[c >> 1][8 * (c & 1) + e];
+    bf16x8_t fb[3], fa[3][4];
+    split_b(v, fb);
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int a = c >> 1; a < 4; ++a) fa[t][a] = frag32_tr_own(sP[cur] + t * kPanelPlane, kPanelLD, 32 * a, lane);
+#pragma unroll
+    for (int t = 0; t < 6; ++t)
+#pragma unroll
+      for (int a = c >> 1; a < 4; ++a) out[a] = mfma32(fa[kX6A[t]][a], fb[kX6B[t]], out[a]);
+    if (c + 1 < P / 16) {
+      put_p(cur ^ 1, (u + 1) % D, nk1 + c + 1);
+      __syncthreads();
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int row = 32 * a + mfma32_row(lane, r);
+      if (cok && row < pw) B[(p + row) * ldb + col] = out[a][r];
+    }
+}
+
 // ------------------------------------------------------------------ diagonal block: factor and invert
 
 // One workgroup per matrix factors the P x P diagonal block, A11 = U11^T U11, and inverts
@@ -410,12 +669,17 @@ LOCA_DEV void mm16(typename Dg<T>::acc_t& acc, const T* Am, const T* Bm, int ld,
   }
 }
 
-template <typename T, int P>
-__global__ __launch_bounds__(4 * P) void k_diag_inv(int64_t d, int64_t p, T* __restrict__ Fall,
+// In fp32 the block first takes the update by its super-panel's earlier panels, A11 -= sum over
+// the rows kk in [k0, p) of F[kk][p + i] F[kk][p + j] (strip_update): in a launch of its own,
+// with the rest of the panel's rows, that update was one more link of the chain.
+template <typename T, int P, bool V4>
+__global__ __launch_bounds__(4 * P) void k_diag_inv(int64_t d, int64_t k0, int64_t p, T* __restrict__ Fall,
                                                     int32_t* __restrict__ dev_info) {
   constexpr int NB = P / 16, LD = P + Dg<T>::LD_PAD, NT = 4 * P, NW = NT / 64;
   static_assert(NW == NB, "one wave per block of a row panel");
   __shared__ __attribute__((aligned(16))) T sA[P * LD];
+  constexpr bool UPD = sizeof(T) == 4;
+  __shared__ __attribute__((aligned(16))) uint16_t sP[UPD ? 2 : 1][UPD ? 3 * kPanelPlane : 8];
   const int64_t mi = blockIdx.x;
   T* F = Fall + mi * d * d + p * d + p;  // the diagonal block
   const int pw = (int)((d - p) < P ? (d - p) : P);
@@ -436,6 +700,8 @@ __global__ __launch_bounds__(4 * P) void k_diag_inv(int64_t d, int64_t p, T* __r
       if (c < r && r < pw) F[(int64_t)r * d + c] = (T)0;
     }
   }
+  if constexpr (UPD)
+    if (p > k0) diag_strip_update<V4, LD>(Fall + mi * d * d, d, k0, p, sP, sA, tid, lane, wid);
   __syncthreads();
   auto blk = [&](int r, int s) { return sA + 16 * r * LD + 16 * s; };
   auto update = [&](int q, int r, int s) {  // block (r, s) -= U_qr^T block (q, s)
@@ -619,47 +885,27 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2))) void k_
 
 // ------------------------------------------------------------------ trailing update on bf16 matrix cores
 
-// A float a is carried as three bfloat16 parts, h = bf16(a), m = bf16(a - h),
-// l = bf16(a - h - m) (each difference is exact in float), which hold a to about 2^-27
-// relative.  The product of two split values keeps the six terms of order 2^-16 and
-// larger (h*h, h*m, m*h, h*l, l*h, m*m) and drops m*l, l*m, l*l (order 2^-24 and
-// below), so the update has float-class error while running on bf16 MFMA, which
-// retires sixteen times the flops of the fp32 MFMA per cycle.
-// The split is split3_pair (loca_bf16.h): hardware conversions, two values at a time.
-
-// Panel products on bf16 matrix cores, Out[i][j] (op)= sum_kk Pn[kk][i] Qn[kk][j]:
-//   kX6Trail: F[i][j] -= sum_{kk in [k0, k0 + kw)} F[kk][i] F[kk][j] on the upper
-//             256 x 256 tiles of the trailing region [off, d);
-//   kX6Strip: the same for the rows [off, off + 128) only (128 x 256 tiles, columns
-//             from off), the update of a panel by the earlier panels of its super-panel;
-//   kX6Row:   F[p + i][j] = sum_kk X[kk][i] F[p + kk][j] for the columns j >= p + 128 of
-//             the panel rows (128 x 256 tiles), X = U11^{-1} in the diagonal block.
+// Trailing products on bf16 matrix cores, Out[i][j] -= sum_kk F[kk][i] Qn[kk][j], kk in [k0, k0 + kw):
+//   kX6Trail: F on the upper 256 x 256 tiles of the trailing region [off, d), then (jobs past
+//             the nF tiles) the right-hand sides' 256-row blocks, Qn and the output in R
+//             (d x m per matrix, m % 4 == 0), all m columns;
+//   kX6TrailRhs: only the right-hand-side jobs, in a layout for their few columns: a workgroup
+//             takes 256 rows x 32 columns (eight waves of 32 x 32; columns 32 blockIdx.z ..),
+//             so it does an eighth of the matrix-core work of a 256 x 256 tile.
 // A stage is 16 rows of K: each operand is loaded into registers several stages ahead (a
 // ring of D stages), split, and written to LDS as three bf16 planes [16][LD]; eight waves
 // (2 x 4) read their MFMA operands with transpose reads (LD = 288: the four rows a
 // half-wave reads start 64 bytes apart modulo 256, so the reads are conflict-free).
 // Requires d % 4 == 0.
 constexpr int kX6BK = 16, kX6LD = 288;
-enum X6Mode { kX6Trail = 0, kX6Strip = 1, kX6Row = 2, kX6TrailRhs = 3 };
+enum X6Mode { kX6Trail = 0, kX6TrailRhs = 1 };
 
-LOCA_DEV float4 ld4_or_zero(const float* base, int64_t idx, bool ok) {
-  const float4 v = *(const float4*)(base + (ok ? idx : 0));
-  return ok ? v : make_float4(0.f, 0.f, 0.f, 0.f);
-}
-LOCA_DEV float4 ld4_or_zero_ro(const float* __restrict__ base, int64_t idx, bool ok) { return ld4_or_zero(base, idx, ok); }
-
-// Jobs past the nF tiles of F are right-hand-side jobs: the same product with Qn and the
-// output taken from R (d x m per matrix, m % 4 == 0): the 256-row block u of the trailing
-// region (kX6Trail), or the panel rows (kX6Strip, kX6Row), all m columns.
-// kX6TrailRhs: only the right-hand-side jobs of kX6Trail, in a layout for their few
-// columns: a workgroup takes 256 rows x 32 columns (eight waves of 32 x 32; columns
-// 32 blockIdx.z ..), so it does an eighth of the matrix-core work of a 256 x 256 tile.
 template <int MODE>
 __global__ __launch_bounds__(512) void k_panel_x6(int64_t d, int64_t k0, int64_t kw, int64_t off,
                                                   float* __restrict__ Fall, float* __restrict__ Rall, int64_t m,
                                                   int nF) {
   constexpr bool RH = MODE == kX6TrailRhs;
-  constexpr int BR = (MODE == kX6Trail || RH) ? 256 : 128;  // output rows per tile
+  constexpr int BR = 256;  // output rows per tile
   constexpr int BC = RH ? 32 : 256, WGN = RH ? 1 : 4, WGM = 8 / WGN;
   constexpr int WM = BR / WGM, WN = BC / WGN, NBM = WM / 32, NBN = WN / 32;
   constexpr int LD = kX6LD, PLANE = kX6BK * LD;
@@ -671,42 +917,29 @@ __global__ __launch_bounds__(512) void k_panel_x6(int64_t d, int64_t k0, int64_t
   float* R = Rall + mi * d * m;
   const bool rhs = RH || (int)blockIdx.x >= nF;
   const int job = rhs && !RH ? (int)blockIdx.x - nF : (int)blockIdx.x;
-  int64_t orow, ocol, pcol;
+  int64_t orow, ocol;
   bool diag = false;
   if (RH) {
     orow = off + (int64_t)job * BR;
     ocol = (int64_t)blockIdx.z * BC;
-    pcol = orow;
-  } else if (MODE == kX6Trail) {
-    if (rhs) {
-      orow = off + (int64_t)job * BC;
-      ocol = 0;
-    } else {
-      const int T2 = (int)((d - off + BC - 1) / BC);
-      int I, J;
-      upper_tile_c(job, T2, I, J);
-      diag = I == J;
-      orow = off + (int64_t)I * BC;
-      ocol = off + (int64_t)J * BC;
-    }
-    pcol = orow;
-  } else if (MODE == kX6Strip) {
-    diag = !rhs && job == 0;
-    orow = off;
-    ocol = rhs ? 0 : off + (int64_t)job * BC;
-    pcol = orow;
-  } else {  // kX6Row: K rows and output rows [k0, k0 + 128), Pn = the diagonal block
-    orow = k0;
-    ocol = rhs ? 0 : k0 + 128 + (int64_t)job * BC;
-    pcol = k0;
+  } else if (rhs) {
+    orow = off + (int64_t)job * BC;
+    ocol = 0;
+  } else {
+    const int T2 = (int)((d - off + BC - 1) / BC);
+    int I, J;
+    upper_tile_c(job, T2, I, J);
+    diag = I == J;
+    orow = off + (int64_t)I * BC;
+    ocol = off + (int64_t)J * BC;
   }
+  const int64_t pcol = orow;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, wi = wid / WGN, wj = wid % WGN;
   const bool active = !(diag && (wj + 1) * WN <= wi * WM);
   const float* gP = F + k0 * d + pcol;
   float* Out = rhs ? R : F;                          // Qn and the output
   const int64_t ldq = rhs ? m : d, qend = rhs ? m : d;
   const float* gQ = Out + k0 * ldq + ocol;
-  const int64_t pend = MODE == kX6Row ? k0 + 128 : d;  // columns of Pn that exist: < pend
 
   // a ring of D stages of global loads in flight: the loads of stage kc + D are issued
   // when stage kc is consumed, so D - 1 stages of matrix-core work cover their latency
@@ -716,7 +949,7 @@ __global__ __launch_bounds__(512) void k_panel_x6(int64_t d, int64_t k0, int64_t
 #pragma unroll
     for (int q = 0; q < QP; ++q) {
       const int c = tid + 512 * q, kk = c / (BR / 4), c4 = 4 * (c % (BR / 4));
-      rp[slot][q] = ld4_or_zero(gP, (int64_t)(kc0 + kk) * d + c4, kc0 + kk < kw && pcol + c4 < pend);
+      rp[slot][q] = ld4_or_zero(gP, (int64_t)(kc0 + kk) * d + c4, kc0 + kk < kw && pcol + c4 < d);
     }
 #pragma unroll
     for (int q = 0; q < QQ; ++q) {
@@ -777,22 +1010,19 @@ __global__ __launch_bounds__(512) void k_panel_x6(int64_t d, int64_t k0, int64_t
         for (int b = 0; b < NBN; ++b)
           fb[t][b] = frag32_tr(&sm[cur][(3 + t) * PLANE], LD, wj * WN + 32 * b, 0, lane);
       }
-      // the six kept terms, smallest first; each term runs over all blocks, so the MFMAs
-      // into one accumulator are NBM * NBN instructions apart
-      constexpr int TA[6] = {2, 0, 1, 1, 0, 0}, TB[6] = {0, 2, 1, 0, 1, 0};
+      // each kept term runs over all blocks, so the MFMAs into one accumulator are NBM * NBN
+      // instructions apart
 #pragma unroll
       for (int t = 0; t < 6; ++t)
 #pragma unroll
         for (int a = 0; a < NBM; ++a)
 #pragma unroll
-          for (int b = 0; b < NBN; ++b) acc[a][b] = mfma32(fa[TA[t]][a], fb[TB[t]][b], acc[a][b]);
+          for (int b = 0; b < NBN; ++b) acc[a][b] = mfma32(fa[kX6A[t]][a], fb[kX6B[t]][b], acc[a][b]);
       if (kc + 1 < nk) store(cur ^ 1, (u + 1) % D);
       __syncthreads();
     }
   }
   if (!active) return;
-  int64_t rend = MODE == kX6Row ? k0 + 128 : (MODE == kX6Strip ? off + 128 : d);
-  if (rend > d) rend = d;  // a ragged last panel
 #pragma unroll
   for (int a = 0; a < NBM; ++a)
 #pragma unroll
@@ -800,18 +1030,15 @@ __global__ __launch_bounds__(512) void k_panel_x6(int64_t d, int64_t k0, int64_t
       const int64_t col = ocol + wj * WN + 32 * b + mfma32_col(lane);
       const int64_t rb = orow + wi * WM + 32 * a;
       float old[16];
-      if (MODE != kX6Row) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int64_t row = rb + mfma32_row(lane, r);
-          old[r] = ld_or_zero(Out, row * ldq + col, row < rend && col < qend && (rhs || col >= row));
-        }
+      for (int r = 0; r < 16; ++r) {
+        const int64_t row = rb + mfma32_row(lane, r);
+        old[r] = ld_or_zero(Out, row * ldq + col, row < d && col < qend && (rhs || col >= row));
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int64_t row = rb + mfma32_row(lane, r);
-        if (row < rend && col < qend && (rhs || col >= row))
-          Out[row * ldq + col] = MODE == kX6Row ? acc[a][b][r] : old[r] - acc[a][b][r];
+        if (row < d && col < qend && (rhs || col >= row)) Out[row * ldq + col] = old[r] - acc[a][b][r];
       }
     }
 }
@@ -1258,6 +1485,27 @@ __global__ void k_unscale(int64_t d, int64_t m, const T* __restrict__ Rall, cons
 }
 
 
+// The panel rows in workgroups of eight waves (32 columns each), or four where eight would
+// leave compute units idle: eight share the staging and splitting of the first operand, which a
+// workgroup of two waves spends longer on than on its products.  Whole solves, two/four waves ->
+// four/eight: one matrix of d = 2048 1396 -> 1346 us, 28 of 1536 1233 -> 1198 us, 84 of 3584
+// 11.03 -> 10.90 ms (two waves everywhere: 11.16).
+hipError_t launch_panel_f32(hipStream_t st, int64_t nm, int64_t d, int64_t k0, int64_t p, float* F, float* R, int64_t m) {
+  const int64_t nrem = d - p - 128;
+  const int nF = nrem > 0 ? (int)((nrem + 31) / 32) : 0, nc = nF + (int)((m + 31) / 32);
+  const bool v4 = d % 4 == 0;
+#define LOCA_PANEL(NWV)                                                                                          \
+  {                                                                                                              \
+    const dim3 g((unsigned)((nc + NWV - 1) / NWV), (unsigned)nm);                                                \
+    if (v4) k_panel_f32<NWV, true><<<g, 64 * NWV, 0, st>>>(d, k0, p, F, R, m, nF);                               \
+    else k_panel_f32<NWV, false><<<g, 64 * NWV, 0, st>>>(d, k0, p, F, R, m, nF);                                 \
+  }
+  if (nm * ((nc + 7) / 8) >= 256) LOCA_PANEL(8)
+  else LOCA_PANEL(4)
+#undef LOCA_PANEL
+  return hipGetLastError();
+}
+
 template <typename T>
 size_t solve_ws_t(int64_t nb, int64_t d, int64_t m, int64_t nl, int64_t r_prev) {
   const int64_t nm = nb * nl;
@@ -1344,7 +1592,7 @@ hipError_t run_group(const SolveArgs& a, int64_t b0, int64_t nbg, hipStream_t st
   // panels (one pass over it per kSuper * P columns); inside a super-panel each panel
   // first receives the contributions of the super-panel's earlier panels (a strip
   // update of its own rows), then is factored (diagonal block) and solved (row panel).
-  constexpr int P = Mf<T>::P, kSuper = 4;
+  constexpr int P = Mf<T>::P, kSuper = 4;  // eight made the fp32 solves 5-20% slower (their strips' six products)
   const bool x6 = sizeof(T) == 4 && d % 4 == 0;
   const bool x6r = x6 && m % 4 == 0 && m <= 256;  // right-hand sides inside the same launches
   const int64_t TM = (m + P - 1) / P;
@@ -1354,23 +1602,15 @@ hipError_t run_group(const SolveArgs& a, int64_t b0, int64_t nbg, hipStream_t st
       const int64_t pw = (d - pp) < P ? (d - pp) : P;
       const int64_t nrem = d - pp - pw;
       const int64_t nchF = (nrem + P - 1) / P;
-      if (pp > P0) {
+      if (pp > P0 && sizeof(T) == 8) {
         e = emit([=]() {
           const int64_t T2 = (d - pp + P - 1) / P;
-          if (x6) {
-            const int nF = (int)((d - pp + 255) / 256);
-            k_panel_x6<kX6Strip><<<dim3((unsigned)(nF + (x6r ? 1 : 0)), (unsigned)nm), 512, 0, st>>>(
-                d, P0, pp - P0, pp, (float*)F, (float*)R, m, nF);
-            if (!x6r)
-              k_panel_product<T, kTrailing><<<dim3((unsigned)TM, (unsigned)nm), kT, 0, st>>>(
-                  d, m, 0, P0, pp - P0, pp, 1, (int)T2, F, R);
-          } else if (reuse) {
+          if (reuse)
             k_panel_product<T, kTrailing><<<dim3((unsigned)TM, (unsigned)nm), kT, 0, st>>>(
                 d, m, 0, P0, pp - P0, pp, 1, (int)T2, F, R);
-          } else {
+          else
             k_panel_product<T, kTrailing><<<dim3((unsigned)(T2 + TM), (unsigned)nm), kT, 0, st>>>(
                 d, m, 0, P0, pp - P0, pp, 1, 0, F, R);
-          }
           return hipGetLastError();
         });
         if (e != hipSuccess) return e;
@@ -1378,20 +1618,18 @@ hipError_t run_group(const SolveArgs& a, int64_t b0, int64_t nbg, hipStream_t st
       const bool rec = after_diag && pp == 0;
       if (rec && emit.ops) emit.stagger_at = (int)emit.ops->size();
       e = emit([=]() {
-        if (!reuse) k_diag_inv<T, P><<<(unsigned)nm, 4 * P, 0, st>>>(d, pp, F, info);
+        if (!reuse) {
+          if (d % 4 == 0) k_diag_inv<T, P, true><<<(unsigned)nm, 4 * P, 0, st>>>(d, P0, pp, F, info);
+          else k_diag_inv<T, P, false><<<(unsigned)nm, 4 * P, 0, st>>>(d, P0, pp, F, info);
+        }
         const hipError_t er = hipGetLastError();
         if (er != hipSuccess || !rec) return er;
         return hipEventRecord(after_diag, st);
       });
       if (e != hipSuccess) return e;
       e = emit([=]() {
-        if (x6 && nrem > 0) {
-          const int nF = (int)((nrem + 255) / 256);
-          k_panel_x6<kX6Row><<<dim3((unsigned)(nF + (x6r ? 1 : 0)), (unsigned)nm), 512, 0, st>>>(
-              d, pp, pw, 0, (float*)F, (float*)R, m, nF);
-          if (!x6r)
-            k_panel_product<T, kRowPanel><<<dim3((unsigned)TM, (unsigned)nm), kT, 0, st>>>(d, m, pp, 0, 0, 0, 0,
-                                                                                                 (int)nchF, F, R);
+        if constexpr (sizeof(T) == 4) {
+          return launch_panel_f32(st, nm, d, P0, pp, (float*)F, (float*)R, m);
         } else if (reuse) {
           k_panel_product<T, kRowPanel><<<dim3((unsigned)TM, (unsigned)nm), kT, 0, st>>>(d, m, pp, 0, 0, 0, 0,
                                                                                           (int)nchF, F, R);
@@ -1485,21 +1723,23 @@ hipError_t run_group(const SolveArgs& a, int64_t b0, int64_t nbg, hipStream_t st
 }
 
 // Extra streams and events per device, made on first use: the only state the library
-// keeps.  The blocks of a call are split into up to kGroups groups on the caller's stream
+// keeps.  The blocks of a large call are split into kGroups groups on the caller's stream
 // and kGroups - 1 internal streams, group g started once group g - 1 has factored its
-// first diagonal block: the latency-bound launches of one group (diagonal blocks, strips,
+// first diagonal block: the latency-bound launches of one group (diagonal blocks,
 // back substitution: few workgroups each) then run beside the matrix-core updates of the
-// others instead of leaving most of the GPU idle.
+// other instead of leaving most of the GPU idle.  A call whose factorizations are below
+// kGroupFlops runs as one group: there the launches, not the matrix cores, set the time.
+// Whole solves with one, two and three groups: 84 matrices of d = 3584 11.98 / 11.55 /
+// 11.73 ms, 48 of 5120 18.91 / 17.84 / 17.98 ms; 28 of 1536 (3.4e10) 1253 / 1275 / 1332 us,
+// 24 of 896 736 / 938 / 1125 us.
 //
 // The streams and events are shared by every call on a device, so creating them and the
 // whole submission of a call that uses them (fork record, waits, launches, join records)
 // happen under the device's mutex.  A wait on an event takes the event's state at the time
 // the wait is enqueued, so once a call has left the critical section its internal work is
 // ordered behind its own fork point and the next call may record the events again.
-#ifndef LOCA_SOLVE_GROUPS
-#define LOCA_SOLVE_GROUPS 3
-#endif
-constexpr int kGroups = LOCA_SOLVE_GROUPS;
+constexpr int kGroups = 2;
+constexpr double kGroupFlops = 5e10;
 constexpr int kMaxDevices = 64;
 struct Aux {
   std::mutex mu;
@@ -1542,7 +1782,8 @@ hipError_t run_solve(const SolveArgs& a) {
   k_fill_zero_i32<<<(unsigned)((nm + 255) / 256), 256, 0, a.stream>>>(a.dev_info, nm);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int G = (int)(a.nb < kGroups ? a.nb : kGroups);
+  const bool large = (double)nm * (double)d * (double)d * (double)d / 3.0 >= kGroupFlops;
+  const int G = large ? (int)(a.nb < kGroups ? a.nb : kGroups) : 1;
   if (G < 2) {
     Emit now;
     return run_group<T, ST>(a, 0, a.nb, a.stream, F, R, D, Mp, SLp, dlam, nullptr, now);
