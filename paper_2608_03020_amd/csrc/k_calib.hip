@@ -5,9 +5,8 @@
 // block b, d x Np), in its dual form (Section S5's theorem): F_hat = G_b (E^T E + beta I)^{-1} E^T,
 // evaluated as a Cholesky solve in Np unknowns:
 //   1. Gamma = E^T E (fp64, split over the rows of E, fixed-order sums);
-//   2. Gamma + beta I = L L^T (one workgroup, fp64);
-//   3. R = (Gamma + beta I)^{-1} E^T (Np x d), one column of E^T per thread (forward and
-//      back substitution with L);
+//   2. Gamma + beta I = U^T U and X = U^{-1} (one workgroup, fp64);
+//   3. R = (Gamma + beta I)^{-1} E^T = X (X^T E^T) (Np x d);
 //   4. the best rank-k approximation F_b = U_k S_k V_k^T of F_hat = G_b R (the rank-
 //      truncation lemma of Section S5) with the factored Eckart-Young truncation of the
 //      hot path (M = G_b, right factor R shared by all blocks);
@@ -27,139 +26,140 @@ constexpr int kT = 256;
 constexpr int kMaxNp = 64;
 constexpr int kRows = 32;
 
+LOCA_DEV double to_f64(float v) { return (double)v; }
+LOCA_DEV double to_f64(double v) { return v; }
+LOCA_DEV double to_f64(uint16_t v) { return (double)bf16_to_f32(v); }
+
 // part[(b * ns + z) * kL * kR + j * kR + n] = sum_{c in rows of z} L_b(c, j) R_b(c, n), fp64,
-// L_b(c, j) = L[b * l_bs + c * l_sc + j * l_sj] (likewise R); rows split in ns equal ranges
-// of 32-row multiples (grid: x = z, y = b).
-template <typename RT>
-__global__ __launch_bounds__(kT) void k_tall_cross(int64_t d, int kL, int kR, const float* __restrict__ L,
+// L_b(c, j) = L[b * l_bs + c * l_sc + j * l_sj] (likewise R), kL, kR <= 64; rows split in ns
+// equal ranges of 32-row multiples (grid: x = z, y = b).  On the fp64 matrix cores: wave
+// (wi, wj) of 2 x 2 owns the outputs 32 wi .., 32 wj .. as 2 x 2 blocks of 16 x 16 and loads
+// its operands straight into their layout (four rows of 16 consecutive j per load when l_sj =
+// 1), the next 32 rows in flight while the current ones are multiplied.  28 blocks of 3584 x
+// 64 by 64: 107 us with one fp64 FMA per pair of LDS reads; the calibration's figures stand at
+// launch_feedback_fit.
+template <typename LT, typename RT>
+__global__ __launch_bounds__(kT) void k_tall_cross(int64_t d, int kL, int kR, const LT* __restrict__ L,
                                                    int64_t l_bs, int64_t l_sc, int64_t l_sj,
                                                    const RT* __restrict__ R, int64_t r_bs, int64_t r_sc,
                                                    int64_t r_sn, int ns, double* __restrict__ part) {
-  __shared__ double sL[kRows][kMaxNp + 1];
-  __shared__ double sR[kRows][kMaxNp + 1];
+  constexpr int NS = kRows / 4;  // matrix-core steps per 32 rows
   const int64_t b = blockIdx.y;
   const int z = blockIdx.x;
   const int64_t chunk = ((d + ns - 1) / ns + kRows - 1) / kRows * kRows;
   const int64_t ib = (int64_t)z * chunk, ie = ib + chunk < d ? ib + chunk : d;
-  const float* Lb = L + b * l_bs;
-  const RT* Rb = R + b * r_bs;
-  const int nout = kL * kR;
-  double acc[(kMaxNp * kMaxNp) / kT];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, wi = wid >> 1, wj = wid & 1, li = lane & 15, lk = lane >> 4;
+  if (32 * wi >= kL || 32 * wj >= kR) return;
+  const LT* lp[2];  // entries past kL, kR read the last column: not stored
+  const RT* rp[2];
 #pragma unroll
-  for (int q = 0; q < (kMaxNp * kMaxNp) / kT; ++q) acc[q] = 0.0;
-  for (int64_t i0 = ib; i0 < ie; i0 += kRows) {
-    __syncthreads();
-    for (int e = threadIdx.x; e < kRows * kMaxNp; e += kT) {
-      const int r = e / kMaxNp, c = e % kMaxNp;
-      const int64_t i = i0 + r;
-      sL[r][c] = (i < ie && c < kL) ? (double)Lb[i * l_sc + c * l_sj] : 0.0;
-      sR[r][c] = (i < ie && c < kR) ? (double)Rb[i * r_sc + c * r_sn] : 0.0;
-    }
-    __syncthreads();
+  for (int q = 0; q < 2; ++q) {
+    const int j = 32 * wi + 16 * q + li, n = 32 * wj + 16 * q + li;
+    lp[q] = L + b * l_bs + (j < kL ? j : kL - 1) * l_sj;
+    rp[q] = R + b * r_bs + (n < kR ? n : kR - 1) * r_sn;
+  }
+  LT lv[NS][2];
+  RT rv[NS][2];
+  auto load = [&](int64_t i0) {
 #pragma unroll
-    for (int q = 0; q < (kMaxNp * kMaxNp) / kT; ++q) {
-      const int e = threadIdx.x + kT * q;
-      if (e < nout) {
-        const int j = e / kR, n = e % kR;
-        double s = acc[q];
-        for (int r = 0; r < kRows; ++r) s += sL[r][j] * sR[r][n];
-        acc[q] = s;
+    for (int t = 0; t < NS; ++t) {
+      const int64_t i = i0 + 4 * t + lk, ic = i < d ? i : d - 1;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        lv[t][q] = lp[q][ic * l_sc];
+        rv[t][q] = rp[q][ic * r_sc];
       }
     }
-  }
-  double* out = part + (b * ns + z) * (int64_t)nout;
+  };
+  f64x4_t acc[2][2];
 #pragma unroll
-  for (int q = 0; q < (kMaxNp * kMaxNp) / kT; ++q) {
-    const int e = threadIdx.x + kT * q;
-    if (e < nout) out[e] = acc[q];
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) acc[a][q] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  if (ib < ie) load(ib);
+  for (int64_t i0 = ib; i0 < ie; i0 += kRows) {
+    double fa[NS][2], fb[NS][2];
+#pragma unroll
+    for (int t = 0; t < NS; ++t)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const bool ok = i0 + 4 * t + lk < ie;
+        fa[t][q] = ok ? to_f64(lv[t][q]) : 0.0;
+        fb[t][q] = ok ? to_f64(rv[t][q]) : 0.0;
+      }
+    load(i0 + kRows);  // past the range: rows that exist, not used
+#pragma unroll
+    for (int t = 0; t < NS; ++t)
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) acc[a][q] = mfma_f64(fa[t][a], fb[t][q], acc[a][q]);
   }
+  double* out = part + (b * ns + z) * (int64_t)kL * kR;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int j = 32 * wi + 16 * a + lk + 4 * r, n = 32 * wj + 16 * q + li;
+        if (j < kL && n < kR) out[j * kR + n] = acc[a][q][r];
+      }
 }
 
-// Lmat = chol(sum_z part_z + beta I) (lower, np x np, fp64, row-major), one workgroup.
-__global__ __launch_bounds__(kT) void k_chol_small(int np_, int ns, const double* __restrict__ part, double beta,
-                                                   double* __restrict__ Lmat, int32_t* __restrict__ dev_info,
-                                                   int64_t nb) {
-  __shared__ double sA[kMaxNp][kMaxNp + 1];
-  const int tid = threadIdx.x;
-  for (int e = tid; e < np_ * np_; e += kT) {
-    const int i = e / np_, j = e % np_;
-    double s = 0.0;
-    for (int z = 0; z < ns; ++z) s += part[(int64_t)z * np_ * np_ + e];
-    sA[i][j] = s + (i == j ? beta : 0.0);
-  }
-  __syncthreads();
-  for (int j = 0; j < np_; ++j) {
-    if (tid == 0) {
-      const double piv = sA[j][j];
-      if (!(piv > 0.0))
-        for (int64_t b = 0; b < nb; ++b) atomicCAS(&dev_info[b], 0, j + 1);
-      sA[j][j] = sqrt(piv);
-    }
-    __syncthreads();
-    for (int i = j + 1 + tid; i < np_; i += kT) sA[i][j] /= sA[j][j];
-    __syncthreads();
-    for (int e = tid; e < (np_ - j - 1) * (np_ - j - 1); e += kT) {
-      const int i = j + 1 + e / (np_ - j - 1), c = j + 1 + e % (np_ - j - 1);
-      if (c <= i) sA[i][c] -= sA[i][j] * sA[c][j];
-    }
-    __syncthreads();
-  }
-  for (int e = tid; e < np_ * np_; e += kT) {
-    const int i = e / np_, j = e % np_;
-    Lmat[e] = j <= i ? sA[i][j] : 0.0;
-  }
+// Gamma + beta I (np x np, fp64) from the partials, in the order of the row ranges.
+__global__ void k_gamma_sum(int np_, int ns, const double* __restrict__ part, double beta, double* __restrict__ out) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= np_ * np_) return;
+  double s = 0.0;
+  for (int z = 0; z < ns; ++z) s += part[(int64_t)z * np_ * np_ + e];
+  out[e] = s + (e / np_ == e % np_ ? beta : 0.0);
 }
 
-// R[:, c] = (L L^T)^{-1} E[c, :]^T for every column c < d (thread per column; R is np x d).
-__global__ __launch_bounds__(kT) void k_ridge_cols(int64_t d, int np_, const float* __restrict__ E,
-                                                   const double* __restrict__ Lmat, float* __restrict__ R) {
-  __shared__ double sL[kMaxNp * kMaxNp];
-  for (int e = threadIdx.x; e < np_ * np_; e += kT) sL[e] = Lmat[e];
-  __syncthreads();
-  const int64_t c = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (c >= d) return;
-  double y[kMaxNp];
+// R[:, c] = X X^T E[c, :]^T for every column c < d (R is np x d), X = U^{-1} (np x np, upper) of
+// U^T U = Gamma + beta I: Y = X^T E^T, then R = X Y, both on the fp64 matrix cores.  A wave owns
+// 16 columns; a result of the first product is, where the matrix cores leave it, an operand of
+// the second (rows 16 a + 4 r + lane / 16 of lane are step r of block a).
+__global__ __launch_bounds__(64) void k_ridge_cols(int64_t d, int np_, const float* __restrict__ E,
+                                                   const double* __restrict__ X, float* __restrict__ R) {
+  const int lane = threadIdx.x, li = lane & 15, lk = lane >> 4;
+  const int64_t c = (int64_t)blockIdx.x * 16 + li;
+  const float* Ec = E + (c < d ? c : d - 1) * np_;
+  auto x = [&](int i, int k) { return i < np_ && k < np_ ? X[i * np_ + k] : 0.0; };
+  double ev[16];
 #pragma unroll
-  for (int i = 0; i < kMaxNp; ++i) y[i] = i < np_ ? (double)E[c * np_ + i] : 0.0;
-  // forward: L y' = e
+  for (int s = 0; s < 16; ++s) ev[s] = 4 * s + lk < np_ ? (double)Ec[4 * s + lk] : 0.0;
+  f64x4_t y[4];
 #pragma unroll
-  for (int i = 0; i < kMaxNp; ++i) {
-    if (i < np_) {
-      double s = y[i];
+  for (int a = 0; a < 4; ++a) {
+    y[a] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int j = 0; j < i; ++j) s -= sL[i * np_ + j] * y[j];
-      y[i] = s / sL[i * np_ + i];
-    }
-  }
-  // back: L^T x = y'
-#pragma unroll
-  for (int i = kMaxNp - 1; i >= 0; --i) {
-    if (i < np_) {
-      double s = y[i];
-#pragma unroll
-      for (int j = i + 1; j < kMaxNp; ++j)
-        if (j < np_) s -= sL[j * np_ + i] * y[j];
-      y[i] = s / sL[i * np_ + i];
-    }
+    for (int s = 0; s < 4 * (a + 1); ++s) y[a] = mfma_f64(x(4 * s + lk, 16 * a + li), ev[s], y[a]);  // X[j][i] = 0, j > i
   }
 #pragma unroll
-  for (int i = 0; i < kMaxNp; ++i)
-    if (i < np_) R[(int64_t)i * d + c] = (float)y[i];
+  for (int a = 0; a < 4; ++a) {
+    f64x4_t o = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 4 * a; s < 16; ++s) o = mfma_f64(x(16 * a + li, 4 * s + lk), y[s / 4][s % 4], o);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 16 * a + lk + 4 * r;
+      if (i < np_ && c < d) R[(int64_t)i * d + c] = (float)o[r];
+    }
+  }
 }
 
 // Per block: B~ = S_k U_k^T from U_k^T (a) and sigma; V_k = (V_k S_k) / S_k from b (zero where
-// sigma = 0), kept for A~.  Grid: x over d, y = block.
+// sigma = 0), kept for A~.  One thread per entry of each, in memory order.  Grid: x over d k, y = block.
 __global__ void k_calib_factors(int64_t d, int k, int np_, const float* __restrict__ a, const float* __restrict__ bvs,
                                 const float* __restrict__ sigma, float* __restrict__ bt_out, int64_t bt_bstride,
                                 float* __restrict__ vk) {
   const int64_t b = blockIdx.y;
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= d) return;
-  for (int j = 0; j < k; ++j) {
-    const float s = sigma[b * np_ + j];
-    bt_out[b * bt_bstride + (int64_t)j * d + c] = s * a[(b * k + j) * d + c];
-    vk[(b * d + c) * k + j] = s > 0.f ? bvs[(b * d + c) * k + j] / s : 0.f;
-  }
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= d * k) return;
+  const float su = sigma[b * np_ + e / d], sv = sigma[b * np_ + e % k];
+  bt_out[b * bt_bstride + e] = su * a[b * k * d + e];
+  vk[b * d * k + e] = sv > 0.f ? bvs[b * d * k + e] / sv : 0.f;
 }
 
 // alpha_b = <P, Q> / (||Q|| ||G||) from the fixed-order sums of the partial products
@@ -168,10 +168,11 @@ __global__ void k_calib_factors(int64_t d, int k, int np_, const float* __restri
 // pP + h * nb * ns * k * 64 with row length w_h, those of G_h^T G_h at pG2 + h * nb * ns * 64 * 64).
 // One workgroup per block: thread e sums entry e over the row ranges in order, then
 // fixed-order workgroup sums.
-__global__ __launch_bounds__(kT) void k_calib_alpha(int64_t nb, int k, int np_, int ns, const double* __restrict__ pP,
+constexpr int kTA = 1024;
+__global__ __launch_bounds__(kTA) void k_calib_alpha(int64_t nb, int k, int np_, int ns, const double* __restrict__ pP,
                                                     const double* __restrict__ pQ, const double* __restrict__ pG2,
                                                     double* __restrict__ alpha_out) {
-  __shared__ double red[3][kT / 64];
+  __shared__ double red[3][kTA / 64];
   const int64_t b = blockIdx.x;
   double pq = 0.0, qq = 0.0, gg = 0.0;
   for (int h = 0; h * kMaxNp < np_; ++h) {
@@ -179,8 +180,9 @@ __global__ __launch_bounds__(kT) void k_calib_alpha(int64_t nb, int k, int np_, 
     const double* P = pP + (int64_t)h * nb * ns * k * kMaxNp;
     const double* Q = pQ + (int64_t)h * nb * ns * k * kMaxNp;
     const double* G2 = pG2 + (int64_t)h * nb * ns * kMaxNp * kMaxNp;
-    for (int e = threadIdx.x; e < k * w; e += kT) {
+    for (int e = threadIdx.x; e < k * w; e += kTA) {
       double p = 0.0, q = 0.0;
+#pragma unroll 4
       for (int z = 0; z < ns; ++z) {
         p += P[(b * ns + z) * k * w + e];
         q += Q[(b * ns + z) * k * w + e];
@@ -188,7 +190,8 @@ __global__ __launch_bounds__(kT) void k_calib_alpha(int64_t nb, int k, int np_, 
       pq += p * q;
       qq += q * q;
     }
-    for (int e = threadIdx.x; e < w; e += kT)
+    for (int e = threadIdx.x; e < w; e += kTA)
+#pragma unroll 4
       for (int z = 0; z < ns; ++z) gg += G2[(b * ns + z) * w * w + e * w + e];
   }
   pq = block_sum(pq, red[0]);
@@ -302,6 +305,17 @@ __global__ __launch_bounds__(kT) void k_head_fold(int64_t vocab, int64_t d, int 
       const int col = 32 * q + (lane & 31);
       if (row < vocab && col < k) at_out[b * at_bstride + row * k + col] = acc[q][r];
     }
+}
+
+// at_out[b][v][j] = sum_z part_z (k_tall_cross partials of W_u V_k), in order
+__global__ void k_fold_sum(int cnt, int ns, const double* __restrict__ part, float* __restrict__ at_out,
+                           int64_t at_bstride) {
+  const int64_t b = blockIdx.y;
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= cnt) return;
+  double s = 0.0;
+  for (int z = 0; z < ns; ++z) s += part[(b * ns + z) * cnt + e];
+  at_out[b * at_bstride + e] = (float)s;
 }
 
 // vk_out[b][c][j] = V_k (the internal copy, d x k per block, packed)
@@ -426,13 +440,13 @@ hipError_t launch_realization_error(const FitArgs& a) {
   k_fit_lams<<<1, 64, 0, st>>>(fl, dlam, (int)nl);
   const dim3 g((unsigned)ns, (unsigned)nb);
   // R R^T from the rows of R (R^T(c, j) = R[j][c])
-  k_tall_cross<float><<<g, kT, 0, st>>>(d, (int)kp, (int)kp, a.r, a.r_bstride, 1, d, a.r, a.r_bstride, 1, d, ns, pRR);
+  k_tall_cross<float, float><<<g, kT, 0, st>>>(d, (int)kp, (int)kp, a.r, a.r_bstride, 1, d, a.r, a.r_bstride, 1, d, ns, pRR);
   if (rp > 0) {
     if (a.acc == LOCA_F64)
-      k_tall_cross<double><<<g, kT, 0, st>>>(d, (int)rp, (int)k, a.lp, a.lp_bstride, rp, 1, (const double*)a.K,
+      k_tall_cross<float, double><<<g, kT, 0, st>>>(d, (int)rp, (int)k, a.lp, a.lp_bstride, rp, 1, (const double*)a.K,
                                              a.k_bstride, k, 1, ns, pLK);
     else
-      k_tall_cross<float><<<g, kT, 0, st>>>(d, (int)rp, (int)k, a.lp, a.lp_bstride, rp, 1, (const float*)a.K,
+      k_tall_cross<float, float><<<g, kT, 0, st>>>(d, (int)rp, (int)k, a.lp, a.lp_bstride, rp, 1, (const float*)a.K,
                                             a.k_bstride, k, 1, ns, pLK);
   }
   for (int64_t l = 0; l < nl; ++l) {
@@ -441,14 +455,14 @@ hipError_t launch_realization_error(const FitArgs& a) {
     double* oMK = pMK + l * nb * ns * kp * k;
     double* oMM = pMM + l * nb * ns * kp * kp;
     if (a.acc == LOCA_F64)
-      k_tall_cross<double><<<g, kT, 0, st>>>(d, (int)kp, (int)k, Ml, mbs, kp, 1, (const double*)a.K, a.k_bstride, k,
+      k_tall_cross<float, double><<<g, kT, 0, st>>>(d, (int)kp, (int)k, Ml, mbs, kp, 1, (const double*)a.K, a.k_bstride, k,
                                              1, ns, oMK);
     else
-      k_tall_cross<float><<<g, kT, 0, st>>>(d, (int)kp, (int)k, Ml, mbs, kp, 1, (const float*)a.K, a.k_bstride, k,
+      k_tall_cross<float, float><<<g, kT, 0, st>>>(d, (int)kp, (int)k, Ml, mbs, kp, 1, (const float*)a.K, a.k_bstride, k,
                                             1, ns, oMK);
-    k_tall_cross<float><<<g, kT, 0, st>>>(d, (int)kp, (int)kp, Ml, mbs, kp, 1, Ml, mbs, kp, 1, ns, oMM);
+    k_tall_cross<float, float><<<g, kT, 0, st>>>(d, (int)kp, (int)kp, Ml, mbs, kp, 1, Ml, mbs, kp, 1, ns, oMM);
     if (rp > 0)
-      k_tall_cross<float><<<g, kT, 0, st>>>(d, (int)rp, (int)kp, a.lp, a.lp_bstride, rp, 1, Ml, mbs, kp, 1, ns,
+      k_tall_cross<float, float><<<g, kT, 0, st>>>(d, (int)rp, (int)kp, a.lp, a.lp_bstride, rp, 1, Ml, mbs, kp, 1, ns,
                                             pLM + l * nb * ns * rp * kp);
   }
   k_fit_finalize<<<(unsigned)(nb * nl), kT, 0, st>>>(nb, (int)nl, (int)kp, (int)k, (int)rp, ns, pMK, pMM, pRR, pLK,
@@ -469,7 +483,7 @@ size_t calib_factor_ws(int64_t nb, int64_t d, int64_t kp, int64_t k) {
 }
 
 hipError_t launch_calib_factors(const CalibArgs& a, const float* M, int64_t m_bs, const float* R, int64_t r_bs,
-                                int64_t r_group, int64_t kp, char* p, float** ut_out, float** vs_out) {
+                                int64_t r_group, int64_t kp, char* p, float** ut_out, float** vs_out, double* fold_part) {
   const int64_t d = a.d, k = a.k, nb = a.nb;
   float* ut = (float*)p; p += align256(sizeof(float) * nb * k * d);
   float* vs = (float*)p; p += align256(sizeof(float) * nb * d * k);
@@ -481,13 +495,28 @@ hipError_t launch_calib_factors(const CalibArgs& a, const float* M, int64_t m_bs
               tinfo, p};
   hipError_t e = launch_lowrank_truncate(t);
   if (e != hipSuccess) return e;
-  k_calib_factors<<<dim3((unsigned)((d + 255) / 256), (unsigned)nb), 256, 0, st>>>(
+  k_calib_factors<<<dim3((unsigned)((d * k + 255) / 256), (unsigned)nb), 256, 0, st>>>(
       d, (int)k, (int)kp, ut, vs, a.sigma_out, a.bt_out, a.bt_bstride, vk);
   if (a.vk_out) {
     dim3 g((unsigned)((d * k + 255) / 256), (unsigned)nb);
     k_copy_vk<<<g, 256, 0, st>>>(d, (int)k, vk, a.vk_out, a.vk_bstride);
   }
-  if (a.wu && a.at_out) {
+  // The head fold of a label set of at most 64 classes, given room for its partials (nb ns 64 k
+  // doubles), splits the width instead of the head's rows, of which one workgroup holds them all
+  // and walks the width alone (five classes, 28 blocks of 3584: 163 us).
+  if (a.wu && a.at_out && a.vocab <= kMaxNp && fold_part) {
+    const int ns = calib_splits(d);
+    const dim3 g((unsigned)ns, (unsigned)nb);
+    if (a.wu_dtype == LOCA_BF16)
+      k_tall_cross<uint16_t, float><<<g, kT, 0, st>>>(d, (int)a.vocab, (int)k, (const uint16_t*)a.wu, 0, 1, d, vk, d * k,
+                                                      k, 1, ns, fold_part);
+    else
+      k_tall_cross<float, float><<<g, kT, 0, st>>>(d, (int)a.vocab, (int)k, (const float*)a.wu, 0, 1, d, vk, d * k, k, 1,
+                                                   ns, fold_part);
+    const int cnt = (int)(a.vocab * k);
+    k_fold_sum<<<dim3((unsigned)((cnt + 255) / 256), (unsigned)nb), 256, 0, st>>>(cnt, ns, fold_part, a.at_out,
+                                                                                  a.at_bstride);
+  } else if (a.wu && a.at_out) {
     dim3 g((unsigned)((a.vocab + kFoldR - 1) / kFoldR), (unsigned)nb);
     if (a.wu_dtype == LOCA_BF16)
       k_head_fold<uint16_t><<<g, kT, 0, st>>>(a.vocab, d, (int)k, (const uint16_t*)a.wu, vk, a.at_out, a.at_bstride);
@@ -537,7 +566,7 @@ static hipError_t fit_tail(const CalibArgs& a, const float* R, char* p) {
   double* pG = apart + 2 * nch * nb * ns * k * kMaxNp;
   hipStream_t st = a.stream;
   float *ut = nullptr, *vs = nullptr;
-  hipError_t e = launch_calib_factors(a, a.g, a.g_bstride, R, 0, nb, np_, p, &ut, &vs);
+  hipError_t e = launch_calib_factors(a, a.g, a.g_bstride, R, 0, nb, np_, p, &ut, &vs, apart);
   if (e != hipSuccess) return e;
   // P = U_k^T G (U_k^T is k x d: L(c, j) = ut[j * d + c]); Q = (V_k S_k)^T E; ||G||^2 from the
   // diagonal of G^T G; each over column chunks of at most 64 probes
@@ -545,17 +574,22 @@ static hipError_t fit_tail(const CalibArgs& a, const float* R, char* p) {
     const int64_t c0 = h * kMaxNp;
     const int w = (int)(np_ - c0 < kMaxNp ? np_ - c0 : kMaxNp);
     const dim3 g((unsigned)ns, (unsigned)nb);
-    k_tall_cross<float><<<g, kT, 0, st>>>(d, (int)k, w, ut, k * d, 1, d, a.g + c0, a.g_bstride, np_, 1, ns,
+    k_tall_cross<float, float><<<g, kT, 0, st>>>(d, (int)k, w, ut, k * d, 1, d, a.g + c0, a.g_bstride, np_, 1, ns,
                                           pP + h * nb * ns * k * kMaxNp);
-    k_tall_cross<float><<<g, kT, 0, st>>>(d, (int)k, w, vs, d * k, k, 1, a.e + c0, 0, np_, 1, ns,
+    k_tall_cross<float, float><<<g, kT, 0, st>>>(d, (int)k, w, vs, d * k, k, 1, a.e + c0, 0, np_, 1, ns,
                                           pQ + h * nb * ns * k * kMaxNp);
-    k_tall_cross<float><<<g, kT, 0, st>>>(d, w, w, a.g + c0, a.g_bstride, np_, 1, a.g + c0, a.g_bstride, np_, 1, ns,
+    k_tall_cross<float, float><<<g, kT, 0, st>>>(d, w, w, a.g + c0, a.g_bstride, np_, 1, a.g + c0, a.g_bstride, np_, 1, ns,
                                           pG + h * nb * ns * kMaxNp * kMaxNp);
   }
-  k_calib_alpha<<<(unsigned)nb, kT, 0, st>>>(nb, (int)k, (int)np_, ns, pP, pQ, pG, a.alpha_out);
+  k_calib_alpha<<<(unsigned)nb, kTA, 0, st>>>(nb, (int)k, (int)np_, ns, pP, pQ, pG, a.alpha_out);
   return hipGetLastError();
 }
 
+// 28 blocks of d = 3584 from 64 probes, k = 32, five classes: 1413 us while the tall products
+// were LDS-bound (4 x 107 us), the Cholesky of Gamma took three barriers per column in one
+// workgroup (133 us), R one thread per column (14 workgroups, 120 us) and the head fold one
+// workgroup per block (163 us); now 655 us, of which the tall products take 4 x 24, the fold
+// 29, Gamma's factor 15, R 21 and the truncation core 355.
 hipError_t launch_feedback_fit(const CalibArgs& a) {
   const int64_t d = a.d, np_ = a.np_, nb = a.nb;
   const int ns = calib_splits(d);
@@ -567,11 +601,14 @@ hipError_t launch_feedback_fit(const CalibArgs& a) {
     double* gpart = (double*)p; p += align256(sizeof(double) * ns * np_ * np_);
     double* Lmat = (double*)p; p += align256(sizeof(double) * np_ * np_);
     float* R = (float*)p;
-    k_tall_cross<float><<<dim3((unsigned)ns, 1), kT, 0, st>>>(d, (int)np_, (int)np_, a.e, 0, np_, 1, a.e, 0, np_, 1,
+    k_tall_cross<float, float><<<dim3((unsigned)ns, 1), kT, 0, st>>>(d, (int)np_, (int)np_, a.e, 0, np_, 1, a.e, 0, np_, 1,
                                                               ns, gpart);
-    k_chol_small<<<1, kT, 0, st>>>((int)np_, ns, gpart, a.beta, Lmat, a.dev_info, nb);
-    k_ridge_cols<<<(unsigned)((d + kT - 1) / kT), kT, 0, st>>>(d, (int)np_, a.e, Lmat, R);
-    hipError_t e = hipGetLastError();
+    k_gamma_sum<<<(unsigned)((np_ * np_ + 255) / 256), 256, 0, st>>>((int)np_, ns, gpart, a.beta, Lmat);
+    hipError_t e = launch_chol_inv64(st, np_, Lmat, a.dev_info);  // X = U^{-1}, U^T U = Gamma + beta I
+    if (e != hipSuccess) return e;
+    k_copy_info<<<1, 64, 0, st>>>(a.dev_info, a.dev_info, nb);
+    k_ridge_cols<<<(unsigned)((d + 15) / 16), 64, 0, st>>>(d, (int)np_, a.e, Lmat, R);
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     return fit_tail(a, R, p);
   }

@@ -1848,6 +1848,11 @@ size_t ridge_solve_ws(int64_t nb, int64_t d, int64_t m, int64_t n_lambda, loca_d
   return s;
 }
 
+hipError_t launch_chol_inv64(hipStream_t s, int64_t n, double* A, int32_t* info) {
+  k_diag_inv<double, 64, true><<<1, 256, 0, s>>>(n, 0, 0, A, info);
+  return hipGetLastError();
+}
+
 hipError_t launch_ridge_solve(const SolveArgs& a) {
   if (a.acc == LOCA_F64) return run_solve<double, double>(a);
   return run_solve<float, float>(a);

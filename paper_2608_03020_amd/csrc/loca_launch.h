@@ -162,7 +162,7 @@ hipError_t launch_feedback_fit_large(const CalibArgs& a);
 // returns U_k^T (k x d) and V_k S_k (d x k) per block, both inside the workspace.
 size_t calib_factor_ws(int64_t nb, int64_t d, int64_t kp, int64_t k);
 hipError_t launch_calib_factors(const CalibArgs& a, const float* M, int64_t m_bs, const float* R, int64_t r_bs,
-                                int64_t r_group, int64_t kp, char* ws, float** ut, float** vs);
+                                int64_t r_group, int64_t kp, char* ws, float** ut, float** vs, double* fold_part = nullptr);
 
 // Realisation error of the fitted adapters (Section S6).
 struct FitArgs {
@@ -185,6 +185,9 @@ hipError_t launch_dense_targets(hipStream_t s, int64_t nb, int64_t n, int64_t k,
                                 const float* y, int64_t y_bstride, const loca_mb* mb,
                                 const float* credit_b, int64_t b_bstride, float* t_out,
                                 int64_t t_bstride);
+// A (n x n fp64, n <= 64, upper part read) = U^T U; U^{-1} over A, zero below its diagonal.
+// *info, when 0, takes the first non-positive pivot (1-based).
+hipError_t launch_chol_inv64(hipStream_t s, int64_t n, double* A, int32_t* info);
 // out (rows x cols) = L (rows x kk, ld kk) * R (kk x cols, ld cols), float, batched.
 hipError_t launch_lowrank_product(hipStream_t s, int64_t nmat, int64_t rows, int64_t cols,
                                   int64_t kk, const float* L, int64_t l_bstride, int64_t l_ld,

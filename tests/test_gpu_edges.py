@@ -99,3 +99,40 @@ def test_ridge_solve_block_edges(d, acc):
         for i, lam in enumerate(lams):
             ref = np.linalg.solve(ref_s[b] + lam * np.eye(d), K[b].double().cpu().numpy())
             assert rel(M[b, i].cpu().numpy(), ref) < (9 * np.sqrt(d) * 2.0 ** -24 if acc == "f32" else 0) + 2.0 ** -23
+
+
+# the dual fit at the edges of its 16-wide blocks and 32-row ranges, and the head fold on both
+# sides of the 64-class split.  float32 outputs of float64 sums; the map's truncation at rank k
+# amplifies rounding by sigma_k / (sigma_k - sigma_k+1), kept small by a rank-k probe map
+@pytest.mark.parametrize("d,n_p,k,V,wu16", [(16, 16, 4, 1, 0), (33, 17, 5, 3, 1), (300, 63, 8, 64, 0),
+                                            (1031, 64, 12, 65, 1), (2048, 31, 16, 40, 0), (65, 1, 1, 7, 0)])
+def test_dual_fit_edges(d, n_p, k, V, wu16):
+    import torch
+    from paper_2608_03020_amd import loca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + n_p)
+    nb, beta = 3, 0.1
+    rn = lambda *s: torch.randn(s, generator=g, device="cuda")
+    E = rn(d, n_p)
+    G = rn(nb, d, k) / d ** 0.5 @ (rn(nb, k, d) @ E) + 0.01 * rn(nb, d, n_p)
+    Wu = rn(V, d) / d ** 0.5
+    Wu = Wu.to(torch.bfloat16) if wu16 else Wu
+    kw = dict(dtype=torch.float32, device="cuda")
+    bt, at = torch.full((nb, k, d), float("nan"), **kw), torch.full((nb, V, k), float("nan"), **kw)
+    sig, info = torch.empty((nb, n_p), **kw), torch.full((nb,), 9, dtype=torch.int32, device="cuda")
+    alpha = torch.empty(nb, dtype=torch.float64, device="cuda")
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_FEEDBACK_FIT, nb, n_p, d, k))
+    ws.fill_(255)
+    log("dual fit", d, n_p, k, V, wu16)
+    loca.loca_feedback_fit(E, G, beta, bt, sig, alpha, info, ws, wu=Wu, at_out=at)
+    assert info.eq(0).all()
+    e = E.double().cpu().numpy()
+    for b in range(nb):
+        gb = G[b].double().cpu().numpy()
+        F = gb @ np.linalg.solve(e.T @ e + beta * np.eye(n_p), e.T)
+        U, s, Vt = np.linalg.svd(F, full_matrices=False)
+        Fk = (U[:, :k] * s[:k]) @ Vt[:k]
+        assert rel(sig[b].cpu().numpy()[:k], s[:k]) < 1e-6
+        FE = Fk @ e
+        assert abs(float(alpha[b]) - (FE * gb).sum() / np.linalg.norm(FE) / np.linalg.norm(gb)) < 1e-6
+        assert rel((at[b].double() @ bt[b].double()).cpu().numpy(), Wu.double().cpu().numpy() @ Fk.T) < 5e-6
