@@ -6,17 +6,18 @@
 // e_t = W_u^T E_t of the paper's order (then V_k^T e_t per block); Vm = [A~_1 | ... | A~_L]
 // gives every block's credit coordinates Y_b = E A~_b at once.
 //
-// The logits are never stored.  A workgroup (8 waves) owns 128 tokens, a tile of at most 64
-// columns of Vm and a contiguous range of the vocabulary, and walks that range in chunks
-// of 256:
-//   1. z^T (256 x 128) = W_u[chunk] h_rows^T on the matrix cores (v_mfma_f32_32x32x16_bf16,
+// The logits are never stored.  A workgroup (8 waves) owns 256 tokens (128 for calls of at most
+// 128), a tile of at most 64 columns of Vm and a contiguous range of the vocabulary, and walks
+// that range in chunks of 256:
+//   1. z^T (256 x tokens) = W_u[chunk] h_rows^T on the matrix cores (v_mfma_f32_32x32x16_bf16,
 //      fp32 accumulation), both operands copied straight into LDS (buffer loads to LDS) in
-//      32-wide slices of d through a four-slot ring that runs across chunk boundaries;
-//   2. an online softmax per token, in registers: the running maximum m and sum s (fp32)
-//      are updated with the chunk, the accumulated output is rescaled by exp(m_old - m_new),
-//      and P = exp(z - m_new) is split into bf16 hi + lo parts (about 16 significant bits);
+//      64-wide slices of d through two slots that run across chunk boundaries;
+//   2. an online softmax per token, in registers: the running maximum m and sums s (fp32)
+//      are updated with the chunk, the accumulated output is rescaled by exp(m_old - m_new)
+//      where m rose, and P = exp(z - m_new) is split into bf16 hi + lo parts (about 16
+//      significant bits);
 //   3. out += (P_hi + P_lo) Vm[chunk] on the matrix cores (Vm exact in bf16), P taken from
-//      the registers of step 1 and the Vm^T slice from LDS.
+//      the registers of step 1 and Vm, laid out as the other operand beforehand, from cache.
 // Each vocabulary range leaves (m, s) per token and its partial output; a second kernel
 // combines the ranges in a fixed order in float64 and subtracts the label term.  Columns of
 // Vm beyond one 64-wide tile recompute the logits (c / 64 passes over W_u).
@@ -27,26 +28,23 @@ namespace loca {
 
 namespace {
 
-constexpr int kFT = 512;        // threads: 8 waves, (vocabulary quarter wv) x (token half wt)
-constexpr int kFR = 128;        // tokens per tile
+constexpr int kFT = 512;        // threads: 8 waves, (vocabulary part wv) x (64-token part wt)
 constexpr int kFV = 256;        // vocabulary per chunk
 constexpr int kFC = 64;         // columns of Vm per tile
-constexpr int kFK = 32;         // hidden width per stage
-constexpr int kFStages = 4;     // ring slots: three stages in flight while one is read
-constexpr int kFLA = kFStages - 1;
-constexpr int kFStage = (kFV + kFR) * kFK * 2;  // bytes per stage: W_u rows, then h rows (64 B each)
-constexpr int kFCopies = kFStage / 16 / kFT;     // 16-byte copies per thread per stage (3)
-constexpr int kFVt = kFC * kFV * 2;              // bytes of the Vm^T slice
-constexpr int kFNV = kFVt / 16 / kFT;            // its copies per thread (4)
+constexpr int kFK = 64;         // hidden width per stage: whole 128-byte lines of W_u and h
+// Tile shapes by tokens TR: TR / 64 token parts, the rest of the eight waves splitting the
+// vocabulary chunk; two ring slots of 64 KB (TR = 256) or 48 KB (TR = 128).
+template <int TR> struct FusedTile {
+  static constexpr int WT = TR / 64, WV = 8 / WT;      // waves along the tokens, along the vocabulary
+  static constexpr int MV = kFV / WV / 32;             // 32-entry vocabulary blocks per wave
+  static constexpr int STAGE = (kFV + TR) * kFK * 2;   // bytes per stage: W_u rows, then h rows (128 B each)
+  static constexpr int COPIES = STAGE / 16 / kFT;      // 16-byte copies per thread per stage (8 or 6)
+};
 
-// A stage holds 384 rows of 64 bytes (32 bf16 of d): rows 0..255 the chunk's W_u rows,
-// rows 256..383 the tile's h rows.  Chunk c (16 bytes) of row r sits at position
-// c ^ ((r >> 2) & 3), so that the 16 lanes of a half wave reading one chunk of 16
-// consecutive rows hit 16 distinct bank groups.
-LOCA_DEV int fz_swz(int r) { return (r >> 2) & 3; }
-// The Vm^T slice: 64 rows (columns of Vm) of 512 bytes (256 vocabulary entries), chunk c
-// of row r at position c ^ (r & 15).
-LOCA_DEV int fv_swz(int r) { return r & 15; }
+// A stage holds 256 + TR rows of 128 bytes (64 bf16 of d): rows 0..255 the chunk's W_u rows,
+// then the tile's h rows.  Chunk c (16 bytes) of row r sits at position c ^ ((r >> 1) & 7), so
+// that the 16 lanes that read one chunk of 16 consecutive rows hit 16 distinct bank groups.
+LOCA_DEV int fz_swz(int r) { return (r >> 1) & 7; }
 
 // (m, s) of two disjoint parts of a row, combined
 LOCA_DEV void fz_combine(float& m, float& s, float m2, float s2) {
@@ -76,84 +74,63 @@ LOCA_DEV void wait_vm(int a) {
 
 // The logits are formed transposed, z^T = W_u[chunk] h_tile^T (vocabulary x tokens), so
 // that lane l of a 32 x 32 result block holds token l % 32 and 16 vocabulary entries:
-// the softmax statistics of a token stay within a lane pair (l, l ^ 32) and the four
-// waves that split the chunk's vocabulary, and the exponentials of a block are already
+// the softmax statistics of a token stay within a lane pair (l, l ^ 32) and the waves
+// that split the chunk's vocabulary, and the exponentials of a block are already
 // the matrix-core operand of the product with Vm (the sum over the vocabulary taken in
-// the order the result layout gives).
+// the order the result layout gives; k_vm_frag lays Vm out as the other operand).  The waves
+// share a token's running maximum, exchanged once per chunk; each keeps the sum of its own
+// exponentials, and the sums meet at the end.
 //
-// Copy accounting: stage s is issued kFLA iterations ahead of its use (the prologue issues
-// stages 0 .. kFLA - 1); the Vm^T slice of chunk j is issued at the top of iteration j nks,
-// before that iteration's stage.  Every wait counts the copies issued after the one it
-// needs, and vector-memory operations complete in order.
+// Bound by the matrix cores and the stream of W_u and h from L2: a stage's copies are (256 + TR)
+// rows for 256 TR products per unit of d, so 256 tokens a tile stream a third less per product
+// than 128.  n = 4096, V = 151936, d = 2048, 64 columns: 5.35 ms with 128 tokens, slices of 32
+// (half lines, each line fetched twice), run-time stage arithmetic and every exponential taken
+// twice; 2.56 ms now (1.03 PFLOP/s).
+template <int TR>
 __global__ __launch_bounds__(kFT) void k_fused_head(int64_t n, int64_t V, int64_t d, int64_t c,
                                                     const uint16_t* __restrict__ h, int64_t ldh,
                                                     const uint16_t* __restrict__ wu,
-                                                    const uint16_t* __restrict__ vmt, int64_t ldvt, int ntr, int nct,
-                                                    int64_t vper, float* __restrict__ part_o,
-                                                    float2* __restrict__ part_ms) {
-  __shared__ __attribute__((aligned(1024))) uint8_t ring[kFStages * kFStage];
-  __shared__ __attribute__((aligned(1024))) uint8_t sVt[kFVt];
-  __shared__ float2 sEx[4][kFR];
+                                                    const uint16_t* __restrict__ vmf, int ntr, int nct, int64_t vper,
+                                                    float* __restrict__ part_o, float2* __restrict__ part_ms) {
+  typedef FusedTile<TR> TL;
+  constexpr int WT = TL::WT, WV = TL::WV, MV = TL::MV, VW = kFV / WV, NCP = TL::COPIES;
   constexpr int NQ = kFC / 32;  // 32-column output blocks per wave
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, wv = wid >> 1, wt = wid & 1;
-  const int l32 = lane & 31, lh = lane >> 5;
+  __shared__ __attribute__((aligned(1024))) uint8_t ring[2 * TL::STAGE];
+  __shared__ float sEx[WV][TR];
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wv = wid / WT, wt = wid % WT, l32 = lane & 31, lh = lane >> 5;
   // tiles that share a vocabulary range are consecutive within an XCD (W_u read once there)
   const int logical = xcd_logical((int)blockIdx.x, (int)gridDim.x);
   const int rt = logical % ntr, ct = (logical / ntr) % nct, sp = logical / (ntr * nct);
-  const int64_t r0 = (int64_t)rt * kFR, c0 = (int64_t)ct * kFC;
+  const int64_t r0 = (int64_t)rt * TR, c0 = (int64_t)ct * kFC;
   const int64_t vb = (int64_t)sp * vper, ve = (vb + vper < V) ? vb + vper : V;
   const int nks = (int)((d + kFK - 1) / kFK);
   const int nch = (int)((ve - vb + kFV - 1) / kFV);
-  const int total = nch * nks;  // stages of this workgroup
 
-  const int64_t nrow = (n - r0 < kFR) ? n - r0 : kFR;
+  const int64_t nrow = (n - r0 < TR) ? n - r0 : TR;
   const i32x4_t rsH = buffer_rsrc(h + r0 * ldh, (uint32_t)(nrow * ldh * 2));
-  const int64_t ncol = (c - c0 < kFC) ? c - c0 : kFC;
-  const i32x4_t rsV = buffer_rsrc(vmt + c0 * ldvt, (uint32_t)(ncol * ldvt * 2));
   const uint32_t ring_lds = (uint32_t)(uintptr_t)(LOCA_LDS void*)ring;
-  const uint32_t vt_lds = (uint32_t)(uintptr_t)(LOCA_LDS void*)sVt;
-  const int wq = __builtin_amdgcn_readfirstlane(wid);
-
-  // stage g = (chunk g / nks, slice g % nks) into ring slot g % kFStages: 24 blocks of 1 KB
-  // (16 rows each), blocks 0..15 the W_u rows, 16..23 the h rows; byte offsets fit 31 bits
-  // (V, d, ldh <= 2^23 are checked by the caller)
-  auto issue_stage = [&](int g) {
-    const int64_t v0 = vb + (int64_t)(g / nks) * kFV;
-    const int k0 = (g % nks) * kFK;
-    const uint32_t slot = ring_lds + (uint32_t)((g % kFStages) * kFStage);
+  // Copy j of a wave fills the 1 KB block (8 rows) wid + 8 j of a stage: W_u rows for j < 4, then
+  // h rows.  Lane l takes row l / 8 of the block, position l % 8.  Byte offsets fit 31 bits (V, d,
+  // ldh <= 2^23 are checked by the caller); rows past V or n lie past the buffer and read zero.
+  // Blocks eight apart hold rows 64 apart, which share the swizzle: one offset per operand.
+  const int crow = 8 * wid + (lane >> 3);
+  const uint32_t ck = 8u * (uint32_t)((lane & 7) ^ fz_swz(crow));  // the lane's first k in a slice
+  const uint32_t offw = 2u * ((uint32_t)crow * (uint32_t)d + ck), offh = 2u * ((uint32_t)crow * (uint32_t)ldh + ck);
+  const uint32_t stepw = 128u * (uint32_t)d, steph = 128u * (uint32_t)ldh;
+  auto issue_stage = [&](i32x4_t rsW, int ks, int slot) {
+    const uint32_t dst = ring_lds + (uint32_t)(slot * TL::STAGE + wid * 1024), k0 = (uint32_t)(ks * kFK);
+    const bool in = k0 + ck < (uint32_t)d;
+#pragma unroll
+    for (int j = 0; j < NCP; ++j) {
+      const uint32_t step = j < kFV / 64 ? j * stepw : (j - kFV / 64) * steph;
+      const uint32_t off = in ? (j < kFV / 64 ? offw : offh) + (step + 2u * k0) : kBufOutside;
+      lds_dma16_buf(off, j < kFV / 64 ? rsW : rsH, dst + (uint32_t)(j * 8192));
+    }
+  };
+  auto rsrc_w = [&](int64_t v0) {
     const int64_t nvr = (V - v0 < kFV) ? V - v0 : kFV;
-    const i32x4_t rsW = buffer_rsrc(wu + v0 * d, (uint32_t)(nvr * d * 2));
-#pragma unroll
-    for (int j = 0; j < kFCopies; ++j) {
-      const int blk = wq * kFCopies + j;
-      const int row = 16 * blk + (lane >> 2);
-      const int k = k0 + 8 * ((lane & 3) ^ fz_swz(row));
-      if (blk < kFV / 16) {
-        const uint32_t off = k < (int)d ? 2u * (uint32_t)(row * (int)d + k) : kBufOutside;
-        lds_dma16_buf(off, rsW, slot + (uint32_t)blk * 1024u);
-      } else {
-        const uint32_t off = k < (int)d ? 2u * (uint32_t)((row - kFV) * (int)ldh + k) : kBufOutside;
-        lds_dma16_buf(off, rsH, slot + (uint32_t)blk * 1024u);
-      }
-    }
-  };
-  // the chunk's Vm^T slice (64 columns of Vm x 256 vocabulary entries; zero past V)
-  auto issue_vt = [&](int64_t v0) {
-#pragma unroll
-    for (int j = 0; j < kFNV; ++j) {
-      const int blk = wq * kFNV + j;  // 1 KB: rows 2 blk, 2 blk + 1
-      const int row = 2 * blk + (lane >> 5);
-      const uint32_t off = 2u * (uint32_t)(row * (int)ldvt + (int)v0 + 8 * ((lane & 31) ^ fv_swz(row)));
-      lds_dma16_buf(off, rsV, vt_lds + (uint32_t)blk * 1024u);
-    }
-  };
-  // copies issued before the top of iteration g, and up to and including stage s
-  auto issued_before = [&](int g) {
-    const int st = (g + kFLA < total) ? g + kFLA : total;
-    return kFCopies * st + kFNV * (g >= 1 ? (g - 1) / nks + 1 : 0);
-  };
-  auto through_stage = [&](int s) {
-    return kFCopies * (s + 1) + kFNV * (s >= kFLA ? (s - kFLA) / nks + 1 : 0);
+    return buffer_rsrc(wu + v0 * d, (uint32_t)(nvr * d * 2));
   };
 
   f32x16_t o[2][NQ];
@@ -163,115 +140,106 @@ __global__ __launch_bounds__(kFT) void k_fused_head(int64_t n, int64_t V, int64_
     for (int q = 0; q < NQ; ++q)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[mt][q][r] = 0.f;
-  float m_run[2] = {-__builtin_inff(), -__builtin_inff()}, s_run[2] = {0.f, 0.f};  // token l32 of block mt
-  f32x16_t z[2][2];
+  // token l32 of block mt: the running maximum, and the sum of this lane's exponentials
+  float m_run[2] = {-__builtin_inff(), -__builtin_inff()}, s_run[2] = {0.f, 0.f};
+  // operand addresses in a slot: row r's chunk 2 kk + lh at 128 r + 16 ((2 kk + lh) ^ swz(r)); rows
+  // 32 apart share the swizzle
+  const uint32_t ra = (uint32_t)(wv * VW + l32), rb = (uint32_t)(kFV + wt * 64 + l32);
+  const uint32_t la = 128 * ra + 16 * (uint32_t)(lh ^ fz_swz((int)ra)), lb = 128 * rb + 16 * (uint32_t)(lh ^ fz_swz((int)rb));
 
-  for (int s = 0; s < kFLA && s < total; ++s) issue_stage(s);
-  for (int g = 0; g < total; ++g) {
-    const int ks = g % nks;
-    wait_vm(issued_before(g) - through_stage(g));
-    __syncthreads();  // every thread's copies of stage g landed; the slot refilled below is free
-    if (ks == 0) {
-      issue_vt(vb + (int64_t)(g / nks) * kFV);
+  i32x4_t rsW = rsrc_w(vb);
+  int slot = 0;
+  if (nch > 0) issue_stage(rsW, 0, 0);
+  for (int j = 0; j < nch; ++j) {
+    const int64_t v0 = vb + (int64_t)j * kFV;
+    // 1. z^T = W_u[chunk] h[tile]^T
+    f32x16_t z[MV][2];
 #pragma unroll
-      for (int mv = 0; mv < 2; ++mv)
+    for (int mv = 0; mv < MV; ++mv)
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+      for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) z[mv][mt][r] = 0.f;
-    }
-    if (g + kFLA < total) issue_stage(g + kFLA);
-    // 1. z^T += W_u[chunk, slice] h[tile, slice]^T
-    const uint8_t* st = ring + (g % kFStages) * kFStage;
-#pragma unroll
-    for (int kk = 0; kk < kFK / 16; ++kk) {
-      bf16x8_t a[2], b[2];
-      const int ch = 2 * kk + lh;  // 16-byte chunk of the row: k = 16 kk + 8 lh
-#pragma unroll
-      for (int mv = 0; mv < 2; ++mv) {
-        const int row = wv * 64 + 32 * mv + l32;
-        a[mv] = *(const bf16x8_t*)(st + row * 64 + 16 * (ch ^ fz_swz(row)));
+        for (int r = 0; r < 16; ++r) z[mv][mt][r] = 0.f;
+    for (int ks = 0; ks < nks; ++ks) {
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // the stage landed (this thread's copies)
+      barrier_nofence();                         // ... everyone's; the other slot is no longer read
+      if (ks + 1 < nks) {
+        issue_stage(rsW, ks + 1, slot ^ 1);
+      } else if (j + 1 < nch) {
+        rsW = rsrc_w(v0 + kFV);
+        issue_stage(rsW, 0, slot ^ 1);
       }
+      const uint8_t* st = ring + slot * TL::STAGE;
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt) {
-        const int row = kFV + wt * 64 + 32 * mt + l32;
-        b[mt] = *(const bf16x8_t*)(st + row * 64 + 16 * (ch ^ fz_swz(row)));
+      for (int kk = 0; kk < kFK / 16; ++kk) {
+        bf16x8_t a[MV], b[2];
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) b[mt] = *(const bf16x8_t*)(st + (lb ^ (32u * kk)) + 4096 * mt);
+#pragma unroll
+        for (int mv = 0; mv < MV; ++mv) a[mv] = *(const bf16x8_t*)(st + (la ^ (32u * kk)) + 4096 * mv);
+#pragma unroll
+        for (int mv = 0; mv < MV; ++mv)
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt) z[mv][mt] = mfma32(a[mv], b[mt], z[mv][mt]);
       }
-#pragma unroll
-      for (int mv = 0; mv < 2; ++mv)
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) z[mv][mt] = mfma32(a[mv], b[mt], z[mv][mt]);
+      slot ^= 1;
     }
-    if (ks != nks - 1) continue;
 
     // 2. online softmax over the chunk.  Entry r of lane l in block (mv, mt): vocabulary
-    // v0 + 64 wv + 32 mv + 8 (r >> 2) + 4 lh + (r & 3), token 64 wt + 32 mt + l32.
-    const int j = g / nks;
-    const int64_t v0 = vb + (int64_t)j * kFV;
-    const int nv = (V - v0 < kFV) ? (int)(V - v0) : kFV;
-    const bool full = nv == kFV;
-    auto valid = [&](int mv, int r) { return full || 64 * wv + 32 * mv + 8 * (r >> 2) + 4 * lh + (r & 3) < nv; };
-    float lm[2], ls[2];
+    // v0 + VW wv + 32 mv + 8 (r >> 2) + 4 lh + (r & 3), token 64 wt + 32 mt + l32.
+    if (V - v0 < kFV) {  // the ragged last chunk: entries past V are excluded
+      const int nv = (int)(V - v0);
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-      float mx = -__builtin_inff();
-#pragma unroll
-      for (int mv = 0; mv < 2; ++mv)
+      for (int mv = 0; mv < MV; ++mv)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          if (valid(mv, r)) mx = fmaxf(mx, z[mv][mt][r]);
+          if (VW * wv + 32 * mv + 8 * (r >> 2) + 4 * lh + (r & 3) >= nv) z[mv][0][r] = z[mv][1][r] = -__builtin_inff();
+    }
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+      float mx = z[0][mt][0];
+#pragma unroll
+      for (int mv = 0; mv < MV; ++mv)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, z[mv][mt][r]);
       mx = fmaxf(mx, __shfl_xor(mx, 32));
-      float sm = 0.f;
-      if (mx > -__builtin_inff()) {
-#pragma unroll
-        for (int mv = 0; mv < 2; ++mv)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (valid(mv, r)) sm += __expf(z[mv][mt][r] - mx);
-      }
-      sm += __shfl_xor(sm, 32);
-      lm[mt] = mx;
-      ls[mt] = sm;
+      if (lh == 0) sEx[wv][wt * 64 + 32 * mt + l32] = mx;
     }
-    if (lh == 0)
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt) sEx[wv][wt * 64 + 32 * mt + l32] = make_float2(lm[mt], ls[mt]);
-    // the Vm^T slice of this chunk: covered by the stage waits when a later stage was issued
-    // after it and has been waited for (nks > kFLA), else waited for here
-    if (nks <= kFLA) {
-      const int g0 = j * nks;
-      const int after_vt = kFCopies * ((g + kFLA + 1 < total ? g + kFLA + 1 : total) -
-                                       (g0 + kFLA < total ? g0 + kFLA : total));
-      wait_vm(after_vt);
-    }
-    __syncthreads();
-    float al[2];
+    wave_lds_sync();
+    barrier_nofence();
+    float al[2], ms[2];
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
       const int tk = wt * 64 + 32 * mt + l32;
-      float cm = sEx[0][tk].x, cs = sEx[0][tk].y;
+      float mn = m_run[mt];
 #pragma unroll
-      for (int u = 1; u < 4; ++u) fz_combine(cm, cs, sEx[u][tk].x, sEx[u][tk].y);  // the same order in all waves
-      const float mn = fmaxf(m_run[mt], cm);
-      al[mt] = __expf(m_run[mt] - mn);
-      s_run[mt] = s_run[mt] * al[mt] + cs * __expf(cm - mn);
+      for (int u = 0; u < WV; ++u) mn = fmaxf(mn, sEx[u][tk]);
+      ms[mt] = mn == -__builtin_inff() ? 0.f : mn;  // nothing but excluded entries so far
+      al[mt] = __expf(m_run[mt] - ms[mt]);
       m_run[mt] = mn;
+      s_run[mt] *= al[mt];
     }
-    // rescale the output rows: row r of an output block is token 8 (r >> 2) + 4 lh + (r & 3)
+    // rescale the output rows where a maximum rose: row r of an output block is token
+    // 8 (r >> 2) + 4 lh + (r & 3)
+    if (__ballot(al[0] != 1.f || al[1] != 1.f))
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+      for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float a_r = __shfl(al[mt], 8 * (r >> 2) + 4 * lh + (r & 3));
+        for (int r = 0; r < 16; ++r) {
+          const float a_r = __shfl(al[mt], 8 * (r >> 2) + 4 * lh + (r & 3));
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) o[mt][q][r] *= a_r;
-      }
+          for (int q = 0; q < NQ; ++q) o[mt][q][r] *= a_r;
+        }
     // 3. out += (P_hi + P_lo) Vm[chunk]: k step (mv, ks2) takes the entries r = 8 ks2 .. 8 ks2 + 7
+    const uint4* vf = (const uint4*)vmf + (((v0 + VW * wv) / 16 * nct + ct) * NQ) * 64 + lane;
 #pragma unroll
-    for (int mv = 0; mv < 2; ++mv)
+    for (int mv = 0; mv < MV; ++mv)
 #pragma unroll
       for (int ks2 = 0; ks2 < 2; ++ks2) {
         bf16x8_t phi[2], plo[2], bv[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+          bv[q] = __builtin_bit_cast(bf16x8_t, vf[((int64_t)(2 * mv + ks2) * nct * NQ + q) * 64]);
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) {
           uint32_t hv[4], lv[4];
@@ -279,24 +247,14 @@ __global__ __launch_bounds__(kFT) void k_fused_head(int64_t n, int64_t V, int64_
           for (int e2 = 0; e2 < 4; ++e2) {
             // hi and lo parts rounded to nearest even by the hardware conversion, in pairs
             const int r = 8 * ks2 + 2 * e2;
-            const float p0 = valid(mv, r) ? __expf(z[mv][mt][r] - m_run[mt]) : 0.f;
-            const float p1 = valid(mv, r + 1) ? __expf(z[mv][mt][r + 1] - m_run[mt]) : 0.f;
+            const float p0 = __expf(z[mv][mt][r] - ms[mt]), p1 = __expf(z[mv][mt][r + 1] - ms[mt]);
+            s_run[mt] += p0 + p1;
             const uint32_t h2 = cvt_pk_bf16(p0, p1);
             hv[e2] = h2;
             lv[e2] = cvt_pk_bf16(p0 - bf16_lo(h2), p1 - bf16_hi(h2));
           }
           phi[mt] = __builtin_bit_cast(bf16x8_t, make_uint4(hv[0], hv[1], hv[2], hv[3]));
           plo[mt] = __builtin_bit_cast(bf16x8_t, make_uint4(lv[0], lv[1], lv[2], lv[3]));
-        }
-        // B entry e of lane (col, lh): vocabulary 64 wv + 32 mv + 16 ks2 + 8 (e >> 2) + 4 lh + (e & 3)
-        const int va = 64 * wv + 32 * mv + 16 * ks2 + 4 * lh, vc = va + 8;
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-          const int row = 32 * q + l32;
-          const uint8_t* rp = sVt + row * (2 * kFV);
-          const uint2 lo4 = *(const uint2*)(rp + 16 * ((va >> 3) ^ fv_swz(row)) + 2 * (va & 7));
-          const uint2 hi4 = *(const uint2*)(rp + 16 * ((vc >> 3) ^ fv_swz(row)) + 2 * (vc & 7));
-          bv[q] = __builtin_bit_cast(bf16x8_t, make_uint4(lo4.x, lo4.y, hi4.x, hi4.y));
         }
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
@@ -308,32 +266,40 @@ __global__ __launch_bounds__(kFT) void k_fused_head(int64_t n, int64_t V, int64_
       }
   }
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-  __syncthreads();  // the ring is free: the four vocabulary quarters' outputs meet there
-  // partial outputs summed as (O_0 + O_2) + (O_1 + O_3), in a fixed order
-  float* red = (float*)ring;  // 2 x 128 tokens x (64 + 4) floats
+  __syncthreads();  // the ring is free: the vocabulary parts' sums and outputs meet there
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt) {
+    s_run[mt] += __shfl_xor(s_run[mt], 32);
+    if (lh == 0) sEx[wv][wt * 64 + 32 * mt + l32] = s_run[mt];
+  }
+  // partial outputs summed in a fixed order: (O_0 + O_2) + (O_1 + O_3), or O_0 + O_1
+  float* red = (float*)ring;  // WV / 2 x TR tokens x (64 + 4) floats
   constexpr int RLD = kFC + 4;
-  auto put = [&](int slot) {
+  static_assert(WV / 2 * TR * RLD * 4 <= 2 * TL::STAGE, "the outputs fit the ring");
+  auto put = [&](int slot2) {
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
       for (int q = 0; q < NQ; ++q)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          red[(slot * kFR + wt * 64 + 32 * mt + 8 * (r >> 2) + 4 * lh + (r & 3)) * RLD + 32 * q + l32] = o[mt][q][r];
+          red[(slot2 * TR + wt * 64 + 32 * mt + 8 * (r >> 2) + 4 * lh + (r & 3)) * RLD + 32 * q + l32] = o[mt][q][r];
   };
-  auto add = [&](int slot) {
+  auto add = [&](int slot2) {
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
       for (int q = 0; q < NQ; ++q)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          o[mt][q][r] += red[(slot * kFR + wt * 64 + 32 * mt + 8 * (r >> 2) + 4 * lh + (r & 3)) * RLD + 32 * q + l32];
+          o[mt][q][r] += red[(slot2 * TR + wt * 64 + 32 * mt + 8 * (r >> 2) + 4 * lh + (r & 3)) * RLD + 32 * q + l32];
   };
-  if (wv >= 2) put(wv - 2);
-  __syncthreads();
-  if (wv < 2) add(wv);
-  __syncthreads();
+  if (WV == 4) {
+    if (wv >= 2) put(wv - 2);
+    __syncthreads();
+    if (wv < 2) add(wv);
+    __syncthreads();
+  }
   if (wv == 1) put(0);
   __syncthreads();
   if (wv == 0) {
@@ -352,10 +318,33 @@ __global__ __launch_bounds__(kFT) void k_fused_head(int64_t n, int64_t V, int64_
     if (ct == 0 && lh == 0)
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt) {
-        const int64_t row = r0 + wt * 64 + 32 * mt + l32;
-        if (row < n) part_ms[(int64_t)sp * n + row] = make_float2(m_run[mt], s_run[mt]);
+        const int tk = wt * 64 + 32 * mt + l32;
+        const int64_t row = r0 + tk;
+        float sm = sEx[0][tk];
+#pragma unroll
+        for (int u = 1; u < WV; ++u) sm += sEx[u][tk];
+        if (row < n) part_ms[(int64_t)sp * n + row] = make_float2(m_run[mt], sm);
       }
   }
+}
+
+// Vm as k_fused_head's second operand: 16 vocabulary entries x 32 columns a fragment of 64 lanes x
+// 16 bytes, fragment (g, q) of vocabulary entries 16 g .. and columns 32 q .. (q < 2 nct) at 1 KB x
+// (2 nct g + q); lane l holds column 32 q + l % 32 and the entries 8 (e / 4) + 4 (l / 32) + e % 4,
+// e = 0..7 (the order in which the logits' result layout leaves them).  Zero past V and c.
+__global__ void k_vm_frag(int64_t V, int64_t c, const uint16_t* __restrict__ vm, int64_t ld_vm, int nq, int64_t nfrag,
+                          uint4* __restrict__ vmf) {
+  const int64_t f = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (f >= nfrag) return;
+  const int lane = threadIdx.x & 63;
+  const int64_t g = f / nq, col = 32 * (f % nq) + (lane & 31);
+  uint32_t x[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int64_t v = 16 * g + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+    x[e] = (v < V && col < c) ? vm[v * ld_vm + col] : (uint16_t)0;
+  }
+  vmf[f * 64 + lane] = make_uint4(x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16), x[6] | (x[7] << 16));
 }
 
 // dev_info protocol: INT32_MAX while nothing is wrong; atomicMin with 1 + a bad row or with
@@ -626,21 +615,32 @@ __global__ __launch_bounds__(256) void k_head_online(int64_t n, int64_t V, const
 }
 
 struct FusedPlan {
-  int ct, ntr, nct, nsp;
+  int ct, tr, ntr, nct, nsp;
   int64_t vper, ldvt;
 };
 
 FusedPlan fused_plan(int64_t n, int64_t V, int64_t c) {
   FusedPlan p;
   p.ct = kFC;  // a wider column tile holds more accumulators than the register file keeps
-  p.ntr = (int)((n + kFR - 1) / kFR);
+  // 256 tokens a tile unless half of them would be empty
+  p.tr = n > 128 ? 256 : 128;
+  p.ntr = (int)((n + p.tr - 1) / p.tr);
   p.nct = (int)((c + p.ct - 1) / p.ct);
   const int64_t tiles = (int64_t)p.ntr * p.nct, nchunk = (V + kFV - 1) / kFV;
-  int64_t want = (1024 + tiles - 1) / tiles;  // about four workgroups per compute unit
-  if (want > kMaxFusedSplits) want = kMaxFusedSplits;
-  if (want > nchunk) want = nchunk;
-  if (want < 1) want = 1;
-  p.vper = ((nchunk + want - 1) / want) * kFV;
+  // One workgroup fits a compute unit: the number of vocabulary ranges with the least rounds of
+  // 256 workgroups times chunks per range (and half a chunk's time per round for its prologue and
+  // its write of the partial outputs).
+  int64_t best = 1;
+  double cost = 1e300;
+  for (int64_t s = 1; s <= kMaxFusedSplits && s <= nchunk; ++s) {
+    const int64_t per = (nchunk + s - 1) / s, ns = (nchunk + per - 1) / per;
+    const double t = (double)((tiles * ns + 255) / 256) * ((double)per + 0.5);
+    if (t < cost) {
+      cost = t;
+      best = per;
+    }
+  }
+  p.vper = best * kFV;
   p.nsp = (int)((V + p.vper - 1) / p.vper);  // every range holds at least one chunk
   p.ldvt = nchunk * kFV;
   return p;
@@ -705,7 +705,7 @@ size_t fused_head_ws(int64_t n, int64_t V, int64_t c) {
   const FusedPlan p = fused_plan(n, V, c);
   size_t s = align256(sizeof(float) * p.nsp * n * c);
   s += align256(sizeof(float2) * p.nsp * n);
-  s += align256(sizeof(uint16_t) * c * p.ldvt);
+  s += align256(sizeof(uint16_t) * p.nct * kFC * p.ldvt);
   return s;
 }
 
@@ -714,14 +714,19 @@ hipError_t launch_fused_head(const FusedArgs& a) {
   char* w = a.ws;
   float* part_o = (float*)w; w += align256(sizeof(float) * p.nsp * a.n * a.c);
   float2* part_ms = (float2*)w; w += align256(sizeof(float2) * p.nsp * a.n);
-  uint16_t* vmt = (uint16_t*)w;
+  uint16_t* vmf = (uint16_t*)w;
   hipStream_t st = a.stream;
   k_fused_info_init<<<1, 64, 0, st>>>(a.dev_info);
-  k_vm_transpose<<<dim3((unsigned)((p.ldvt + 31) / 32), (unsigned)((a.c + 31) / 32)), 256, 0, st>>>(
-      a.V, a.c, a.vm, a.ld_vm, a.c, 0, vmt, p.ldvt);
+  const int nq = p.nct * (kFC / 32);
+  const int64_t nfrag = p.ldvt / 16 * nq;
+  k_vm_frag<<<(unsigned)((nfrag + 3) / 4), 256, 0, st>>>(a.V, a.c, a.vm, a.ld_vm, nq, nfrag, (uint4*)vmf);
   const unsigned grid = (unsigned)((int64_t)p.ntr * p.nct * p.nsp);
-  k_fused_head<<<grid, kFT, 0, st>>>(a.n, a.V, a.d, a.c, a.h, a.ldh, a.wu, vmt, p.ldvt, p.ntr, p.nct, p.vper,
-                                          part_o, part_ms);
+  if (p.tr == 256)
+    k_fused_head<256><<<grid, kFT, 0, st>>>(a.n, a.V, a.d, a.c, a.h, a.ldh, a.wu, vmf, p.ntr, p.nct, p.vper, part_o,
+                                            part_ms);
+  else
+    k_fused_head<128><<<grid, kFT, 0, st>>>(a.n, a.V, a.d, a.c, a.h, a.ldh, a.wu, vmf, p.ntr, p.nct, p.vper, part_o,
+                                            part_ms);
   k_fused_combine<<<(unsigned)a.n, 256, 0, st>>>(a.n, a.c, a.V, p.nsp, part_o, part_ms, a.labels, a.w, a.vm, a.ld_vm,
                                                  a.c, 0, a.out, a.ld_out, 0, nullptr, a.dev_info);
   k_fused_info_finish<<<1, 64, 0, st>>>(a.dev_info);

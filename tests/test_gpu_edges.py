@@ -136,3 +136,35 @@ def test_dual_fit_edges(d, n_p, k, V, wu16):
         FE = Fk @ e
         assert abs(float(alpha[b]) - (FE * gb).sum() / np.linalg.norm(FE) / np.linalg.norm(gb)) < 1e-6
         assert rel((at[b].double() @ bt[b].double()).cpu().numpy(), Wu.double().cpu().numpy() @ Fk.T) < 5e-6
+
+
+# the fused head at the edges of its token tiles (128, 256), 256-entry vocabulary chunks, 64-wide
+# slices of d and 64-column tiles, with a maximum that rises late and an excluded tail.  The
+# exponentials carry 2^-17 (two bf16 parts), far below the 1e-5 asked of the output's norm
+@pytest.mark.parametrize("n,V,d,c", [(1, 1, 8, 1), (128, 255, 64, 64), (129, 257, 72, 33), (256, 256, 128, 65),
+                                     (257, 1000, 200, 130), (60, 5000, 1096, 4), (300, 777, 2048, 64)])
+def test_fused_head_edges(n, V, d, c):
+    import torch
+    from paper_2608_03020_amd import loca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + V + d)
+    rn = lambda *s: torch.randn(s, generator=g, device="cuda")
+    h, Wu, Vm = (2 * rn(n, d)).bfloat16(), (rn(V, d) / d ** 0.5).bfloat16(), rn(V, c).bfloat16()
+    Wu[-1] *= 6  # the last entry moves many maxima
+    y = torch.randint(0, V, (n,), generator=g, device="cuda", dtype=torch.int32)
+    w = torch.rand(n, generator=g, device="cuda")
+    out = torch.full((n, c), float("nan"), device="cuda")
+    info = torch.full((1,), 5, dtype=torch.int32, device="cuda")
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_FUSED_HEAD, 1, n, d, c, C=V))
+    ws.fill_(255)
+    log("fused head", n, V, d, c)
+    loca.loca_fused_head(h, Wu, y, Vm, out, info, ws, w=w)
+    assert int(info) == 0
+    H, W, M = (t.double().cpu().numpy() for t in (h, Wu, Vm))
+    z = H @ W.T
+    e = np.exp(z - z.max(1, keepdims=True))
+    e /= e.sum(1, keepdims=True)
+    e[np.arange(n), y.cpu().numpy()] -= 1
+    ref = (e @ M) * w.double().cpu().numpy()[:, None]
+    scale = np.linalg.norm(M) * np.linalg.norm(w.double().cpu().numpy()) / np.sqrt(V)
+    assert np.linalg.norm(out.double().cpu().numpy() - ref) < 1e-5 * max(scale, np.linalg.norm(ref))
