@@ -488,64 +488,121 @@ __global__ void k_error_finalize(int64_t n, int64_t nparts, const double* __rest
 }
 
 // Paper-order credit coordinates (Section S11): Y_b = e V_k,b (n x k) from the top errors
-// e (n x d) and sum_q2 partials as in the error kernels.  64 tokens per workgroup, d in
-// chunks of 64 through LDS; thread t owns token t % 64 and the columns t / 64 + 4u (u < KQ),
-// fp64 accumulation.
-template <int KQ>
+// e (n x d) and sum_q2 partials as in the error kernels, on the fp64 matrix cores (products of
+// floats exact, sums in fp64).  64 tokens per workgroup, wave (wi, wj) of 2 x 2 owning 32 of them and
+// the columns 32 wj .. of every 64 (NC 64-column tiles); d in chunks of 64 through LDS, the next chunk in
+// registers meanwhile.  ||q_t||^2 = Y_t G Y_t^T of the stored (float) coordinates is a second
+// product, T = Y G, then the sum of T Y entry by entry.  24 blocks of n = 4096, d = 896, k = 64 took
+// 1132 us with one fp64 FMA per LDS read and k^2 of them per token in one wave; 320 us now.
+template <int NC>
 __global__ __launch_bounds__(256) void k_credit_project(int64_t n, int64_t d, int64_t k, const float* __restrict__ e,
                                                         int64_t ld_e, const float* __restrict__ Vk, int64_t v_bstride,
                                                         const double* __restrict__ G, const float* __restrict__ aw,
                                                         float* __restrict__ y_out, int64_t y_bstride,
                                                         double* __restrict__ partial) {
-  constexpr int KW = 4 * KQ;
-  __shared__ float sE[64][65];
-  __shared__ float sV[64][KW];
-  __shared__ double sY[64][KW + 1];
+  constexpr int KW = 64 * NC, LDE = 66, LDV = KW + 16;  // rows apart by 2 and 16 banks: reads of either kind spread
+  __shared__ float sE[64 * LDE];
+  __shared__ float sV[64 * LDV];
+  __shared__ float sY[64 * (KW + 2)];
   __shared__ double sred[4];
   const int64_t b = blockIdx.y;
   const int64_t t0 = (int64_t)blockIdx.x * 64;
-  const int tid = threadIdx.x, r = tid & 63, q = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, wi = wid >> 1, wj = wid & 1, li = lane & 15, lk = lane >> 4;
   const float* V = Vk + b * v_bstride;
-  double acc[KQ];
+  float re[16], rv[16 * NC];
+  auto load = [&](int64_t c0) {
 #pragma unroll
-  for (int u = 0; u < KQ; ++u) acc[u] = 0.0;
+    for (int u = 0; u < 16; ++u) {
+      const int x = tid + 256 * u, rr = x / 64, cc = x % 64;
+      re[u] = ld_or_zero(e, (t0 + rr) * ld_e + c0 + cc, t0 + rr < n && c0 + cc < d);
+    }
+#pragma unroll
+    for (int u = 0; u < 16 * NC; ++u) {
+      const int x = tid + 256 * u, cc = x / KW, j = x % KW;
+      rv[u] = ld_or_zero(V, (c0 + cc) * k + j, c0 + cc < d && j < k);
+    }
+  };
+  f64x4_t acc[2][2 * NC];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int q = 0; q < 2 * NC; ++q) acc[a][q] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  auto col = [&](int q) { return 64 * (q >> 1) + 32 * wj + 16 * (q & 1); };  // first column of block q
+  load(0);
   for (int64_t c0 = 0; c0 < d; c0 += 64) {
     __syncthreads();
-    for (int x = tid; x < 64 * 64; x += 256) {
-      const int rr = x / 64, cc = x % 64;
-      sE[rr][cc] = (t0 + rr < n && c0 + cc < d) ? e[(t0 + rr) * ld_e + c0 + cc] : 0.f;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int x = tid + 256 * u;
+      sE[(x / 64) * LDE + x % 64] = re[u];
     }
-    for (int x = tid; x < 64 * KW; x += 256) {
-      const int cc = x / KW, j = x % KW;
-      sV[cc][j] = (c0 + cc < d && j < k) ? V[(c0 + cc) * k + j] : 0.f;
+#pragma unroll
+    for (int u = 0; u < 16 * NC; ++u) {
+      const int x = tid + 256 * u;
+      sV[(x / KW) * LDV + x % KW] = rv[u];
     }
     __syncthreads();
-    for (int cc = 0; cc < 64; ++cc) {
-      const double ev = (double)sE[r][cc];
+    if (c0 + 64 < d) load(c0 + 64);
+#pragma unroll 4
+    for (int s = 0; s < 64; s += 4) {
+      double fa[2], fb[2 * NC];
 #pragma unroll
-      for (int u = 0; u < KQ; ++u) acc[u] += ev * (double)sV[cc][q + 4 * u];
+      for (int a = 0; a < 2; ++a) fa[a] = (double)sE[(32 * wi + 16 * a + li) * LDE + s + lk];
+#pragma unroll
+      for (int q = 0; q < 2 * NC; ++q) fb[q] = (double)sV[(s + lk) * LDV + col(q) + li];
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int q = 0; q < 2 * NC; ++q)
+          if (col(q) < k) acc[a][q] = mfma_f64(fa[a], fb[q], acc[a][q]);
     }
   }
-  const int64_t t = t0 + r;
+  constexpr int LDY = KW + 2;
 #pragma unroll
-  for (int u = 0; u < KQ; ++u) {
-    const int j = q + 4 * u;
-    const float yv = (float)acc[u];
-    sY[r][j] = (double)yv;
-    if (t < n && j < k) y_out[b * y_bstride + t * k + j] = yv;
-  }
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int q = 0; q < 2 * NC; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 32 * wi + 16 * a + lk + 4 * r, j = col(q) + li;
+        const float yv = j < k ? (float)acc[a][q][r] : 0.f;
+        sY[row * LDY + j] = yv;
+        if (t0 + row < n && j < k) y_out[b * y_bstride + (t0 + row) * k + j] = yv;
+      }
   __syncthreads();
-  // q_t = Y_t G Y_t^T of the stored (float) coordinates, weighted by the statistic weight
-  double qv = 0.0;
-  if (tid < 64 && t0 + tid < n) {
-    const double* Gb = G + b * k * k;
-    for (int a2 = 0; a2 < k; ++a2) {
-      double rr = 0.0;
-      for (int c = 0; c < k; ++c) rr += Gb[a2 * k + c] * sY[tid][c];
-      qv += sY[tid][a2] * rr;
+  // T = Y G, then sum_t a_t T_t Y_t^T over this workgroup's tokens
+  const double* Gb = G + b * k * k;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int q = 0; q < 2 * NC; ++q) acc[a][q] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  for (int s = 0; s < k; s += 4) {
+    const int x = s + lk;
+    double fa[2], fb[2 * NC];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) fa[a] = (double)sY[(32 * wi + 16 * a + li) * LDY + x];  // columns past k are zero
+#pragma unroll
+    for (int q = 0; q < 2 * NC; ++q) {
+      const int j = col(q) + li;
+      fb[q] = ld_or_zero(Gb, (int64_t)x * k + j, x < k && j < k);
     }
-    if (aw) qv *= (double)aw[t0 + tid];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int q = 0; q < 2 * NC; ++q)
+        if (col(q) < k) acc[a][q] = mfma_f64(fa[a], fb[q], acc[a][q]);
   }
+  double qv = 0.0;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 32 * wi + 16 * a + lk + 4 * r;
+      double v = 0.0;
+#pragma unroll
+      for (int q = 0; q < 2 * NC; ++q) v += acc[a][q][r] * (double)sY[row * LDY + col(q) + li];
+      if (t0 + row < n) qv += aw ? v * (double)aw[t0 + row] : v;
+    }
   const double tot = block_sum(qv, sred);
   if (threadIdx.x == 0) partial[b * gridDim.x + blockIdx.x] = tot;
 }
@@ -805,13 +862,11 @@ hipError_t launch_credit_from_top_error(const CreditArgs& a) {
   double* partial = (double*)((char*)gpart + credit_gram_part_ws(a.nb, a.k));
   launch_credit_gram(a.stream, a.nb, a.k, a.d, a.credit_b, a.b_bstride, gpart, G, a.k);
   dim3 g((unsigned)((a.n + 63) / 64), (unsigned)a.nb);
-#define LOCA_PROJ(KQ)                                                                                          \
-  k_credit_project<KQ><<<g, 256, 0, a.stream>>>(a.n, a.d, a.k, a.e, a.ld_e, a.vk, a.v_bstride, G, a.a_w, a.y_out, \
+#define LOCA_PROJ(NC)                                                                                          \
+  k_credit_project<NC><<<g, 256, 0, a.stream>>>(a.n, a.d, a.k, a.e, a.ld_e, a.vk, a.v_bstride, G, a.a_w, a.y_out, \
                                                  a.y_bstride, partial)
-  if (a.k <= 16) LOCA_PROJ(4);
-  else if (a.k <= 32) LOCA_PROJ(8);
-  else if (a.k <= 64) LOCA_PROJ(16);
-  else LOCA_PROJ(32);
+  if (a.k <= 64) LOCA_PROJ(1);
+  else LOCA_PROJ(2);
 #undef LOCA_PROJ
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

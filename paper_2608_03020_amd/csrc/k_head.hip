@@ -8,8 +8,8 @@
 //
 //   1. k_softmax_stats: per token the row maximum m_t and s_t = sum_c exp(z_tc - m_t)
 //      (one workgroup per token, fixed-order combination of the partial pairs);
-//   2. k_top_error_gemm: part_z = P W_u over the vocabulary chunk z, P_tc = w_t exp(z_tc -
-//      m_t) / s_t formed while the logits tile is staged, split into bf16 hi + lo parts
+//   2. k_top_error_gemm: part_z = P W_u over the vocabulary range z, P_tc = w_t exp(z_tc -
+//      m_t) / s_t formed in registers from the logits, split into bf16 hi + lo parts
 //      (about 16 significant bits), each multiplied by the exact bf16 W_u on the matrix
 //      cores (v_mfma_f32_32x32x16_bf16; W_u read transposed from LDS);
 //   3. k_top_error_reduce: e = sum_z part_z in a fixed order (fp64), minus w_t W_u[y_t].
@@ -29,8 +29,6 @@ namespace loca {
 namespace {
 
 constexpr int kHT = 256;
-constexpr int kHM = 128, kHK = 32;  // token rows, vocabulary per stage
-constexpr int kLDA = kHK + 8;                  // bf16 per LDS row of P (80 bytes)
 
 // dev_info: INT32_MAX while no bad label is seen, then 1 + the smallest bad row, or
 // LOCA_INFO_NONFINITE once a row's softmax sum is not finite; INT32_MAX becomes 0 at the end
@@ -138,145 +136,150 @@ __global__ __launch_bounds__(kHT) void k_softmax_stats(int64_t n, int64_t V, con
   }
 }
 
-// Tiles of 128 tokens x HN columns (HN = 128, or 64 when there are at most 64 columns), one
-// vocabulary chunk per grid.z; four waves of 64 columns each: 2 x 2 waves of 64 x 64 (HN =
-// 128) or 4 x 1 of 32 x 64 (HN = 64).  Column j of the right operand is column j % kc of
-// group j / kc: W + (j / kc) w_bstride (V x kc bf16 each).  d = total columns.  Requires
-// ld % 8 == 0 (bf16) or % 4 == 0 (f32), kc % 8 == 0, d % kc == 0, kchunk % 32 == 0.
-template <typename LT, int HN>
-__global__ __launch_bounds__(kHT) void k_top_error_gemm(int64_t n, int64_t V, int64_t d, const LT* __restrict__ z,
-                                                        int64_t ld, const float* __restrict__ w,
-                                                        const float* __restrict__ ms, const uint16_t* __restrict__ wu,
-                                                        int64_t kc, int64_t w_bstride, int64_t kchunk,
-                                                        float* __restrict__ part) {
-  constexpr int WGN = HN / 64, WGM = 4 / WGN, WM = kHM / WGM, NBM = WM / 32;
-  constexpr int LDB = HN + 16;                  // bf16 per LDS row of W (conflict-free transpose reads)
-  constexpr int NQB = HN * kHK / 8 / kHT;       // 16-byte chunks of the W stage per thread
-  __shared__ __attribute__((aligned(16))) uint16_t sAh[2][kHM * kLDA];
-  __shared__ __attribute__((aligned(16))) uint16_t sAl[2][kHM * kLDA];
-  __shared__ __attribute__((aligned(16))) uint16_t sB[2][kHK * LDB];
-  const int64_t t0 = (int64_t)blockIdx.x * kHM, j0 = (int64_t)blockIdx.y * HN;
-  const int64_t cb = (int64_t)blockIdx.z * kchunk;
-  const int64_t ce = std::min<int64_t>(V, cb + kchunk);
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int wi = wid / WGN, wj = wid % WGN;
+// Tiles of 128 tokens x 32 NB columns, one vocabulary range each; four waves of 32 tokens and all
+// the columns.  The logits of a wave's tokens are the first operand as they lie: lane l's 16 bytes
+// are token l % 32 and eight consecutive entries, so P = w exp(z - m) / s is formed in registers,
+// once per column tile, and split into bf16 hi + lo (packed hardware conversions, loca_bf16.h).
+// The right operand's rows go straight to LDS in blocks of 64 entries (two stages of 32 rows x 256
+// columns, swizzled as in loca_common.h), double-buffered; a block's logits are loaded one block
+// ahead.  The column tiles of one token tile are neighbours on an XCD, so the logits come from
+// beyond its L2 once.  Column j of the right operand is column j % kc of group j / kc:
+// W + (j / kc) w_bstride (V x kc bf16 each); d = total columns.  Requires ld % 8 == 0 (bf16) or % 4
+// == 0 (f32), kc % 8 == 0, d % kc == 0, kchunk % 64 == 0.
+//
+// Bound by the matrix cores (the split doubles their work) and the exponentials beside them: n =
+// 4096, V = 151936, 896 columns took 4.50 ms in 128-column tiles that formed P seven times and
+// waited for each 32-entry stage's loads; the figures now stand at the launch.
+__device__ const uint32_t g_zero16[4] __attribute__((aligned(16))) = {0, 0, 0, 0};
+constexpr int kHT2 = 256, kHM = 128, kHK = 64;  // threads, token rows, vocabulary per block
+template <typename LT> struct LogitChunk;       // eight logits
+template <> struct LogitChunk<uint16_t> {
+  uint4 v;
+  // the chunk at p + c, of which [c, end) exists; past it the chunk at p + safe
+  LOCA_DEV void load(const uint16_t* p, int64_t c, int64_t end, int64_t safe) { v = *(const uint4*)(p + (c < end ? c : safe)); }
+  LOCA_DEV float get(int i) const {
+    const uint32_t x = i < 2 ? v.x : (i < 4 ? v.y : (i < 6 ? v.z : v.w));
+    return (i & 1) ? bf16_hi(x) : bf16_lo(x);
+  }
+};
+template <> struct LogitChunk<float> {
+  float4 a, b;
+  LOCA_DEV void load(const float* p, int64_t c, int64_t end, int64_t safe) {
+    a = *(const float4*)(p + (c < end ? c : safe));
+    b = *(const float4*)(p + (c + 4 < end ? c + 4 : safe));
+  }
+  LOCA_DEV float get(int i) const {
+    const float4 t = i < 4 ? a : b;
+    return (i & 3) == 0 ? t.x : ((i & 3) == 1 ? t.y : ((i & 3) == 2 ? t.z : t.w));
+  }
+};
 
-  // staging: A chunk q of this thread = row (tid + 256 q) / 4, vocabulary 8 ((tid + 256 q) % 4);
-  // B chunk q = vocabulary row (tid + 256 q) / (HN / 8), columns 8 ((tid + 256 q) % (HN / 8))
-  int arow[2], acol[2], brow[NQB], bcol[NQB];
-  float rmax[2], rscale[2];
-  const LT* zrow[2];  // this thread's logits rows (row 0 for rows past n: never read)
+template <typename LT, int NB>
+__global__ __launch_bounds__(kHT2, 2) void k_top_error_gemm(int64_t n, int64_t V, int64_t d, const LT* __restrict__ z,
+                                                           int64_t ld, const float* __restrict__ w,
+                                                           const float* __restrict__ ms,
+                                                           const uint16_t* __restrict__ wu, int64_t kc,
+                                                           int64_t w_bstride, int ntr, int nct, int64_t kchunk,
+                                                           float* __restrict__ part) {
+  constexpr int BLK = kHK * 256;  // bf16 of a block in LDS (rows of 256 columns, whatever NB)
+  __shared__ __attribute__((aligned(1024))) uint16_t sb0[BLK];
+  __shared__ __attribute__((aligned(1024))) uint16_t sb1[BLK];
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6), lh = lane >> 5;
+  const int logical = xcd_logical((int)blockIdx.x, (int)gridDim.x);
+  const int ct = logical % nct, rt = (logical / nct) % ntr, sp = logical / (nct * ntr);
+  const int64_t j0 = (int64_t)ct * 32 * NB, t0 = (int64_t)rt * kHM + 32 * wid;
+  const int64_t cb = (int64_t)sp * kchunk, ce = std::min<int64_t>(V, cb + kchunk);
+  const int nblk = (int)((ce - cb + kHK - 1) / kHK);
+
+  const int64_t t = t0 + (lane & 31);
+  const bool tok = t < n;
+  const LT* zr = z + (tok ? t : 0) * ld;
+  const float rmax = tok ? ms[2 * t] : 0.f;
+  const float rscale = tok ? (w ? w[t] : 1.f) / ms[2 * t + 1] : 0.f;
+
+  // copy q of this thread: row 8 q + tid / 32 of a block, 16-byte chunk ch of the columns (the same
+  // for every q).  Rows past the range are zeros: they meet whatever the logits' row holds there,
+  // kept finite by the cap of its exponent at 0 (no effect on the row's own entries).  Columns past
+  // the last repeat it and are not stored.
+  const int wrow = tid >> 5, ch = (tid & 31) ^ dl_swz(wrow);
+  const int64_t jc = std::min<int64_t>(j0 + 8 * ch, d - 8), grp = jc / kc;
+  const uint16_t* wp = wu + grp * w_bstride + (jc - grp * kc);
+  auto issue = [&](uint16_t* buf, int64_t c0) {
+    const uint32_t dst = (uint32_t)(uintptr_t)(LOCA_LDS void*)buf + (uint32_t)wid * 1024u;
+    if (ch < 4 * NB)
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int e = tid + kHT * q;
-    arow[q] = e >> 2;
-    acol[q] = 8 * (e & 3);
-    const int64_t t = t0 + arow[q];
-    const bool ok = t < n;
-    zrow[q] = z + (ok ? t : 0) * ld;
-    rmax[q] = ok ? ms[2 * t] : 0.f;
-    const float st = ok ? ms[2 * t + 1] : 1.f;
-    rscale[q] = ok ? (w ? w[t] : 1.f) / st : 0.f;
-  }
-#pragma unroll
-  for (int q = 0; q < NQB; ++q) {
-    const int e = tid + kHT * q;
-    brow[q] = e / (HN / 8);
-    bcol[q] = 8 * (e % (HN / 8));
-  }
-  uint4 ph[2], pl[2], wb[NQB];
-  auto load_stage = [&](int64_t c0) {
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int64_t t = t0 + arow[q], c = c0 + acol[q];
-      float v[8];
-      if (t < n && c + 8 <= ce) {
-        load8(zrow[q] + c, v);
-      } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = (t < n && c + i < ce) ? load_as_f32(zrow[q] + c + i) : -INFINITY;
+      for (int q = 0; q < kHK / 8; ++q)
+      {
+        const int64_t r = c0 + 8 * q + wrow;
+        lds_dma16(r < ce ? wp + r * kc : (const uint16_t*)g_zero16, __builtin_amdgcn_readfirstlane(dst + q * 4096u));
       }
-      // P = w exp(z - m) / s split into bf16 hi + lo (packed hardware conversions, loca_bf16.h)
-      uint32_t h[4], l[4];
+  };
+  auto load_z = [&](LogitChunk<LT> (&zb)[4], int64_t c0) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) zb[s].load(zr, c0 + 16 * s + 8 * lh, ce, cb);
+  };
+
+  f32x16_t acc[NB];
+#pragma unroll
+  for (int q = 0; q < NB; ++q)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[q][r] = 0.f;
+
+  auto block = [&](uint16_t* cur, uint16_t* nxt, const LogitChunk<LT> (&zc)[4], LogitChunk<LT> (&zn)[4], int b) {
+    const int64_t c0 = cb + (int64_t)b * kHK;
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // this thread's copies and logits of the block landed
+    barrier_nofence();                         // ... everyone's; the other buffer is no longer read
+    if (b + 1 < nblk) {
+      issue(nxt, c0 + kHK);
+      load_z(zn, c0 + kHK);
+    }
+    // P of step s + 1 is formed beside the products of step s (and no further ahead: the
+    // scheduling barrier keeps the registers of one step in flight)
+    bf16x8_t fh, fl, gh, gl;
+    auto form = [&](int s, bf16x8_t& oh, bf16x8_t& ol) {
+      uint32_t ph[4], pl[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float p0 = __expf(v[2 * i] - rmax[q]) * rscale[q];
-        const float p1 = __expf(v[2 * i + 1] - rmax[q]) * rscale[q];
-        h[i] = cvt_pk_bf16(p0, p1);
-        l[i] = cvt_pk_bf16(p0 - bf16_lo(h[i]), p1 - bf16_hi(h[i]));
+        const float p0 = __expf(fminf(zc[s].get(2 * i) - rmax, 0.f)) * rscale;
+        const float p1 = __expf(fminf(zc[s].get(2 * i + 1) - rmax, 0.f)) * rscale;
+        ph[i] = cvt_pk_bf16(p0, p1);
+        pl[i] = cvt_pk_bf16(p0 - bf16_lo(ph[i]), p1 - bf16_hi(ph[i]));
       }
-      ph[q] = make_uint4(h[0], h[1], h[2], h[3]);
-      pl[q] = make_uint4(l[0], l[1], l[2], l[3]);
-    }
+      oh = __builtin_bit_cast(bf16x8_t, make_uint4(ph[0], ph[1], ph[2], ph[3]));
+      ol = __builtin_bit_cast(bf16x8_t, make_uint4(pl[0], pl[1], pl[2], pl[3]));
+    };
+    form(0, fh, fl);
 #pragma unroll
-    for (int q = 0; q < NQB; ++q) {
-      const int64_t cr = c0 + brow[q], j = j0 + bcol[q];
-      const int64_t grp = j / kc, jc = j - grp * kc;
-      wb[q] = (cr < ce && j < d) ? *(const uint4*)(wu + grp * w_bstride + cr * kc + jc) : make_uint4(0, 0, 0, 0);
+    for (int s = 0; s < 4; ++s) {
+      __builtin_amdgcn_sched_barrier(0);
+      bf16x8_t fb[NB];
+#pragma unroll
+      for (int q = 0; q < NB; ++q) fb[q] = frag32_tr_swz(cur + (s >> 1) * (BLK / 2), 32 * q, 16 * (s & 1), lane);
+#pragma unroll
+      for (int q = 0; q < NB; ++q) acc[q] = mfma32(fh, fb[q], acc[q]);
+      if (s < 3) form(s + 1, gh, gl);
+#pragma unroll
+      for (int q = 0; q < NB; ++q) acc[q] = mfma32(fl, fb[q], acc[q]);
+      fh = gh;
+      fl = gl;
     }
+    __builtin_amdgcn_sched_barrier(0);
   };
-  auto store_stage = [&](int buf) {
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      *(uint4*)&sAh[buf][arow[q] * kLDA + acol[q]] = ph[q];
-      *(uint4*)&sAl[buf][arow[q] * kLDA + acol[q]] = pl[q];
-    }
-#pragma unroll
-    for (int q = 0; q < NQB; ++q) *(uint4*)&sB[buf][brow[q] * LDB + bcol[q]] = wb[q];
-  };
-
-  f32x16_t acc[NBM][2];
-#pragma unroll
-  for (int m = 0; m < NBM; ++m)
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[m][q][r] = 0.f;
-
-  const int nk = (int)((ce - cb + kHK - 1) / kHK);
-  if (nk > 0) {
-    load_stage(cb);
-    store_stage(0);
+  LogitChunk<LT> za[4], zb[4];
+  issue(sb0, cb);
+  load_z(za, cb);
+  for (int b = 0; b < nblk; b += 2) {
+    block(sb0, sb1, za, zb, b);
+    if (b + 1 < nblk) block(sb1, sb0, zb, za, b + 1);
   }
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) load_stage(cb + (int64_t)(kt + 1) * kHK);
+  float* out = part + (int64_t)sp * n * d;
 #pragma unroll
-    for (int ks = 0; ks < kHK; ks += 16) {
-      bf16x8_t fh[NBM], fl[NBM], fb[2];
+  for (int q = 0; q < NB; ++q)
 #pragma unroll
-      for (int m = 0; m < NBM; ++m) {
-        const int row = wi * WM + 32 * m + (lane & 31);
-        const int off = row * kLDA + ks + 8 * (lane >> 5);
-        fh[m] = __builtin_bit_cast(bf16x8_t, *(const uint4*)&sAh[cur][off]);
-        fl[m] = __builtin_bit_cast(bf16x8_t, *(const uint4*)&sAl[cur][off]);
-      }
-#pragma unroll
-      for (int q = 0; q < 2; ++q) fb[q] = frag32_tr(sB[cur], LDB, wj * 64 + 32 * q, ks, lane);
-#pragma unroll
-      for (int m = 0; m < NBM; ++m)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) acc[m][q] = mfma32(fh[m], fb[q], acc[m][q]);
-#pragma unroll
-      for (int m = 0; m < NBM; ++m)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) acc[m][q] = mfma32(fl[m], fb[q], acc[m][q]);
+    for (int r = 0; r < 16; ++r) {
+      const int64_t tr = t0 + mfma32_row(lane, r), j = j0 + 32 * q + mfma32_col(lane);
+      if (tr < n && j < d) out[tr * d + j] = acc[q][r];
     }
-    if (kt + 1 < nk) store_stage(cur ^ 1);
-    __syncthreads();
-  }
-  float* out = part + (int64_t)blockIdx.z * n * d;
-#pragma unroll
-  for (int m = 0; m < NBM; ++m)
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t t = t0 + wi * WM + 32 * m + mfma32_row(lane, r);
-        const int64_t j = j0 + wj * 64 + 32 * q + mfma32_col(lane);
-        if (t < n && j < d) out[t * d + j] = acc[m][q][r];
-      }
 }
 
 // out[(j / kc) o_bstride + t ld_o + j % kc] = sum_z part_z[t][j] (fp64, in order) - w_t W[y_t][j]
@@ -296,22 +299,61 @@ __global__ void k_top_error_reduce(int64_t n, int64_t d, int nsplit, const float
   out[grp * o_bstride + t * ld_o + jc] = (float)s;
 }
 
-// columns per tile of the product: 64 when there are at most 64, else 128
-int head_hn(int64_t d) { return d <= 64 ? 64 : 128; }
+// Column tiles of at most 256, evenly cut in 32s (nb of them, as instantiated); the vocabulary in
+// ns ranges of whole blocks: the count with the least rounds of 512 workgroups (two fit a compute
+// unit) times blocks per range, an added range costing its partial sums' way through memory
+// (about 1e-6 blocks per value, at 1.6 us a block and 5 TB/s).
+struct HeadPlan {
+  int ntr, nct, nb, ns;
+  int64_t kchunk;
+};
+HeadPlan head_plan(int64_t n, int64_t V, int64_t cols) {
+  HeadPlan p;
+  p.ntr = (int)((n + kHM - 1) / kHM);
+  p.nct = (int)((cols + 255) / 256);
+  p.nb = (int)((cols + 32 * p.nct - 1) / (32 * p.nct));
+  p.nb = p.nb <= 2 ? 2 : (p.nb <= 4 ? 4 : p.nb);
+  const int64_t tiles = (int64_t)p.ntr * p.nct, nblk = (V + kHK - 1) / kHK;
+  int64_t per = nblk;
+  double best = 1e300;
+  for (int64_t s = 1; s <= 32 && s <= nblk; ++s) {
+    const int64_t pr = (nblk + s - 1) / s, ns = (nblk + pr - 1) / pr;
+    const double t = (double)((tiles * ns + 511) / 512) * (double)(pr + 4) + (double)ns * (double)n * (double)cols * 1e-6;
+    if (t < best) {
+      best = t;
+      per = pr;
+    }
+  }
+  p.kchunk = per * kHK;
+  p.ns = (int)((nblk + per - 1) / per);
+  return p;
+}
 
-int head_splits(int64_t n, int64_t V, int64_t d) {
-  const int64_t tiles = ((n + kHM - 1) / kHM) * ((d + head_hn(d) - 1) / head_hn(d));
-  int64_t s = (2048 + tiles - 1) / tiles;
-  s = std::max<int64_t>(1, std::min<int64_t>(s, 32));
-  s = std::min<int64_t>(s, std::max<int64_t>(1, (V + 255) / 256));  // at least 256 vocabulary entries a chunk
-  return (int)s;
+template <typename LT>
+void launch_product(const SoftmaxProductArgs& a, const HeadPlan& p, const float* ms, float* part) {
+  const LT* z = (const LT*)a.logits;
+  const int64_t cols = a.groups * a.kc;
+  const unsigned grid = (unsigned)((int64_t)p.ntr * p.nct * p.ns);
+  k_softmax_stats<LT><<<(unsigned)a.n, kHT, 0, a.stream>>>(a.n, a.V, z, a.ld_logits, a.labels, (float*)ms, a.dev_info);
+#define LOCA_HEAD(NB)                                                                                          \
+  k_top_error_gemm<LT, NB><<<grid, kHT2, 0, a.stream>>>(a.n, a.V, cols, z, a.ld_logits, a.w, ms, a.W, a.kc,     \
+                                                       a.w_bstride, p.ntr, p.nct, p.kchunk, part)
+  switch (p.nb) {
+    case 2: LOCA_HEAD(2); break;
+    case 4: LOCA_HEAD(4); break;
+    case 5: LOCA_HEAD(5); break;
+    case 6: LOCA_HEAD(6); break;
+    case 7: LOCA_HEAD(7); break;
+    default: LOCA_HEAD(8); break;
+  }
+#undef LOCA_HEAD
 }
 
 }  // namespace
 
 // At most 64 columns (one tile of the single-pass kernel) the logits are read once, by the
 // online-softmax product; wider products keep the statistics pass and a product pass per
-// 128 columns.
+// column tile.
 // (Its buffer loads take 31-bit byte offsets within 128 rows of logits and 64 rows of the
 // right operand.)
 static bool product_online(const SoftmaxProductArgs& a) {
@@ -321,7 +363,7 @@ static bool product_online(const SoftmaxProductArgs& a) {
 }
 
 static size_t two_pass_ws(int64_t n, int64_t V, int64_t cols) {
-  return align256(sizeof(float) * 2 * n) + align256(sizeof(float) * (size_t)head_splits(n, V, cols) * n * cols);
+  return align256(sizeof(float) * 2 * n) + align256(sizeof(float) * (size_t)head_plan(n, V, cols).ns * n * cols);
 }
 
 size_t softmax_product_ws(int64_t n, int64_t V, int64_t cols) {
@@ -336,34 +378,14 @@ hipError_t launch_softmax_product(const SoftmaxProductArgs& a) {
   float* ms = (float*)a.ws;
   float* part = (float*)(a.ws + align256(sizeof(float) * 2 * a.n));
   const int64_t cols = a.groups * a.kc;
-  const int ns = head_splits(a.n, a.V, cols);
-  const int64_t kchunk = ((a.V + ns - 1) / ns + kHK - 1) / kHK * kHK;
+  const HeadPlan pl = head_plan(a.n, a.V, cols);
   hipStream_t st = a.stream;
-  const int hn = head_hn(cols);
-  dim3 g((unsigned)((a.n + kHM - 1) / kHM), (unsigned)((cols + hn - 1) / hn), (unsigned)ns);
-  if (a.logits_dtype == LOCA_BF16) {
-    const uint16_t* zb = (const uint16_t*)a.logits;
-    k_softmax_stats<uint16_t><<<(unsigned)a.n, kHT, 0, st>>>(a.n, a.V, zb, a.ld_logits, a.labels, ms, a.dev_info);
-    if (hn == 64)
-      k_top_error_gemm<uint16_t, 64><<<g, kHT, 0, st>>>(a.n, a.V, cols, zb, a.ld_logits, a.w, ms, a.W, a.kc,
-                                                        a.w_bstride, kchunk, part);
-    else
-      k_top_error_gemm<uint16_t, 128><<<g, kHT, 0, st>>>(a.n, a.V, cols, zb, a.ld_logits, a.w, ms, a.W, a.kc,
-                                                         a.w_bstride, kchunk, part);
-  } else {
-    const float* zf = (const float*)a.logits;
-    k_softmax_stats<float><<<(unsigned)a.n, kHT, 0, st>>>(a.n, a.V, zf, a.ld_logits, a.labels, ms, a.dev_info);
-    if (hn == 64)
-      k_top_error_gemm<float, 64><<<g, kHT, 0, st>>>(a.n, a.V, cols, zf, a.ld_logits, a.w, ms, a.W, a.kc,
-                                                     a.w_bstride, kchunk, part);
-    else
-      k_top_error_gemm<float, 128><<<g, kHT, 0, st>>>(a.n, a.V, cols, zf, a.ld_logits, a.w, ms, a.W, a.kc,
-                                                      a.w_bstride, kchunk, part);
-  }
+  if (a.logits_dtype == LOCA_BF16) launch_product<uint16_t>(a, pl, ms, part);
+  else launch_product<float>(a, pl, ms, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   k_top_error_reduce<<<(unsigned)((a.n * cols + 255) / 256), 256, 0, st>>>(
-      a.n, cols, ns, part, a.w, a.labels, a.V, a.W, a.kc, a.w_bstride, a.out, a.ld_o, a.o_bstride);
+      a.n, cols, pl.ns, part, a.w, a.labels, a.V, a.W, a.kc, a.w_bstride, a.out, a.ld_o, a.o_bstride);
   return hipGetLastError();
 }
 

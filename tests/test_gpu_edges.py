@@ -168,3 +168,48 @@ def test_fused_head_edges(n, V, d, c):
     ref = (e @ M) * w.double().cpu().numpy()[:, None]
     scale = np.linalg.norm(M) * np.linalg.norm(w.double().cpu().numpy()) / np.sqrt(V)
     assert np.linalg.norm(out.double().cpu().numpy() - ref) < 1e-5 * max(scale, np.linalg.norm(ref))
+
+
+# the paper-order head at the edges of its 128-token tiles, 64-entry blocks and column tiles
+# (one to three of 32 to 256 columns, float and bf16 logits), NaN in the rows' padding, and the
+# blocks' coordinates on both sides of 64 columns.  P as two bf16 parts: 2^-17 of each term
+@pytest.mark.parametrize("n,V,d,k,bf", [(1, 5, 8, 1, 1), (127, 64, 40, 16, 0), (129, 65, 72, 33, 1), (130, 1003, 136, 64, 0),
+                                        (64, 300, 200, 65, 1), (200, 130, 264, 128, 0), (33, 9000, 520, 12, 1)])
+def test_paper_order_head_edges(n, V, d, k, bf):
+    import torch
+    from paper_2608_03020_amd import loca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + V + d)
+    rn = lambda *s: torch.randn(s, generator=g, device="cuda")
+    per = 8 if bf else 4
+    buf = torch.full((n, -(-V // per) * per), float("nan"), device="cuda", dtype=torch.bfloat16 if bf else torch.float32)
+    buf[:, :V] = 3 * rn(n, V)
+    z, nb = buf[:, :V], 2
+    if V > 8:
+        z[:, 3] = float("-inf")  # an excluded class
+    Wu, Vk, B = (rn(V, d) / d ** 0.5).bfloat16(), rn(nb, d, k) / d ** 0.5, rn(nb, k, d)
+    y = torch.randint(4 if V > 8 else 0, V, (n,), generator=g, device="cuda", dtype=torch.int32)
+    w, a = torch.rand(n, generator=g, device="cuda"), torch.rand(n, generator=g, device="cuda")
+    e, Y = torch.full((n, d), float("nan"), device="cuda"), torch.full((nb, n, k), float("nan"), device="cuda")
+    mb, info = loca.new_mb(nb), torch.full((1,), 5, dtype=torch.int32, device="cuda")
+    ws = loca.alloc_workspace(max(loca.workspace_size(loca.LOCA_OP_TOP_ERROR, 1, n, d, 1, V),
+                                  loca.workspace_size(loca.LOCA_OP_CREDIT_FROM_TOP_ERROR, nb, n, d, k)))
+    ws.fill_(255)
+    log("paper-order head", n, V, d, k, bf)
+    loca.loca_top_error(z, y, Wu, e, info, ws, w=w)
+    loca.loca_credit_from_top_error(e, Vk, B, Y, mb, ws, a_w=a)
+    assert int(info) == 0
+    Z, W = z.double().cpu().numpy(), Wu.double().cpu().numpy()
+    E = np.exp(Z - Z.max(1, keepdims=True))
+    E /= E.sum(1, keepdims=True)
+    E[np.arange(n), y.cpu().numpy()] -= 1
+    ref = (E @ W) * w.double().cpu().numpy()[:, None]
+    scale = np.linalg.norm(W) * np.linalg.norm(w.double().cpu().numpy()) / np.sqrt(V)
+    assert np.linalg.norm(e.double().cpu().numpy() - ref) < 1e-5 * max(scale, np.linalg.norm(ref))
+    ed = e.double().cpu().numpy()
+    for b in range(nb):  # float64 sums of exact products, rounded once; q2 from the rounded Y
+        Yr = ed @ Vk[b].double().cpu().numpy()
+        assert rel(Y[b].cpu().numpy(), Yr) < 2.0 ** -23
+        Bd, Yd = B[b].double().cpu().numpy(), Y[b].double().cpu().numpy()
+        q2 = (a.double().cpu().numpy() * ((Yd @ Bd) ** 2).sum(1)).sum()
+        assert abs(float(mb[b, 0]) - q2) < 1e-12 * q2
