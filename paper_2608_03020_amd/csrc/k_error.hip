@@ -13,6 +13,7 @@
 //    sum of exp(z - m) A~[c] alongside; Y = acc / s - A~[y].
 // Both write per-workgroup partial sums of ||Q||^2 (fp64) that a finalize
 // kernel adds in a fixed order, so results are bitwise reproducible.
+#include <algorithm>
 #include <mutex>
 
 #include "loca_launch.h"
@@ -126,9 +127,7 @@ static size_t credit_gram_part_ws(int64_t nb, int64_t k) { return align256(sizeo
 //     each lane multiplies its entries of M_w by those of G (KB x KB, zero past k; blocks off
 //     the diagonal count twice).
 // The tile reuses the A~ area once it is consumed.
-// HC > 0 (label sets of C <= HC classes): since y_t = e_t A~, the same sum is
-// sum_t a_t e_t H e_t^T with the C x C matrix H = A~ G A~^T (fp64, formed in LDS by every
-// workgroup), HC^2 fp64 FMAs per token in place of the matrix-core pass over the tile.
+// (Label sets of at most 16 classes take k_error_rows below.)
 static int64_t small_kb(int64_t k) { return k <= 16 ? 16 : k <= 32 ? 32 : 64; }
 template <int KB>
 struct SmallLds {
@@ -138,7 +137,7 @@ struct SmallLds {
   static constexpr int BYTES = IN > ST ? IN : ST;
 };
 
-template <typename LT, typename AT, int KB, int HC>
+template <typename LT, typename AT, int KB>
 __global__ __launch_bounds__(kSmallThreads) void k_error_small(
     int64_t n, int64_t C, int64_t k, const LT* __restrict__ logits, int64_t ld,
     const int32_t* __restrict__ labels, const float* __restrict__ w, const float* __restrict__ aw,
@@ -150,8 +149,6 @@ __global__ __launch_bounds__(kSmallThreads) void k_error_small(
   __shared__ __attribute__((aligned(16))) unsigned char lds[L::BYTES];
   __shared__ float sW[kSmallThreads];  // statistic weight of each token (0 past n)
   __shared__ double sred[kSmallThreads / 64];
-  __shared__ double sAG[HC > 0 ? HC * KB : 1];  // A~ G (HC x KB)
-  __shared__ double sH[HC > 0 ? HC * HC : 1];   // A~ G A~^T, zero past C
   float* sA = (float*)lds;  // C x KB, zero past k (the products below need no bound)
   const int64_t b = blockIdx.y;
   const AT* Ab = A + b * a_bstride;
@@ -161,49 +158,12 @@ __global__ __launch_bounds__(kSmallThreads) void k_error_small(
     sA[e] = j < k ? load_as_f32(Ab + c * k + j) : 0.f;
   }
   __syncthreads();
-  if constexpr (HC > 0) {
-    // A~ G: thread (j, iq) = (tid / 4, tid % 4) reads G[i][j] for its quarter of i once (the
-    // loads issued together) and adds it into all HC rows; the quarters meet by shuffles
-    static_assert(kSmallThreads == 4 * 64, "64 columns x 4 quarters");
-    const int j = (int)threadIdx.x >> 2, iq = (int)threadIdx.x & 3;
-    constexpr int IQ = KB / 4;
-    if (j < KB) {
-      double g[IQ];
-#pragma unroll
-      for (int ii = 0; ii < IQ; ++ii) g[ii] = Gb[(iq * IQ + ii) * KB + j];
-      double v[HC];
-#pragma unroll
-      for (int c = 0; c < HC; ++c) {
-        v[c] = 0.0;
-#pragma unroll
-        for (int ii = 0; ii < IQ; ++ii) v[c] = fma((double)sA[(c < C ? c : 0) * KB + iq * IQ + ii], g[ii], v[c]);
-      }
-#pragma unroll
-      for (int c = 0; c < HC; ++c) {
-        v[c] += __shfl_xor(v[c], 1, 64);
-        v[c] += __shfl_xor(v[c], 2, 64);
-        if (iq == 0) sAG[c * KB + j] = c < C ? v[c] : 0.0;
-      }
-    }
-    __syncthreads();
-    for (int e = (int)threadIdx.x; e < HC * HC; e += kSmallThreads) {
-      const int c = e / HC, c2 = e % HC;
-      double v = 0.0;
-      if (c < C && c2 < C)
-        for (int j = 0; j < KB; ++j) v = fma(sAG[c * KB + j], (double)sA[c2 * KB + j], v);
-      sH[e] = v;
-    }
-    // sH is read after the barrier below that retires the reads of sA
-  }
 
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   float y[KB];
 #pragma unroll
   for (int j = 0; j < KB; ++j) y[j] = 0.f;
   float wq = 0.f;  // weight of this token in ||Q||^2
-  float ev[HC > 0 ? HC : 1];  // this token's error row (HC > 0), zero past C
-#pragma unroll
-  for (int c = 0; c < (HC > 0 ? HC : 1); ++c) ev[c] = 0.f;
   if (t < n) {
     const LT* zt = logits + t * ld;
     const int32_t yt = labels[t];
@@ -234,34 +194,16 @@ __global__ __launch_bounds__(kSmallThreads) void k_error_small(
       }
       const float inv = 1.0f / s;
       const float wt = w ? w[t] : 1.0f;
-      if constexpr (HC > 0) {  // the chunks unrolled, so that ev is indexed by constants
+      for (int64_t c0 = 0; c0 < C; c0 += 8) {
+        if (c0 > 0 || C > 8) chunk(c0);
 #pragma unroll
-        for (int c0 = 0; c0 < HC; c0 += 8) {
-          if (c0 >= C) break;
-          if (c0 > 0 || C > 8) chunk(c0);
+        for (int u = 0; u < 8; ++u) {
+          const int64_t c = c0 + u;
+          if (c >= C) break;
+          const float e = wt * (__expf(zc[u] - m) * inv - (c == yt ? 1.0f : 0.0f));
+          if (e_out) e_out[t * C + c] = e;
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const int c = c0 + u;
-            if (c >= C) break;
-            const float e = wt * (__expf(zc[u] - m) * inv - (c == yt ? 1.0f : 0.0f));
-            if (e_out) e_out[t * C + c] = e;
-            ev[c] = e;
-#pragma unroll
-            for (int j = 0; j < KB; ++j) y[j] = fmaf(e, sA[c * KB + j], y[j]);
-          }
-        }
-      } else {
-        for (int64_t c0 = 0; c0 < C; c0 += 8) {
-          if (c0 > 0 || C > 8) chunk(c0);
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const int64_t c = c0 + u;
-            if (c >= C) break;
-            const float e = wt * (__expf(zc[u] - m) * inv - (c == yt ? 1.0f : 0.0f));
-            if (e_out) e_out[t * C + c] = e;
-#pragma unroll
-            for (int j = 0; j < KB; ++j) y[j] = fmaf(e, sA[c * KB + j], y[j]);
-          }
+          for (int j = 0; j < KB; ++j) y[j] = fmaf(e, sA[c * KB + j], y[j]);
         }
       }
       wq = aw ? aw[t] : 1.0f;  // statistic weight of the position
@@ -305,20 +247,6 @@ __global__ __launch_bounds__(kSmallThreads) void k_error_small(
     }
   }
 
-  if constexpr (HC > 0) {  // a_t e_t H e_t^T of this thread's token (ev and wq zero past n)
-    double q = 0.0;
-#pragma unroll
-    for (int c = 0; c < HC; ++c) {
-      double u = 0.0;
-#pragma unroll
-      for (int c2 = 0; c2 < HC; ++c2) u = fma(sH[c * HC + c2], (double)ev[c2], u);
-      q = fma((double)ev[c], u, q);
-    }
-    const double tot = block_sum((double)wq * q, sred);
-    if (threadIdx.x == 0) partial[b * gridDim.x + blockIdx.x] = tot;
-    return;
-  }
-
   // this wave's part of ||Q||^2
   const float* sWw = sW + 64 * wv;
   const int kr = lane >> 4, cr = lane & 15;
@@ -344,6 +272,206 @@ __global__ __launch_bounds__(kSmallThreads) void k_error_small(
     }
   const double tot = block_sum(q, sred);
   if (threadIdx.x == 0) partial[b * gridDim.x + blockIdx.x] = tot;
+}
+
+// ------------------------------------------------------------------ label sets of at most 16 classes
+
+// A token's error row e_t (C values) is the same for every block, so ||Q_b||^2 = sum_t a_t e_t H_b
+// e_t^T, H_b = A~_b G_b A~_b^T, is <H_b, M> with the one C x C matrix M = sum_t a_t e_t^T e_t, and
+// what a block needs per token is C FMAs per entry of Y.  The call is bound by the write of Y.
+//
+// Workgroups of y = 0: the rows' labels and weights checked, e_out, and M: workgroup x sums the
+// 256-token tiles x, x + gridDim-stride, ... into its partial (fp64, a fixed order).  Workgroups of y
+// > 0: one tile and `bper` blocks: the error rows formed once into LDS, then per block a lane holds
+// four columns of A~_b and writes 16 bytes of Y per token, a wave's store covering whole rows (V4: k
+// % 4 == 0 and 16-byte aligned rows).  8192 tokens, 48 blocks, five classes, k = 64: 44.1 us a call with
+// the rows formed again for every block, H by every workgroup and Y through an LDS tile; 34.4 us now (this
+// kernel 22 us, 4.6 TB/s).
+constexpr int kRowTok = 256, kMaxMParts = 512;
+template <int HC, typename LT>
+LOCA_DEV float error_row(float (&ev)[HC], int64_t t, int64_t n, int C, const LT* __restrict__ logits, int64_t ld,
+                         const int32_t* __restrict__ labels, const float* __restrict__ w,
+                         const float* __restrict__ aw, int32_t* dev_info) {
+#pragma unroll
+  for (int c = 0; c < HC; ++c) ev[c] = 0.f;
+  if (t >= n) return 0.f;
+  const int32_t yt = labels[t];
+  if (yt < 0 || yt >= C) {
+    if (dev_info) atomicMin(dev_info, (int32_t)(t + 1));
+    return 0.f;
+  }
+  const LT* zt = logits + t * ld;
+  float z[HC];
+#pragma unroll
+  for (int c = 0; c < HC; ++c) z[c] = c < C ? load_as_f32(zt + c) : -INFINITY;
+  float m = z[0];
+#pragma unroll
+  for (int c = 1; c < HC; ++c)
+    if (c < C) m = fmaxf(m, z[c]);
+  float s = 0.f;
+#pragma unroll
+  for (int c = 0; c < HC; ++c)
+    if (c < C) {
+      ev[c] = __expf(z[c] - m);
+      s += ev[c];
+    }
+  const float inv = 1.0f / s, wt = w ? w[t] : 1.0f;
+#pragma unroll
+  for (int c = 0; c < HC; ++c)
+    if (c < C) ev[c] = wt * (ev[c] * inv - (c == yt ? 1.0f : 0.0f));
+  return aw ? aw[t] : 1.0f;
+}
+
+template <typename LT, typename AT, int KB, int HC, bool V4>
+__global__ __launch_bounds__(kRowTok) void k_error_rows(
+    int64_t n, int C, int64_t k, const LT* __restrict__ logits, int64_t ld, const int32_t* __restrict__ labels,
+    const float* __restrict__ w, const float* __restrict__ aw, const AT* __restrict__ A, int64_t a_bstride, int64_t nb,
+    int bper, int ntile, int mparts, float* __restrict__ y_out, int64_t y_bstride, float* __restrict__ e_out,
+    double* __restrict__ mpart, int32_t* __restrict__ dev_info) {
+  constexpr int R4 = KB / 4, TPI = 64 / R4, NE = HC * HC, NS = kRowTok / NE;  // NS threads per entry of M
+  __shared__ __attribute__((aligned(16))) float sE[kRowTok][HC];
+  __shared__ float sW[kRowTok];
+  __shared__ double sM[kRowTok];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  float ev[HC];
+  if (blockIdx.y == 0) {
+    if ((int)blockIdx.x >= mparts) return;
+    const int en = tid % NE, part = tid / NE, c1 = en / HC, c2 = en % HC;
+    double m = 0.0;
+    for (int tile = blockIdx.x; tile < ntile; tile += mparts) {
+      const int64_t t = (int64_t)tile * kRowTok + tid;
+      __syncthreads();  // the previous tile is no longer read
+      sW[tid] = error_row<HC>(ev, t, n, C, logits, ld, labels, w, aw, dev_info);
+#pragma unroll
+      for (int c = 0; c < HC; ++c) {
+        sE[tid][c] = ev[c];
+        if (e_out && t < n && c < C) e_out[t * C + c] = ev[c];
+      }
+      __syncthreads();
+      for (int p = part * (kRowTok / NS); p < (part + 1) * (kRowTok / NS); ++p)
+        m = fma((double)sW[p] * (double)sE[p][c1], (double)sE[p][c2], m);
+    }
+    sM[tid] = m;
+    __syncthreads();
+    if (tid < NE) {
+      double v = sM[tid];
+#pragma unroll
+      for (int u = 1; u < NS; ++u) v += sM[tid + NE * u];
+      mpart[(int64_t)blockIdx.x * NE + tid] = v;
+    }
+    return;
+  }
+  const int64_t t0 = (int64_t)blockIdx.x * kRowTok;
+  error_row<HC>(ev, t0 + tid, n, C, logits, ld, labels, w, aw, nullptr);
+#pragma unroll
+  for (int c = 0; c < HC; c += 4) *(float4*)&sE[tid][c] = make_float4(ev[c], ev[c + 1], ev[c + 2], ev[c + 3]);
+  wave_lds_sync();  // a wave reads its own 64 tokens only
+  const int64_t b0 = (int64_t)(blockIdx.y - 1) * bper, b1 = b0 + bper < nb ? b0 + bper : nb;
+  const int j = 4 * (lane % R4), sub = lane / R4;
+  for (int64_t b = b0; b < b1; ++b) {
+    const AT* Ab = A + b * a_bstride;
+    float a[HC][4];
+#pragma unroll
+    for (int c = 0; c < HC; ++c)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const bool ok = c < C && j + u < k;
+        const AT v = Ab[ok ? c * k + j + u : 0];
+        a[c][u] = ok ? load_as_f32(&v) : 0.f;
+      }
+    float* yb = y_out + b * y_bstride;
+#pragma unroll 4
+    for (int i = 0; i < R4; ++i) {
+      const int p = 64 * wid + TPI * i + sub;
+      float e[HC];
+#pragma unroll
+      for (int c = 0; c < HC; c += 4) {
+        const float4 v = *(const float4*)&sE[p][c];
+        e[c] = v.x; e[c + 1] = v.y; e[c + 2] = v.z; e[c + 3] = v.w;
+      }
+      float y[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < HC; ++c) {
+        if (c >= C) break;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) y[u] = fmaf(e[c], a[c][u], y[u]);
+      }
+      const int64_t t = t0 + p;
+      if (t >= n || j >= k) continue;
+      float* dst = yb + t * k + j;
+      if (V4) {
+        *(float4*)dst = make_float4(y[0], y[1], y[2], y[3]);
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (j + u < k) dst[u] = y[u];
+      }
+    }
+  }
+}
+
+// Per block: H = A~ G A~^T (fp64), M from its partials in a fixed order, sum_q2 = <H, M>; the record
+// and dev_info as k_error_finalize leaves them.
+template <typename AT, int KB, int HC>
+__global__ __launch_bounds__(256) void k_error_rows_finalize(int64_t n, int C, int64_t k, int mparts,
+                                                             const double* __restrict__ mpart,
+                                                             const AT* __restrict__ A, int64_t a_bstride,
+                                                             const double* __restrict__ G, loca_mb* __restrict__ mb,
+                                                             int32_t* __restrict__ dev_info) {
+  constexpr int NE = HC * HC, NS = 256 / NE;
+  __shared__ float sA[HC * KB];
+  __shared__ double sAG[HC * KB];
+  __shared__ double sM[256];
+  __shared__ double sred[4];
+  const int64_t b = blockIdx.x;
+  const int tid = threadIdx.x;
+  const AT* Ab = A + b * a_bstride;
+  const double* Gb = G + b * KB * KB;
+  for (int e = tid; e < HC * KB; e += 256) {
+    const int c = e / KB, j = e % KB;
+    sA[e] = c < C && j < k ? load_as_f32(Ab + c * k + j) : 0.f;
+  }
+  double m = 0.0;
+#pragma unroll 4
+  for (int x = tid / NE; x < mparts; x += NS) m += mpart[(int64_t)x * NE + tid % NE];
+  sM[tid] = m;
+  __syncthreads();
+  // A~ G: thread (j, iq) = (tid / 4, tid % 4) reads G[i][j] for its quarter of i once and adds it
+  // into all rows; the quarters meet by shuffles
+  {
+    const int j = tid >> 2, iq = tid & 3;
+    constexpr int IQ = KB / 4;
+    double g[IQ];
+#pragma unroll
+    for (int ii = 0; ii < IQ; ++ii) g[ii] = j < KB ? Gb[(iq * IQ + ii) * KB + j] : 0.0;
+#pragma unroll
+    for (int c = 0; c < HC; ++c) {
+      double v = 0.0;
+#pragma unroll
+      for (int ii = 0; ii < IQ; ++ii) v = fma((double)sA[c * KB + iq * IQ + ii], g[ii], v);
+      v += __shfl_xor(v, 1, 64);
+      v += __shfl_xor(v, 2, 64);
+      if (iq == 0 && j < KB) sAG[c * KB + j] = v;
+    }
+  }
+  __syncthreads();
+  double q = 0.0;
+  if (tid < NE) {
+    const int c1 = tid / HC, c2 = tid % HC;
+    double h = 0.0, v = sM[tid];
+#pragma unroll
+    for (int u = 1; u < NS; ++u) v += sM[tid + NE * u];
+    for (int j = 0; j < KB; ++j) h = fma(sAG[c1 * KB + j], (double)sA[c2 * KB + j], h);
+    q = h * v;
+  }
+  const double tot = block_sum(q, sred);
+  if (tid != 0) return;
+  if (!__builtin_isfinite(tot)) atomicMin(dev_info, (int32_t)LOCA_INFO_NONFINITE);
+  if (b == 0) atomicCAS(dev_info, INT32_MAX, 0);
+  mb[b].sum_q2 = tot;
+  mb[b].sum_x2 = 0.0;
+  mb[b].eta_bar = 0.0;
+  mb[b].n = n;
 }
 
 // Large vocabulary (or k > 64): TOK tokens per workgroup, 256 threads = TOK x LPT
@@ -695,12 +823,21 @@ static bool use_product(const ErrorArgs& a) {
 // for k <= 64, else k.
 static int64_t g_ld_max(int64_t k) { return k <= kSmallMaxK ? small_kb(k) : k; }
 
+constexpr int64_t kRowsMaxC = 16;
+static int rows_mparts(int64_t n) { return (int)std::min<int64_t>((n + kRowTok - 1) / kRowTok, kMaxMParts); }
+
 size_t error_targets_ws(int64_t nb, int64_t n, int64_t C, int64_t k) {
   const int64_t lg = g_ld_max(k);
   size_t s = align256(sizeof(double) * nb * lg * lg);  // G
-  s += credit_gram_part_ws(nb, k);                   // partials of G
   const int64_t parts = use_small(C, k) ? (n + kSmallThreads - 1) / kSmallThreads : (n + kLargeTok - 1) / kLargeTok;
-  s += align256(sizeof(double) * nb * parts);          // partials
+  // partials of G, then of ||Q||^2; the partials of M (label sets of at most 16 classes) share
+  // the place of both, G being complete by then
+  size_t p = credit_gram_part_ws(nb, k) + align256(sizeof(double) * nb * parts);
+  if (use_small(C, k) && C <= kRowsMaxC) {
+    const size_t mp = align256(sizeof(double) * rows_mparts(n) * (C <= 8 ? 64 : 256));
+    p = p > mp ? p : mp;
+  }
+  s += p;
   if (!use_small(C, k)) {
     const size_t large = align256(sizeof(float) * 2 * n);  // (m, s) per token
     const size_t prod = (k % 8 == 0) ? softmax_product_ws(n, C, nb * k) : 0;
@@ -710,25 +847,47 @@ size_t error_targets_ws(int64_t nb, int64_t n, int64_t C, int64_t k) {
 }
 
 template <typename LT, typename AT>
-static hipError_t dispatch_error(const ErrorArgs& a, double* G, double* partial, float* ms) {
+static hipError_t dispatch_error(const ErrorArgs& a, double* G, double* mpart, double* partial, float* ms) {
   const LT* z = (const LT*)a.logits;
   const AT* A = (const AT*)a.credit_a;
   if (use_small(a.C, a.k)) {
+    if (a.C <= kRowsMaxC) {
+      // blocks per workgroup: about four workgroups a compute unit, so that a tile's error rows
+      // are formed few times
+      const int ntile = (int)((a.n + kRowTok - 1) / kRowTok), mparts = rows_mparts(a.n);
+      const int bper = (int)((a.nb * ntile + 1023) / 1024);
+      const dim3 g((unsigned)ntile, (unsigned)(1 + (a.nb + bper - 1) / bper));
+      const bool v4 = a.k % 4 == 0 && (a.nb == 1 || a.y_bstride % 4 == 0) && ((uintptr_t)a.y_out & 15) == 0;
+#define LOCA_ROWS2(KB, HC, V4)                                                                                    \
+  k_error_rows<LT, AT, KB, HC, V4><<<g, kRowTok, 0, a.stream>>>(                                                  \
+      a.n, (int)a.C, a.k, z, a.ld_logits, a.labels, a.w, a.a_w, A, a.a_bstride, a.nb, bper, ntile, mparts, a.y_out, \
+      a.y_bstride, a.e_out, mpart, a.dev_info)
+#define LOCA_ROWS(KB, HC)                                                                                         \
+  {                                                                                                               \
+    if (v4) LOCA_ROWS2(KB, HC, true);                                                                             \
+    else LOCA_ROWS2(KB, HC, false);                                                                               \
+    k_error_rows_finalize<AT, KB, HC><<<(unsigned)a.nb, 256, 0, a.stream>>>(a.n, (int)a.C, a.k, mparts, mpart, A,  \
+                                                                            a.a_bstride, G, a.mb_out, a.dev_info); \
+  }
+#define LOCA_ROWS_KB(KB)        \
+  if (a.C <= 8) LOCA_ROWS(KB, 8) \
+  else LOCA_ROWS(KB, 16)
+      if (a.k <= 16) { LOCA_ROWS_KB(16) }
+      else if (a.k <= 32) { LOCA_ROWS_KB(32) }
+      else { LOCA_ROWS_KB(64) }
+#undef LOCA_ROWS_KB
+#undef LOCA_ROWS
+#undef LOCA_ROWS2
+      return hipGetLastError();
+    }
     dim3 grid((unsigned)((a.n + kSmallThreads - 1) / kSmallThreads), (unsigned)a.nb);
-    // ||Q||^2 through the C x C matrix A~ G A~^T for label sets of at most 16 classes,
-    // else on the fp64 matrix cores from the tile of Y
-#define LOCA_SMALL(KB, HC)                                                                          \
-  k_error_small<LT, AT, KB, HC><<<grid, kSmallThreads, 0, a.stream>>>(                              \
+#define LOCA_SMALL(KB)                                                                              \
+  k_error_small<LT, AT, KB><<<grid, kSmallThreads, 0, a.stream>>>(                                  \
       a.n, a.C, a.k, z, a.ld_logits, a.labels, a.w, a.a_w, A, a.a_bstride, G, a.y_out, a.y_bstride, a.e_out, \
       partial, a.dev_info)
-#define LOCA_SMALL_KB(KB)                      \
-  if (a.C <= 8) LOCA_SMALL(KB, 8);             \
-  else if (a.C <= 16) LOCA_SMALL(KB, 16);      \
-  else LOCA_SMALL(KB, 0);
-    if (a.k <= 16) { LOCA_SMALL_KB(16) }
-    else if (a.k <= 32) { LOCA_SMALL_KB(32) }
-    else { LOCA_SMALL_KB(64) }
-#undef LOCA_SMALL_KB
+    if (a.k <= 16) LOCA_SMALL(16);
+    else if (a.k <= 32) LOCA_SMALL(32);
+    else LOCA_SMALL(64);
 #undef LOCA_SMALL
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -757,6 +916,7 @@ hipError_t launch_error_targets(const ErrorArgs& a) {
   const int64_t lg = g_ld_max(a.k);
   p += align256(sizeof(double) * a.nb * g_ld_max(a.k) * g_ld_max(a.k));
   double* gpart = (double*)p;
+  double* mpart = gpart;
   p += credit_gram_part_ws(a.nb, a.k);
   double* partial = (double*)p;
   const int64_t parts = use_small(a.C, a.k) ? (a.n + kSmallThreads - 1) / kSmallThreads : (a.n + kLargeTok - 1) / kLargeTok;
@@ -801,10 +961,10 @@ hipError_t launch_error_targets(const ErrorArgs& a) {
     return hipGetLastError();
   }
   const bool zb = a.logits_dtype == LOCA_BF16, ab = a.a_dtype == LOCA_BF16;
-  if (!zb && !ab) return dispatch_error<float, float>(a, G, partial, ms);
-  if (!zb && ab) return dispatch_error<float, uint16_t>(a, G, partial, ms);
-  if (zb && !ab) return dispatch_error<uint16_t, float>(a, G, partial, ms);
-  return dispatch_error<uint16_t, uint16_t>(a, G, partial, ms);
+  if (!zb && !ab) return dispatch_error<float, float>(a, G, mpart, partial, ms);
+  if (!zb && ab) return dispatch_error<float, uint16_t>(a, G, mpart, partial, ms);
+  if (zb && !ab) return dispatch_error<uint16_t, float>(a, G, mpart, partial, ms);
+  return dispatch_error<uint16_t, uint16_t>(a, G, mpart, partial, ms);
 }
 
 int64_t credit_gram_ld(int64_t k) { return g_ld_max(k); }

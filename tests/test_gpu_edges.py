@@ -213,3 +213,46 @@ def test_paper_order_head_edges(n, V, d, k, bf):
         Bd, Yd = B[b].double().cpu().numpy(), Y[b].double().cpu().numpy()
         q2 = (a.double().cpu().numpy() * ((Yd @ Bd) ** 2).sum(1)).sum()
         assert abs(float(mb[b, 0]) - q2) < 1e-12 * q2
+
+
+# label sets of 1 to 17 classes (both sides of the 8- and 16-class forms and of the register head),
+# tokens around the 256-token tiles, ranks on both sides of the column blocks and of the 16-byte
+# stores, weights, and more tiles than the 512 partials of M.  float32 softmax (a few ulp of terms
+# below 1) times float32 factors: 1e-6 of Y; ||Q||^2 from the same rows in float64: 2e-6
+@pytest.mark.parametrize("n,C,k,nb,wt", [(1, 1, 1, 1, 0), (255, 2, 3, 3, 1), (256, 5, 64, 2, 0), (257, 8, 16, 5, 1),
+                                         (300, 9, 18, 2, 1), (1000, 16, 33, 7, 0), (70, 17, 20, 2, 1),
+                                         (131500, 3, 4, 1, 1)])
+def test_label_set_head_edges(n, C, k, nb, wt):
+    import torch
+    from paper_2608_03020_amd import loca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + C + k)
+    rn = lambda *s: torch.randn(s, generator=g, device="cuda")
+    d = 40
+    z, A, B = 3 * rn(n, C), rn(nb, C, k), rn(nb, k, d)
+    if C > 3:
+        z[0, 1] = float("-inf")
+    y = torch.randint(2 if C > 3 else 0, C, (n,), generator=g, device="cuda", dtype=torch.int32)
+    w = torch.rand(n, generator=g, device="cuda") if wt else None
+    a = torch.rand(n, generator=g, device="cuda") if wt else None
+    Y, e = torch.full((nb, n, k), float("nan"), device="cuda"), torch.full((n, C), float("nan"), device="cuda")
+    mb, info = loca.new_mb(nb), torch.full((1,), 5, dtype=torch.int32, device="cuda")
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_ERROR_TARGETS, nb, n, d, k, C=C))
+    ws.fill_(255)
+    log("label-set head", n, C, k, nb, wt)
+    loca.loca_error_targets(z, y, A, B, Y, mb, info, ws, w=w, a_w=a, e_out=e)
+    assert int(info) == 0
+    Z = z.double().cpu().numpy()
+    E = np.exp(Z - Z.max(1, keepdims=True))
+    E /= E.sum(1, keepdims=True)
+    E[np.arange(n), y.cpu().numpy()] -= 1
+    if wt:
+        E *= w.double().cpu().numpy()[:, None]
+    aw = a.double().cpu().numpy() if wt else np.ones(n)
+    assert np.max(np.abs(e.double().cpu().numpy() - E)) < 1e-6
+    for b in range(nb):
+        Ad, Bd = A[b].double().cpu().numpy(), B[b].double().cpu().numpy()
+        Yr = E @ Ad
+        assert np.linalg.norm(Y[b].double().cpu().numpy() - Yr) <= 1e-6 * np.linalg.norm(Yr)
+        q2 = (aw * ((Yr @ Bd) ** 2).sum(1)).sum()
+        assert abs(float(mb[b, 0]) - q2) <= 2e-6 * q2
