@@ -113,8 +113,8 @@ __global__ __launch_bounds__(kT) void k_small_grams(int64_t d, int64_t kp, const
 // iteration, whose updates are chains of dependent LDS reads and writes.
 constexpr int kTC = 1024;
 // the workgroup's reduction scratch (doubles): two block sums, then flags and scalars
-constexpr int kRedSum0 = 0, kRedSum1 = 16, kRedConv = 32, kRedRot = 33, kRedMax = 40, kRedDiag = 41,
-              kRedFail = 42, kRedLen = 48;
+constexpr int kRedSum0 = 0, kRedSum1 = 16, kRedConv = 32, kRedRot = 33, kRedMax = 40,
+              kRedLen = 48;
 
 // ------------------------------------------------------------------ symmetric eigensolver
 
@@ -131,11 +131,6 @@ LOCA_DEV double rcp64(double x) {
 #pragma unroll
   for (int i = 0; i < 2; ++i) y = fma(y, fma(-x, y, 1.0), y);
   return y;
-}
-// 1/x from the hardware approximation and one Newton step (about 2^-46 relative).
-LOCA_DEV double rcp64_1(double x) {
-  const double y = __builtin_amdgcn_rcp(x);
-  return fma(y, fma(-x, y, 1.0), y);
 }
 LOCA_DEV double rsq64(double x) {
   double y = __builtin_amdgcn_rsq(x);
@@ -293,20 +288,218 @@ LOCA_DEV double safe_pivot(double q, double pivmin) { return fabs(q) < pivmin ? 
 constexpr int kRedEig = 43;   // reduction-scratch slot: a check of eig_top failed
 constexpr int kRedLive = 44;  // ... the number of pairs eig_top returned
 
+// The matrix of a K x K problem (K <= 64) in the registers of eight waves: wave w's lane i holds
+// row i of the columns 8 (kb + s) + w in a[s], s < 8; kb counts the groups of eight columns
+// already finished (next_group drops one).
+constexpr int kRW = 8;          // waves that hold the matrix
+constexpr int kRS = 64 / kRW;   // columns per wave
+LOCA_DEV void next_group(double (&a)[kRS]) {
+#pragma unroll
+  for (int s = 0; s + 1 < kRS; ++s) a[s] = a[s + 1];
+  a[kRS - 1] = 0.0;
+}
+
+// Householder reduction of the packed symmetric A (K <= 64) to tridiagonal form: diagonal dT,
+// off-diagonal eT, reflector k (its scale in tauH[k]) in row k of W (stride 64, zero elsewhere).  A
+// step is one serial chain, so the matrix stays in registers and the chain is kept short: the
+// waves form q = A x for the column x itself, before its norm is known, and with v = x - alpha
+// e_1 take p = tau (q - alpha A e_1) and v^T A v = x^T q - 2 alpha q_1 + alpha^2 A_11, so that
+// both sums over the lanes run side by side.  Two barriers per step; the waves without columns
+// only keep them.  Bound by the broadcast LDS reads of the waves' columns and the chain's latency:
+// K = 64 86 us, 1.4 us per step (cross-lane reads of the columns with a runtime index 111 us, four
+// waves with a branch per column 98 us).  The whole core, K = 64 of rank 32: 312 -> 220 us.
+LOCA_DEV void tridiag64(const double* A, int n, int K, double* W, double* dT, double* eT, double* tauH) {
+  // entries past 63 stay zero: the finished groups' slots read them, without a branch
+  __shared__ double s_col[128], s_nxt[128], s_part[kRW][64], s_q[kRW][128];
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (wid >= kRW) {  // the barriers of the steps below
+    __syncthreads();
+    for (int k = 0; k + 2 < K; ++k) {
+      __syncthreads();
+      __syncthreads();
+    }
+    return;
+  }
+  double a[kRS];
+#pragma unroll
+  for (int s = 0; s < kRS; ++s) {
+    const int c = kRW * s + wid;
+    a[s] = lane < K && c < K ? A[pk(lane, c, n)] : 0.0;
+  }
+  s_q[wid][64 + lane] = 0.0;
+  if (wid == 0) s_col[lane] = a[0];
+  if (wid == 1) s_nxt[lane] = a[0];
+  if (wid == 2) s_col[64 + lane] = s_nxt[64 + lane] = 0.0;
+  __syncthreads();
+  int kb = 0;
+  for (int k = 0; k + 2 < K; ++k) {
+    const double xk = s_col[lane], x0 = s_col[k + 1], a11 = s_nxt[k + 1];
+    const double x = lane > k ? xk : 0.0;
+    const double y = lane > k ? s_nxt[lane] : 0.0;
+    double vc[kRS], yc[kRS], qc[kRS], acc = 0.0;
+#pragma unroll
+    for (int s = 0; s < kRS; ++s) {
+      const int c = kRW * (kb + s) + wid;
+      vc[s] = s == 0 && c <= k ? 0.0 : s_col[c];
+      yc[s] = s_nxt[c];
+      acc = fma(a[s], vc[s], acc);
+    }
+    s_part[wid][lane] = acc;
+    __syncthreads();
+    double q = 0.0;
+    {
+      double t[kRW];
+#pragma unroll
+      for (int u = 0; u < kRW; ++u) t[u] = s_part[u][lane];
+      q = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+    }
+    s_q[wid][lane] = q;  // read back by this wave alone
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const double q1 = s_q[wid][k + 1];
+#pragma unroll
+    for (int s = 0; s < kRS; ++s) {
+      const int c = kRW * (kb + s) + wid;
+      qc[s] = s_q[wid][c];
+    }
+    const double ss = wave_sum_all(x * x), xq = wave_sum_all(x * q);
+    double nx = ss * rsq64(ss);  // ||x||
+    if (!(ss > 1e-280)) nx = sqrt(ss);
+    const bool on = ss > 0.0;
+    const double alpha = on ? (x0 >= 0.0 ? -nx : nx) : x0;
+    const double v0 = x0 - alpha;
+    const double tau = on ? 2.0 * rcp64(ss - x0 * x0 + v0 * v0) : 0.0;
+    const double kk = 0.5 * tau * tau * fma(alpha, fma(alpha, a11, -2.0 * q1), xq);
+    const double v = lane == k + 1 ? v0 : x;
+    const double w = lane > k ? tau * fma(-alpha, y, q) - kk * v : 0.0;
+    // A -= v w^T + w v^T (columns up to k are not read again)
+#pragma unroll
+    for (int s = 0; s < kRS; ++s) {
+      const int c = kRW * (kb + s) + wid;
+      if (s < 2 && c == k + 1) vc[s] = v0;
+      const double wc = tau * fma(-alpha, yc[s], qc[s]) - kk * vc[s];
+      a[s] = fma(-w, vc[s], fma(-v, wc, a[s]));
+    }
+    if ((k & (kRW - 1)) == kRW - 1) {
+      next_group(a);
+      ++kb;
+    }
+    if (wid == ((k + 1) & (kRW - 1))) s_col[lane] = a[0];
+    if (wid == ((k + 2) & (kRW - 1))) s_nxt[lane] = ((k + 2) & (kRW - 1)) == 0 ? a[1] : a[0];
+    if (wid == ((k + 4) & (kRW - 1))) {  // a wave that publishes no column
+      W[k * 64 + lane] = v;  // zero up to column k and past K
+      if (lane == k) {
+        dT[k] = xk;
+        eT[k] = alpha;
+        tauH[k] = tau;
+      }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const int c = kRW * (kb + s) + wid;
+    if (c == K - 2 && lane == K - 2) dT[K - 2] = a[s];
+    if (c == K - 2 && lane == K - 1) eT[K - 2] = a[s];
+    if (c == K - 1 && lane == K - 1) dT[K - 1] = a[s];
+  }
+}
+
+// Gb (K x K, K <= 64) = L L^T, Gb as the sum of nsplit partial sums in order, on the same
+// layout: one barrier per column, step j updating the trailing columns from the unscaled column
+// j, which goes to row j of `raw` (64 x 64 scratch); the square roots follow in one pass, out of
+// the chain.  L into the lower triangle of the 64 x 64 Ld (stride kLd, zero elsewhere), the
+// reciprocals of its diagonal into dinv.  False for every thread when a pivot is not above 1e-10
+// of the largest diagonal entry (Ld then holds no factor).  K = 64: 29 us (44 with the matrix in
+// LDS, sixteen waves updating it there).
+constexpr int kLd = 65;  // odd: a column's entries lie in different banks
+LOCA_DEV bool chol64(const double* part, int nsplit, int K, double* raw, double* Ld, double* dinv, double* red) {
+  __shared__ double s_col[2][128];
+  __shared__ int s_fail;
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (tid == 0) s_fail = 0;
+  double a[kRS], mx = 0.0;
+  if (wid < kRW) {
+#pragma unroll
+    for (int s = 0; s < kRS; ++s) a[s] = 0.0;
+    for (int z = 0; z < nsplit; ++z)
+#pragma unroll
+      for (int s = 0; s < kRS; ++s) {
+        const int c = kRW * s + wid;
+        if (lane < K && c < K) a[s] += part[((int64_t)z * K + lane) * K + c];
+      }
+#pragma unroll
+    for (int s = 0; s < kRS; ++s)
+      if (kRW * s + wid == lane) mx = a[s];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+    if (lane == 0) red[wid] = mx;
+    if (wid == 0) s_col[0][lane] = a[0];
+    if (wid == 1) s_col[0][64 + lane] = s_col[1][64 + lane] = 0.0;
+  }
+  __syncthreads();
+  if (wid >= kRW) {
+    for (int j = 0; j < K; ++j) __syncthreads();
+  } else {
+#pragma unroll
+    for (int u = 0; u < kRW; ++u) mx = fmax(mx, red[u]);
+    const double thr = 1e-10 * mx;
+    bool fail = false;
+    int kb = 0;
+    for (int j = 0; j < K; ++j) {
+      const double* col = s_col[j & 1];
+      const double piv = col[j], x = col[lane];
+      double vc[kRS];
+#pragma unroll
+      for (int s = 0; s < kRS; ++s) {
+        const int c = kRW * (kb + s) + wid;
+        vc[s] = col[c];
+      }
+      fail = fail || !(piv > thr);
+      // columns up to j are finished: what the update leaves in them is not read again
+      const double t = x * rcp64(piv);
+#pragma unroll
+      for (int s = 0; s < kRS; ++s) {
+        const int c = kRW * (kb + s) + wid;
+        a[s] = fma(-t, vc[s], a[s]);
+      }
+      if ((j & (kRW - 1)) == kRW - 1) {
+        next_group(a);
+        ++kb;
+      }
+      if (wid == ((j + 1) & (kRW - 1))) s_col[(j + 1) & 1][lane] = a[0];
+      if (wid == ((j + 2) & (kRW - 1))) raw[j * 64 + lane] = x;
+      __syncthreads();
+    }
+    if (fail && tid == 0) s_fail = 1;
+  }
+  __syncthreads();
+  for (int e = tid; e < 64 * 64; e += kTC) {
+    const int j = e >> 6, i = e & 63;  // entry (i, j): raw is read along its rows
+    double l = 0.0;
+    if (j < K && i >= j && i < K) {
+      const double rs = 1.0 / sqrt(raw[j * 64 + j]);
+      l = raw[j * 64 + i] * rs;
+      if (i == j) dinv[j] = rs;
+    }
+    Ld[i * kLd + j] = l;
+  }
+  __syncthreads();
+  return s_fail == 0;
+}
+
 // All eigenvalues of the packed symmetric K x K matrix A (packed with stride n, K <= KM) and
 // the eigenvectors of its r largest, A left unchanged:
-//   1. Householder reduction T = Q^T A Q to tridiagonal form on the working matrix W (a
-//      dense copy of A, or, PACKED, A's packed triangle in place), two barriers per step:
-//      every wave forms the reflector v of row k itself, p = tau A v with kTC / KM lanes per
-//      row, then every wave w = p - (tau/2)(p^T v) v and the rank-2 update
+//   1. Householder reduction T = Q^T A Q to tridiagonal form: tridiag64 (the reflectors into
+//      the dense W), or, PACKED (K <= 128), on A's packed triangle W in place, two barriers
+//      per step: every wave forms the reflector v of row k itself, p = tau A v with kTC / KM
+//      lanes per row, then every wave w = p - (tau/2)(p^T v) v and the rank-2 update
 //      A -= v w^T + w v^T over a 32 x 32 grid of threads; the reflector is stored in row k
 //      right of the diagonal;
-//   2. every eigenvalue of T by multisection of Sturm counts: L = kTC / KM lanes per
-//      eigenvalue test the L - 1 interior points of L equal steps of its interval; for the r
-//      largest until the widened Gershgorin interval (at most 2.2 ||T||) has shrunk 2^52
-//      times or more, a few units of double rounding of ||T||, the accuracy of the Sturm
-//      counts themselves; 2^40 for the others, whose only use is the float sigma; the
-//      pivots' reciprocals from the hardware approximation and one Newton step;
+//   2. every eigenvalue of T by multisection of Sturm counts (signs of the leading minors):
+//      for the r largest until the widened Gershgorin interval (at most 2.2 ||T||) has shrunk
+//      2^52 times or more, a few units of double rounding of ||T||, the accuracy of the Sturm
+//      counts themselves; 2^40 for the others, whose only use is the float sigma;
 //   3. the eigenvector of T for each of the r largest (one lane each) from the twisted
 //      factorization of T - lambda I: the pivots of the top-down and bottom-up LDL^T, the
 //      twist index where their combination is smallest, and one solve that starts there;
@@ -333,17 +526,14 @@ LOCA_DEV bool eig_top(const double* A, int n, int K, int r, double* W, OutT* Vou
   const int tid = threadIdx.x, lane = tid & 63;
   auto at = [&](int i, int j) -> double& { return PACKED ? W[pk(i, j, n)] : W[i * n + j]; };
   auto segsum = [&](double v) { return LPR == 16 ? seg16_sum(v) : seg8_sum(v); };
-  if (!PACKED)
-    for (int e = tid; e < n * n; e += kTC) {
-      const int i = e / n, j = e % n;
-      W[e] = (i < K && j < K) ? A[pk(i, j, n)] : 0.0;
-    }
   __shared__ int s_cut;  // the number of pairs while it is lowered
   int* cut = &s_cut;
   if (tid == 0) red[kRedEig] = 0.0;
   __syncthreads();
   // 1. reduction to tridiagonal form
-  {
+  if constexpr (!PACKED) {
+    tridiag64(A, n, K, W, dT, eT, tauH);
+  } else {
     const int ty = tid >> 5, tx = tid & 31;
     for (int k = 0; k + 2 < K; ++k) {
       const int m = K - k - 1;  // entries right of the diagonal in row k
@@ -392,8 +582,8 @@ LOCA_DEV bool eig_top(const double* A, int n, int K, int r, double* W, OutT* Vou
           if (c < m) pv += pbuf[c] * (c == 0 ? v0 : xs[u]);
         }
         const double kk = 0.5 * tau * wave_sum_all(pv);
-        // A[k+1+i][k+1+c] -= v_i w_c + w_i v_c, w = p - kk v (upper triangle only when
-        // packed); thread (ty, tx) takes i in {ty + 32 a}, c in {tx + 32 b}
+        // A[k+1+i][k+1+c] -= v_i w_c + w_i v_c, w = p - kk v (upper triangle); thread
+        // (ty, tx) takes i in {ty + 32 a}, c in {tx + 32 b}
 #pragma unroll
         for (int a = 0; a < NU; ++a) {
           const int i = ty + 32 * a;
@@ -403,7 +593,7 @@ LOCA_DEV bool eig_top(const double* A, int n, int K, int r, double* W, OutT* Vou
 #pragma unroll
           for (int b = 0; b < NU; ++b) {
             const int c = tx + 32 * b;
-            if (c >= m || (PACKED && c < i)) continue;
+            if (c >= m || c < i) continue;
             const double vc = c == 0 ? v0 : at(k, k + 1 + c);
             const double wc = pbuf[c] - kk * vc;
             at(k + 1 + i, k + 1 + c) -= vi * wc + wi * vc;
@@ -422,63 +612,128 @@ LOCA_DEV bool eig_top(const double* A, int n, int K, int r, double* W, OutT* Vou
     }
   }
   __syncthreads();
-  for (int i = tid; i + 1 < K; i += kTC) e2[i] = eT[i] * eT[i];
   // Gershgorin interval, widened as in LAPACK's bisection, and the pivot floor
-  double glo = 0.0, ghi = 0.0, emax2 = 0.0;
-  for (int i = 0; i < K; ++i) {
+  double glo = 0.0, ghi = 0.0, emax2 = 0.0, tsum = 0.0;
+  for (int i = lane; i < K; i += 64) {
     const double rad = (i > 0 ? fabs(eT[i - 1]) : 0.0) + (i + 1 < K ? fabs(eT[i]) : 0.0);
-    glo = i == 0 ? dT[i] - rad : fmin(glo, dT[i] - rad);
-    ghi = i == 0 ? dT[i] + rad : fmax(ghi, dT[i] + rad);
+    glo = i == lane ? dT[i] - rad : fmin(glo, dT[i] - rad);
+    ghi = i == lane ? dT[i] + rad : fmax(ghi, dT[i] + rad);
     if (i + 1 < K) emax2 = fmax(emax2, eT[i] * eT[i]);
+    tsum += fabs(dT[i]) + rad;
   }
+  if (lane >= K) {
+    glo = dT[0] - (K > 1 ? fabs(eT[0]) : 0.0);
+    ghi = dT[0] + (K > 1 ? fabs(eT[0]) : 0.0);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    glo = fmin(glo, __shfl_xor(glo, o, 64));
+    ghi = fmax(ghi, __shfl_xor(ghi, o, 64));
+    emax2 = fmax(emax2, __shfl_xor(emax2, o, 64));
+    tsum += __shfl_xor(tsum, o, 64);
+  }
+  if (!(tsum < 1.7e308)) return false;  // an infinity or a NaN (every thread has the same entries)
   const double pivmin = 2.2250738585072014e-308 * fmax(1.0, emax2);
   const double tnorm = fmax(fabs(glo), fabs(ghi));
   glo -= 2.1 * tnorm * 2.220446049250313e-16 * K + 4.2 * pivmin;
   ghi += 2.1 * tnorm * 2.220446049250313e-16 * K + 4.2 * pivmin;
+  // The Sturm counts run on T scaled by a power of two to a norm in [1, 2), as the signs of the
+  // leading minors p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}: two dependent operations per row
+  // without a reciprocal, the signs gathered one bit per row.  e^2 is floored at 1e-50 (a change
+  // of 1e-25 ||T||), so that a p_i of zero costs no sign change; p loses at most 1e-60 per two
+  // rows and grows at most 6-fold per row, and is brought back to [1/2, 1) every eight rows.
+  // Rows past K, up to a multiple of eight, hold 4 (above every x): they change no sign.
+  const int sce = tnorm > 0.0 ? 1 - __builtin_amdgcn_frexp_exp(tnorm) : 0;
+  double* ds = pbuf;
+  const int Kp = (K + 7) & ~7;
+  for (int i = tid; i < Kp; i += kTC) {
+    ds[i] = i < K ? ldexp(dT[i], sce) : 4.0;
+    const double es = i > 0 && i < K ? ldexp(eT[i - 1], sce) : 0.0;
+    e2[i] = i > 0 ? fmax(es * es, 1e-50) : 0.0;
+  }
+  glo = ldexp(glo, sce);
+  ghi = ldexp(ghi, sce);
   __syncthreads();
+  // the number of eigenvalues of the scaled T below x[u], for NXV points at once (one read of
+  // T for all of them)
+  auto sturm = [&](auto& x, auto& cnt) {
+    constexpr int NXV = sizeof(x) / sizeof(x[0]);
+    double p[NXV], pp[NXV];
+    int bits[NXV];
+#pragma unroll
+    for (int u = 0; u < NXV; ++u) {
+      p[u] = 1.0;
+      pp[u] = 0.0;
+      bits[u] = 0;
+      cnt[u] = 0;
+    }
+    for (int i0 = 0; i0 < Kp; i0 += 8) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const double dv = ds[i0 + i], ev = e2[i0 + i];
+#pragma unroll
+        for (int u = 0; u < NXV; ++u) {
+          const double t = fma(dv - x[u], p[u], -(ev * pp[u]));
+          pp[u] = p[u];
+          p[u] = t;
+          bits[u] = (int)__builtin_amdgcn_alignbit((unsigned)bits[u],
+                                                   (unsigned)((unsigned long long)__double_as_longlong(t) >> 32), 31);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < NXV; ++u) {
+        cnt[u] += __builtin_popcount((bits[u] ^ (bits[u] >> 1)) & 0xFF);
+        const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p[u]), fabs(pp[u])));
+        p[u] = ldexp(p[u], ex);
+        pp[u] = ldexp(pp[u], ex);
+      }
+    }
+  };
   const int r_req = r;  // the pairs asked for: their eigenvalues all get the full precision
   {  // only the eigenvalues above 1e-12 ||T|| get vectors: below it the r largest would hold
      // a cluster of numerical zeros (A of rank below r), whose vectors the twisted solves
      // cannot separate and whose directions carry no weight (every thread counts alike)
-    const double x0 = 1e-12 * tnorm;
-    double q = safe_pivot(dT[0] - x0, pivmin);
-    int below = q < 0.0;
-    for (int i = 1; i < K; ++i) {
-      q = safe_pivot((dT[i] - x0) - e2[i - 1] * rcp64_1(q), pivmin);
-      below += q < 0.0;
-    }
-    if (K - below < r) r = K - below;
+    const double x0[1] = {ldexp(1e-12 * tnorm, sce)};
+    int below[1];
+    sturm(x0, below);
+    if (!(tnorm > 0.0)) below[0] = K;
+    if (K - below[0] < r) r = K - below[0];
     if (tid == 0) *cut = r;
   }
-  // 2. multisection: group g = tid / LPR finds the g-th smallest eigenvalue, lane t of the
-  // group testing point t + 1 of LPR equal steps (the last one is hi); for the r largest
-  // asked for (whose vectors follow, and whose singular values are reported to the same
-  // accuracy when they are numerical zeros), 52 bits or more of the interval (13 steps of
-  // 16, 18 of 8), for the others 40 or more (10 of 16, 14 of 8)
+  // 2. multisection: a group of L lanes finds the g-th smallest eigenvalue, lane t testing
+  // points 2t + 1 and 2t + 2 of 2L equal steps (the last one is hi); L from 512 / K, so that
+  // half the waves work whatever K is and two points share each read of T: the counts are bound
+  // by the LDS reads (8 bytes to every lane per value) and the vector fp64 rate alike (K = 64: 32
+  // us; 94 with a quotient recurrence, whose reciprocal took most of each row's issue slots, and
+  // sixteen lanes of one point per eigenvalue).  For the
+  // r largest asked for (whose vectors follow, and whose singular values are reported to the
+  // same accuracy when they are numerical zeros) 52 bits or more of the interval, for the
+  // others 40 or more.
   {
-    constexpr int STEPS_V = LPR == 16 ? 13 : 18, STEPS_S = LPR == 16 ? 10 : 14;
-    const int g = tid / LPR, t = tid % LPR;
-    const int j = g < K ? g : K - 1;
-    const int steps = K - 1 - j < r_req ? STEPS_V : STEPS_S;
-    double lo = glo, hi = ghi;
-    for (int it = 0; it < steps; ++it) {
-      const double h = (hi - lo) * (1.0 / LPR);
-      const double x = lo + (double)(t + 1) * h;
-      double q = safe_pivot(dT[0] - x, pivmin);
-      int cnt = q < 0.0;
-      for (int i = 1; i < K; ++i) {
-        q = safe_pivot((dT[i] - x) - e2[i - 1] * rcp64_1(q), pivmin);
-        cnt += q < 0.0;
+    int lb = KM == 64 ? 3 : 2;  // log2 L
+    while (lb < 6 && (K << (lb + 1)) <= 512) ++lb;
+    const int L = 1 << lb, g = tid >> lb, t = tid & (L - 1);
+    if ((g & ~((64 >> lb) - 1)) < K) {  // waves wholly past the last eigenvalue have nothing to find
+      const int j = g < K ? g : K - 1;
+      const int steps = ((K - 1 - j < r_req ? 52 : 40) + lb) / (lb + 1);
+      double lo = glo, hi = ghi;
+      for (int it = 0; it < steps; ++it) {
+        const double h = ldexp(hi - lo, -(lb + 1));
+        const double x[2] = {lo + (double)(2 * t + 1) * h, lo + (double)(2 * t + 2) * h};
+        int cnt[2];
+        sturm(x, cnt);
+        if (t == L - 1) cnt[1] = K;
+        const unsigned long long seg = ~0ull >> (64 - L);
+        const int sh = lane & ~(L - 1);
+        const unsigned long long b0 = (__ballot(cnt[0] > j) >> sh) & seg, b1 = (__ballot(cnt[1] > j) >> sh) & seg;
+        const int f1 = __builtin_ctzll(b1);  // b1's last lane is set
+        const int f = 2 * f1 + 1 - (int)((b0 >> f1) & 1);
+        const double nlo = f == 0 ? lo : lo + (double)f * h;
+        hi = f == 2 * L - 1 ? hi : lo + (double)(f + 1) * h;
+        lo = nlo;
       }
-      if (t == LPR - 1) cnt = K;
-      const unsigned long long b = __ballot(cnt > j);
-      const unsigned seg = (unsigned)(b >> (lane & (64 - LPR))) & ((1u << LPR) - 1u);  // last lane set
-      const int f = __builtin_ctz(seg);
-      const double nlo = f == 0 ? lo : lo + (double)f * h;
-      hi = f == LPR - 1 ? hi : lo + (double)(f + 1) * h;
-      lo = nlo;
+      if (g < K && t == 0) eig[K - 1 - g] = ldexp(0.5 * (lo + hi), -sce);
     }
-    if (g < K && t == 0) eig[K - 1 - g] = 0.5 * (lo + hi);
   }
   __syncthreads();
   // eigenvalues among the r largest closer than 1e-10 of the largest |lambda| (a repeated
@@ -503,7 +758,7 @@ LOCA_DEV bool eig_top(const double* A, int n, int K, int r, double* W, OutT* Vou
     double dp = safe_pivot(dT[0] - lam, pivmin);
     w[0] = dp;
     for (int i = 0; i + 1 < K; ++i) {
-      dp = safe_pivot((dT[i + 1] - lam) - e2[i] * rcp64(dp), pivmin);
+      dp = safe_pivot((dT[i + 1] - lam) - (eT[i] * eT[i]) * rcp64(dp), pivmin);
       w[i + 1] = dp;
     }
     double dm = safe_pivot(dT[K - 1] - lam, pivmin);
@@ -556,20 +811,31 @@ LOCA_DEV bool eig_top(const double* A, int n, int K, int r, double* W, OutT* Vou
       const int i = t + 16 * q;
       zr[q] = (act && i < K) ? Z[a * K + i] : 0.0;
     }
-    for (int k = K - 3; k >= 0; --k) {
-      const double tau = tauH[k];
-      if (tau == 0.0) continue;
-      double dot = 0.0;
+    if constexpr (!PACKED) {  // rows of W are zero outside their reflector: no conditions
+      for (int k = K - 3; k >= 0; --k) {
+        double vr[NZ];
 #pragma unroll
-      for (int q = 0; q < NZ; ++q) {
-        const int i = t + 16 * q;
-        if (i > k && i < K) dot += at(k, i) * zr[q];
+        for (int q = 0; q < NZ; ++q) vr[q] = W[k * 64 + t + 16 * q];
+        const double f = tauH[k] * seg16_sum(fma(vr[0], zr[0], vr[1] * zr[1]) + fma(vr[2], zr[2], vr[3] * zr[3]));
+#pragma unroll
+        for (int q = 0; q < NZ; ++q) zr[q] = fma(-f, vr[q], zr[q]);
       }
-      const double f = tau * seg16_sum(dot);
+    } else {
+      for (int k = K - 3; k >= 0; --k) {
+        const double tau = tauH[k];
+        if (tau == 0.0) continue;
+        double dot = 0.0;
 #pragma unroll
-      for (int q = 0; q < NZ; ++q) {
-        const int i = t + 16 * q;
-        if (i > k && i < K) zr[q] -= f * at(k, i);
+        for (int q = 0; q < NZ; ++q) {
+          const int i = t + 16 * q;
+          if (i > k && i < K) dot += at(k, i) * zr[q];
+        }
+        const double f = tau * seg16_sum(dot);
+#pragma unroll
+        for (int q = 0; q < NZ; ++q) {
+          const int i = t + 16 * q;
+          if (i > k && i < K) zr[q] -= f * at(k, i);
+        }
       }
     }
     __syncthreads();  // the reflectors and Z are read by every group before Vout is written
@@ -588,6 +854,38 @@ LOCA_DEV bool eig_top(const double* A, int n, int K, int r, double* W, OutT* Vou
   // the check (vectors as stored: a float copy is held to float accuracy)
   constexpr double kRes = sizeof(OutT) == 8 ? 1e-11 : 1e-5, kOrth = sizeof(OutT) == 8 ? 1e-9 : 1e-5;
   const double anorm = fmax(fabs(eig[0]), fabs(eig[K - 1]));
+  if constexpr (!PACKED) {
+    // a wave per 16 x 16 block of A V - V diag(lambda) and of V^T V, on the fp64 matrix cores
+    __shared__ double s_rs[4][64];
+    const int wid = tid >> 6, li = lane & 15, lk = lane >> 4;
+    const int bi = 16 * (wid >> 2), bj = 16 * (wid & 3);
+    const int i = bi + li, j = bj + li;  // this lane's row and column as operands
+    f64x4_t av = {0.0, 0.0, 0.0, 0.0}, vv = {0.0, 0.0, 0.0, 0.0};
+    for (int x0 = 0; x0 < K; x0 += 4) {
+      const int x = x0 + lk;
+      const double vj = x < K && j < r ? Vout[x * n + j] : 0.0;
+      av = mfma_f64(x < K && i < K ? A[pk(i, x, n)] : 0.0, vj, av);
+      vv = mfma_f64(x < K && i < r ? Vout[x * n + i] : 0.0, vj, vv);
+    }
+    double rs = 0.0;
+    bool bad = false;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int row = bi + lk + 4 * u;
+      if (row < K && j < r) {
+        const double t = av[u] - eig[j] * Vout[row * n + j];
+        rs += t * t;
+      }
+      bad = bad || (row < r && j < r && !(fabs(vv[u] - (row == j ? 1.0 : 0.0)) <= kOrth));
+    }
+    rs += __shfl_xor(rs, 16, 64);
+    rs += __shfl_xor(rs, 32, 64);
+    if (lk == 0) s_rs[wid >> 2][j] = rs;
+    __syncthreads();
+    const double tol = kRes * anorm;
+    if (tid < r) bad = bad || !((s_rs[0][tid] + s_rs[1][tid]) + (s_rs[2][tid] + s_rs[3][tid]) <= tol * tol);
+    if (bad) red[kRedEig] = 1.0;
+  } else {
   {
     const int a = tid >> 4, t = tid & 15;
     double rs = 0.0;
@@ -609,6 +907,7 @@ LOCA_DEV bool eig_top(const double* A, int n, int K, int r, double* W, OutT* Vou
     double s = 0.0;
     for (int i = 0; i < K; ++i) s += (double)Vout[i * n + a] * (double)Vout[i * n + b];
     if (!(fabs(s - (a == b ? 1.0 : 0.0)) <= kOrth)) red[kRedEig] = 1.0;
+  }
   }
   __syncthreads();
   return red[kRedEig] == 0.0;
@@ -949,7 +1248,7 @@ __global__ __launch_bounds__(kTC) void k_trunc_core(int64_t kp, int64_t r_a, con
   constexpr int KB2 = kMaxKp * kMaxKp;
   __shared__ double sA[kMaxKp * (kMaxKp + 1) / 2];
   __shared__ double sV[KB2];   // eigenvectors of the current eigensolve; T = Gm H in between
-  __shared__ double sVb[KB2];  // Gb, then its factor: L (Cholesky) or Vb (Jacobi)
+  __shared__ double sVb[kMaxKp * kLd];  // the factor of Gb: L (Cholesky, stride kLd) or Vb (eigenvectors)
   __shared__ double sG[KB2];   // Gm; L^{-T} Vp after the eigensolve (Cholesky path)
   __shared__ double sH[kMaxKp], sHi[kMaxKp], sEig[kMaxKp];
   __shared__ double sT[5][kMaxKp];  // the tridiagonal eigensolver's vectors
@@ -963,78 +1262,48 @@ __global__ __launch_bounds__(kTC) void k_trunc_core(int64_t kp, int64_t r_a, con
   const int n = K + (K & 1);  // even size for the tournament ordering
   const double* GmP = Gpart + (mi * 2) * nsplit * kp * kp;
   const double* GbP = Gpart + (mi * 2 + 1) * nsplit * kp * kp;
-  // 1. Gm into sG and Gb into sVb (n x n, zero padded), each summed over the row ranges in order
+  // 1. Gm into sG (n x n, zero padded), summed over the row ranges in order
   for (int e = tid; e < n * n; e += kTC) {
     const int i = e / n, j = e % n;
-    double gb = 0.0, gm = 0.0;
+    double gm = 0.0;
     if (i < K && j < K)
-      for (int z = 0; z < nsplit; ++z) {
-        gb += GbP[z * kp * kp + i * kp + j];
-        gm += GmP[z * kp * kp + i * kp + j];
-      }
+      for (int z = 0; z < nsplit; ++z) gm += GmP[z * kp * kp + i * kp + j];
     sG[e] = gm;
-    sVb[e] = gb;
   }
-  __syncthreads();
-  // 2. Gb = L L^T (L in the lower triangle of sVb), or a failed pivot.  One barrier per
-  // step: step j updates the trailing lower triangle from the unscaled column j,
-  // A[i][c] -= A[i][j] A[c][j] / A[j][j] (thread (ty, tx) of a 32 x 32 grid takes i in
-  // {ty, ty + 32}, c in {tx, tx + 32}), while column j - 1, no longer read, is scaled into L.
-  {
-    const int ty = tid >> 5, tx = tid & 31;
-    double mx = 0.0;
-    for (int j = 0; j < K; ++j) mx = fmax(mx, sVb[j * n + j]);
-    const double thr = 1e-10 * mx;
-    bool fail = false;
-    int j = 0;
-    for (; j < K; ++j) {
-      const double piv = sVb[j * n + j];
-      if (j > 0) {  // column j - 1 into L
-        const double pj = sVb[(j - 1) * n + j - 1];  // its pivot, still unscaled
-        const double inv = rsq64(pj);
-        for (int i = j + tid; i < K; i += kTC) sVb[i * n + j - 1] *= inv;
-      }
-      if (!(piv > thr)) {  // uniform: every thread reads the same pivot
-        fail = true;
-        break;
-      }
-      const double rp = rcp64(piv);
-#pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        const int i = ty + 32 * a;
-        if (i <= j || i >= K) continue;
-        const double aij = sVb[i * n + j] * rp;
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          const int c = tx + 32 * b;
-          if (c <= j || c > i) continue;
-          sVb[i * n + c] -= aij * sVb[c * n + j];
-        }
-      }
-      __syncthreads();
-    }
-    if (!fail)  // the diagonal of L (the last column has nothing below it)
-      for (int i = tid; i < K; i += kTC) sVb[i * n + i] = sqrt(sVb[i * n + i]);
-    if (tid == 0) red[kRedFail] = fail ? 1.0 : 0.0;
-  }
-  __syncthreads();
-  const bool chol = red[kRedFail] == 0.0;
+  // 2. Gb = L L^T (L in the lower triangle of sVb), or a failed pivot
+  const bool chol = chol64(GbP, nsplit, K, sV, sVb, sHi, red);
   if (chol) {
-    // 3. T = Gm L (into sV), P^T P = L^T T (upper triangle, packed; zero padding)
-    for (int e = tid; e < K * K; e += kTC) {
-      const int i = e / K, c = e % K;
-      double s = 0.0;
-      for (int x = c; x < K; ++x) s += sG[i * n + x] * sVb[x * n + c];
-      sV[i * n + c] = s;
+    // 3. T = Gm L (into sV), P^T P = L^T T (upper triangle, packed; zero padding): a wave per
+    // 16 x 16 block on the fp64 matrix cores (one thread per entry took two LDS reads per
+    // multiplication); the zeros above L's diagonal bound the sums
+    const int lane = tid & 63, li = lane & 15, lk = lane >> 4;
+    const int bi = 16 * (tid >> 8), bj = 16 * ((tid >> 6) & 3);  // this wave's block
+    f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
+    if (bi < K && bj < K) {
+      for (int x0 = bj; x0 < K; x0 += 4) {  // L[x][c] = 0 for x < c
+        const int x = x0 + lk;
+        acc = mfma_f64(bi + li < K && x < K ? sG[x * n + bi + li] : 0.0,  // Gm is symmetric
+                       sVb[x * kLd + bj + li], acc);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (bi + lk + 4 * r < n && bj + li < n) sV[(bi + lk + 4 * r) * n + bj + li] = acc[r];
     }
     __syncthreads();
-    for (int e = tid; e < n * n; e += kTC) {
-      const int i = e / n, j = e % n;
-      if (i > j) continue;
-      double s = 0.0;
-      if (j < K)
-        for (int x = i; x < K; ++x) s += sVb[x * n + i] * sV[x * n + j];
-      sA[pk(i, j, n)] = s;
+    for (int e = tid; e < n * (n + 1) / 2; e += kTC) sA[e] = 0.0;
+    __syncthreads();
+    if (bi < K && bj < K && bi <= bj) {
+      acc = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+      for (int x0 = bi; x0 < K; x0 += 4) {
+        const int x = x0 + lk;
+        acc = mfma_f64(sVb[x * kLd + bi + li],
+                       bj + li < K && x < K ? sV[x * n + bj + li] : 0.0, acc);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = bi + lk + 4 * r, j = bj + li;
+        if (i <= j && j < K) sA[pk(i, j, n)] = acc[r];
+      }
     }
     __syncthreads();
   } else {
@@ -1127,10 +1396,10 @@ __global__ __launch_bounds__(kTC) void k_trunc_core(int64_t kp, int64_t r_a, con
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int x = t + 16 * q;
-          if (x > c && x < K) sum += sVb[x * n + c] * zq[q];
+          sum = fma(sVb[x * kLd + c], zq[q], sum);  // zq[x] is zero up to x = c and past K
         }
         sum = seg16_sum(sum);
-        const double zc = (sV[c * n + col] - sum) / sVb[c * n + c];
+        const double zc = (sV[c * n + col] - sum) * sHi[c];
 #pragma unroll
         for (int q = 0; q < 4; ++q)
           if (c == t + 16 * q) zq[q] = zc;
@@ -1163,7 +1432,7 @@ __global__ __launch_bounds__(kTC) void k_trunc_core(int64_t kp, int64_t r_a, con
     const double sa = sqrt(fmax(sEig[col], 0.0));
     double u = 0.0, v = 0.0;
     if (chol) {
-      for (int x = 0; x <= c; ++x) u += sVb[c * n + x] * sV[x * n + col];
+      for (int x = 0; x <= c; ++x) u += sVb[c * kLd + x] * sV[x * n + col];
       v = sG[c * n + col];
     } else {
       for (int x = 0; x < n; ++x) {

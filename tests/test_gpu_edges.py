@@ -256,3 +256,35 @@ def test_label_set_head_edges(n, C, k, nb, wt):
         assert np.linalg.norm(Y[b].double().cpu().numpy() - Yr) <= 1e-6 * np.linalg.norm(Yr)
         q2 = (aw * ((Yr @ Bd) ** 2).sum(1)).sum()
         assert abs(float(mb[b, 0]) - q2) <= 2e-6 * q2
+
+
+# the truncation's small eigenproblem at the sizes where its column groups of four, its rows of
+# eight in the Sturm counts and its 16 x 16 blocks end, over norms whose squares leave the float
+# range, up to the switch to the larger core at kp = 65.  The factors are rounded to float, so
+# each entry of W is off by about 2^-23 of its products, and so are the singular values; 1e-6
+# leaves a factor of eight
+@pytest.mark.parametrize("scale", [1.0, 1e-16, 1e14])
+@pytest.mark.parametrize("kp,r", [(1, 1), (2, 1), (3, 3), (4, 4), (7, 5), (8, 8), (9, 2), (15, 15), (16, 8), (17, 17), (31, 16),
+                                  (32, 32), (33, 12), (48, 32), (63, 63), (64, 64), (65, 20), (128, 64)])
+def test_truncation_core_edges(kp, r, scale):
+    import torch
+    from paper_2608_03020_amd import loca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(kp)
+    nm, d = 2, 150
+    m = torch.randn((nm, d, kp), generator=g, device="cuda") * (0.9 ** torch.arange(kp, device="cuda") * scale)
+    b = torch.randn((nm, kp, d), generator=g, device="cuda")
+    kw = dict(dtype=torch.float32, device="cuda")
+    a_o, b_o = torch.full((nm, r, d), float("nan"), **kw), torch.full((nm, d, r), float("nan"), **kw)
+    sig, info = torch.full((nm, kp), float("nan"), **kw), torch.zeros(nm, dtype=torch.int32, device="cuda")
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_LOWRANK_TRUNCATE, nm, 0, d, kp, r_a=r))
+    log("truncation core", kp, r, scale)
+    loca.loca_lowrank_truncate(m, b, r, a_o, b_o, sig, info, ws)
+    W = np.einsum("bri,bjr->bij", a_o.double().cpu().numpy(), b_o.double().cpu().numpy())
+    for i in range(nm):
+        U, s, Vh = np.linalg.svd(m[i].double().cpu().numpy() @ b[i].double().cpu().numpy(), full_matrices=False)
+        ref = (U[:, :r] * s[:r]) @ Vh[:r]
+        e_w, e_s = rel(W[i], ref), rel(sig[i].double().cpu().numpy(), s[:kp])
+        log(f"  W_r {e_w:.1e} sigma {e_s:.1e}")
+        assert e_w < 1e-6 and e_s < 1e-6
+    assert not info.any()
