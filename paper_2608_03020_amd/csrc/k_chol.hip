@@ -175,47 +175,66 @@ __global__ __launch_bounds__(256) void k_equil_setup_v4(int64_t d, int64_t m, in
     }
 }
 
-// SLp[b] = S_sym Lp (d x r_prev, fp64) from the upper triangle of S.  A workgroup owns 64
-// rows and RC columns of the product (grid: x over row tiles, y = block, z over column
-// chunks) and walks the 64-wide column tiles of S in order: tiles on or above the
-// diagonal are read row-major, tiles below it as the transpose of the stored tile above
-// (both with coalesced rows), the diagonal tile mirrored from its upper half.  Thread t
-// owns row t % 64 and all RC columns; wave q = t / 64 takes the columns 16q .. 16q + 15 of
-// each tile, and the four waves' sums are added in a fixed order at the end.
+// out[b] = S_sym L (d x r, fp64) from the upper triangle of S; L(j, c) = L[j l_sj + c l_sc].  A
+// workgroup owns 64 rows and 16 NC columns of the product (grid: x over row tiles, y = block, z
+// over column chunks) and walks the 64-wide column tiles of S in order: tiles on or above the
+// diagonal are read row-major, tiles below it as the transpose of the stored tile above (both
+// with coalesced rows), the diagonal tile mirrored from its upper half.  A wave forms 16 of the
+// rows on the fp64 matrix cores, and the next tile's loads are in flight meanwhile: with one
+// tile at a time and a thread per row on the vector unit, the load, the conversions of L and the
+// sums followed one another (24 blocks of
+// d = 896, r = 8: 135 -> 45 us; the projected form of one fp64 block of d = 896: 206 -> 35 us).
 constexpr int kSM = 64;
-template <typename ST, int RC>
-__global__ __launch_bounds__(256) void k_sym_mul(int64_t d, int64_t r_prev, const ST* __restrict__ S,
-                                                 int64_t s_bstride, const float* __restrict__ Lp,
-                                                 int64_t lp_bstride, double* __restrict__ out) {
-  __shared__ ST sS[kSM][kSM + 1];
-  __shared__ __attribute__((aligned(16))) float sL[kSM][RC];
-  __shared__ double sR[3][kSM][RC + 1];
+template <typename ST, int NC>
+__global__ __launch_bounds__(256) void k_sym_mul(int64_t d, int64_t r, const ST* __restrict__ S, int64_t s_bstride,
+                                                 const float* __restrict__ Lall, int64_t l_bstride, int64_t l_sj,
+                                                 int64_t l_sc, double* __restrict__ out) {
+  constexpr int RC = 16 * NC, SU = kSM * kSM / 256, LU = kSM * RC / 256;
+  __shared__ ST sS[kSM][kSM + 1];     // [row][column j]
+  __shared__ float sL[RC][kSM + 1];   // [column c][j]
   const int64_t b = blockIdx.y;
-  const int64_t i0 = (int64_t)blockIdx.x * kSM;
-  const int64_t c0 = (int64_t)blockIdx.z * RC;
+  const int64_t i0 = (int64_t)blockIdx.x * kSM, c0 = (int64_t)blockIdx.z * RC;
   const ST* Sb = S + b * s_bstride;
-  const float* L = Lp + b * lp_bstride;
-  const int t = threadIdx.x, r = t & 63, q = t >> 6;
-  double acc[RC];
+  const float* L = Lall + b * l_bstride;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, li = lane & 15, lk = lane >> 4;
+  const bool jfast = l_sj == 1;  // L's contiguous direction: lanes along it
+  f64x4_t acc[NC][2];
 #pragma unroll
-  for (int u = 0; u < RC; ++u) acc[u] = 0.0;
+  for (int q = 0; q < NC; ++q)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) acc[q][h] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  ST vS[SU];
+  float vL[LU];
+  auto load = [&](int64_t j0) {  // the stored tile: rows r0.., columns q0.. (transposed left of the diagonal)
+    const int64_t r0 = j0 < i0 ? j0 : i0, q0 = j0 < i0 ? i0 : j0;
+#pragma unroll
+    for (int u = 0; u < SU; ++u) {
+      const int e = t + 256 * u;
+      const int64_t gi = r0 + e / kSM, gj = q0 + e % kSM;
+      vS[u] = gi < d && gj < d ? Sb[gi * d + gj] : (ST)0;
+    }
+#pragma unroll
+    for (int u = 0; u < LU; ++u) {
+      const int e = t + 256 * u;
+      const int64_t j = j0 + (jfast ? e % kSM : e / RC), c = c0 + (jfast ? e / kSM : e % RC);
+      vL[u] = j < d && c < r ? L[j * l_sj + c * l_sc] : 0.f;
+    }
+  };
+  load(0);
   for (int64_t j0 = 0; j0 < d; j0 += kSM) {
-    __syncthreads();
-    // sS[rr][cc] = S_sym[i0 + rr][j0 + cc]
-    for (int e = t; e < kSM * kSM; e += 256) {
-      const int rr = e / kSM, cc = e % kSM;
-      if (j0 >= i0) {  // rows i0 + rr, columns j0 + cc (the diagonal tile is fixed up below)
-        const int64_t gi = i0 + rr, gj = j0 + cc;
-        sS[rr][cc] = (gi < d && gj < d) ? Sb[gi * d + gj] : (ST)0;
-      } else {         // stored tile (j0, i0): rows j0 + rr, columns i0 + cc, transposed
-        const int64_t gi = j0 + rr, gj = i0 + cc;
-        sS[cc][rr] = (gi < d && gj < d) ? Sb[gi * d + gj] : (ST)0;
-      }
+    __syncthreads();  // the previous tile is no longer read
+#pragma unroll
+    for (int u = 0; u < SU; ++u) {
+      const int e = t + 256 * u, rr = e / kSM, cc = e % kSM;
+      if (j0 < i0) sS[cc][rr] = vS[u];
+      else sS[rr][cc] = vS[u];
     }
-    for (int e = t; e < kSM * RC; e += 256) {
-      const int rr = e / RC, cc = e % RC;
-      sL[rr][cc] = (j0 + rr < d && c0 + cc < r_prev) ? L[(j0 + rr) * r_prev + c0 + cc] : 0.f;
+#pragma unroll
+    for (int u = 0; u < LU; ++u) {
+      const int e = t + 256 * u;
+      sL[jfast ? e / kSM : e % RC][jfast ? e % kSM : e / RC] = vL[u];
     }
+    if (j0 + kSM < d) load(j0 + kSM);
     __syncthreads();
     if (j0 == i0) {  // mirror the upper half of the diagonal tile
       for (int e = t; e < kSM * kSM; e += 256) {
@@ -224,29 +243,33 @@ __global__ __launch_bounds__(256) void k_sym_mul(int64_t d, int64_t r_prev, cons
       }
       __syncthreads();
     }
-#pragma unroll 4
-    for (int jj = 16 * q; jj < 16 * q + 16; ++jj) {
-      const double sv = (double)sS[r][jj];
 #pragma unroll
-      for (int u = 0; u < RC; u += 4) {
-        const float4 l = *(const float4*)&sL[jj][u];
-        acc[u] += sv * (double)l.x;
-        acc[u + 1] += sv * (double)l.y;
-        acc[u + 2] += sv * (double)l.z;
-        acc[u + 3] += sv * (double)l.w;
-      }
+    for (int ks = 0; ks < kSM; ks += 4) {
+      const double fa = (double)sS[16 * w + li][ks + lk];
+#pragma unroll
+      for (int q = 0; q < NC; ++q)
+        acc[q][(ks >> 2) & 1] = mfma_f64(fa, (double)sL[16 * q + li][ks + lk], acc[q][(ks >> 2) & 1]);
     }
   }
-  if (q > 0)
 #pragma unroll
-    for (int u = 0; u < RC; ++u) sR[q - 1][r][u] = acc[u];
-  __syncthreads();
-  if (q == 0 && i0 + r < d)
+  for (int q = 0; q < NC; ++q)
 #pragma unroll
-    for (int u = 0; u < RC; ++u) {
-      const double v = ((acc[u] + sR[0][r][u]) + sR[1][r][u]) + sR[2][r][u];
-      if (c0 + u < r_prev) out[b * d * r_prev + (i0 + r) * r_prev + c0 + u] = v;
+    for (int u = 0; u < 4; ++u) {
+      const int64_t i = i0 + 16 * w + lk + 4 * u, c = c0 + 16 * q + li;
+      if (i < d && c < r) out[(b * d + i) * r + c] = acc[q][0][u] + acc[q][1][u];
     }
+}
+
+template <typename ST>
+hipError_t sym_mul(hipStream_t s, int64_t nb, int64_t d, int64_t r, const ST* S, int64_t s_bstride, const float* L,
+                   int64_t l_bstride, int64_t l_sj, int64_t l_sc, double* out) {
+  const unsigned gx = (unsigned)((d + kSM - 1) / kSM);
+  if (r <= 16)
+    k_sym_mul<ST, 1><<<dim3(gx, (unsigned)nb), 256, 0, s>>>(d, r, S, s_bstride, L, l_bstride, l_sj, l_sc, out);
+  else
+    k_sym_mul<ST, 2><<<dim3(gx, (unsigned)nb, (unsigned)((r + 31) / 32)), 256, 0, s>>>(d, r, S, s_bstride, L, l_bstride,
+                                                                                       l_sj, l_sc, out);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ matrix-core tile products
@@ -1557,13 +1580,8 @@ hipError_t run_group(const SolveArgs& a, int64_t b0, int64_t nbg, hipStream_t st
   const int64_t lp_bstride = a.lp_bstride;
   hipError_t e = emit([=]() {
     if (r_prev > 0) {
-      if (r_prev <= 16) {
-        dim3 g((unsigned)((d + kSM - 1) / kSM), (unsigned)nbg, 1);
-        k_sym_mul<ST, 16><<<g, 256, 0, st>>>(d, r_prev, S, s_bstride, lp, lp_bstride, SLp);
-      } else {
-        dim3 g((unsigned)((d + kSM - 1) / kSM), (unsigned)nbg, (unsigned)((r_prev + 31) / 32));
-        k_sym_mul<ST, 32><<<g, 256, 0, st>>>(d, r_prev, S, s_bstride, lp, lp_bstride, SLp);
-      }
+      hipError_t e = sym_mul<ST>(st, nbg, d, r_prev, S, s_bstride, lp, lp_bstride, r_prev, 1, SLp);
+      if (e != hipSuccess) return e;
     }
     if (reuse) {  // D and F from the earlier call: the right-hand sides only
       dim3 gr((unsigned)((d * m + 255) / 256), (unsigned)nm);
@@ -1856,6 +1874,11 @@ hipError_t launch_chol_inv64(hipStream_t s, int64_t n, double* A, int32_t* info)
 hipError_t launch_ridge_solve(const SolveArgs& a) {
   if (a.acc == LOCA_F64) return run_solve<double, double>(a);
   return run_solve<float, float>(a);
+}
+
+hipError_t launch_sym_mul_f64(hipStream_t s, int64_t nb, int64_t d, int64_t r, const double* S, int64_t s_bstride,
+                              const float* L, int64_t l_bstride, int64_t l_sj, int64_t l_sc, double* out) {
+  return sym_mul<double>(s, nb, d, r, S, s_bstride, L, l_bstride, l_sj, l_sc, out);
 }
 
 }  // namespace loca

@@ -1782,23 +1782,8 @@ hipError_t launch_lowrank_truncate(const TruncArgs& a) {
 
 namespace {
 
-// T1[b][i][a] = sum_j S_sym[i][j] PA[a][j]  (fp64, d x r_a); S_sym from the upper triangle.
-template <typename ST>
-__global__ void k_proj_sa(int64_t d, int64_t r_a, const ST* __restrict__ S, int64_t s_bstride,
-                          const float* __restrict__ PA, int64_t pa_bstride, double* __restrict__ T1) {
-  const int64_t b = blockIdx.y;
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= d * r_a) return;
-  const int64_t i = e / r_a, a = e % r_a;
-  const ST* Sb = S + b * s_bstride;
-  const float* P = PA + b * pa_bstride + a * d;
-  double s = 0.0;
-  for (int64_t j = 0; j < i; ++j) s += (double)Sb[j * d + i] * (double)P[j];
-  for (int64_t j = i; j < d; ++j) s += (double)Sb[i * d + j] * (double)P[j];
-  T1[b * d * r_a + e] = s;
-}
-
-// The same product for fp32 S on the fp32 matrix cores (v_mfma_f32_32x32x2f32), reading S
+// T1[b][i][a] = sum_j S_sym[i][j] PA[a][j] (d x r_a, S_sym from the upper triangle) for fp32 S
+// on the fp32 matrix cores (v_mfma_f32_32x32x2f32), reading S
 // once per use with coalesced loads.  One workgroup per (64-row panel I, block b); the
 // panel's rows of the symmetric S are staged 64 columns at a time: chunks right of the
 // diagonal straight from the stored upper triangle, chunks left of it as the transposes of
@@ -2151,11 +2136,12 @@ hipError_t launch_ridge_solve_projected(const ProjArgs& a) {
   k_set_lams8<<<1, 64, 0, a.stream>>>(l8, dlam, (int)a.n_lambda);
   const int64_t nm = a.nb * a.n_lambda;
   k_fill_zero<<<(unsigned)((nm + 255) / 256), 256, 0, a.stream>>>(a.dev_info, nm);
-  dim3 g1((unsigned)((a.d * a.r_a + 255) / 256), (unsigned)a.nb);
   if (a.r_a + a.k > kProjT) return hipErrorInvalidValue;  // one thread per column of [T1 | K]
   dim3 g2(1u, (unsigned)a.nb, kProjSplit);
   if (a.acc == LOCA_F64) {
-    k_proj_sa<double><<<g1, 256, 0, a.stream>>>(a.d, a.r_a, (const double*)a.S, a.s_bstride, a.proj_a, a.pa_bstride, T1);
+    const hipError_t e = launch_sym_mul_f64(a.stream, a.nb, a.d, a.r_a, (const double*)a.S, a.s_bstride, a.proj_a,
+                                            a.pa_bstride, 1, a.d, T1);
+    if (e != hipSuccess) return e;
     if (a.r_a <= 32)
       k_proj_small_part<double, 32><<<g2, kProjT, 0, a.stream>>>(a.d, a.k, a.r_a, a.proj_a, a.pa_bstride, T1,
                                                                   (const double*)a.K, a.k_bstride, gpart);

@@ -185,6 +185,9 @@ hipError_t launch_dense_targets(hipStream_t s, int64_t nb, int64_t n, int64_t k,
                                 const float* y, int64_t y_bstride, const loca_mb* mb,
                                 const float* credit_b, int64_t b_bstride, float* t_out,
                                 int64_t t_bstride);
+// out[b] = S_sym L (d x r, fp64) from the upper triangle of S; L(j, c) = L[j l_sj + c l_sc].
+hipError_t launch_sym_mul_f64(hipStream_t s, int64_t nb, int64_t d, int64_t r, const double* S, int64_t s_bstride,
+                              const float* L, int64_t l_bstride, int64_t l_sj, int64_t l_sc, double* out);
 // A (n x n fp64, n <= 64, upper part read) = U^T U; U^{-1} over A, zero below its diagonal.
 // *info, when 0, takes the first non-positive pivot (1-based).
 hipError_t launch_chol_inv64(hipStream_t s, int64_t n, double* A, int32_t* info);

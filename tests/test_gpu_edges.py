@@ -288,3 +288,48 @@ def test_truncation_core_edges(kp, r, scale):
         log(f"  W_r {e_w:.1e} sigma {e_s:.1e}")
         assert e_w < 1e-6 and e_s < 1e-6
     assert not info.any()
+
+
+# S_sym L at the edges of its 64-row tiles and 16- and 32-column chunks, L along its rows (the
+# current adapters of the solve) and along its columns (the projected form in float64); entries of
+# S below the diagonal are NaN.  As for the solve alone: float32 rounding of the result, and with
+# float32 statistics the solve's own 9 sqrt(d) 2^-24
+@pytest.mark.parametrize("acc", ["f32", "f64"])
+@pytest.mark.parametrize("d,r", [(1, 1), (63, 1), (64, 16), (65, 17), (129, 32), (130, 33), (200, 60)])
+def test_symmetric_product_edges(d, r, acc):
+    import torch
+    from paper_2608_03020_amd import loca
+    g = np.random.default_rng(d + r)
+    nb, k, lam = 2, 3, 0.7
+    dt = torch.float32 if acc == "f32" else torch.float64
+    lacc = loca.LOCA_F32 if acc == "f32" else loca.LOCA_F64
+    X = g.standard_normal((nb, 4 * d + 4, d))
+    S = torch.triu(torch.from_numpy(X.transpose(0, 2, 1) @ X).to("cuda", dt))
+    ref_s = S.double().cpu().numpy()
+    ref_s = ref_s + np.triu(ref_s, 1).transpose(0, 2, 1)
+    S += torch.tril(torch.full_like(S, float("nan")), -1)
+    kw = dict(dtype=torch.float32, device="cuda")
+    K = torch.from_numpy(g.standard_normal((nb, d, k))).to("cuda", dt)
+    lp, rp = (torch.from_numpy(g.standard_normal(s)).to(**kw) for s in ((nb, d, r), (nb, r, d)))
+    B = torch.from_numpy(g.standard_normal((nb, k, d))).to(**kw)
+    M = torch.full((nb, 1, d, r + k), float("nan"), **kw)
+    info = torch.full((nb,), 77, dtype=torch.int32, device="cuda")
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_RIDGE_SOLVE, nb, 0, d, r + k, n_lambda=1, acc=lacc))
+    log("symmetric product", d, r, acc)
+    loca.loca_ridge_solve(S, K, [lam], M, info, ws, lp=lp, rp=rp)
+    assert info.eq(0).all()
+    bound = (9 * np.sqrt(d) * 2.0 ** -24 if acc == "f32" else 0) + 2.0 ** -23
+    for b in range(nb):
+        rhs = np.concatenate([ref_s[b] @ lp[b].double().cpu().numpy(), K[b].double().cpu().numpy()], axis=1)
+        assert rel(M[b, 0].cpu().numpy(), np.linalg.solve(ref_s[b] + lam * np.eye(d), rhs)) < bound
+    if acc == "f64" and r <= min(d, 64):
+        Bp = torch.full((nb, 1, d, r), float("nan"), **kw)
+        ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_RIDGE_SOLVE_PROJECTED, nb, 0, d, k, r_a=r, n_lambda=1,
+                                                      acc=lacc))
+        loca.loca_ridge_solve_projected(S, K, B, rp, [lam], Bp, info, ws)
+        assert info.eq(0).all()
+        for b in range(nb):
+            P = rp[b].double().cpu().numpy()
+            G = P @ ref_s[b] @ P.T + lam * np.eye(r)
+            ref = np.linalg.solve(G, P @ K[b].double().cpu().numpy() @ B[b].double().cpu().numpy()).T
+            assert rel(Bp[b, 0].cpu().numpy(), ref) < 2.0 ** -23
