@@ -652,10 +652,13 @@ __global__ __launch_bounds__(kThreads) void k_cross_bf16(int64_t n, int64_t d, i
 
 // ------------------------------------------------------------------ fp64 path (fp32 mode)
 
-// 64 x 64 tiles, 4 waves of 32 x 32 (2 x 2 blocks of 16 x 16), 16 tokens per stage.
+// 64 x 64 tiles, 4 waves of 32 x 32 (2 x 2 blocks of 16 x 16), 32 tokens per stage, the next
+// stage's loads in flight during this one's products: few tiles run at a time (one block of
+// d = 896: 119), so a stage's load latency is not hidden by other workgroups (n = 512: 129 us in
+// stages of 16 tokens that waited for their loads, 39 now; the same sums in the same order).
 // Jobs [0, nS) are upper tiles of S (Q = X); jobs [nS, nS + nK) are tiles of
 // Kraw = X^T Y (Q = Y, k columns).
-constexpr int kBM64 = 64, kBK64 = 16, kLD64 = kBM64 + 1;
+constexpr int kBM64 = 64, kBK64 = 32, kLD64 = kBM64 + 1;
 
 __global__ __launch_bounds__(kThreads) void k_gram_f64(int64_t n, int64_t d, int64_t k,
                                                        const float* __restrict__ Xall, int64_t ldx,
@@ -693,20 +696,32 @@ __global__ __launch_bounds__(kThreads) void k_gram_f64(int64_t n, int64_t d, int
 #pragma unroll
     for (int q = 0; q < 2; ++q) acc[m][q] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
 
+  // this thread's column of both tiles, rows lrow + (kThreads / 64) u of a stage
+  constexpr int U = kBK64 * kBM64 / kThreads;
+  const int lc = threadIdx.x % kBM64, lrow = threadIdx.x / kBM64;
+  const bool okp = cI + lc < d, okq = cJ + lc < qcols;
+  const float* Q = kjob ? Y : X;
+  const int64_t ldq = kjob ? k : ldx;
+  float vp[U], vq[U], vw[U];
+  auto load = [&](int64_t t0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t t = t0 + lrow + kThreads / kBM64 * u;
+      vp[u] = t < n && okp ? X[t * ldx + cI + lc] : 0.f;
+      vq[u] = t < n && okq ? Q[t * ldq + cJ + lc] : 0.f;
+      vw[u] = aw && t < n && okq ? aw[t] : 1.f;
+    }
+  };
+  if (n > 0) load(0);
   for (int64_t t0 = 0; t0 < n; t0 += kBK64) {
     __syncthreads();
-    for (int e = threadIdx.x; e < kBK64 * kBM64; e += kThreads) {
-      const int row = e / kBM64, c = e % kBM64;
-      const int64_t t = t0 + row;
-      const int64_t ci = cI + c, cj = cJ + c;
-      sP[row * kLD64 + c] = (t < n && ci < d) ? (double)X[t * ldx + ci] : 0.0;
-      double qv = 0.0;
-      if (t < n && cj < qcols) {
-        qv = kjob ? (double)Y[t * k + cj] : (double)X[t * ldx + cj];
-        if (aw) qv *= (double)aw[t];  // statistic weight (an exact product in fp64)
-      }
-      sQ[row * kLD64 + c] = qv;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int row = lrow + kThreads / kBM64 * u;
+      sP[row * kLD64 + lc] = (double)vp[u];
+      sQ[row * kLD64 + lc] = (double)vq[u] * (double)vw[u];  // statistic weight: an exact product in fp64
     }
+    if (t0 + kBK64 < n) load(t0 + kBK64);
     __syncthreads();
 #pragma unroll
     for (int ks = 0; ks < kBK64; ks += 4) {

@@ -290,6 +290,37 @@ def test_truncation_core_edges(kp, r, scale):
     assert not info.any()
 
 
+# the float64 statistics at the edges of their 32-token stages and 64-wide tiles: float64 sums of
+# exact products, n 2^-53 of the sum of magnitudes, far below 1e-13
+@pytest.mark.parametrize("d,n,k,w", [(1, 1, 1, 0), (63, 31, 5, 1), (64, 32, 64, 0), (65, 33, 65, 1), (200, 64, 8, 0), (130, 97, 3, 1)])
+def test_float64_statistics_edges(d, n, k, w):
+    import torch
+    from paper_2608_03020_amd import loca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + n)
+    nb, ld = 2, -(-d // 4) * 4
+    buf = torch.full((nb, n, ld), float("nan"), dtype=torch.float32, device="cuda")
+    buf[:, :, :d] = torch.randn((nb, n, d), generator=g, device="cuda")
+    x, y = buf[:, :, :d], torch.randn((nb, n, k), generator=g, device="cuda")
+    a = torch.rand(n, generator=g, device="cuda") if w else None
+    mb = loca.new_mb(nb)
+    mb[:, 0] = 7.0
+    S = torch.full((nb, d, d), float("nan"), dtype=torch.float64, device="cuda")
+    K = torch.full((nb, d, k), float("nan"), dtype=torch.float64, device="cuda")
+    info = torch.zeros(nb, dtype=torch.int32, device="cuda")
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_ACCUMULATE_STATS, nb, n, d, k, acc=loca.LOCA_F64))
+    log("float64 statistics", d, n, k, w)
+    loca.loca_accumulate_stats(x, y, 0.5, mb, S, K, ws, a_w=a, dev_info=info, overwrite=True)
+    aw = (a.double() if w else torch.ones(n, dtype=torch.float64, device="cuda"))[:, None].cpu()
+    for b in range(nb):
+        X, Y = x[b].double().cpu(), y[b].double().cpu()
+        eta = 0.5 * float(np.sqrt(float((aw * X * X).sum()) / 7.0))
+        iu = np.triu_indices(d)
+        assert rel(S[b].cpu().numpy()[iu], (X.T @ (aw * X)).numpy()[iu]) < 1e-13
+        assert rel(K[b].cpu().numpy(), (-eta * (X.T @ (aw * Y))).numpy()) < 1e-13
+    assert not info.any()
+
+
 # S_sym L at the edges of its 64-row tiles and 16- and 32-column chunks, L along its rows (the
 # current adapters of the solve) and along its columns (the projected form in float64); entries of
 # S below the diagonal are NaN.  As for the solve alone: float32 rounding of the result, and with
