@@ -1515,14 +1515,14 @@ __global__ __launch_bounds__(kT) void k_trunc_apply(int64_t d, int64_t kp, int64
 }
 
 // out[i][j] = sum_c L(i, c) R(c, j) with general strides, products and sums in fp64 (on the
-// fp64 matrix cores), rounded to float once.  A workgroup takes 64 rows x 256 columns, a wave
-// 64 x 64 of them as 4 x 4 blocks of 16 x 16.  Block q of a wave's columns holds the columns
+// fp64 matrix cores), rounded to float once.  A workgroup takes 32 rows x 256 columns, a wave
+// 32 x 64 of them as 2 x 4 blocks of 16 x 16.  Block q of a wave's columns holds the columns
 // j0 + 4 (lane % 16) + q, so that a lane's four results of a row are consecutive columns and
 // leave in one 16-byte store (V4: cols % 4 == 0 and 16-byte aligned output rows); the factors
-// are small and come from cache.  Bound by the write of the output: 28 x 1536 x 1536 with
-// kk = 16 (264 MB) took 1812 us with one thread per entry, each reading 2 kk scalars through
-// the cache; now the whole truncation with that product takes 305 us (1948 before).
-constexpr int kLPR = 64, kLPC = 256;  // rows and columns per workgroup
+// are small and come from cache.  Bound by the write of the output and the wait for the factors
+// before it: 28 x 1536 x 1536 with kk = 16 (264 MB) 87 us, 125 with 64 rows a wave (half the
+// waves in flight; prefetching the factors alone gave 122), 1812 with one thread per entry.
+constexpr int kLPR = 32, kLPC = 256, kLPA = kLPR / 16;  // rows and columns per workgroup
 template <bool V4>
 __global__ __launch_bounds__(256) void k_lowrank_product(int64_t rows, int64_t cols, int64_t kk,
                                                          const float* __restrict__ L, int64_t l_bstride, int64_t l_si,
@@ -1535,43 +1535,55 @@ __global__ __launch_bounds__(256) void k_lowrank_product(int64_t rows, int64_t c
   if (j0 >= cols) return;
   const float* Lm = L + mi * l_bstride;
   const float* Rm = R + (mi / r_group) * r_bstride;
-  int64_t li_off[4], rj_off[4];  // entries past the edge read the last row or column: never stored
+  int64_t li_off[kLPA], rj_off[4];  // entries past the edge read the last row or column: never stored
+#pragma unroll
+  for (int q = 0; q < kLPA; ++q) {
+    const int64_t i = i0 + 16 * q + li;
+    li_off[q] = (i < rows ? i : rows - 1) * l_si;
+  }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const int64_t i = i0 + 16 * q + li, j = j0 + 4 * li + q;
-    li_off[q] = (i < rows ? i : rows - 1) * l_si;
+    const int64_t j = j0 + 4 * li + q;
     rj_off[q] = (j < cols ? j : cols - 1) * r_sj;
   }
-  f64x4_t acc[4][4];
+  f64x4_t acc[kLPA][4];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < kLPA; ++a)
 #pragma unroll
     for (int q = 0; q < 4; ++q) acc[a][q] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  float nl[kLPA], nr[4];  // the next four-deep step's operands, in flight during this step's products
+  auto load = [&](int64_t c0) {
+    const int64_t c = c0 + lk < kk ? c0 + lk : kk - 1;  // past the end: read, not used
+#pragma unroll
+    for (int q = 0; q < kLPA; ++q) nl[q] = Lm[li_off[q] + c * l_sc];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) nr[q] = Rm[rj_off[q] + c * r_sc];
+  };
+  load(0);
   for (int64_t c0 = 0; c0 < kk; c0 += 4) {
-    const int64_t c = c0 + lk;
-    const bool ok = c < kk;
-    double fa[4], fb[4];
+    const bool ok = c0 + lk < kk;
+    double fa[kLPA], fb[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float x = Lm[li_off[q] + (ok ? c : 0) * l_sc], y = Rm[rj_off[q] + (ok ? c : 0) * r_sc];
-      fa[q] = ok ? (double)x : 0.0;
-      fb[q] = ok ? (double)y : 0.0;
-    }
+    for (int q = 0; q < kLPA; ++q) fa[q] = ok ? (double)nl[q] : 0.0;
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int q = 0; q < 4; ++q) fb[q] = ok ? (double)nr[q] : 0.0;
+    if (c0 + 4 < kk) load(c0 + 4);
+#pragma unroll
+    for (int a = 0; a < kLPA; ++a)
 #pragma unroll
       for (int q = 0; q < 4; ++q) acc[a][q] = mfma_f64(fa[a], fb[q], acc[a][q]);
   }
   float* O = out + mi * out_bstride;
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < kLPA; ++a)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int64_t i = i0 + 16 * a + lk + 4 * r, j = j0 + 4 * li;
       if (i >= rows || j >= cols) continue;
       float* dst = O + i * cols + j;
       if (V4) {
-        *(float4*)dst = make_float4((float)acc[a][0][r], (float)acc[a][1][r], (float)acc[a][2][r], (float)acc[a][3][r]);
+        const f32x4_t v = {(float)acc[a][0][r], (float)acc[a][1][r], (float)acc[a][2][r], (float)acc[a][3][r]};
+        __builtin_nontemporal_store(v, (f32x4_t*)dst);  // written once, larger than the caches
       } else {
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -1783,8 +1795,8 @@ hipError_t launch_lowrank_truncate(const TruncArgs& a) {
 namespace {
 
 // T1[b][i][a] = sum_j S_sym[i][j] PA[a][j] (d x r_a, S_sym from the upper triangle) for fp32 S
-// on the fp32 matrix cores (v_mfma_f32_32x32x2f32), reading S
-// once per use with coalesced loads.  One workgroup per (64-row panel I, block b); the
+// on the fp32 matrix cores (v_mfma_f32_32x32x2f32), reading S once per use with coalesced loads.
+// One workgroup per (64-row panel I, block b); the
 // panel's rows of the symmetric S are staged 64 columns at a time: chunks right of the
 // diagonal straight from the stored upper triangle, chunks left of it as the transposes of
 // the stored tiles above the diagonal, the diagonal chunk mirrored in LDS; the chunk of
