@@ -629,14 +629,18 @@ FusedPlan fused_plan(int64_t n, int64_t V, int64_t c) {
   const int64_t tiles = (int64_t)p.ntr * p.nct, nchunk = (V + kFV - 1) / kFV;
   // One workgroup fits a compute unit: the number of vocabulary ranges with the least rounds of
   // 256 workgroups times chunks per range (and half a chunk's time per round for its prologue and
-  // its write of the partial outputs).  A range holds at most 20 chunks: its sums run in float32,
-  // and longer ones cost precision (n = 4096, V = 151936, 64 columns: rms error against float64
-  // 5.4e-8 in ranges of 38 chunks, 5.2e-8 in ranges of 19, for 3% of the time).
+  // its write of the partial outputs).  The ranges are no longer than
+  // 1024 workgroups of 128 tokens would make them: their sums run in float32, and longer ones cost
+  // precision (n = 4096, V = 151936, 64 columns: rms error against float64 5.4e-8 in ranges of 38
+  // chunks, 5.2e-8 in ranges of 19, for 3% of the time); more of them cost workspace.
+  const int64_t wgs = ((n + 127) / 128) * p.nct;
+  const int64_t want = std::min<int64_t>(kMaxFusedSplits, (wgs + 1023) / wgs);
+  const int64_t longest = (nchunk + want - 1) / want;
   int64_t best = 1;
   double cost = 1e300;
   for (int64_t s = 1; s <= kMaxFusedSplits && s <= nchunk; ++s) {
     const int64_t per = (nchunk + s - 1) / s, ns = (nchunk + per - 1) / per;
-    if (per > 20 && s < kMaxFusedSplits && s < nchunk) continue;
+    if (per > longest) continue;
     const double t = (double)((tiles * ns + 255) / 256) * ((double)per + 0.5);
     if (t < cost) {
       cost = t;

@@ -302,9 +302,10 @@ __global__ void k_top_error_reduce(int64_t n, int64_t d, int nsplit, const float
 // Column tiles of at most 256, evenly cut in 32s (nb of them, as instantiated); the vocabulary in
 // ns ranges of whole blocks: the count with the least rounds of 512 workgroups (two fit a compute
 // unit) times blocks per range, an added range costing its partial sums' way through memory
-// (about 1e-6 blocks per value, at 1.6 us a block and 5 TB/s).  A range holds at most 240 blocks:
-// its sums run in float32, and longer ones cost precision (n = 4096, V = 151936, 896 columns: rms
-// error against float64 7.0e-8 in ranges of 594 blocks, 6.2e-8 in ranges of 198).
+// (about 1e-6 blocks per value, at 1.6 us a block and 5 TB/s).  The ranges are no
+// longer than 2048 tiles of 128 x 128 would make them: their sums run in float32, and longer ones
+// cost precision (n = 4096, V = 151936, 896 columns: rms error against float64 7.0e-8 in ranges of
+// 594 blocks, 6.2e-8 in ranges of 198, for 2% of the time); more of them cost workspace.
 struct HeadPlan {
   int ntr, nct, nb, ns;
   int64_t kchunk;
@@ -316,11 +317,13 @@ HeadPlan head_plan(int64_t n, int64_t V, int64_t cols) {
   p.nb = (int)((cols + 32 * p.nct - 1) / (32 * p.nct));
   p.nb = p.nb <= 2 ? 2 : (p.nb <= 4 ? 4 : p.nb);
   const int64_t tiles = (int64_t)p.ntr * p.nct, nblk = (V + kHK - 1) / kHK;
+  const int64_t want = std::min<int64_t>(32, (2047 / (p.ntr * ((cols + 127) / 128)) + 1));
+  const int64_t longest = (nblk + want - 1) / want;
   int64_t per = nblk;
   double best = 1e300;
   for (int64_t s = 1; s <= 32 && s <= nblk; ++s) {
     const int64_t pr = (nblk + s - 1) / s, ns = (nblk + pr - 1) / pr;
-    if (pr > 240 && s < 32 && s < nblk) continue;
+    if (pr > longest) continue;
     const double t = (double)((tiles * ns + 511) / 512) * (double)(pr + 4) + (double)ns * (double)n * (double)cols * 1e-6;
     if (t < best) {
       best = t;
