@@ -138,7 +138,8 @@ struct XStage {
 
 // ------------------------------------------------------------------ S += X^T X (bf16)
 
-// Register-staged form, for weighted blocks of X past 2 GB only (see launch_accumulate_stats):
+// Register-staged form, for weighted blocks of X or of split targets past 2 GB only (see
+// launch_accumulate_stats):
 // BM x BM tiles of S on or above the diagonal; WGM x WGN waves, each owning a
 // (BM/WGM) x (BM/WGN) block of 32 x 32 MFMA tiles.  Statistic weights from `wpad` (zero
 // past n, readable up to the next multiple of kBK).
@@ -979,11 +980,12 @@ hipError_t launch_accumulate_stats(const StatsArgs& a) {
   constexpr int BM = 256;
   const int T = (int)((a.d + BM - 1) / BM);
   const int64_t w2 = 2 * a.k, w2p = (w2 + 7) / 8 * 8;
-  // buffer-path copies when a block's X (and its split targets) fit 31-bit byte offsets
-  const bool buf = (a.n * a.ldx * 2) < ((int64_t)1 << 31);
+  // buffer-path copies when a block's X and its split targets each fit 31-bit byte offsets (at k =
+  // 128 the targets are the wider ones up to ldx = 256)
+  const bool buf = a.n * std::max(a.ldx, w2p) * 2 < ((int64_t)1 << 31);
   // direct-to-LDS kernel; with weights only on the buffer path (the global-address
-  // variant runs out of scalar registers with the weights, so blocks of X over 2 GB
-  // take the register-staged kernel when weighted)
+  // variant runs out of scalar registers with the weights, so blocks of X or of split
+  // targets over 2 GB take the register-staged kernel when weighted)
   const bool dl = buf || !wt;
   const bool fused = w2p <= 64;
   // wider split targets: cross tiles in the same launch (one per row panel of each block)

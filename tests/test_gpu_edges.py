@@ -69,6 +69,44 @@ def test_statistics_at_every_width(d, n, k, w):
         assert rel(K[b].cpu().numpy(), -eta * X[b].T @ ((aw * Y)[b] if w else Y[b])) < 1e-5
 
 
+# split targets past 2 GB beside an X below it: their byte offsets leave 31 bits first when 2k >
+# ldx, and 2^32 bytes at n = 2^23, k = 128.  The n / 16 additions into a float32 sum round by at most
+# 2^-24 of the running sum each, and the entries that make up the norm grow steadily to their
+# final value: n / 16 2^-24 of it (3e-2 at n = 2^23, where 1.3e-4 is seen); a target read as zero
+# or from another row is off by its own size
+@pytest.mark.parametrize("n,d,w", [(1 << 23, 64, 0), ((1 << 22) + 5, 20, 0), ((1 << 22) + 5, 20, 1)])
+def test_statistics_with_split_targets_past_2gb(n, d, w):
+    import torch
+    from paper_2608_03020_amd import loca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + w)
+    k, ld = 128, -(-d // 8) * 8
+    x = torch.randn((1, n, ld), generator=g, device="cuda").bfloat16()[:, :, :d]
+    y = torch.randn((1, n, k), generator=g, device="cuda")
+    y += x[0, :, :1].float()  # a part that the sums keep
+    a = torch.rand(n, generator=g, device="cuda") if w else None
+    mb = loca.new_mb(1)
+    mb[:, 0] = 7.0
+    kw = dict(dtype=torch.float32, device="cuda")
+    S, K = torch.full((1, d, d), float("nan"), **kw), torch.full((1, d, k), float("nan"), **kw)
+    info = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_ACCUMULATE_STATS, 1, n, d, k))
+    log("statistics with split targets past 2 GB", n, d, w)
+    loca.loca_accumulate_stats(x, y, 0.5, mb, S, K, ws, a_w=a, dev_info=info, overwrite=True)
+    refS = torch.zeros((d, d), dtype=torch.float64, device="cuda")
+    refK = torch.zeros((d, k), dtype=torch.float64, device="cuda")
+    for lo in range(0, n, 1 << 20):
+        X, Y = x[0, lo:lo + (1 << 20)].double(), y[0, lo:lo + (1 << 20)].double()
+        aX = a[lo:lo + (1 << 20), None].double() * X if w else X
+        refS += X.T @ aX
+        refK += aX.T @ Y
+    refK *= -0.5 * float(refS.trace() / 7.0) ** 0.5
+    iu = np.triu_indices(d)
+    e_s, e_k = rel(S[0].cpu().numpy()[iu], refS.cpu().numpy()[iu]), rel(K[0].cpu().numpy(), refK.cpu().numpy())
+    log(f"  S {e_s:.1e} K {e_k:.1e}")
+    assert int(info[0]) == 0 and max(e_s, e_k) < n / 16 * 2.0 ** -24
+
+
 # widths at the edges of the 16-wide blocks, the 64- and 128-wide panels and the 512-wide
 # super-panels.  S from 4 d Gaussian rows: the equilibrated matrix's condition number is about
 # (1 + 1/2)^2 / (1 - 1/2)^2 = 9; a backward stable solve errs by a small multiple of
