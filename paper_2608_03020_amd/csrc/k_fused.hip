@@ -39,7 +39,12 @@ template <int TR> struct FusedTile {
   static constexpr int MV = kFV / WV / 32;             // 32-entry vocabulary blocks per wave
   static constexpr int STAGE = (kFV + TR) * kFK * 2;   // bytes per stage: W_u rows, then h rows (128 B each)
   static constexpr int COPIES = STAGE / 16 / kFT;      // 16-byte copies per thread per stage (8 or 6)
+  // Buffer offsets are 31-bit, so a buffer of 256 rows takes rows of at most 2^22 values.  The
+  // 128-token tile serves rows of up to 2^23: its chunk of W_u is addressed as two halves.
+  static constexpr int WH = TR == 128 ? 2 : 1;         // buffers per chunk of W_u
+  static constexpr int WR = kFV / WH;                  // rows of each
 };
+constexpr int64_t kMaxLd256 = (int64_t)1 << 22;        // longest row of h for 256 tokens a tile
 
 // A stage holds 256 + TR rows of 128 bytes (64 bf16 of d): rows 0..255 the chunk's W_u rows,
 // then the tile's h rows.  Chunk c (16 bytes) of row r sits at position c ^ ((r >> 1) & 7), so
@@ -111,26 +116,31 @@ __global__ __launch_bounds__(kFT) void k_fused_head(int64_t n, int64_t V, int64_
   const i32x4_t rsH = buffer_rsrc(h + r0 * ldh, (uint32_t)(nrow * ldh * 2));
   const uint32_t ring_lds = (uint32_t)(uintptr_t)(LOCA_LDS void*)ring;
   // Copy j of a wave fills the 1 KB block (8 rows) wid + 8 j of a stage: W_u rows for j < 4, then
-  // h rows.  Lane l takes row l / 8 of the block, position l % 8.  Byte offsets fit 31 bits (V, d,
-  // ldh <= 2^23 are checked by the caller); rows past V or n lie past the buffer and read zero.
+  // h rows.  Lane l takes row l / 8 of the block, position l % 8.  Byte offsets fit 31 bits (d <=
+  // ldh <= 2^23 is checked by the caller, and rows past kMaxLd256 take the 128-token tile); rows
+  // past V or n lie past the buffer and read zero.
   // Blocks eight apart hold rows 64 apart, which share the swizzle: one offset per operand.
   const int crow = 8 * wid + (lane >> 3);
   const uint32_t ck = 8u * (uint32_t)((lane & 7) ^ fz_swz(crow));  // the lane's first k in a slice
   const uint32_t offw = 2u * ((uint32_t)crow * (uint32_t)d + ck), offh = 2u * ((uint32_t)crow * (uint32_t)ldh + ck);
   const uint32_t stepw = 128u * (uint32_t)d, steph = 128u * (uint32_t)ldh;
-  auto issue_stage = [&](i32x4_t rsW, int ks, int slot) {
+  i32x4_t rsW[TL::WH];
+  auto issue_stage = [&](int ks, int slot) {
     const uint32_t dst = ring_lds + (uint32_t)(slot * TL::STAGE + wid * 1024), k0 = (uint32_t)(ks * kFK);
     const bool in = k0 + ck < (uint32_t)d;
 #pragma unroll
     for (int j = 0; j < NCP; ++j) {
-      const uint32_t step = j < kFV / 64 ? j * stepw : (j - kFV / 64) * steph;
+      const uint32_t step = j < kFV / 64 ? (j % (TL::WR / 64)) * stepw : (j - kFV / 64) * steph;
       const uint32_t off = in ? (j < kFV / 64 ? offw : offh) + (step + 2u * k0) : kBufOutside;
-      lds_dma16_buf(off, j < kFV / 64 ? rsW : rsH, dst + (uint32_t)(j * 8192));
+      lds_dma16_buf(off, j < kFV / 64 ? rsW[j / (TL::WR / 64)] : rsH, dst + (uint32_t)(j * 8192));
     }
   };
-  auto rsrc_w = [&](int64_t v0) {
-    const int64_t nvr = (V - v0 < kFV) ? V - v0 : kFV;
-    return buffer_rsrc(wu + v0 * d, (uint32_t)(nvr * d * 2));
+  auto chunk_w = [&](int64_t v0) {
+#pragma unroll
+    for (int q = 0; q < TL::WH; ++q) {
+      const int64_t v = v0 + q * TL::WR < V ? v0 + q * TL::WR : V, nvr = V - v < TL::WR ? V - v : TL::WR;
+      rsW[q] = buffer_rsrc(wu + v * d, (uint32_t)(nvr * d * 2));
+    }
   };
 
   f32x16_t o[2][NQ];
@@ -147,9 +157,9 @@ __global__ __launch_bounds__(kFT) void k_fused_head(int64_t n, int64_t V, int64_
   const uint32_t ra = (uint32_t)(wv * VW + l32), rb = (uint32_t)(kFV + wt * 64 + l32);
   const uint32_t la = 128 * ra + 16 * (uint32_t)(lh ^ fz_swz((int)ra)), lb = 128 * rb + 16 * (uint32_t)(lh ^ fz_swz((int)rb));
 
-  i32x4_t rsW = rsrc_w(vb);
   int slot = 0;
-  if (nch > 0) issue_stage(rsW, 0, 0);
+  chunk_w(vb);
+  if (nch > 0) issue_stage(0, 0);
   for (int j = 0; j < nch; ++j) {
     const int64_t v0 = vb + (int64_t)j * kFV;
     // 1. z^T = W_u[chunk] h[tile]^T
@@ -164,10 +174,10 @@ __global__ __launch_bounds__(kFT) void k_fused_head(int64_t n, int64_t V, int64_
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // the stage landed (this thread's copies)
       barrier_nofence();                         // ... everyone's; the other slot is no longer read
       if (ks + 1 < nks) {
-        issue_stage(rsW, ks + 1, slot ^ 1);
+        issue_stage(ks + 1, slot ^ 1);
       } else if (j + 1 < nch) {
-        rsW = rsrc_w(v0 + kFV);
-        issue_stage(rsW, 0, slot ^ 1);
+        chunk_w(v0 + kFV);
+        issue_stage(0, slot ^ 1);
       }
       const uint8_t* st = ring + slot * TL::STAGE;
 #pragma unroll
@@ -717,7 +727,11 @@ size_t fused_head_ws(int64_t n, int64_t V, int64_t c) {
 }
 
 hipError_t launch_fused_head(const FusedArgs& a) {
-  const FusedPlan p = fused_plan(a.n, a.V, a.c);
+  FusedPlan p = fused_plan(a.n, a.V, a.c);
+  if (p.tr == 256 && a.ldh > kMaxLd256) {  // the same ranges in tiles of 128 tokens
+    p.tr = 128;
+    p.ntr = (int)((a.n + 127) / 128);
+  }
   char* w = a.ws;
   float* part_o = (float*)w; w += align256(sizeof(float) * p.nsp * a.n * a.c);
   float2* part_ms = (float2*)w; w += align256(sizeof(float2) * p.nsp * a.n);

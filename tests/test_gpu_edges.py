@@ -208,6 +208,44 @@ def test_fused_head_edges(n, V, d, c):
     assert np.linalg.norm(out.double().cpu().numpy() - ref) < 1e-5 * max(scale, np.linalg.norm(ref))
 
 
+# rows of h (and of W_u) at the ends of the 31-bit byte offsets: 256 rows of 2^23 values are 2^32
+# bytes, 256 rows past 2^22 leave the out-of-range offset inside the buffer (d % 64 != 0 reads it;
+# NaN in the gaps between the rows must stay unread).  float32 sums of d products: the logits are
+# off by d / 16 2^-24 of their size (about 2) at worst, the output by as much of its norm;
+# hidden states or head rows read as zero are off by the output itself
+@pytest.mark.parametrize("n,ldh,d,V", [(256, 1 << 23, 64, 300), (200, 1 << 23, 72, 300), (256, (1 << 22) + 8, 72, 300),
+                                       (130, 1 << 23, 1 << 23, 256), (3, 1 << 23, (1 << 23) - 8, 300)])
+def test_fused_head_long_rows(n, ldh, d, V):
+    import torch
+    from paper_2608_03020_amd import loca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + V)
+    rn = lambda *s: torch.randn(s, generator=g, device="cuda")
+    c = 5
+    buf = torch.empty((n * ldh,), dtype=torch.bfloat16, device="cuda").view(n, ldh)
+    h, Wu = buf[:, :d], torch.empty((V, d), dtype=torch.bfloat16, device="cuda")
+    for t in (h, Wu):
+        for i in range(0, t.shape[0], 16):
+            t[i:i + 16] = rn(t[i:i + 16].shape[0], d) * (2 * d ** -0.25 if t is h else d ** -0.25)
+    if ldh > d:
+        buf[:, d:] = float("nan")
+    Vm = rn(V, c).bfloat16()
+    y = torch.randint(0, V, (n,), generator=g, device="cuda", dtype=torch.int32)
+    out = torch.full((n, c), float("nan"), device="cuda")
+    info = torch.full((1,), 5, dtype=torch.int32, device="cuda")
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_FUSED_HEAD, 1, n, d, c, C=V))
+    log("fused head, long rows", n, ldh, d, V)
+    loca.loca_fused_head(h, Wu, y, Vm, out, info, ws)
+    z = torch.zeros((n, V), dtype=torch.float64, device="cuda")
+    for lo in range(0, d, 1 << 17):
+        z += h[:, lo:lo + (1 << 17)].double() @ Wu[:, lo:lo + (1 << 17)].double().T
+    p = torch.softmax(z, 1)
+    p[torch.arange(n), y.long()] -= 1
+    e = rel(out.cpu().numpy(), (p @ Vm.double()).cpu().numpy())
+    log(f"  out {e:.1e}")
+    assert int(info) == 0 and e < max(1e-5, d / 16 * 2.0 ** -24)
+
+
 # the paper-order head at the edges of its 128-token tiles, 64-entry blocks and column tiles
 # (one to three of 32 to 256 columns, float and bf16 logits), NaN in the rows' padding, and the
 # blocks' coordinates on both sides of 64 columns.  P as two bf16 parts: 2^-17 of each term
