@@ -21,6 +21,8 @@
 // Each vocabulary range leaves (m, s) per token and its partial output; a second kernel
 // combines the ranges in a fixed order in float64 and subtracts the label term.  Columns of
 // Vm beyond one 64-wide tile recompute the logits (c / 64 passes over W_u).
+#include <algorithm>
+
 #include "loca_bf16.h"
 #include "loca_launch.h"
 
@@ -341,20 +343,23 @@ __global__ __launch_bounds__(kFT) void k_fused_head(int64_t n, int64_t V, int64_
 // Vm as k_fused_head's second operand: 16 vocabulary entries x 32 columns a fragment of 64 lanes x
 // 16 bytes, fragment (g, q) of vocabulary entries 16 g .. and columns 32 q .. (q < 2 nct) at 1 KB x
 // (2 nct g + q); lane l holds column 32 q + l % 32 and the entries 8 (e / 4) + 4 (l / 32) + e % 4,
-// e = 0..7 (the order in which the logits' result layout leaves them).  Zero past V and c.
+// e = 0..7 (the order in which the logits' result layout leaves them).  Zero past V and c.  One
+// fragment per wave up to kFragBlocks workgroups (2^31 entries); larger operands loop, since one
+// launch holds fewer than 2^32 threads.
+constexpr int64_t kFragBlocks = (int64_t)1 << 20;
 __global__ void k_vm_frag(int64_t V, int64_t c, const uint16_t* __restrict__ vm, int64_t ld_vm, int nq, int64_t nfrag,
                           uint4* __restrict__ vmf) {
-  const int64_t f = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (f >= nfrag) return;
   const int lane = threadIdx.x & 63;
-  const int64_t g = f / nq, col = 32 * (f % nq) + (lane & 31);
-  uint32_t x[8];
+  for (int64_t f = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); f < nfrag; f += (int64_t)gridDim.x * 4) {
+    const int64_t g = f / nq, col = 32 * (f % nq) + (lane & 31);
+    uint32_t x[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int64_t v = 16 * g + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-    x[e] = (v < V && col < c) ? vm[v * ld_vm + col] : (uint16_t)0;
+    for (int e = 0; e < 8; ++e) {
+      const int64_t v = 16 * g + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+      x[e] = (v < V && col < c) ? vm[v * ld_vm + col] : (uint16_t)0;
+    }
+    vmf[f * 64 + lane] = make_uint4(x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16), x[6] | (x[7] << 16));
   }
-  vmf[f * 64 + lane] = make_uint4(x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16), x[6] | (x[7] << 16));
 }
 
 // dev_info protocol: INT32_MAX while nothing is wrong; atomicMin with 1 + a bad row or with
@@ -740,7 +745,7 @@ hipError_t launch_fused_head(const FusedArgs& a) {
   k_fused_info_init<<<1, 64, 0, st>>>(a.dev_info);
   const int nq = p.nct * (kFC / 32);
   const int64_t nfrag = p.ldvt / 16 * nq;
-  k_vm_frag<<<(unsigned)((nfrag + 3) / 4), 256, 0, st>>>(a.V, a.c, a.vm, a.ld_vm, nq, nfrag, (uint4*)vmf);
+  k_vm_frag<<<(unsigned)std::min<int64_t>((nfrag + 3) / 4, kFragBlocks), 256, 0, st>>>(a.V, a.c, a.vm, a.ld_vm, nq, nfrag, (uint4*)vmf);
   const unsigned grid = (unsigned)((int64_t)p.ntr * p.nct * p.nsp);
   if (p.tr == 256)
     k_fused_head<256><<<grid, kFT, 0, st>>>(a.n, a.V, a.d, a.c, a.h, a.ldh, a.wu, vmf, p.ntr, p.nct, p.vper, part_o,

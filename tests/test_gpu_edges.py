@@ -246,6 +246,40 @@ def test_fused_head_long_rows(n, ldh, d, V):
     assert int(info) == 0 and e < max(1e-5, d / 16 * 2.0 ** -24)
 
 
+# a right operand of 2^35 entries (64 GiB, and as much again laid out in the workspace): one wave per
+# fragment of 512 would be 2^32 threads, which no launch holds.  P as two bf16 parts: 2^-17 of each
+# term, far below 1e-5 of the output's norm
+def test_fused_head_operand_of_64_gib():
+    import torch
+    from paper_2608_03020_amd import loca
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 170 << 30:
+        pytest.skip("needs 170 GiB of free device memory")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(8)
+    n, V, d, c = 2, 1 << 18, 8, 1 << 17
+    h, Wu = (torch.randn(s, generator=g, device="cuda").bfloat16() for s in ((n, d), (V, d)))
+    y = torch.tensor([0, V - 1], dtype=torch.int32, device="cuda")
+    out = torch.full((n, c), float("nan"), device="cuda")
+    info = torch.full((1,), 5, dtype=torch.int32, device="cuda")
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_FUSED_HEAD, 1, n, d, c, C=V))
+    Vm = torch.empty((V, c), dtype=torch.bfloat16, device="cuda")
+    for i in range(0, V, 1 << 13):
+        Vm[i:i + (1 << 13)].normal_(generator=g)
+    log("fused head, operand of 64 GiB")
+    loca.loca_fused_head(h, Wu, y, Vm, out, info, ws)
+    p = torch.softmax(h.double() @ Wu.double().T, 1)
+    p[torch.arange(n), y.long()] -= 1
+    ref = torch.zeros((n, c), dtype=torch.float64, device="cuda")
+    for i in range(0, V, 1 << 12):
+        ref += p[:, i:i + (1 << 12)] @ Vm[i:i + (1 << 12)].double()
+    e = rel(out.cpu().numpy(), ref.cpu().numpy())
+    log(f"  out {e:.1e}")
+    del Vm, ws
+    torch.cuda.empty_cache()
+    assert int(info) == 0 and e < 1e-5
+
+
 # the paper-order head at the edges of its 128-token tiles, 64-entry blocks and column tiles
 # (one to three of 32 to 256 columns, float and bf16 logits), NaN in the rows' padding, and the
 # blocks' coordinates on both sides of 64 columns.  P as two bf16 parts: 2^-17 of each term
