@@ -98,7 +98,8 @@ __global__ __launch_bounds__(kFT) void k_fused_head(int64_t n, int64_t V, int64_
                                                     const uint16_t* __restrict__ h, int64_t ldh,
                                                     const uint16_t* __restrict__ wu,
                                                     const uint16_t* __restrict__ vmf, int ntr, int nct, int64_t vper,
-                                                    float* __restrict__ part_o, float2* __restrict__ part_ms) {
+                                                    int nsub, float* __restrict__ part_o,
+                                                    float2* __restrict__ part_ms) {
   typedef FusedTile<TR> TL;
   constexpr int WT = TL::WT, WV = TL::WV, MV = TL::MV, VW = kFV / WV, NCP = TL::COPIES;
   constexpr int NQ = kFC / 32;  // 32-column output blocks per wave
@@ -146,197 +147,213 @@ __global__ __launch_bounds__(kFT) void k_fused_head(int64_t n, int64_t V, int64_
   };
 
   f32x16_t o[2][NQ];
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-    for (int q = 0; q < NQ; ++q)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[mt][q][r] = 0.f;
-  // token l32 of block mt: the running maximum, and the sum of this lane's exponentials
-  float m_run[2] = {-__builtin_inff(), -__builtin_inff()}, s_run[2] = {0.f, 0.f};
+  float m_run[2], s_run[2];  // token l32 of block mt: the running maximum, and the sum of this lane's exponentials
   // operand addresses in a slot: row r's chunk 2 kk + lh at 128 r + 16 ((2 kk + lh) ^ swz(r)); rows
   // 32 apart share the swizzle
   const uint32_t ra = (uint32_t)(wv * VW + l32), rb = (uint32_t)(kFV + wt * 64 + l32);
   const uint32_t la = 128 * ra + 16 * (uint32_t)(lh ^ fz_swz((int)ra)), lb = 128 * rb + 16 * (uint32_t)(lh ^ fz_swz((int)rb));
 
   int slot = 0;
-  chunk_w(vb);
-  if (nch > 0) issue_stage(0, 0);
-  for (int j = 0; j < nch; ++j) {
-    const int64_t v0 = vb + (int64_t)j * kFV;
-    // 1. z^T = W_u[chunk] h[tile]^T
-    f32x16_t z[MV][2];
-#pragma unroll
-    for (int mv = 0; mv < MV; ++mv)
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) z[mv][mt][r] = 0.f;
-    for (int ks = 0; ks < nks; ++ks) {
-      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // the stage landed (this thread's copies)
-      barrier_nofence();                         // ... everyone's; the other slot is no longer read
-      if (ks + 1 < nks) {
-        issue_stage(ks + 1, slot ^ 1);
-      } else if (j + 1 < nch) {
-        chunk_w(v0 + kFV);
-        issue_stage(0, slot ^ 1);
-      }
-      const uint8_t* st = ring + slot * TL::STAGE;
-#pragma unroll
-      for (int kk = 0; kk < kFK / 16; ++kk) {
-        bf16x8_t a[MV], b[2];
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) b[mt] = *(const bf16x8_t*)(st + (lb ^ (32u * kk)) + 4096 * mt);
-#pragma unroll
-        for (int mv = 0; mv < MV; ++mv) a[mv] = *(const bf16x8_t*)(st + (la ^ (32u * kk)) + 4096 * mv);
-#pragma unroll
-        for (int mv = 0; mv < MV; ++mv)
-#pragma unroll
-          for (int mt = 0; mt < 2; ++mt) z[mv][mt] = mfma32(a[mv], b[mt], z[mv][mt]);
-      }
-      slot ^= 1;
-    }
-
-    // 2. online softmax over the chunk.  Entry r of lane l in block (mv, mt): vocabulary
-    // v0 + VW wv + 32 mv + 8 (r >> 2) + 4 lh + (r & 3), token 64 wt + 32 mt + l32.
-    if (V - v0 < kFV) {  // the ragged last chunk: entries past V are excluded
-      const int nv = (int)(V - v0);
-#pragma unroll
-      for (int mv = 0; mv < MV; ++mv)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (VW * wv + 32 * mv + 8 * (r >> 2) + 4 * lh + (r & 3) >= nv) z[mv][0][r] = z[mv][1][r] = -__builtin_inff();
-    }
+  for (int sub = 0; sub < nsub; ++sub) {  // the parts of the range, each with sums of its own
+    const int j0 = sub == 0 ? 0 : (nch + 1) / 2, j1 = sub + 1 < nsub ? (nch + 1) / 2 : nch;
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
-      float mx = z[0][mt][0];
+      m_run[mt] = -__builtin_inff();
+      s_run[mt] = 0.f;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[mt][q][r] = 0.f;
+    }
+    if (j0 < j1) {
+      chunk_w(vb + (int64_t)j0 * kFV);
+      issue_stage(0, slot);
+    }
+    for (int j = j0; j < j1; ++j) {
+      const int64_t v0 = vb + (int64_t)j * kFV;
+      // 1. z^T = W_u[chunk] h[tile]^T
+      f32x16_t z[MV][2];
 #pragma unroll
       for (int mv = 0; mv < MV; ++mv)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, z[mv][mt][r]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
-      if (lh == 0) sEx[wv][wt * 64 + 32 * mt + l32] = mx;
-    }
-    wave_lds_sync();
-    barrier_nofence();
-    float al[2], ms[2];
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-      const int tk = wt * 64 + 32 * mt + l32;
-      float mn = m_run[mt];
-#pragma unroll
-      for (int u = 0; u < WV; ++u) mn = fmaxf(mn, sEx[u][tk]);
-      ms[mt] = mn == -__builtin_inff() ? 0.f : mn;  // nothing but excluded entries so far
-      al[mt] = __expf(m_run[mt] - ms[mt]);
-      m_run[mt] = mn;
-      s_run[mt] *= al[mt];
-    }
-    // rescale the output rows where a maximum rose: row r of an output block is token
-    // 8 (r >> 2) + 4 lh + (r & 3)
-    if (__ballot(al[0] != 1.f || al[1] != 1.f))
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float a_r = __shfl(al[mt], 8 * (r >> 2) + 4 * lh + (r & 3));
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) o[mt][q][r] *= a_r;
-        }
-    // 3. out += (P_hi + P_lo) Vm[chunk]: k step (mv, ks2) takes the entries r = 8 ks2 .. 8 ks2 + 7
-    const uint4* vf = (const uint4*)vmf + (((v0 + VW * wv) / 16 * nct + ct) * NQ) * 64 + lane;
-#pragma unroll
-    for (int mv = 0; mv < MV; ++mv)
-#pragma unroll
-      for (int ks2 = 0; ks2 < 2; ++ks2) {
-        bf16x8_t phi[2], plo[2], bv[NQ];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q)
-          bv[q] = __builtin_bit_cast(bf16x8_t, vf[((int64_t)(2 * mv + ks2) * nct * NQ + q) * 64]);
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-          uint32_t hv[4], lv[4];
-#pragma unroll
-          for (int e2 = 0; e2 < 4; ++e2) {
-            // hi and lo parts rounded to nearest even by the hardware conversion, in pairs
-            const int r = 8 * ks2 + 2 * e2;
-            const float p0 = __expf(z[mv][mt][r] - ms[mt]), p1 = __expf(z[mv][mt][r + 1] - ms[mt]);
-            s_run[mt] += p0 + p1;
-            const uint32_t h2 = cvt_pk_bf16(p0, p1);
-            hv[e2] = h2;
-            lv[e2] = cvt_pk_bf16(p0 - bf16_lo(h2), p1 - bf16_hi(h2));
-          }
-          phi[mt] = __builtin_bit_cast(bf16x8_t, make_uint4(hv[0], hv[1], hv[2], hv[3]));
-          plo[mt] = __builtin_bit_cast(bf16x8_t, make_uint4(lv[0], lv[1], lv[2], lv[3]));
-        }
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-          for (int q = 0; q < NQ; ++q) {
-            o[mt][q] = mfma32(phi[mt], bv[q], o[mt][q]);
-            o[mt][q] = mfma32(plo[mt], bv[q], o[mt][q]);
-          }
-      }
-  }
-  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-  __syncthreads();  // the ring is free: the vocabulary parts' sums and outputs meet there
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt) {
-    s_run[mt] += __shfl_xor(s_run[mt], 32);
-    if (lh == 0) sEx[wv][wt * 64 + 32 * mt + l32] = s_run[mt];
-  }
-  // partial outputs summed in a fixed order: (O_0 + O_2) + (O_1 + O_3), or O_0 + O_1
-  float* red = (float*)ring;  // WV / 2 x TR tokens x (64 + 4) floats
-  constexpr int RLD = kFC + 4;
-  static_assert(WV / 2 * TR * RLD * 4 <= 2 * TL::STAGE, "the outputs fit the ring");
-  auto put = [&](int slot2) {
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int q = 0; q < NQ; ++q)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          red[(slot2 * TR + wt * 64 + 32 * mt + 8 * (r >> 2) + 4 * lh + (r & 3)) * RLD + 32 * q + l32] = o[mt][q][r];
-  };
-  auto add = [&](int slot2) {
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int q = 0; q < NQ; ++q)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          o[mt][q][r] += red[(slot2 * TR + wt * 64 + 32 * mt + 8 * (r >> 2) + 4 * lh + (r & 3)) * RLD + 32 * q + l32];
-  };
-  if (WV == 4) {
-    if (wv >= 2) put(wv - 2);
-    __syncthreads();
-    if (wv < 2) add(wv);
-    __syncthreads();
-  }
-  if (wv == 1) put(0);
-  __syncthreads();
-  if (wv == 0) {
-    add(0);
-    float* po = part_o + (int64_t)sp * n * c;
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int q = 0; q < NQ; ++q)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int tr = wt * 64 + 32 * mt + 8 * (r >> 2) + 4 * lh + (r & 3);
-          const int64_t row = r0 + tr, col = c0 + 32 * q + l32;
-          if (row < n && col < c) po[row * c + col] = o[mt][q][r];
+          for (int r = 0; r < 16; ++r) z[mv][mt][r] = 0.f;
+      for (int ks = 0; ks < nks; ++ks) {
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // the stage landed (this thread's copies)
+        barrier_nofence();                         // ... everyone's; the other slot is no longer read
+        if (ks + 1 < nks) {
+          issue_stage(ks + 1, slot ^ 1);
+        } else if (j + 1 < j1) {
+          chunk_w(v0 + kFV);
+          issue_stage(0, slot ^ 1);
         }
-    if (ct == 0 && lh == 0)
+        const uint8_t* st = ring + slot * TL::STAGE;
+#pragma unroll
+        for (int kk = 0; kk < kFK / 16; ++kk) {
+          bf16x8_t a[MV], b[2];
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt) b[mt] = *(const bf16x8_t*)(st + (lb ^ (32u * kk)) + 4096 * mt);
+#pragma unroll
+          for (int mv = 0; mv < MV; ++mv) a[mv] = *(const bf16x8_t*)(st + (la ^ (32u * kk)) + 4096 * mv);
+#pragma unroll
+          for (int mv = 0; mv < MV; ++mv)
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) z[mv][mt] = mfma32(a[mv], b[mt], z[mv][mt]);
+        }
+        slot ^= 1;
+      }
+
+      // 2. online softmax over the chunk.  Entry r of lane l in block (mv, mt): vocabulary
+      // v0 + VW wv + 32 mv + 8 (r >> 2) + 4 lh + (r & 3), token 64 wt + 32 mt + l32.
+      if (V - v0 < kFV) {  // the ragged last chunk: entries past V are excluded
+        const int nv = (int)(V - v0);
+#pragma unroll
+        for (int mv = 0; mv < MV; ++mv)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (VW * wv + 32 * mv + 8 * (r >> 2) + 4 * lh + (r & 3) >= nv) z[mv][0][r] = z[mv][1][r] = -__builtin_inff();
+      }
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt) {
+        float mx = z[0][mt][0];
+#pragma unroll
+        for (int mv = 0; mv < MV; ++mv)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) mx = fmaxf(mx, z[mv][mt][r]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        if (lh == 0) sEx[wv][wt * 64 + 32 * mt + l32] = mx;
+      }
+      wave_lds_sync();
+      barrier_nofence();
+      float al[2], ms[2];
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt) {
         const int tk = wt * 64 + 32 * mt + l32;
-        const int64_t row = r0 + tk;
-        float sm = sEx[0][tk];
+        float mn = m_run[mt];
 #pragma unroll
-        for (int u = 1; u < WV; ++u) sm += sEx[u][tk];
-        if (row < n) part_ms[(int64_t)sp * n + row] = make_float2(m_run[mt], sm);
+        for (int u = 0; u < WV; ++u) mn = fmaxf(mn, sEx[u][tk]);
+        ms[mt] = mn == -__builtin_inff() ? 0.f : mn;  // nothing but excluded entries so far
+        al[mt] = __expf(m_run[mt] - ms[mt]);
+        m_run[mt] = mn;
+        s_run[mt] *= al[mt];
       }
+      // rescale the output rows where a maximum rose: row r of an output block is token
+      // 8 (r >> 2) + 4 lh + (r & 3)
+      if (__ballot(al[0] != 1.f || al[1] != 1.f))
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float a_r = __shfl(al[mt], 8 * (r >> 2) + 4 * lh + (r & 3));
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) o[mt][q][r] *= a_r;
+          }
+      // 3. out += (P_hi + P_lo) Vm[chunk]: k step (mv, ks2) takes the entries r = 8 ks2 .. 8 ks2 + 7
+      float cs[2] = {0.f, 0.f};  // the chunk's own sums, short chains
+      const uint4* vf = (const uint4*)vmf + (((v0 + VW * wv) / 16 * nct + ct) * NQ) * 64 + lane;
+#pragma unroll
+      for (int mv = 0; mv < MV; ++mv)
+#pragma unroll
+        for (int ks2 = 0; ks2 < 2; ++ks2) {
+          bf16x8_t phi[2], plo[2], bv[NQ];
+#pragma unroll
+          for (int q = 0; q < NQ; ++q)
+            bv[q] = __builtin_bit_cast(bf16x8_t, vf[((int64_t)(2 * mv + ks2) * nct * NQ + q) * 64]);
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt) {
+            uint32_t hv[4], lv[4];
+#pragma unroll
+            for (int e2 = 0; e2 < 4; ++e2) {
+              // hi and lo parts rounded to nearest even by the hardware conversion, in pairs
+              const int r = 8 * ks2 + 2 * e2;
+              const float p0 = __expf(z[mv][mt][r] - ms[mt]), p1 = __expf(z[mv][mt][r + 1] - ms[mt]);
+              cs[mt] += p0 + p1;
+              const uint32_t h2 = cvt_pk_bf16(p0, p1);
+              hv[e2] = h2;
+              lv[e2] = cvt_pk_bf16(p0 - bf16_lo(h2), p1 - bf16_hi(h2));
+            }
+            phi[mt] = __builtin_bit_cast(bf16x8_t, make_uint4(hv[0], hv[1], hv[2], hv[3]));
+            plo[mt] = __builtin_bit_cast(bf16x8_t, make_uint4(lv[0], lv[1], lv[2], lv[3]));
+          }
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+              o[mt][q] = mfma32(phi[mt], bv[q], o[mt][q]);
+              o[mt][q] = mfma32(plo[mt], bv[q], o[mt][q]);
+            }
+        }
+      s_run[0] += cs[0];
+      s_run[1] += cs[1];
+    }
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    __syncthreads();  // the ring is free: the vocabulary parts' sums and outputs meet there
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+      s_run[mt] += __shfl_xor(s_run[mt], 32);
+      if (lh == 0) sEx[wv][wt * 64 + 32 * mt + l32] = s_run[mt];
+    }
+    // (the lane is opaque here, so that no address below is kept in a register over the products)
+    int le = lane;
+    asm volatile("" : "+v"(le));
+    const int e32 = le & 31, eh = le >> 5;
+    // partial outputs summed in a fixed order: (O_0 + O_2) + (O_1 + O_3), or O_0 + O_1
+    float* red = (float*)ring;  // WV / 2 x TR tokens x (64 + 4) floats
+    constexpr int RLD = kFC + 4;
+    static_assert(WV / 2 * TR * RLD * 4 <= 2 * TL::STAGE, "the outputs fit the ring");
+    auto put = [&](int slot2) {
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            red[(slot2 * TR + wt * 64 + 32 * mt + 8 * (r >> 2) + 4 * eh + (r & 3)) * RLD + 32 * q + e32] = o[mt][q][r];
+    };
+    auto add = [&](int slot2) {
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            o[mt][q][r] += red[(slot2 * TR + wt * 64 + 32 * mt + 8 * (r >> 2) + 4 * eh + (r & 3)) * RLD + 32 * q + e32];
+    };
+    if (WV == 4) {
+      if (wv >= 2) put(wv - 2);
+      __syncthreads();
+      if (wv < 2) add(wv);
+      __syncthreads();
+    }
+    if (wv == 1) put(0);
+    __syncthreads();
+    if (wv == 0) {
+      add(0);
+      const int64_t pi = (int64_t)sp * nsub + sub;
+      float* po = part_o + pi * n * c;
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int tr = wt * 64 + 32 * mt + 8 * (r >> 2) + 4 * eh + (r & 3);
+            const int64_t row = r0 + tr, col = c0 + 32 * q + e32;
+            if (row < n && col < c) po[row * c + col] = o[mt][q][r];
+          }
+      if (ct == 0 && eh == 0)
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+          const int tk = wt * 64 + 32 * mt + e32;
+          const int64_t row = r0 + tk;
+          float sm = sEx[0][tk];
+#pragma unroll
+          for (int u = 1; u < WV; ++u) sm += sEx[u][tk];
+          if (row < n) part_ms[pi * n + row] = make_float2(m_run[mt], sm);
+        }
+    }
+    if (sub + 1 < nsub) __syncthreads();  // the ring and the sums are free for the next part
   }
 }
 
@@ -389,8 +406,10 @@ __global__ void k_vm_transpose(int64_t V, int64_t c, const uint16_t* __restrict_
   }
 }
 
-// out_t = w_t (sum_i O_i[t] e^{m_i - M} / S - Vm[y_t]), S = sum_i s_i e^{m_i - M}: the ranges
-// in order, float64.  One workgroup per token.  Column j of Vm and of the output is column
+// out_t = w_t (sum_i O_i[t] e^{m_i - M} / S - Vm[y_t]), S = sum_i s_i e^{m_i - M}: the ranges (or
+// their parts) in order, float64, each exponential taken by one thread (taken by all of them, 64
+// parts cost the 4096-token head of a 2.6 ms call 0.1 ms).  One
+// workgroup per token.  Column j of Vm and of the output is column
 // j % kc of group j / kc (Vm entries as for k_vm_transpose; output at
 // out[(j / kc) o_gstride + t ld_out + j % kc]).  A bad label drops the label term and is
 // reported; a sum that is not finite or not positive is reported as non-finite data.  With
@@ -403,19 +422,19 @@ __global__ __launch_bounds__(256) void k_fused_combine(int64_t n, int64_t c, int
                                                        int64_t gstride, float* __restrict__ out, int64_t ld_out,
                                                        int64_t o_gstride, float* __restrict__ ms_out,
                                                        int32_t* __restrict__ info) {
-  __shared__ double sc[kMaxFusedSplits];
+  __shared__ double sc[2 * kMaxFusedSplits];
+  __shared__ float2 sms[2 * kMaxFusedSplits];
   const int64_t t = blockIdx.x;
-  // every range holds a valid chunk, so each finite s_i is at least 1
-  double M = -__builtin_inf();
-  for (int i = 0; i < nsp; ++i) M = fmax(M, (double)part_ms[(int64_t)i * n + t].x);
-  double S = 0.0;
-  for (int i = 0; i < nsp; ++i) {
-    const float2 ms = part_ms[(int64_t)i * n + t];
-    const double e = exp((double)ms.x - M);
-    S += (double)ms.y * e;
-    if ((int)threadIdx.x == i) sc[i] = e;
-  }
+  const int tid = threadIdx.x;
+  if (tid < nsp) sms[tid] = part_ms[(int64_t)tid * n + t];
   __syncthreads();
+  // every part with a chunk has a finite s_i of at least 1; one without has m_i = -inf, s_i = 0
+  double M = -__builtin_inf();
+  for (int i = 0; i < nsp; ++i) M = fmax(M, (double)sms[i].x);
+  if (tid < nsp) sc[tid] = exp((double)sms[tid].x - M);
+  __syncthreads();
+  double S = 0.0;
+  for (int i = 0; i < nsp; ++i) S += (double)sms[i].y * sc[i];
   const int32_t y = labels[t];
   const bool bad = y < 0 || (int64_t)y >= V;
   const bool nonfin = !isfinite(M) || !isfinite(S) || !(S > 0.0);
@@ -630,7 +649,7 @@ __global__ __launch_bounds__(256) void k_head_online(int64_t n, int64_t V, const
 }
 
 struct FusedPlan {
-  int ct, tr, ntr, nct, nsp;
+  int ct, tr, ntr, nct, nsp, nsub;  // nsp ranges, each summed in nsub parts
   int64_t vper, ldvt;
 };
 
@@ -643,23 +662,29 @@ FusedPlan fused_plan(int64_t n, int64_t V, int64_t c) {
   p.nct = (int)((c + p.ct - 1) / p.ct);
   const int64_t tiles = (int64_t)p.ntr * p.nct, nchunk = (V + kFV - 1) / kFV;
   // One workgroup fits a compute unit: the number of vocabulary ranges with the least rounds of
-  // 256 workgroups times chunks per range (and half a chunk's time per round for its prologue and
-  // its write of the partial outputs).  The ranges are no longer than
-  // 1024 workgroups of 128 tokens would make them: their sums run in float32, and longer ones cost
-  // precision (n = 4096, V = 151936, 64 columns: rms error against float64 5.4e-8 in ranges of 38
-  // chunks, 5.2e-8 in ranges of 19, for 3% of the time); more of them cost workspace.
+  // 256 workgroups times chunks per range (and half a chunk's time for a prologue and a write of
+  // partial outputs).  Never fewer ranges than 1024 workgroups of 128 tokens would make; more of them
+  // cost workspace.
+  //
+  // The sums run in float32, so their length costs precision: in the 128-token tile four waves share
+  // a chunk's vocabulary, in the 256-token tile two, whose sums are twice as long.  Such a range is
+  // summed in two parts where it is longer than half the longest (n = 4096, V = 151936, 64 columns,
+  // ranges of 19 chunks, rms error against float64 in one part, in two and in the 128-token tile: d =
+  // 2048 5.17e-8, 5.03e-8 and 5.13e-8; an operand of ones, whose output is 0, 6.6e-8, 3.4e-8 and
+  // 3.7e-8; 2.52 ms in one part and in two).
   const int64_t wgs = ((n + 127) / 128) * p.nct;
-  const int64_t want = std::min<int64_t>(kMaxFusedSplits, (wgs + 1023) / wgs);
+  const int64_t want = std::max<int64_t>(1, std::min({(int64_t)kMaxFusedSplits, (1024 + wgs - 1) / wgs, nchunk}));
   const int64_t longest = (nchunk + want - 1) / want;
-  int64_t best = 1;
+  int64_t best = longest;
   double cost = 1e300;
-  for (int64_t s = 1; s <= kMaxFusedSplits && s <= nchunk; ++s) {
+  for (int64_t s = want; s <= kMaxFusedSplits && s <= nchunk; ++s) {
     const int64_t per = (nchunk + s - 1) / s, ns = (nchunk + per - 1) / per;
-    if (per > longest) continue;
-    const double t = (double)((tiles * ns + 255) / 256) * ((double)per + 0.5);
+    const int parts = p.tr == 256 && 2 * per > longest + 1 ? 2 : 1;
+    const double t = (double)((tiles * ns + 255) / 256) * ((double)per + 0.5 * parts);
     if (t < cost) {
       cost = t;
       best = per;
+      p.nsub = parts;
     }
   }
   p.vper = best * kFV;
@@ -725,8 +750,9 @@ hipError_t launch_softmax_product_online(const SoftmaxProductArgs& a) {
 
 size_t fused_head_ws(int64_t n, int64_t V, int64_t c) {
   const FusedPlan p = fused_plan(n, V, c);
-  size_t s = align256(sizeof(float) * p.nsp * n * c);
-  s += align256(sizeof(float2) * p.nsp * n);
+  const int64_t np = (int64_t)p.nsp * p.nsub;
+  size_t s = align256(sizeof(float) * np * n * c);
+  s += align256(sizeof(float2) * np * n);
   s += align256(sizeof(uint16_t) * p.nct * kFC * p.ldvt);
   return s;
 }
@@ -738,8 +764,9 @@ hipError_t launch_fused_head(const FusedArgs& a) {
     p.ntr = (int)((a.n + 127) / 128);
   }
   char* w = a.ws;
-  float* part_o = (float*)w; w += align256(sizeof(float) * p.nsp * a.n * a.c);
-  float2* part_ms = (float2*)w; w += align256(sizeof(float2) * p.nsp * a.n);
+  const int64_t np = (int64_t)p.nsp * p.nsub;
+  float* part_o = (float*)w; w += align256(sizeof(float) * np * a.n * a.c);
+  float2* part_ms = (float2*)w; w += align256(sizeof(float2) * np * a.n);
   uint16_t* vmf = (uint16_t*)w;
   hipStream_t st = a.stream;
   k_fused_info_init<<<1, 64, 0, st>>>(a.dev_info);
@@ -748,12 +775,12 @@ hipError_t launch_fused_head(const FusedArgs& a) {
   k_vm_frag<<<(unsigned)std::min<int64_t>((nfrag + 3) / 4, kFragBlocks), 256, 0, st>>>(a.V, a.c, a.vm, a.ld_vm, nq, nfrag, (uint4*)vmf);
   const unsigned grid = (unsigned)((int64_t)p.ntr * p.nct * p.nsp);
   if (p.tr == 256)
-    k_fused_head<256><<<grid, kFT, 0, st>>>(a.n, a.V, a.d, a.c, a.h, a.ldh, a.wu, vmf, p.ntr, p.nct, p.vper, part_o,
-                                            part_ms);
+    k_fused_head<256><<<grid, kFT, 0, st>>>(a.n, a.V, a.d, a.c, a.h, a.ldh, a.wu, vmf, p.ntr, p.nct, p.vper, p.nsub,
+                                            part_o, part_ms);
   else
-    k_fused_head<128><<<grid, kFT, 0, st>>>(a.n, a.V, a.d, a.c, a.h, a.ldh, a.wu, vmf, p.ntr, p.nct, p.vper, part_o,
-                                            part_ms);
-  k_fused_combine<<<(unsigned)a.n, 256, 0, st>>>(a.n, a.c, a.V, p.nsp, part_o, part_ms, a.labels, a.w, a.vm, a.ld_vm,
+    k_fused_head<128><<<grid, kFT, 0, st>>>(a.n, a.V, a.d, a.c, a.h, a.ldh, a.wu, vmf, p.ntr, p.nct, p.vper, p.nsub,
+                                            part_o, part_ms);
+  k_fused_combine<<<(unsigned)a.n, 256, 0, st>>>(a.n, a.c, a.V, (int)np, part_o, part_ms, a.labels, a.w, a.vm, a.ld_vm,
                                                  a.c, 0, a.out, a.ld_out, 0, nullptr, a.dev_info);
   k_fused_info_finish<<<1, 64, 0, st>>>(a.dev_info);
   return hipGetLastError();

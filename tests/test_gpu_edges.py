@@ -246,6 +246,29 @@ def test_fused_head_long_rows(n, ldh, d, V):
     assert int(info) == 0 and e < max(1e-5, d / 16 * 2.0 ** -24)
 
 
+# an operand of ones: sum P / sum P - 1 is 0, and what is left is the rounding of the float32 sums of
+# one part of a vocabulary range against each other, averaged over the parts.  3/4 of 2^-24 (half a
+# unit of the quotient, 1) holds while a wave's sums stay at 10 chunks of 128 entries (3.5e-8; sums
+# twice as long leave 6.6e-8)
+def test_fused_head_length_of_sums():
+    import torch
+    from paper_2608_03020_amd import loca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(0)
+    n, V, d, c = 4096, 151936, 64, 8
+    h, Wu = (2 * torch.randn((n, d), generator=g, device="cuda")).bfloat16(), torch.randn((V, d), generator=g, device="cuda")
+    y = torch.randint(0, V, (n,), generator=g, device="cuda", dtype=torch.int32)
+    out = torch.full((n, c), float("nan"), device="cuda")
+    info = torch.full((1,), 5, dtype=torch.int32, device="cuda")
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_FUSED_HEAD, 1, n, d, c, C=V))
+    ws.fill_(255)
+    log("fused head, operand of ones")
+    loca.loca_fused_head(h, (Wu * d ** -0.5).bfloat16(), y, torch.ones((V, c), device="cuda").bfloat16(), out, info, ws)
+    rms = float(out.double().pow(2).mean().sqrt())
+    log(f"  rms {rms:.2e}")
+    assert int(info) == 0 and rms < 0.75 * 2.0 ** -24
+
+
 # a right operand of 2^35 entries (64 GiB, and as much again laid out in the workspace): one wave per
 # fragment of 512 would be 2^32 threads, which no launch holds.  P as two bf16 parts: 2^-17 of each
 # term, far below 1e-5 of the output's norm
