@@ -599,7 +599,12 @@ template <> struct Dg<float> {
   static constexpr int LD_PAD = 20;  // row length = P + 20: operand reads of either kind fall on distinct banks
   static LOCA_DEV acc_t mma(float a, float b, acc_t c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
   static LOCA_DEV int row(int lane, int r) { return 4 * (lane >> 4) + r; }
-  static LOCA_DEV float rsq(float v) { return __builtin_amdgcn_rsqf(v); }  // about 1 ulp
+  // the hardware estimate, whose error of up to an ulp leans one way, and a Newton step (without it
+  // the solution leaned by -7e-8 to -9e-8, d = 896 to 5120; with it by -2e-8 to -4e-8)
+  static LOCA_DEV float rsq(float v) {
+    const float y = __builtin_amdgcn_rsqf(v), h = 0.5f * y, g = v * y;
+    return fmaf(fmaf(-g, h, 0.5f), y, y);
+  }
   template <int CTRL> static LOCA_DEV float dpp(float v) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
   }

@@ -139,6 +139,34 @@ def test_ridge_solve_block_edges(d, acc):
             assert rel(M[b, i].cpu().numpy(), ref) < (9 * np.sqrt(d) * 2.0 ** -24 if acc == "f32" else 0) + 2.0 ** -23
 
 
+# the float32 solve's errors lean neither way: <M - ref, ref> / ||ref||^2, averaged over eight blocks
+# (the errors themselves are 5e-7, of either sign).  Every column of the factor and of the inverse
+# takes a reciprocal root, and a root that leans by a part of its unit 2^-24 moves all of M by as
+# much: half of 2^-24 tells it from the roundings' own lean of about 2e-8
+@pytest.mark.parametrize("d", [512, 897])
+def test_ridge_solve_errors_are_unbiased(d):
+    import torch
+    from paper_2608_03020_amd import loca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    nb, k, lam = 8, 64, 1e-2
+    X = torch.randn((nb, 2 * d, d), generator=g, device="cuda", dtype=torch.float64)
+    S = (X.transpose(1, 2).contiguous() @ X).float()
+    K = (X.transpose(1, 2).contiguous() @ torch.randn((nb, 2 * d, k), generator=g, device="cuda", dtype=torch.float64)).float()
+    M = torch.full((nb, 1, d, k), float("nan"), device="cuda")
+    info = torch.full((nb,), 77, dtype=torch.int32, device="cuda")
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_RIDGE_SOLVE, nb, 0, d, k, n_lambda=1))
+    log("bias of the solve", d)
+    loca.loca_ridge_solve(S, K, [lam], M, info, ws)
+    U = torch.triu(S).double()
+    T = U + torch.triu(U, 1).transpose(1, 2) + lam * torch.eye(d, device="cuda", dtype=torch.float64)
+    ref = torch.linalg.solve(T.cpu(), K.double().cpu())
+    D = M[:, 0].double().cpu() - ref
+    bias = ((D * ref).sum((1, 2)) / (ref * ref).sum((1, 2))).mean()
+    log(f"  bias {float(bias):+.1e} rel {float(D.norm() / ref.norm()):.1e}")
+    assert info.eq(0).all() and abs(float(bias)) < 0.5 * 2.0 ** -24
+
+
 # the dual fit at the edges of its 16-wide blocks and 32-row ranges, and the head fold on both
 # sides of the 64-class split.  float32 outputs of float64 sums; the map's truncation at rank k
 # amplifies rounding by sigma_k / (sigma_k - sigma_k+1), kept small by a rank-k probe map
