@@ -826,7 +826,7 @@ static int64_t g_ld_max(int64_t k) { return k <= kSmallMaxK ? small_kb(k) : k; }
 constexpr int64_t kRowsMaxC = 16;
 static int rows_mparts(int64_t n) { return (int)std::min<int64_t>((n + kRowTok - 1) / kRowTok, kMaxMParts); }
 
-size_t error_targets_ws(int64_t nb, int64_t n, int64_t C, int64_t k) {
+static size_t error_ws(int64_t nb, int64_t n, int64_t C, int64_t k, bool lean) {
   const int64_t lg = g_ld_max(k);
   size_t s = align256(sizeof(double) * nb * lg * lg);  // G
   const int64_t parts = use_small(C, k) ? (n + kSmallThreads - 1) / kSmallThreads : (n + kLargeTok - 1) / kLargeTok;
@@ -840,10 +840,20 @@ size_t error_targets_ws(int64_t nb, int64_t n, int64_t C, int64_t k) {
   s += p;
   if (!use_small(C, k)) {
     const size_t large = align256(sizeof(float) * 2 * n);  // (m, s) per token
-    const size_t prod = (k % 8 == 0) ? softmax_product_ws(n, C, nb * k) : 0;
+    const size_t prod = (k % 8 == 0) ? softmax_product_ws(n, C, nb * k, lean) : 0;
     s += large > prod ? large : prod;
   }
   return s;
+}
+// The vocabulary product takes its fewest ranges where only they fit the fixed scratch array of
+// loca_error_targets_noalloc, which therefore takes every size they allow; the rule does not ask
+// which entry point is called, so that both give the same bits.
+static bool lean_product(int64_t nb, int64_t n, int64_t C, int64_t k) {
+  const size_t cap = error_targets_scratch_bytes();
+  return error_ws(nb, n, C, k, false) > cap && error_ws(nb, n, C, k, true) <= cap;
+}
+size_t error_targets_ws(int64_t nb, int64_t n, int64_t C, int64_t k) {
+  return error_ws(nb, n, C, k, lean_product(nb, n, C, k));
 }
 
 template <typename LT, typename AT>
@@ -934,7 +944,7 @@ hipError_t launch_error_targets(const ErrorArgs& a) {
     char* pw = (char*)partial + align256(sizeof(double) * a.nb * parts);
     SoftmaxProductArgs sp{a.stream, a.n, a.C, a.logits, a.logits_dtype, a.ld_logits, a.labels, a.w,
                           (const uint16_t*)a.credit_a, a.nb, a.k, a.nb > 1 ? a.a_bstride : 0, a.y_out, a.k,
-                          a.y_bstride, a.dev_info, pw};
+                          a.y_bstride, a.dev_info, pw, lean_product(a.nb, a.n, a.C, a.k)};
     if ((e = launch_softmax_product(sp)) != hipSuccess) return e;
     const bool kb = a.k <= kSmallMaxK;  // 16 tokens per workgroup, else 256
     dim3 gq((unsigned)(kb ? (a.n + 15) / 16 : (a.n + 255) / 256), (unsigned)a.nb);

@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kHT) void k_softmax_stats(int64_t n, int64_t V, con
 // ahead.  The column tiles of one token tile are neighbours on an XCD, so the logits come from
 // beyond its L2 once.  Column j of the right operand is column j % kc of group j / kc:
 // W + (j / kc) w_bstride (V x kc bf16 each); d = total columns.  Requires ld % 8 == 0 (bf16) or % 4
-// == 0 (f32), kc % 8 == 0, d % kc == 0, kchunk % 64 == 0.
+// == 0 (f32), kc % 8 == 0, d % kc == 0, kchunk % 8 == 0.
 //
 // Bound by the matrix cores (the split doubles their work) and the exponentials beside them: n =
 // 4096, V = 151936, 896 columns took 4.50 ms in 128-column tiles that formed P seven times and
@@ -300,38 +300,38 @@ __global__ void k_top_error_reduce(int64_t n, int64_t d, int nsplit, const float
 }
 
 // Column tiles of at most 256, evenly cut in 32s (nb of them, as instantiated); the vocabulary in
-// ns ranges of whole blocks: the count with the least rounds of 512 workgroups (two fit a compute
-// unit) times blocks per range, an added range costing its partial sums' way through memory
-// (about 1e-6 blocks per value, at 1.6 us a block and 5 TB/s).  The ranges are no
-// longer than 2048 tiles of 128 x 128 would make them: their sums run in float32, and longer ones
-// cost precision (n = 4096, V = 151936, 896 columns: rms error against float64 7.0e-8 in ranges of
-// 594 blocks, 6.2e-8 in ranges of 198, for 2% of the time); more of them cost workspace.
+// ns ranges of 32-entry multiples.  Never fewer ranges than 2048 tiles of 128 x 128 (of 128 x 64 up
+// to 64 columns) would make, of at least 256 entries: the sums run in float32, and longer ones cost
+// precision (n = 4096, V = 151936, 896 columns: rms error against float64 7.0e-8 in ranges of 594
+// blocks, 6.2e-8 in ranges of 198, for 2% of the time).  From there up to twice as many, the count
+// with the least rounds of 512 workgroups (two fit a compute unit; a last round of one each is the
+// shorter) times blocks per range, an added range costing its partial sums' way through memory
+// (about 1e-6 blocks per value, at 1.6 us a block and 5 TB/s).  Beyond twice the workspace would
+// grow out of proportion.  `lean`: the fewest ranges, for calls whose workspace has to stay small.
 struct HeadPlan {
   int ntr, nct, nb, ns;
   int64_t kchunk;
 };
-HeadPlan head_plan(int64_t n, int64_t V, int64_t cols) {
+HeadPlan head_plan(int64_t n, int64_t V, int64_t cols, bool lean) {
   HeadPlan p;
   p.ntr = (int)((n + kHM - 1) / kHM);
   p.nct = (int)((cols + 255) / 256);
   p.nb = (int)((cols + 32 * p.nct - 1) / (32 * p.nct));
   p.nb = p.nb <= 2 ? 2 : (p.nb <= 4 ? 4 : p.nb);
-  const int64_t tiles = (int64_t)p.ntr * p.nct, nblk = (V + kHK - 1) / kHK;
-  const int64_t want = std::min<int64_t>(32, (2047 / (p.ntr * ((cols + 127) / 128)) + 1));
-  const int64_t longest = (nblk + want - 1) / want;
-  int64_t per = nblk;
+  const int64_t tiles = (int64_t)p.ntr * p.nct, t128 = p.ntr * ((cols + 127) / 128);
+  const int64_t want = std::max<int64_t>(1, std::min({(2048 + t128 - 1) / t128, (int64_t)32, (V + 255) / 256}));
   double best = 1e300;
-  for (int64_t s = 1; s <= 32 && s <= nblk; ++s) {
-    const int64_t pr = (nblk + s - 1) / s, ns = (nblk + pr - 1) / pr;
-    if (pr > longest) continue;
-    const double t = (double)((tiles * ns + 511) / 512) * (double)(pr + 4) + (double)ns * (double)n * (double)cols * 1e-6;
+  for (int64_t s = want; s <= (lean ? want : 2 * want); ++s) {
+    const int64_t chunk = ((V + s - 1) / s + 31) / 32 * 32, ns = (V + chunk - 1) / chunk;
+    const int64_t full = tiles * ns / 512, rest = tiles * ns % 512;
+    const double rounds = (double)full + (rest == 0 ? 0.0 : rest <= 256 ? 0.6 : 1.0);
+    const double t = rounds * (double)((chunk + kHK - 1) / kHK + 4) + (double)ns * (double)n * (double)cols * 1e-6;
     if (t < best) {
       best = t;
-      per = pr;
+      p.kchunk = chunk;
+      p.ns = (int)ns;
     }
   }
-  p.kchunk = per * kHK;
-  p.ns = (int)((nblk + per - 1) / per);
   return p;
 }
 
@@ -368,12 +368,12 @@ static bool product_online(const SoftmaxProductArgs& a) {
          64 * ((a.V + 63) / 64) * 64 * 2 < ((int64_t)1 << 31);
 }
 
-static size_t two_pass_ws(int64_t n, int64_t V, int64_t cols) {
-  return align256(sizeof(float) * 2 * n) + align256(sizeof(float) * (size_t)head_plan(n, V, cols).ns * n * cols);
+static size_t two_pass_ws(int64_t n, int64_t V, int64_t cols, bool lean) {
+  return align256(sizeof(float) * 2 * n) + align256(sizeof(float) * (size_t)head_plan(n, V, cols, lean).ns * n * cols);
 }
 
-size_t softmax_product_ws(int64_t n, int64_t V, int64_t cols) {
-  const size_t two = two_pass_ws(n, V, cols);
+size_t softmax_product_ws(int64_t n, int64_t V, int64_t cols, bool lean) {
+  const size_t two = two_pass_ws(n, V, cols, lean);
   if (cols > 64) return two;
   const size_t one = softmax_product_online_ws(n, V, cols);
   return one > two ? one : two;  // the path is chosen at the launch (it also depends on the strides)
@@ -384,7 +384,7 @@ hipError_t launch_softmax_product(const SoftmaxProductArgs& a) {
   float* ms = (float*)a.ws;
   float* part = (float*)(a.ws + align256(sizeof(float) * 2 * a.n));
   const int64_t cols = a.groups * a.kc;
-  const HeadPlan pl = head_plan(a.n, a.V, cols);
+  const HeadPlan pl = head_plan(a.n, a.V, cols, a.lean);
   hipStream_t st = a.stream;
   if (a.logits_dtype == LOCA_BF16) launch_product<uint16_t>(a, pl, ms, part);
   else launch_product<float>(a, pl, ms, part);
@@ -395,13 +395,13 @@ hipError_t launch_softmax_product(const SoftmaxProductArgs& a) {
   return hipGetLastError();
 }
 
-size_t top_error_ws(int64_t n, int64_t V, int64_t d) { return softmax_product_ws(n, V, d); }
+size_t top_error_ws(int64_t n, int64_t V, int64_t d) { return softmax_product_ws(n, V, d, false); }
 
 hipError_t launch_top_error(const TopErrorArgs& a) {
   hipStream_t st = a.stream;
   k_fill_i32_head<<<1, 64, 0, st>>>(a.dev_info);
   SoftmaxProductArgs p{st, a.n, a.V, a.logits, a.logits_dtype, a.ld_logits, a.labels, a.w, (const uint16_t*)a.wu,
-                       1, a.d, 0, a.e_out, a.ld_e, 0, a.dev_info, a.ws};
+                       1, a.d, 0, a.e_out, a.ld_e, 0, a.dev_info, a.ws, false};
   hipError_t e = launch_softmax_product(p);
   if (e != hipSuccess) return e;
   k_finish_info_head<<<1, 64, 0, st>>>(a.dev_info);

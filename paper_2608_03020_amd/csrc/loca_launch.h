@@ -55,8 +55,9 @@ struct SoftmaxProductArgs {
   float* out; int64_t ld_o, o_bstride;
   int32_t* dev_info;
   char* ws;
+  bool lean;  // the fewest vocabulary ranges (and the least workspace) the precision allows
 };
-size_t softmax_product_ws(int64_t n, int64_t V, int64_t cols);
+size_t softmax_product_ws(int64_t n, int64_t V, int64_t cols, bool lean);
 hipError_t launch_softmax_product(const SoftmaxProductArgs& a);
 // the same product in one pass over the logits (online softmax), one pass per 64 columns
 size_t softmax_product_online_ws(int64_t n, int64_t V, int64_t cols);

@@ -5,6 +5,7 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -323,3 +324,35 @@ def test_binding_rejects_layouts_the_abi_cannot_describe(lib):
     assert lib._ptr(torch.zeros(10, 16)[:, :8], False) is not None  # arrays with a leading dimension
     assert lib._ptr(torch.zeros(10, 16)[2:5]) is not None
     assert lib._ptr(torch.zeros(4, 1, 3)) is not None
+
+
+def test_noalloc_takes_what_the_fewest_ranges_fit(lib):
+    """The vocabulary product may take more ranges than its precision needs, but no size whose
+    scratch fits the fixed array with the fewest (2048 tiles of 128 x 128, at least 256 entries
+    each) is refused for that; nor does any call's partial sums' space more than double."""
+    cap = lib.error_targets_noalloc_max_bytes()
+    up = lambda x: -(-x // 256) * 256
+
+    def scratch(nb, n, C, k, times):  # k % 8 == 0, more than 64 classes, more than 64 columns
+        lg, cols, rt = (16 if k <= 16 else 32 if k <= 32 else 64 if k <= 64 else k), nb * k, -(-n // 128)
+        tiles = rt * -(-cols // 128)
+        s = max(1, min(32, -(-2048 // tiles), -(-C // 256)))
+        ranges = -(-C // (32 * -(-C // (32 * s))))
+        return (up(8 * nb * lg * lg) + up(64 * nb * k * k) + up(8 * nb * -(-n // 16)) + up(8 * n) +
+                times * up(4 * ranges * n * cols) + 256)
+
+    def need(*a):
+        return lib.workspace_size(lib.LOCA_OP_ERROR_TARGETS, a[0], a[1], 512, a[3], a[2])
+
+    for a in [(38, 3826, 146, 16), (8, 391, 5052, 48), (13, 608, 1680, 32), (9, 595, 1469, 72)]:
+        assert scratch(*a, 1) <= cap and need(*a) <= cap, a
+    rng = np.random.default_rng(0)
+    taken = 0
+    for _ in range(3000):
+        a = (int(rng.integers(9, 49)), int(np.exp(rng.uniform(0, 11))), int(np.exp(rng.uniform(4.2, 12))),
+             int(rng.choice([8, 16, 24, 32, 64, 72, 128])))
+        if scratch(*a, 1) <= cap:
+            taken += 1
+            assert need(*a) <= cap, a
+        assert need(*a) <= scratch(*a, 2.25), a  # twice the ranges asked for, each rounded up by itself
+    assert taken > 500

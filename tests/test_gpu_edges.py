@@ -331,6 +331,32 @@ def test_fused_head_operand_of_64_gib():
     assert int(info) == 0 and e < 1e-5
 
 
+# a vocabulary product whose scratch fits the fixed array only with the fewest ranges: taken by the
+# allocation-free call, with the bits of the workspace call.  P as two bf16 parts: 2^-17 of each term
+def test_allocation_free_vocabulary_product():
+    import torch
+    from paper_2608_03020_amd import loca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(13)
+    rn = lambda *s: torch.randn(s, generator=g, device="cuda")
+    nb, n, C, k, d = 13, 608, 1680, 32, 64
+    z, A, B = (3 * rn(n, C)).bfloat16(), rn(nb, C, k).bfloat16(), rn(nb, k, d)
+    y = torch.randint(0, C, (n,), generator=g, device="cuda", dtype=torch.int32)
+    Y, Yn = (torch.full((nb, n, k), float("nan"), device="cuda") for _ in range(2))
+    mb, mbn = loca.new_mb(nb), loca.new_mb(nb)
+    info, infon = (torch.full((1,), 5, dtype=torch.int32, device="cuda") for _ in range(2))
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_ERROR_TARGETS, nb, n, d, k, C=C))
+    ws.fill_(255)
+    log("allocation-free vocabulary product")
+    loca.loca_error_targets(z, y, A, B, Y, mb, info, ws)
+    loca.loca_error_targets_noalloc(z, y, A, B, Yn, mbn, infon)
+    assert int(info) == 0 and int(infon) == 0 and torch.equal(Y, Yn) and torch.equal(mb, mbn)
+    E = torch.softmax(z.double(), 1)
+    E[torch.arange(n), y.long()] -= 1
+    for b in range(nb):
+        assert rel(Y[b].cpu().numpy(), (E @ A[b].double()).cpu().numpy()) < 1e-5
+
+
 # the paper-order head at the edges of its 128-token tiles, 64-entry blocks and column tiles
 # (one to three of 32 to 256 columns, float and bf16 logits), NaN in the rows' padding, and the
 # blocks' coordinates on both sides of 64 columns.  P as two bf16 parts: 2^-17 of each term
