@@ -663,8 +663,10 @@ FusedPlan fused_plan(int64_t n, int64_t V, int64_t c) {
   const int64_t tiles = (int64_t)p.ntr * p.nct, nchunk = (V + kFV - 1) / kFV;
   // One workgroup fits a compute unit: the number of vocabulary ranges with the least rounds of
   // 256 workgroups times chunks per range (and half a chunk's time for a prologue and a write of
-  // partial outputs).  Never fewer ranges than 1024 workgroups of 128 tokens would make; more of them
-  // cost workspace.
+  // partial outputs).  Never fewer ranges than 1024 workgroups of 128 tokens would make, and at most
+  // twice as many: beyond, the partial outputs would grow out of proportion to the output (n = 51085,
+  // V = 156192, d = 256, 142 columns: a workspace of 560 MB and 19.7 ms in 17 ranges, 119 MB and
+  // 20.2 ms now).
   //
   // The sums run in float32, so their length costs precision: in the 128-token tile four waves share
   // a chunk's vocabulary, in the 256-token tile two, whose sums are twice as long.  Such a range is
@@ -677,7 +679,7 @@ FusedPlan fused_plan(int64_t n, int64_t V, int64_t c) {
   const int64_t longest = (nchunk + want - 1) / want;
   int64_t best = longest;
   double cost = 1e300;
-  for (int64_t s = want; s <= kMaxFusedSplits && s <= nchunk; ++s) {
+  for (int64_t s = want; s <= std::min({(int64_t)kMaxFusedSplits, 2 * want, nchunk}); ++s) {
     const int64_t per = (nchunk + s - 1) / s, ns = (nchunk + per - 1) / per;
     const int parts = p.tr == 256 && 2 * per > longest + 1 ? 2 : 1;
     const double t = (double)((tiles * ns + 255) / 256) * ((double)per + 0.5 * parts);

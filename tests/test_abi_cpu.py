@@ -356,3 +356,18 @@ def test_noalloc_takes_what_the_fewest_ranges_fit(lib):
             assert need(*a) <= cap, a
         assert need(*a) <= scratch(*a, 2.25), a  # twice the ranges asked for, each rounded up by itself
     assert taken > 500
+
+
+def test_fused_head_workspace_is_bounded(lib):
+    """The partial outputs of the fused head: at most four times (twice the vocabulary ranges, two
+    parts each) those of the ranges that 1024 workgroups of 128 tokens make, plus the operand laid
+    out in whole 64-column tiles and 256-entry chunks."""
+    rng = np.random.default_rng(1)
+    for i in range(3000):
+        n, V, c = (int(np.exp(rng.uniform(0, hi))) for hi in (11.5, 12, 8))
+        if i == 0:
+            n, V, c = 51085, 156192, 142
+        chunks, wgs = -(-V // 256), -(-n // 128) * -(-c // 64)
+        ranges = min(64, -(-1024 // wgs), chunks)
+        bound = 4 * ranges * n * (4 * c + 8) + -(-c // 64) * 64 * chunks * 512 + 1024
+        assert lib.workspace_size(lib.LOCA_OP_FUSED_HEAD, 1, n, 512, c, V) <= bound, (n, V, c)
