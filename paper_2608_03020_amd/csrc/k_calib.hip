@@ -325,9 +325,11 @@ __global__ void k_copy_vk(int64_t d, int k, const float* __restrict__ vk, float*
   if (e < d * k) out[b * bstride + e] = vk[b * d * k + e];
 }
 
-// the primal form's single solve serves every block: its status goes to each block's dev_info
-__global__ void k_copy_info(const int32_t* __restrict__ src, int32_t* __restrict__ dst, int64_t nb) {
-  for (int64_t b = threadIdx.x; b < nb; b += blockDim.x) dst[b] = src[0];
+// one factorization serves every block: its status goes to each block's dev_info (one wave, which
+// reads the status before it writes any: src may be dst)
+__global__ void k_copy_info(const int32_t* src, int32_t* dst, int64_t nb) {
+  const int32_t v = *src;
+  for (int64_t b = threadIdx.x; b < nb; b += blockDim.x) dst[b] = v;
 }
 
 __global__ void k_zero_i32(int32_t* p, int64_t cnt) {

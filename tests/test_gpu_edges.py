@@ -204,6 +204,25 @@ def test_dual_fit_edges(d, n_p, k, V, wu16):
         assert rel((at[b].double() @ bt[b].double()).cpu().numpy(), Wu.double().cpu().numpy() @ Fk.T) < 5e-6
 
 
+# one factorization serves all blocks: a NaN in the probes is every block's first failed pivot, also
+# past the 64 lanes that spread it
+@pytest.mark.parametrize("fit,col", [("loca_feedback_fit", 0), ("loca_feedback_fit", 17), ("loca_feedback_fit_primal", 0)])
+def test_fit_status_reaches_every_block(fit, col):
+    import torch
+    from paper_2608_03020_amd import loca
+    nb, d, n_p, k = 130, 48, 20, 3
+    E, G = torch.randn((d, n_p), device="cuda"), torch.randn((nb, d, n_p), device="cuda")
+    E[5, col] = float("nan")
+    kw = dict(dtype=torch.float32, device="cuda")
+    info = torch.full((nb,), 99, dtype=torch.int32, device="cuda")
+    op = loca.LOCA_OP_FEEDBACK_FIT if fit == "loca_feedback_fit" else loca.LOCA_OP_FEEDBACK_FIT_PRIMAL
+    ws = loca.alloc_workspace(loca.workspace_size(op, nb, n_p, d, k))
+    log("fit status", fit, col)
+    getattr(loca, fit)(E, G, 0.1, torch.empty((nb, k, d), **kw), torch.empty((nb, n_p), **kw),
+                       torch.empty(nb, dtype=torch.float64, device="cuda"), info, ws)
+    assert info.eq(col + 1 if fit == "loca_feedback_fit" else 6).all(), info
+
+
 # the fused head at the edges of its token tiles (128, 256), 256-entry vocabulary chunks, 64-wide
 # slices of d and 64-column tiles, with a maximum that rises late and an excluded tail.  The
 # exponentials carry 2^-17 (two bf16 parts), far below the 1e-5 asked of the output's norm
