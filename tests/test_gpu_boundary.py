@@ -6,8 +6,9 @@
 * Every call of a step has its own dev_info slice, so a solve's pivot code is still
   there after the truncation has run.
 * Two host threads, each running statistics and then the ridge solve on its own
-  stream and buffers, give the bits of the single-threaded runs (the solve's internal
-  streams are shared between them).
+  stream and buffers, give the bits of the single-threaded runs and of solves of one
+  block each (the solves are large enough for two groups, whose internal stream the
+  threads share).
 * The projected solve on the step's side stream, beside the ridge solves, gives the
   bits of the same calls run alone.
 """
@@ -179,11 +180,16 @@ def test_solve_pivot_code_survives_the_step():
 
 def test_concurrent_solves_from_two_threads():
     """Two host threads, each on its own stream with its own buffers, run the statistics
-    and then the ridge solve (three blocks: the solve uses its internal streams) several
-    times; every result equals, bit for bit, the same work run alone."""
+    and then the ridge solve several times; every result equals, bit for bit, the same work
+    run alone, and that one the solves of one block each, which have one group.  Nine
+    factorizations of d = 2560, 5.03e10 multiply-adds in all: past the 5e10 from which a
+    solve of two or more blocks runs in two groups, one of them on the internal stream."""
     import torch
+    from paper_2608_03020_amd import loca
     from paper_2608_03020_amd.step import BlockStep
-    cfg = gen.custom_config("thr", blocks=3, d=1024, n=2048, micro=1024, C=5, k=16, r_a=8, lambdas=(1e-2, 1e-1))
+    cfg = gen.custom_config("thr", blocks=3, d=2560, n=5120, micro=2560, C=5, k=16, r_a=8, lambdas=(1e-2, 1e-1, 1.0))
+    nl = len(cfg.lambdas)
+    assert 3 * nl * cfg.d ** 3 / 3 >= 5e10
     inputs = []
     for seed in (1, 2):
         xs, zs, ys, As, Bs = host_inputs(cfg, range(3), seed=seed)
@@ -200,6 +206,12 @@ def test_concurrent_solves_from_two_threads():
         work(i, st)
         torch.cuda.synchronize()
         ref.append((st.S.cpu().numpy(), st.K.cpu().numpy(), st.M.cpu().numpy(), st.sigma.cpu().numpy()))
+        for b in range(3):
+            M = torch.full((1, nl, cfg.d, cfg.k), float("nan"), device="cuda")
+            info = torch.full((nl,), 77, dtype=torch.int32, device="cuda")
+            ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_RIDGE_SOLVE, 1, 0, cfg.d, cfg.k, n_lambda=nl))
+            loca.loca_ridge_solve(st.S[b:b + 1], st.K[b:b + 1], cfg.lambdas, M, info, ws)
+            assert info.eq(0).all() and torch.equal(M[0], st.M[b]), (i, b)
     log("case two threads: references done")
     reps = 4
     steps = [[BlockStep(cfg, 3) for _ in range(reps)] for _ in range(2)]
@@ -231,20 +243,21 @@ def test_concurrent_solves_from_two_threads():
 
 
 def test_projected_solve_beside_ridge_solves():
-    """The projected solve runs on the step's side stream beside the ridge solves (three
-    blocks, so the solves use their internal streams too); over three steps in a row M,
-    the truncation and B* equal, bit for bit, the ridge solve run alone and the projected
-    solve called alone on the same statistics."""
+    """The projected solve runs on the step's side stream beside the ridge solves (nine
+    factorizations of d = 2560: two groups, so the solves use their internal stream too); over
+    three steps in a row M, the truncation and B* equal, bit for bit, the ridge solve run alone
+    and the projected solve called alone on the same statistics."""
     import torch
     from paper_2608_03020_amd import loca
     from paper_2608_03020_amd.step import BlockStep
-    cfg = gen.custom_config("side", blocks=3, d=1024, n=2048, micro=1024, C=5, k=16, r_a=8, lambdas=(1e-2, 1e-1))
+    cfg = gen.custom_config("side", blocks=3, d=2560, n=5120, micro=2560, C=5, k=16, r_a=8, lambdas=(1e-2, 1e-1, 1.0))
+    assert 3 * len(cfg.lambdas) * cfg.d ** 3 / 3 >= 5e10
     xs, zs, ys, As, Bs = host_inputs(cfg, range(3), seed=3)
     x_all = padded_rows(np.stack([np.concatenate(xb) for xb in xs]))
     z_all, y_all = to_dev(np.concatenate(zs)), to_dev(np.concatenate(ys))
     A, B = to_dev(np.stack(As)), to_dev(np.stack(Bs))
     proj = gen.torch_gen_adapter_projection(cfg, 3)
-    log("case projected solve on the side stream: 3 blocks, 2 lambdas, 3 steps")
+    log("case projected solve on the side stream: 3 blocks, 3 lambdas, 3 steps")
     ref = BlockStep(cfg, 3)
     ref.run(x_all, z_all, y_all, A, B)
     nl = len(cfg.lambdas)

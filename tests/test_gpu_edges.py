@@ -139,6 +139,35 @@ def test_ridge_solve_block_edges(d, acc):
             assert rel(M[b, i].cpu().numpy(), ref) < (9 * np.sqrt(d) * 2.0 ** -24 if acc == "f32" else 0) + 2.0 ** -23
 
 
+# enough matrices for the panel kernel's workgroups of eight waves (at least 256 of them), with and
+# without 16-byte rows, a ragged last panel, waves past the last column and right-hand sides on both
+# sides of a wave's 32 columns; bound as above
+@pytest.mark.parametrize("d,k", [(130, 5), (132, 33), (301, 8), (300, 40)])
+def test_ridge_solve_of_many_matrices(d, k):
+    import torch
+    from paper_2608_03020_amd import loca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    nb, lams = 64, [1e-2, 0.1, 1.0, 10.0]
+    X = torch.randn((nb, 4 * d, d), generator=g, device="cuda", dtype=torch.float64)
+    S = (X.transpose(1, 2).contiguous() @ X).float()
+    K = torch.randn((nb, d, k), generator=g, device="cuda")
+    U = torch.triu(S).double().cpu()
+    U = U + torch.triu(U, 1).transpose(1, 2)
+    S += torch.tril(torch.full_like(S, float("nan")), -1)  # never read
+    M = torch.full((nb, 4, d, k), float("nan"), device="cuda")
+    info = torch.full((nb * 4,), 77, dtype=torch.int32, device="cuda")
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_RIDGE_SOLVE, nb, 0, d, k, n_lambda=4))
+    ws.fill_(255)
+    log("ridge solve of many matrices", d, k)
+    loca.loca_ridge_solve(S, K, lams, M, info, ws)
+    assert info.eq(0).all()
+    for i, lam in enumerate(lams):
+        ref = torch.linalg.solve(U + lam * torch.eye(d, dtype=torch.float64), K.double().cpu())
+        e = (M[:, i].double().cpu() - ref).norm(dim=(1, 2)) / ref.norm(dim=(1, 2))
+        assert float(e.max()) < 9 * np.sqrt(d) * 2.0 ** -24 + 2.0 ** -23
+
+
 # the float32 solve's errors lean neither way: <M - ref, ref> / ||ref||^2, averaged over eight blocks
 # (the errors themselves are 5e-7, of either sign).  Every column of the factor and of the inverse
 # takes a reciprocal root, and a root that leans by a part of its unit 2^-24 moves all of M by as
