@@ -464,7 +464,7 @@ __global__ __launch_bounds__(64 * NWV) void k_panel_f32(int64_t d, int64_t k0, i
   const int64_t col = c0 + (lane & 31);
   const bool cok = col < ldb;  // false in the waves that the last workgroup has to spare
   const int pw = (int)((d - p) < P ? (d - p) : P);
-  const int nk1 = (int)((p - k0) / 16), ns = nk1 + P / 16;  // nk1: a multiple of 8
+  const int nk1 = (int)((p - k0) / 16);  // stages of the update (a multiple of 8), X's after them
 
   float4 rp[D][QP];
   auto load_p = [&](int slot, int s) {
@@ -698,7 +698,7 @@ LOCA_DEV void mm16(typename Dg<T>::acc_t& acc, const T* Am, const T* Bm, int ld,
 }
 
 // In fp32 the block first takes the update by its super-panel's earlier panels, A11 -= sum over
-// the rows kk in [k0, p) of F[kk][p + i] F[kk][p + j] (strip_update): in a launch of its own,
+// the rows kk in [k0, p) of F[kk][p + i] F[kk][p + j] (diag_strip_update): in a launch of its own,
 // with the rest of the panel's rows, that update was one more link of the chain.
 template <typename T, int P, bool V4>
 __global__ __launch_bounds__(4 * P) void k_diag_inv(int64_t d, int64_t k0, int64_t p, T* __restrict__ Fall,
@@ -1106,22 +1106,8 @@ LOCA_DEV void split2h_pair(float a0, float a1, uint32_t& hp, uint32_t& lp) {
   lp = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, f16x2_v));
 }
 // the 8 fp32 operand values of lane `lane` (rows 8 (lane / 32) + e of the stage, column
-// c0 + lane % 32 of the panel) from a swizzled stage, split into three MFMA operands
-LOCA_DEV void frag_f32_split(const float* stage, int c0, int lane, bf16x8_t& fh, bf16x8_t& fm, bf16x8_t& fl) {
-  const int hw = lane >> 5, cc = c0 + (lane & 31);
-  const float* p = stage + 8 * hw * 256 + 4 * ((cc >> 2) ^ (8 * hw)) + (cc & 3);
-  float v[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = p[e * 256];
-  uint32_t h[4], m[4], l[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) split3_pair(v[2 * e], v[2 * e + 1], h[e], m[e], l[e]);
-  fh = __builtin_bit_cast(bf16x8_t, make_uint4(h[0], h[1], h[2], h[3]));
-  fm = __builtin_bit_cast(bf16x8_t, make_uint4(m[0], m[1], m[2], m[3]));
-  fl = __builtin_bit_cast(bf16x8_t, make_uint4(l[0], l[1], l[2], l[3]));
-}
-// the 8 fp32 operand values of lane `lane` (as for frag_f32_split), split into two fp16
-// MFMA operands of 2^8 times their value
+// c0 + lane % 32 of the panel) from a swizzled stage, split into two fp16 MFMA operands of
+// 2^8 times their value
 LOCA_DEV void frag_f32_split2h(const float* stage, int c0, int lane, f16x8_t& fh, f16x8_t& fl) {
   const int hw = lane >> 5, cc = c0 + (lane & 31);
   const float* p = stage + 8 * hw * 256 + 4 * ((cc >> 2) ^ (8 * hw)) + (cc & 3);
@@ -1246,26 +1232,6 @@ __global__ __launch_bounds__(512) void k_syrk_f32_dl(int64_t d, int64_t k0, int6
 }
 
 // ------------------------------------------------------------------ back substitution, one row block
-
-// acc[m][q] += sum_kk sA[i][kk] sB[kk][j]: like tile_mma, with the first operand stored
-// with K along its rows (row stride lda, odd so that column reads are conflict-free).
-template <typename T>
-LOCA_DEV void tile_mma_kt(const T* sA, int lda, const T* sB, int ldb, int K, int wi, int wj, int lane,
-                          typename Mf<T>::acc_t (&acc)[2][2]) {
-  constexpr int BLK = Mf<T>::BLK, KS = Mf<T>::KS, WT = Mf<T>::P / 2;
-  const int kr = lane / BLK, cr = lane % BLK;
-  for (int kk = 0; kk < K; kk += KS) {
-    T a[2], b[2];
-#pragma unroll
-    for (int m = 0; m < 2; ++m) a[m] = sA[(wi * WT + m * BLK + cr) * lda + kk + kr];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) b[q] = sB[(kk + kr) * ldb + wj * WT + q * BLK + cr];
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-      for (int q = 0; q < 2; ++q) acc[m][q] = Mf<T>::mma(a[m], b[q], acc[m][q]);
-  }
-}
 
 // Right-looking back substitution for row block [p, p + pw) of U M' = Y, where the rows
 // of R (= Y) have already received the contributions of every block below:

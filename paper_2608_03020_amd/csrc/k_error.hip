@@ -5,14 +5,18 @@
 // denominator of the scale-normalised step (Eq. 10) is
 // ||Q||_F^2 = sum_t Y_t (B~ B~^T) Y_t^T, so Q = Y B~ is never formed.
 //
-// Two kernels:
-//  * small label sets (C <= 64): one thread per token; A~ and G = B~ B~^T are
-//    staged in LDS; softmax in fp32 with the row maximum subtracted.
-//  * large vocabularies: one workgroup per group of tokens streams the logits
-//    once with an online (running-max) softmax, accumulating the rescaled
-//    sum of exp(z - m) A~[c] alongside; Y = acc / s - A~[y].
-// Both write per-workgroup partial sums of ||Q||^2 (fp64) that a finalize
-// kernel adds in a fixed order, so results are bitwise reproducible.
+// Four paths, with ||Q||^2 from fp64 partial sums added in a fixed order, so that results are
+// bitwise reproducible:
+//  * label sets of at most 16 classes (k <= 64): k_error_rows, the error rows formed once per token
+//    tile and shared by the blocks, ||Q||^2 through one C x C sum;
+//  * label sets of 17 to 64 classes (k <= 64): k_error_small, one thread per token, A~ staged in LDS,
+//    softmax in fp32 with the row maximum subtracted;
+//  * large vocabularies with bf16 A~ (k % 8 == 0, aligned operands): a matrix-core product over the
+//    vocabulary (launch_softmax_product), then k_q2_rows;
+//  * the rest: k_error_large, one workgroup per group of tokens streaming the logits once with an
+//    online (running-max) softmax, accumulating the rescaled sum of exp(z - m) A~[c] alongside; Y =
+//    acc / s - A~[y].
+// The paper-order head's per-block coordinates are k_credit_project.
 #include <algorithm>
 #include <mutex>
 
@@ -170,8 +174,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_error_small(
     if (yt < 0 || yt >= C) {
       atomicMin(dev_info, (int32_t)(t + 1));
     } else {
-      // the logits in chunks of 8 classes, each chunk's loads issued together (held in
-      // registers for the three passes when C <= 8)
+      // the logits in chunks of 8 classes, each chunk's loads issued together, in three passes
       float zc[8];
       auto chunk = [&](int64_t c0) {
 #pragma unroll
@@ -187,7 +190,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_error_small(
       }
       float s = 0.f;
       for (int64_t c0 = 0; c0 < C; c0 += 8) {
-        if (c0 > 0 || C > 8) chunk(c0);
+        chunk(c0);
 #pragma unroll
         for (int u = 0; u < 8; ++u)
           if (c0 + u < C) s += __expf(zc[u] - m);
@@ -195,7 +198,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_error_small(
       const float inv = 1.0f / s;
       const float wt = w ? w[t] : 1.0f;
       for (int64_t c0 = 0; c0 < C; c0 += 8) {
-        if (c0 > 0 || C > 8) chunk(c0);
+        chunk(c0);
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           const int64_t c = c0 + u;

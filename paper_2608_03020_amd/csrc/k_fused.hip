@@ -53,32 +53,6 @@ constexpr int64_t kMaxLd256 = (int64_t)1 << 22;        // longest row of h for 2
 // that the 16 lanes that read one chunk of 16 consecutive rows hit 16 distinct bank groups.
 LOCA_DEV int fz_swz(int r) { return (r >> 1) & 7; }
 
-// (m, s) of two disjoint parts of a row, combined
-LOCA_DEV void fz_combine(float& m, float& s, float m2, float s2) {
-  if (s2 == 0.f) return;
-  if (s == 0.f) {
-    m = m2;
-    s = s2;
-    return;
-  }
-  const float mm = fmaxf(m, m2);
-  s = s * __expf(m - mm) + s2 * __expf(m2 - mm);
-  m = mm;
-}
-
-// s_waitcnt vmcnt(a) for a run-time a in 0..31
-LOCA_DEV void wait_vm(int a) {
-  switch (a) {
-#define LOCA_W(N) case N: __builtin_amdgcn_s_waitcnt(vmcnt_imm(N)); break;
-    LOCA_W(0) LOCA_W(1) LOCA_W(2) LOCA_W(3) LOCA_W(4) LOCA_W(5) LOCA_W(6) LOCA_W(7) LOCA_W(8) LOCA_W(9)
-    LOCA_W(10) LOCA_W(11) LOCA_W(12) LOCA_W(13) LOCA_W(14) LOCA_W(15) LOCA_W(16) LOCA_W(17) LOCA_W(18)
-    LOCA_W(19) LOCA_W(20) LOCA_W(21) LOCA_W(22) LOCA_W(23) LOCA_W(24) LOCA_W(25) LOCA_W(26) LOCA_W(27)
-    LOCA_W(28) LOCA_W(29) LOCA_W(30)
-#undef LOCA_W
-    default: __builtin_amdgcn_s_waitcnt(vmcnt_imm(0)); break;
-  }
-}
-
 // The logits are formed transposed, z^T = W_u[chunk] h_tile^T (vocabulary x tokens), so
 // that lane l of a 32 x 32 result block holds token l % 32 and 16 vocabulary entries:
 // the softmax statistics of a token stay within a lane pair (l, l ^ 32) and the waves

@@ -276,7 +276,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gram_bf16(int64_t n, int64_t
 // 248 x 32 x 3705 874 -> 216 (the staging waited for every stage's loads; here three are in
 // flight).
 constexpr int kDLStages = 4;
-constexpr int kDLRowBytes = 512;
 
 // WGM x WGN waves of (256 / WGM) x (256 / WGN) columns each: 2 x 4 waves (two per SIMD)
 // or 2 x 2 waves of 128 x 128 (one per SIMD, a third fewer LDS reads per MFMA).

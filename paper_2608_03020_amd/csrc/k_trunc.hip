@@ -459,10 +459,7 @@ LOCA_DEV bool chol64(const double* part, int nsplit, int K, double* raw, double*
       // columns up to j are finished: what the update leaves in them is not read again
       const double t = x * rcp64(piv);
 #pragma unroll
-      for (int s = 0; s < kRS; ++s) {
-        const int c = kRW * (kb + s) + wid;
-        a[s] = fma(-t, vc[s], a[s]);
-      }
+      for (int s = 0; s < kRS; ++s) a[s] = fma(-t, vc[s], a[s]);
       if ((j & (kRW - 1)) == kRW - 1) {
         next_group(a);
         ++kb;
@@ -524,8 +521,7 @@ LOCA_DEV bool eig_top(const double* A, int n, int K, int r, double* W, OutT* Vou
   constexpr int LPR = kTC / KM;  // lanes per row of p, and per eigenvalue in the multisection
   constexpr int NX = KM / 64, NP = KM / LPR, NU = KM / 32, NZ = KM / 16;
   const int tid = threadIdx.x, lane = tid & 63;
-  auto at = [&](int i, int j) -> double& { return PACKED ? W[pk(i, j, n)] : W[i * n + j]; };
-  auto segsum = [&](double v) { return LPR == 16 ? seg16_sum(v) : seg8_sum(v); };
+  auto at = [&](int i, int j) -> double& { return W[pk(i, j, n)]; };  // PACKED only
   __shared__ int s_cut;  // the number of pairs while it is lowered
   int* cut = &s_cut;
   if (tid == 0) red[kRedEig] = 0.0;
@@ -562,6 +558,7 @@ LOCA_DEV bool eig_top(const double* A, int n, int K, int r, double* W, OutT* Vou
         dT[k] = at(k, k);
       }
       if (tau != 0.0) {  // uniform: every wave has the same ss
+        static_assert(!PACKED || LPR == 8, "seg8_sum below");
         {  // p_i = tau sum_c A[k+1+i][k+1+c] v_c, LPR lanes per row i
           const int row = tid / LPR, part = tid % LPR;
           double acc = 0.0;
@@ -571,7 +568,7 @@ LOCA_DEV bool eig_top(const double* A, int n, int K, int r, double* W, OutT* Vou
               const int c = part + LPR * u;
               if (c < m) acc += at(k + 1 + row, k + 1 + c) * (c == 0 ? v0 : at(k, k + 1 + c));
             }
-          acc = segsum(acc);
+          acc = seg8_sum(acc);
           if (row < m && part == 0) pbuf[row] = tau * acc;
         }
         __syncthreads();
