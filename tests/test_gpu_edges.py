@@ -105,6 +105,9 @@ def test_statistics_with_split_targets_past_2gb(n, d, w):
     e_s, e_k = rel(S[0].cpu().numpy()[iu], refS.cpu().numpy()[iu]), rel(K[0].cpu().numpy(), refK.cpu().numpy())
     log(f"  S {e_s:.1e} K {e_k:.1e}")
     assert int(info[0]) == 0 and max(e_s, e_k) < n / 16 * 2.0 ** -24
+    once = S.clone()
+    loca.loca_accumulate_stats(x, y, 0.5, mb, S, K, ws, a_w=a, dev_info=info)  # adds the same to itself
+    assert torch.equal(torch.triu(S), 2 * torch.triu(once)) and int(info[0]) == 0
 
 
 # widths at the edges of the 16-wide blocks, the 64- and 128-wide panels and the 512-wide

@@ -57,14 +57,14 @@ def _compare(cfg, g, o, b, label):
 
 
 CASES = {
-    # ragged d on 128-wide tiles, two micro-batches (640 + 360 rows), two blocks, two lambdas
+    # ragged d on 256-wide tiles, two micro-batches (640 + 360 rows), two blocks, two lambdas
     "bf16_d600": gen.custom_config("t1", blocks=2, d=600, n=1000, micro=640, C=5, k=16, r_a=4, lambdas=(1e-2, 1.0)),
     # ragged d on 256-wide tiles, three micro-batches with a ragged last one.  bf16 mode keeps fp32
     # statistics, which needs N > d: with N < d rounding in S leaks into the null space of X and is
     # amplified by 1/lambda (fp32 mode, with fp64 statistics, covers N < d).
     "bf16_d1100": gen.custom_config("t2", blocks=1, d=1100, n=2300, micro=1000, C=3, k=32, r_a=8),
-    # d % 8 == 0 and d >= 1024: the direct-to-LDS Gram kernel; ragged against 256-wide tiles and
-    # against the 32-token stages (1400 = 43 x 32 + 24), two blocks
+    # d % 8 == 0, whole 16-byte chunks: ragged against 256-wide tiles and against the 32-token
+    # stages (1400 = 43 x 32 + 24), two blocks
     "bf16_d1040_direct": gen.custom_config("t10", blocks=2, d=1040, n=2400, micro=1400, C=4, k=16, r_a=4),
     # cross statistic inside the Gram launch: widest split target (2k = 64), and a padded one (2k = 10 -> 16)
     "bf16_d1536_k32_fused": gen.custom_config("t11", blocks=1, d=1536, n=2000, micro=1000, C=5, k=32, r_a=8),
@@ -492,8 +492,8 @@ def test_stats_overwrite_equals_cleared_accumulation(d, k, mode, weighted):
     """The overwrite flag (the first micro-batch of a step) leaves S's upper triangle, K and
     the micro-batch records bit for bit as the accumulating call on zeroed S and K, without
     reading the old contents (NaN here); a second, accumulating micro-batch keeps them
-    equal.  Paths: the direct-to-LDS Gram kernel with the cross statistic fused (k = 8)
-    and as cross tiles (k = 40, 64), the register-staged kernel (d = 200), the fp64 kernel."""
+    equal.  Paths: the direct-to-LDS Gram kernel with the cross statistic fused (k = 8, 24)
+    and as cross tiles (k = 40, 64), wide and narrow (d = 200), the fp64 kernel."""
     import torch
     from paper_2608_03020_amd import loca
     nb, n = 2, 300
