@@ -154,8 +154,9 @@ __global__ __launch_bounds__(kFT) void k_fused_head(int64_t n, int64_t V, int64_
 #pragma unroll
           for (int r = 0; r < 16; ++r) z[mv][mt][r] = 0.f;
       for (int ks = 0; ks < nks; ++ks) {
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // the stage landed (this thread's copies)
-        barrier_nofence();                         // ... everyone's; the other slot is no longer read
+        // the stage landed (this thread's copies), and this thread's reads of the other slot are done
+        __builtin_amdgcn_s_waitcnt(kWaitMemLds);
+        barrier_nofence();  // ... everyone's: the other slot may be overwritten
         if (ks + 1 < nks) {
           issue_stage(ks + 1, slot ^ 1);
         } else if (j + 1 < j1) {

@@ -167,6 +167,9 @@ LOCA_DEV bf16x8_t frag32_tr_swz(const uint16_t* tile, int c0, int ks, int lane) 
 // s_waitcnt immediate that waits until at most n vector-memory operations are outstanding
 constexpr int vmcnt_imm(int n) { return (n & 15) | (((n >> 4) & 3) << 14) | (7 << 4) | (15 << 8); }
 
+// ... until none is, and no LDS operation either (vmcnt(0) lgkmcnt(0))
+constexpr int kWaitMemLds = 7 << 4;
+
 // 16-byte global -> LDS copy for every lane: lane l's chunk lands at lds_base + 16 l.
 // Issued as inline assembly so that the compiler does not treat it as a store to the
 // ring slot being read and drain it before every LDS read; completion is tracked by
