@@ -174,7 +174,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_error_small(
     if (yt < 0 || yt >= C) {
       atomicMin(dev_info, (int32_t)(t + 1));
     } else {
-      // the logits in chunks of 8 classes, each chunk's loads issued together, in three passes
+      // the logits in chunks of 8 classes, each chunk's loads issued together, in three passes.
+      // (The condition on the loads of the last two always holds, smaller label sets taking
+      // k_error_rows; without it the compiler schedules the passes worse: 32 blocks of 65536
+      // tokens, 24 classes, k = 4 277 us, with it 227.)
       float zc[8];
       auto chunk = [&](int64_t c0) {
 #pragma unroll
@@ -190,7 +193,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_error_small(
       }
       float s = 0.f;
       for (int64_t c0 = 0; c0 < C; c0 += 8) {
-        chunk(c0);
+        if (c0 > 0 || C > 8) chunk(c0);
 #pragma unroll
         for (int u = 0; u < 8; ++u)
           if (c0 + u < C) s += __expf(zc[u] - m);
@@ -198,7 +201,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_error_small(
       const float inv = 1.0f / s;
       const float wt = w ? w[t] : 1.0f;
       for (int64_t c0 = 0; c0 < C; c0 += 8) {
-        chunk(c0);
+        if (c0 > 0 || C > 8) chunk(c0);
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           const int64_t c = c0 + u;
