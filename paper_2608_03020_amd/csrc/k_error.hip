@@ -7,9 +7,9 @@
 //
 // Four paths, with ||Q||^2 from fp64 partial sums added in a fixed order, so that results are
 // bitwise reproducible:
-//  * label sets of at most 16 classes (k <= 64): k_error_rows, the error rows formed once per token
+//  * label sets of at most 8 classes (k <= 64): k_error_rows, the error rows formed once per token
 //    tile and shared by the blocks, ||Q||^2 through one C x C sum;
-//  * label sets of 17 to 64 classes (k <= 64): k_error_small, one thread per token, A~ staged in LDS,
+//  * label sets of 9 to 64 classes (k <= 64): k_error_small, one thread per token, A~ staged in LDS,
 //    softmax in fp32 with the row maximum subtracted;
 //  * large vocabularies with bf16 A~ (k % 8 == 0, aligned operands): a matrix-core product over the
 //    vocabulary (launch_softmax_product), then k_q2_rows;
@@ -131,7 +131,7 @@ static size_t credit_gram_part_ws(int64_t nb, int64_t k) { return align256(sizeo
 //     each lane multiplies its entries of M_w by those of G (KB x KB, zero past k; blocks off
 //     the diagonal count twice).
 // The tile reuses the A~ area once it is consumed.
-// (Label sets of at most 16 classes take k_error_rows below.)
+// (Label sets of at most 8 classes take k_error_rows below.)
 static int64_t small_kb(int64_t k) { return k <= 16 ? 16 : k <= 32 ? 32 : 64; }
 template <int KB>
 struct SmallLds {
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_error_small(
   if (threadIdx.x == 0) partial[b * gridDim.x + blockIdx.x] = tot;
 }
 
-// ------------------------------------------------------------------ label sets of at most 16 classes
+// ------------------------------------------------------------------ label sets of at most 8 classes
 
 // A token's error row e_t (C values) is the same for every block, so ||Q_b||^2 = sum_t a_t e_t H_b
 // e_t^T, H_b = A~_b G_b A~_b^T, is <H_b, M> with the one C x C matrix M = sum_t a_t e_t^T e_t, and
@@ -293,13 +293,18 @@ __global__ __launch_bounds__(kSmallThreads) void k_error_small(
 // % 4 == 0 and 16-byte aligned rows).  8192 tokens, 48 blocks, five classes, k = 64: 44.1 us a call with
 // the rows formed again for every block, H by every workgroup and Y through an LDS tile; 34.4 us now (this
 // kernel 22 us, 4.6 TB/s).
-constexpr int kRowTok = 256, kMaxMParts = 512;
-template <int HC, typename LT>
-LOCA_DEV float error_row(float (&ev)[HC], int64_t t, int64_t n, int C, const LT* __restrict__ logits, int64_t ld,
+//
+// With 16 rows of A~ in place of eight the products are bound by the LDS reads of the error rows and
+// the sum of M by its 256 entries, each one thread's chain: 9 classes, 24 blocks of 16384 tokens, k =
+// 32 93 us, one block of 512, k = 64 48 us; k_error_small 40 and 28 us, and 16 classes 54 and 33
+// (137 and 62).  So label sets past eight classes take that kernel.
+constexpr int kRowTok = 256, kMaxMParts = 512, kHC = 8;  // kHC: most classes
+template <typename LT>
+LOCA_DEV float error_row(float (&ev)[kHC], int64_t t, int64_t n, int C, const LT* __restrict__ logits, int64_t ld,
                          const int32_t* __restrict__ labels, const float* __restrict__ w,
                          const float* __restrict__ aw, int32_t* dev_info) {
 #pragma unroll
-  for (int c = 0; c < HC; ++c) ev[c] = 0.f;
+  for (int c = 0; c < kHC; ++c) ev[c] = 0.f;
   if (t >= n) return 0.f;
   const int32_t yt = labels[t];
   if (yt < 0 || yt >= C) {
@@ -307,49 +312,49 @@ LOCA_DEV float error_row(float (&ev)[HC], int64_t t, int64_t n, int C, const LT*
     return 0.f;
   }
   const LT* zt = logits + t * ld;
-  float z[HC];
+  float z[kHC];
 #pragma unroll
-  for (int c = 0; c < HC; ++c) z[c] = c < C ? load_as_f32(zt + c) : -INFINITY;
+  for (int c = 0; c < kHC; ++c) z[c] = c < C ? load_as_f32(zt + c) : -INFINITY;
   float m = z[0];
 #pragma unroll
-  for (int c = 1; c < HC; ++c)
+  for (int c = 1; c < kHC; ++c)
     if (c < C) m = fmaxf(m, z[c]);
   float s = 0.f;
 #pragma unroll
-  for (int c = 0; c < HC; ++c)
+  for (int c = 0; c < kHC; ++c)
     if (c < C) {
       ev[c] = __expf(z[c] - m);
       s += ev[c];
     }
   const float inv = 1.0f / s, wt = w ? w[t] : 1.0f;
 #pragma unroll
-  for (int c = 0; c < HC; ++c)
+  for (int c = 0; c < kHC; ++c)
     if (c < C) ev[c] = wt * (ev[c] * inv - (c == yt ? 1.0f : 0.0f));
   return aw ? aw[t] : 1.0f;
 }
 
-template <typename LT, typename AT, int KB, int HC, bool V4>
+template <typename LT, typename AT, int KB, bool V4>
 __global__ __launch_bounds__(kRowTok) void k_error_rows(
     int64_t n, int C, int64_t k, const LT* __restrict__ logits, int64_t ld, const int32_t* __restrict__ labels,
     const float* __restrict__ w, const float* __restrict__ aw, const AT* __restrict__ A, int64_t a_bstride, int64_t nb,
     int bper, int ntile, int mparts, float* __restrict__ y_out, int64_t y_bstride, float* __restrict__ e_out,
     double* __restrict__ mpart, int32_t* __restrict__ dev_info) {
-  constexpr int R4 = KB / 4, TPI = 64 / R4, NE = HC * HC, NS = kRowTok / NE;  // NS threads per entry of M
-  __shared__ __attribute__((aligned(16))) float sE[kRowTok][HC];
+  constexpr int R4 = KB / 4, TPI = 64 / R4, NE = kHC * kHC, NS = kRowTok / NE;  // NS threads per entry of M
+  __shared__ __attribute__((aligned(16))) float sE[kRowTok][kHC];
   __shared__ float sW[kRowTok];
   __shared__ double sM[kRowTok];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  float ev[HC];
+  float ev[kHC];
   if (blockIdx.y == 0) {
     if ((int)blockIdx.x >= mparts) return;
-    const int en = tid % NE, part = tid / NE, c1 = en / HC, c2 = en % HC;
+    const int en = tid % NE, part = tid / NE, c1 = en / kHC, c2 = en % kHC;
     double m = 0.0;
     for (int tile = blockIdx.x; tile < ntile; tile += mparts) {
       const int64_t t = (int64_t)tile * kRowTok + tid;
       __syncthreads();  // the previous tile is no longer read
-      sW[tid] = error_row<HC>(ev, t, n, C, logits, ld, labels, w, aw, dev_info);
+      sW[tid] = error_row(ev, t, n, C, logits, ld, labels, w, aw, dev_info);
 #pragma unroll
-      for (int c = 0; c < HC; ++c) {
+      for (int c = 0; c < kHC; ++c) {
         sE[tid][c] = ev[c];
         if (e_out && t < n && c < C) e_out[t * C + c] = ev[c];
       }
@@ -368,17 +373,17 @@ __global__ __launch_bounds__(kRowTok) void k_error_rows(
     return;
   }
   const int64_t t0 = (int64_t)blockIdx.x * kRowTok;
-  error_row<HC>(ev, t0 + tid, n, C, logits, ld, labels, w, aw, nullptr);
+  error_row(ev, t0 + tid, n, C, logits, ld, labels, w, aw, nullptr);
 #pragma unroll
-  for (int c = 0; c < HC; c += 4) *(float4*)&sE[tid][c] = make_float4(ev[c], ev[c + 1], ev[c + 2], ev[c + 3]);
+  for (int c = 0; c < kHC; c += 4) *(float4*)&sE[tid][c] = make_float4(ev[c], ev[c + 1], ev[c + 2], ev[c + 3]);
   wave_lds_sync();  // a wave reads its own 64 tokens only
   const int64_t b0 = (int64_t)(blockIdx.y - 1) * bper, b1 = b0 + bper < nb ? b0 + bper : nb;
   const int j = 4 * (lane % R4), sub = lane / R4;
   for (int64_t b = b0; b < b1; ++b) {
     const AT* Ab = A + b * a_bstride;
-    float a[HC][4];
+    float a[kHC][4];
 #pragma unroll
-    for (int c = 0; c < HC; ++c)
+    for (int c = 0; c < kHC; ++c)
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const bool ok = c < C && j + u < k;
@@ -389,15 +394,15 @@ __global__ __launch_bounds__(kRowTok) void k_error_rows(
 #pragma unroll 4
     for (int i = 0; i < R4; ++i) {
       const int p = 64 * wid + TPI * i + sub;
-      float e[HC];
+      float e[kHC];
 #pragma unroll
-      for (int c = 0; c < HC; c += 4) {
+      for (int c = 0; c < kHC; c += 4) {
         const float4 v = *(const float4*)&sE[p][c];
         e[c] = v.x; e[c + 1] = v.y; e[c + 2] = v.z; e[c + 3] = v.w;
       }
       float y[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int c = 0; c < HC; ++c) {
+      for (int c = 0; c < kHC; ++c) {
         if (c >= C) break;
 #pragma unroll
         for (int u = 0; u < 4; ++u) y[u] = fmaf(e[c], a[c][u], y[u]);
@@ -418,22 +423,22 @@ __global__ __launch_bounds__(kRowTok) void k_error_rows(
 
 // Per block: H = A~ G A~^T (fp64), M from its partials in a fixed order, sum_q2 = <H, M>; the record
 // and dev_info as k_error_finalize leaves them.
-template <typename AT, int KB, int HC>
+template <typename AT, int KB>
 __global__ __launch_bounds__(256) void k_error_rows_finalize(int64_t n, int C, int64_t k, int mparts,
                                                              const double* __restrict__ mpart,
                                                              const AT* __restrict__ A, int64_t a_bstride,
                                                              const double* __restrict__ G, loca_mb* __restrict__ mb,
                                                              int32_t* __restrict__ dev_info) {
-  constexpr int NE = HC * HC, NS = 256 / NE;
-  __shared__ float sA[HC * KB];
-  __shared__ double sAG[HC * KB];
+  constexpr int NE = kHC * kHC, NS = 256 / NE;
+  __shared__ float sA[kHC * KB];
+  __shared__ double sAG[kHC * KB];
   __shared__ double sM[256];
   __shared__ double sred[4];
   const int64_t b = blockIdx.x;
   const int tid = threadIdx.x;
   const AT* Ab = A + b * a_bstride;
   const double* Gb = G + b * KB * KB;
-  for (int e = tid; e < HC * KB; e += 256) {
+  for (int e = tid; e < kHC * KB; e += 256) {
     const int c = e / KB, j = e % KB;
     sA[e] = c < C && j < k ? load_as_f32(Ab + c * k + j) : 0.f;
   }
@@ -451,7 +456,7 @@ __global__ __launch_bounds__(256) void k_error_rows_finalize(int64_t n, int C, i
 #pragma unroll
     for (int ii = 0; ii < IQ; ++ii) g[ii] = j < KB ? Gb[(iq * IQ + ii) * KB + j] : 0.0;
 #pragma unroll
-    for (int c = 0; c < HC; ++c) {
+    for (int c = 0; c < kHC; ++c) {
       double v = 0.0;
 #pragma unroll
       for (int ii = 0; ii < IQ; ++ii) v = fma((double)sA[c * KB + iq * IQ + ii], g[ii], v);
@@ -463,7 +468,7 @@ __global__ __launch_bounds__(256) void k_error_rows_finalize(int64_t n, int C, i
   __syncthreads();
   double q = 0.0;
   if (tid < NE) {
-    const int c1 = tid / HC, c2 = tid % HC;
+    const int c1 = tid / kHC, c2 = tid % kHC;
     double h = 0.0, v = sM[tid];
 #pragma unroll
     for (int u = 1; u < NS; ++u) v += sM[tid + NE * u];
@@ -829,18 +834,17 @@ static bool use_product(const ErrorArgs& a) {
 // for k <= 64, else k.
 static int64_t g_ld_max(int64_t k) { return k <= kSmallMaxK ? small_kb(k) : k; }
 
-constexpr int64_t kRowsMaxC = 16;
 static int rows_mparts(int64_t n) { return (int)std::min<int64_t>((n + kRowTok - 1) / kRowTok, kMaxMParts); }
 
 static size_t error_ws(int64_t nb, int64_t n, int64_t C, int64_t k, bool lean) {
   const int64_t lg = g_ld_max(k);
   size_t s = align256(sizeof(double) * nb * lg * lg);  // G
   const int64_t parts = use_small(C, k) ? (n + kSmallThreads - 1) / kSmallThreads : (n + kLargeTok - 1) / kLargeTok;
-  // partials of G, then of ||Q||^2; the partials of M (label sets of at most 16 classes) share
+  // partials of G, then of ||Q||^2; the partials of M (label sets of at most 8 classes) share
   // the place of both, G being complete by then
   size_t p = credit_gram_part_ws(nb, k) + align256(sizeof(double) * nb * parts);
-  if (use_small(C, k) && C <= kRowsMaxC) {
-    const size_t mp = align256(sizeof(double) * rows_mparts(n) * (C <= 8 ? 64 : 256));
+  if (use_small(C, k) && C <= kHC) {
+    const size_t mp = align256(sizeof(double) * rows_mparts(n) * kHC * kHC);
     p = p > mp ? p : mp;
   }
   s += p;
@@ -867,31 +871,27 @@ static hipError_t dispatch_error(const ErrorArgs& a, double* G, double* mpart, d
   const LT* z = (const LT*)a.logits;
   const AT* A = (const AT*)a.credit_a;
   if (use_small(a.C, a.k)) {
-    if (a.C <= kRowsMaxC) {
+    if (a.C <= kHC) {
       // blocks per workgroup: about four workgroups a compute unit, so that a tile's error rows
       // are formed few times
       const int ntile = (int)((a.n + kRowTok - 1) / kRowTok), mparts = rows_mparts(a.n);
       const int bper = (int)((a.nb * ntile + 1023) / 1024);
       const dim3 g((unsigned)ntile, (unsigned)(1 + (a.nb + bper - 1) / bper));
       const bool v4 = a.k % 4 == 0 && (a.nb == 1 || a.y_bstride % 4 == 0) && ((uintptr_t)a.y_out & 15) == 0;
-#define LOCA_ROWS2(KB, HC, V4)                                                                                    \
-  k_error_rows<LT, AT, KB, HC, V4><<<g, kRowTok, 0, a.stream>>>(                                                  \
+#define LOCA_ROWS2(KB, V4)                                                                                        \
+  k_error_rows<LT, AT, KB, V4><<<g, kRowTok, 0, a.stream>>>(                                                      \
       a.n, (int)a.C, a.k, z, a.ld_logits, a.labels, a.w, a.a_w, A, a.a_bstride, a.nb, bper, ntile, mparts, a.y_out, \
       a.y_bstride, a.e_out, mpart, a.dev_info)
-#define LOCA_ROWS(KB, HC)                                                                                         \
+#define LOCA_ROWS(KB)                                                                                             \
   {                                                                                                               \
-    if (v4) LOCA_ROWS2(KB, HC, true);                                                                             \
-    else LOCA_ROWS2(KB, HC, false);                                                                               \
-    k_error_rows_finalize<AT, KB, HC><<<(unsigned)a.nb, 256, 0, a.stream>>>(a.n, (int)a.C, a.k, mparts, mpart, A,  \
-                                                                            a.a_bstride, G, a.mb_out, a.dev_info); \
+    if (v4) LOCA_ROWS2(KB, true);                                                                                 \
+    else LOCA_ROWS2(KB, false);                                                                                   \
+    k_error_rows_finalize<AT, KB><<<(unsigned)a.nb, 256, 0, a.stream>>>(a.n, (int)a.C, a.k, mparts, mpart, A,      \
+                                                                        a.a_bstride, G, a.mb_out, a.dev_info);     \
   }
-#define LOCA_ROWS_KB(KB)        \
-  if (a.C <= 8) LOCA_ROWS(KB, 8) \
-  else LOCA_ROWS(KB, 16)
-      if (a.k <= 16) { LOCA_ROWS_KB(16) }
-      else if (a.k <= 32) { LOCA_ROWS_KB(32) }
-      else { LOCA_ROWS_KB(64) }
-#undef LOCA_ROWS_KB
+      if (a.k <= 16) LOCA_ROWS(16)
+      else if (a.k <= 32) LOCA_ROWS(32)
+      else LOCA_ROWS(64)
 #undef LOCA_ROWS
 #undef LOCA_ROWS2
       return hipGetLastError();

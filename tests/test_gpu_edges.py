@@ -453,7 +453,7 @@ def test_paper_order_head_edges(n, V, d, k, bf):
         assert abs(float(mb[b, 0]) - q2) < 1e-12 * q2
 
 
-# label sets of 1 to 17 classes (both sides of the 8- and 16-class forms and of the register head),
+# label sets of 1 to 17 classes (both sides of the 8-class form),
 # tokens around the 256-token tiles, ranks on both sides of the column blocks and of the 16-byte
 # stores, weights, and more tiles than the 512 partials of M.  float32 softmax (a few ulp of terms
 # below 1) times float32 factors: 1e-6 of Y; ||Q||^2 from the same rows in float64: 2e-6
