@@ -628,27 +628,31 @@ __global__ void k_error_finalize(int64_t n, int64_t nparts, const double* __rest
 
 // Paper-order credit coordinates (Section S11): Y_b = e V_k,b (n x k) from the top errors
 // e (n x d) and sum_q2 partials as in the error kernels, on the fp64 matrix cores (products of
-// floats exact, sums in fp64).  64 tokens per workgroup, wave (wi, wj) of 2 x 2 owning 32 of them and
-// the columns 32 wj .. of every 64 (NC 64-column tiles); d in chunks of 64 through LDS, the next chunk in
-// registers meanwhile.  ||q_t||^2 = Y_t G Y_t^T of the stored (float) coordinates is a second
-// product, T = Y G, then the sum of T Y entry by entry.  24 blocks of n = 4096, d = 896, k = 64 took
-// 1132 us with one fp64 FMA per LDS read and k^2 of them per token in one wave; 320 us now.
-template <int NC>
+// floats exact, sums in fp64).  64 tokens per workgroup and KW >= k columns: for KW = 64 and 128 wave
+// (wi, wj) of 2 x 2 owns 32 tokens and the columns 32 wj .. of every 64, for KW = 16 each of the four
+// waves 16 tokens; d in chunks of 64 through LDS, the next chunk in registers meanwhile.
+// ||q_t||^2 = Y_t G Y_t^T of the stored (float) coordinates is a second product, T = Y G, then the
+// sum of T Y entry by entry.  24 blocks of n = 4096, d = 896, k = 64, calls back to back: 1025 us with
+// one fp64 FMA per LDS read and k^2 of them per token in one wave, 312 us now.  Up to 16 columns the
+// 64-wide tile stages 48 columns of zeros and leaves two waves idle: 48 blocks of n = 8192, d = 256, k
+// = 4 196 us with the FMAs, 230 in the 64-wide tile, 104 in the 16-wide one.
+template <int KW>
 __global__ __launch_bounds__(256) void k_credit_project(int64_t n, int64_t d, int64_t k, const float* __restrict__ e,
                                                         int64_t ld_e, const float* __restrict__ Vk, int64_t v_bstride,
                                                         const double* __restrict__ G, const float* __restrict__ aw,
                                                         float* __restrict__ y_out, int64_t y_bstride,
                                                         double* __restrict__ partial) {
-  constexpr int KW = 64 * NC, LDE = 66, LDV = KW + 16;  // rows apart by 2 and 16 banks: reads of either kind spread
+  constexpr int WJ = KW == 16 ? 1 : 2, RB = KW == 16 ? 1 : 2, CB = KW / 16 / WJ;  // waves along the columns; blocks per wave
+  constexpr int LDE = 66, LDV = KW == 16 ? 16 : KW + 16;  // rows apart by 2 and 16 banks: reads of either kind spread
   __shared__ float sE[64 * LDE];
   __shared__ float sV[64 * LDV];
   __shared__ float sY[64 * (KW + 2)];
   __shared__ double sred[4];
   const int64_t b = blockIdx.y;
   const int64_t t0 = (int64_t)blockIdx.x * 64;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, wi = wid >> 1, wj = wid & 1, li = lane & 15, lk = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, wi = wid / WJ, wj = wid % WJ, li = lane & 15, lk = lane >> 4;
   const float* V = Vk + b * v_bstride;
-  float re[16], rv[16 * NC];
+  float re[16], rv[KW / 4];
   auto load = [&](int64_t c0) {
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
@@ -656,16 +660,16 @@ __global__ __launch_bounds__(256) void k_credit_project(int64_t n, int64_t d, in
       re[u] = ld_or_zero(e, (t0 + rr) * ld_e + c0 + cc, t0 + rr < n && c0 + cc < d);
     }
 #pragma unroll
-    for (int u = 0; u < 16 * NC; ++u) {
+    for (int u = 0; u < KW / 4; ++u) {
       const int x = tid + 256 * u, cc = x / KW, j = x % KW;
       rv[u] = ld_or_zero(V, (c0 + cc) * k + j, c0 + cc < d && j < k);
     }
   };
-  f64x4_t acc[2][2 * NC];
+  f64x4_t acc[RB][CB];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < RB; ++a)
 #pragma unroll
-    for (int q = 0; q < 2 * NC; ++q) acc[a][q] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+    for (int q = 0; q < CB; ++q) acc[a][q] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
   auto col = [&](int q) { return 64 * (q >> 1) + 32 * wj + 16 * (q & 1); };  // first column of block q
   load(0);
   for (int64_t c0 = 0; c0 < d; c0 += 64) {
@@ -676,7 +680,7 @@ __global__ __launch_bounds__(256) void k_credit_project(int64_t n, int64_t d, in
       sE[(x / 64) * LDE + x % 64] = re[u];
     }
 #pragma unroll
-    for (int u = 0; u < 16 * NC; ++u) {
+    for (int u = 0; u < KW / 4; ++u) {
       const int x = tid + 256 * u;
       sV[(x / KW) * LDV + x % KW] = rv[u];
     }
@@ -684,26 +688,26 @@ __global__ __launch_bounds__(256) void k_credit_project(int64_t n, int64_t d, in
     if (c0 + 64 < d) load(c0 + 64);
 #pragma unroll 4
     for (int s = 0; s < 64; s += 4) {
-      double fa[2], fb[2 * NC];
+      double fa[RB], fb[CB];
 #pragma unroll
-      for (int a = 0; a < 2; ++a) fa[a] = (double)sE[(32 * wi + 16 * a + li) * LDE + s + lk];
+      for (int a = 0; a < RB; ++a) fa[a] = (double)sE[(16 * (RB * wi + a) + li) * LDE + s + lk];
 #pragma unroll
-      for (int q = 0; q < 2 * NC; ++q) fb[q] = (double)sV[(s + lk) * LDV + col(q) + li];
+      for (int q = 0; q < CB; ++q) fb[q] = (double)sV[(s + lk) * LDV + col(q) + li];
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+      for (int a = 0; a < RB; ++a)
 #pragma unroll
-        for (int q = 0; q < 2 * NC; ++q)
+        for (int q = 0; q < CB; ++q)
           if (col(q) < k) acc[a][q] = mfma_f64(fa[a], fb[q], acc[a][q]);
     }
   }
   constexpr int LDY = KW + 2;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < RB; ++a)
 #pragma unroll
-    for (int q = 0; q < 2 * NC; ++q)
+    for (int q = 0; q < CB; ++q)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int row = 32 * wi + 16 * a + lk + 4 * r, j = col(q) + li;
+        const int row = 16 * (RB * wi + a) + lk + 4 * r, j = col(q) + li;
         const float yv = j < k ? (float)acc[a][q][r] : 0.f;
         sY[row * LDY + j] = yv;
         if (t0 + row < n && j < k) y_out[b * y_bstride + (t0 + row) * k + j] = yv;
@@ -712,34 +716,34 @@ __global__ __launch_bounds__(256) void k_credit_project(int64_t n, int64_t d, in
   // T = Y G, then sum_t a_t T_t Y_t^T over this workgroup's tokens
   const double* Gb = G + b * k * k;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < RB; ++a)
 #pragma unroll
-    for (int q = 0; q < 2 * NC; ++q) acc[a][q] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+    for (int q = 0; q < CB; ++q) acc[a][q] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
   for (int s = 0; s < k; s += 4) {
     const int x = s + lk;
-    double fa[2], fb[2 * NC];
+    double fa[RB], fb[CB];
 #pragma unroll
-    for (int a = 0; a < 2; ++a) fa[a] = (double)sY[(32 * wi + 16 * a + li) * LDY + x];  // columns past k are zero
+    for (int a = 0; a < RB; ++a) fa[a] = (double)sY[(16 * (RB * wi + a) + li) * LDY + x];  // columns past k are zero
 #pragma unroll
-    for (int q = 0; q < 2 * NC; ++q) {
+    for (int q = 0; q < CB; ++q) {
       const int j = col(q) + li;
       fb[q] = ld_or_zero(Gb, (int64_t)x * k + j, x < k && j < k);
     }
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < RB; ++a)
 #pragma unroll
-      for (int q = 0; q < 2 * NC; ++q)
+      for (int q = 0; q < CB; ++q)
         if (col(q) < k) acc[a][q] = mfma_f64(fa[a], fb[q], acc[a][q]);
   }
   double qv = 0.0;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < RB; ++a)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int row = 32 * wi + 16 * a + lk + 4 * r;
+      const int row = 16 * (RB * wi + a) + lk + 4 * r;
       double v = 0.0;
 #pragma unroll
-      for (int q = 0; q < 2 * NC; ++q) v += acc[a][q][r] * (double)sY[row * LDY + col(q) + li];
+      for (int q = 0; q < CB; ++q) v += acc[a][q][r] * (double)sY[row * LDY + col(q) + li];
       if (t0 + row < n) qv += aw ? v * (double)aw[t0 + row] : v;
     }
   const double tot = block_sum(qv, sred);
@@ -1038,11 +1042,12 @@ hipError_t launch_credit_from_top_error(const CreditArgs& a) {
   double* partial = (double*)((char*)gpart + credit_gram_part_ws(a.nb, a.k));
   launch_credit_gram(a.stream, a.nb, a.k, a.d, a.credit_b, a.b_bstride, gpart, G, a.k);
   dim3 g((unsigned)((a.n + 63) / 64), (unsigned)a.nb);
-#define LOCA_PROJ(NC)                                                                                          \
-  k_credit_project<NC><<<g, 256, 0, a.stream>>>(a.n, a.d, a.k, a.e, a.ld_e, a.vk, a.v_bstride, G, a.a_w, a.y_out, \
+#define LOCA_PROJ(KW)                                                                                          \
+  k_credit_project<KW><<<g, 256, 0, a.stream>>>(a.n, a.d, a.k, a.e, a.ld_e, a.vk, a.v_bstride, G, a.a_w, a.y_out, \
                                                  a.y_bstride, partial)
-  if (a.k <= 64) LOCA_PROJ(1);
-  else LOCA_PROJ(2);
+  if (a.k <= 16) LOCA_PROJ(16);
+  else if (a.k <= 64) LOCA_PROJ(64);
+  else LOCA_PROJ(128);
 #undef LOCA_PROJ
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
