@@ -138,12 +138,12 @@ struct XStage {
 
 // ------------------------------------------------------------------ S += X^T X (bf16)
 
-// Register-staged form, for weighted blocks of X or of split targets past 2 GB only (see
-// launch_accumulate_stats):
+// Register-staged form, for calls of few tokens on few tiles and for weighted blocks of X or of
+// split targets past 2 GB (see launch_accumulate_stats):
 // BM x BM tiles of S on or above the diagonal; WGM x WGN waves, each owning a
-// (BM/WGM) x (BM/WGN) block of 32 x 32 MFMA tiles.  Statistic weights from `wpad` (zero
-// past n, readable up to the next multiple of kBK).
-template <int BM, int WGM, int WGN>
+// (BM/WGM) x (BM/WGN) block of 32 x 32 MFMA tiles.
+// WT: statistic weights from `wpad` (zero past n, readable up to the next multiple of kBK).
+template <int BM, int WGM, int WGN, bool WT>
 __global__ __launch_bounds__(64 * WGM * WGN) void k_gram_bf16(int64_t n, int64_t d,
                                                              const uint16_t* __restrict__ Xall, int64_t ldx,
                                                              int64_t x_bstride, float* __restrict__ Sall,
@@ -201,18 +201,21 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gram_bf16(int64_t n, int64_t
         bf16x8_t fb[NBN], fl[NBN];
 #pragma unroll
         for (int q = 0; q < NBN; ++q) fb[q] = frag32_tr(tB, LDT, wj * WN + 32 * q, ks, lane);
-        const float* wl = wpad + (int64_t)kt * kBK + ks + 8 * (lane >> 5);
-        const float4 w0 = *(const float4*)wl, w1 = *(const float4*)(wl + 4);
-        const float wv[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+        if (WT) {
+          const float* wl = wpad + (int64_t)kt * kBK + ks + 8 * (lane >> 5);
+          const float4 w0 = *(const float4*)wl, w1 = *(const float4*)(wl + 4);
+          const float wv[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
 #pragma unroll
-        for (int q = 0; q < NBN; ++q) weight_split(fb[q], wv, fb[q], fl[q]);
+          for (int q = 0; q < NBN; ++q) weight_split(fb[q], wv, fb[q], fl[q]);
+        }
 #pragma unroll
         for (int m = 0; m < NBM; ++m) {
           const bf16x8_t fa = frag32_tr(tA, LDT, wi * WM + 32 * m, ks, lane);
 #pragma unroll
           for (int q = 0; q < NBN; ++q) acc[m][q] = mfma32(fa, fb[q], acc[m][q]);
+          if (WT)
 #pragma unroll
-          for (int q = 0; q < NBN; ++q) acc[m][q] = mfma32(fa, fl[q], acc[m][q]);
+            for (int q = 0; q < NBN; ++q) acc[m][q] = mfma32(fa, fl[q], acc[m][q]);
         }
       }
     }
@@ -268,9 +271,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gram_bf16(int64_t n, int64_t
 // the row lies within one aligned 16-byte granule also in the last row).  Their values, NaN
 // included, reach only entries of S and Kraw in rows or columns past d, which are not written.
 //
-// Every width takes this kernel: the register-staged 128 x 128 tiles that widths below 1024
+// Every width takes this kernel.  The register-staged 128 x 128 tiles that widths below 1024
 // once took, and the 256 x 256 ones of d % 8 != 0, with the cross statistic in a launch of
-// its own, lost at every size measured (us per call, before -> now, d x blocks x tokens):
+// its own, lose at every size but the smallest (us per call, before -> now, d x blocks x tokens):
 // 128 x 24 x 2048 120 -> 57, 256 x 200 x 2048 340 -> 92, 512 x 4 x 2048 164 -> 58,
 // 896 x 1 x 512 43 -> 31, 896 x 24 x 8192 1218 -> 223, 1100 x 12 x 2999 519 -> 90; weighted
 // 248 x 32 x 3705 874 -> 216 (the staging waited for every stage's loads; here three are in
@@ -976,8 +979,6 @@ hipError_t launch_accumulate_stats(const StatsArgs& a) {
     const int64_t npad = weights_pad(a.n);
     k_pad_weights<<<(unsigned)((npad + 255) / 256), 256, 0, a.stream>>>(a.n, npad, a.a_w, wpad);
   }
-  constexpr int BM = 256;
-  const int T = (int)((a.d + BM - 1) / BM);
   const int64_t w2 = 2 * a.k, w2p = (w2 + 7) / 8 * 8;
   // buffer-path copies when a block's X and its split targets each fit 31-bit byte offsets (at k =
   // 128 the targets are the wider ones up to ldx = 256)
@@ -985,7 +986,19 @@ hipError_t launch_accumulate_stats(const StatsArgs& a) {
   // direct-to-LDS kernel; with weights only on the buffer path (the global-address
   // variant runs out of scalar registers with the weights, so blocks of X or of split
   // targets over 2 GB take the register-staged kernel when weighted)
-  const bool dl = buf || !wt;
+  // One or two stages of tokens on few tiles: what counts is the write of S, which four times as many
+  // 128 x 128 tiles spread over four times the compute units, register-staged, as long as the cross
+  // statistic's own launch is short (us per call that adds to S, 256 x 256 -> 128 x 128: d = 896,
+  // 9 blocks, k = 8, 16 tokens 23.9 -> 20.4, 64 tokens 24.3 -> 20.7; d = 384, one block, k = 8, 64
+  // tokens 21.5 -> 19.8; 9 blocks of d = 896, 16 weighted tokens 29.1 -> 22.8; past the line in k,
+  // 100 blocks of d = 128, k = 40, 64 tokens 22.9 -> 27.1).  Where d % 8 != 0 the staged loads are
+  // element by element, and the line is lower (d = 1023, 9 blocks, k = 8, 64 tokens 24.3 -> 31.6).
+  const int64_t t256 = (a.d + 255) / 256;
+  const bool few = a.d < 1024 && a.n <= 64 && w2 <= 64 && a.n * w2 <= 2048 &&
+                   a.nb * (t256 * (t256 + 1) / 2) <= (a.d % 8 == 0 ? 96 : 64);
+  const bool dl = !few && (buf || !wt);
+  const int BM = few ? 128 : 256;
+  const int T = (int)((a.d + BM - 1) / BM);
   const bool fused = w2p <= 64;
   // wider split targets: cross tiles in the same launch (one per row panel of each block)
   const bool ctiles = !fused;
@@ -1017,8 +1030,13 @@ hipError_t launch_accumulate_stats(const StatsArgs& a) {
     }
   } else {
     const dim3 grid((unsigned)(T * (T + 1) / 2), (unsigned)a.nb);
-    k_gram_bf16<BM, 2, 4><<<grid, 512, 0, a.stream>>>(a.n, a.d, X, a.ldx, a.x_bstride, (float*)a.S, a.s_bstride,
-                                                      diag_part, wpad, a.overwrite ? 0 : 1);
+#define LOCA_STAGED(BM, WGN, WT)                                                                                      \
+  k_gram_bf16<BM, 2, WGN, WT><<<grid, 128 * WGN, 0, a.stream>>>(a.n, a.d, X, a.ldx, a.x_bstride, (float*)a.S, a.s_bstride, \
+                                                                diag_part, wpad, a.overwrite ? 0 : 1)
+    if (!few) LOCA_STAGED(256, 4, true);
+    else if (wt) LOCA_STAGED(128, 2, true);
+    else LOCA_STAGED(128, 2, false);
+#undef LOCA_STAGED
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

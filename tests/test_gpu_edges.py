@@ -69,6 +69,41 @@ def test_statistics_at_every_width(d, n, k, w):
         assert rel(K[b].cpu().numpy(), -eta * X[b].T @ ((aw * Y)[b] if w else Y[b])) < 1e-5
 
 
+# few tokens on few tiles take 128-wide register-staged tiles: both sides of the rule's lines in
+# tokens, target columns, width and tiles, weighted and not, S and K overwritten and then added to.
+# Float32 sums of exact products and two bf16 parts of Y as above
+@pytest.mark.parametrize("nb,d,n,k", [(1, 1, 1, 1), (2, 129, 64, 16), (2, 129, 65, 16), (2, 129, 64, 17), (1, 1023, 33, 8),
+                                      (6, 1023, 31, 8), (7, 1001, 31, 8), (9, 1000, 31, 8), (10, 1000, 31, 8),
+                                      (1, 1024, 20, 4), (64, 41, 64, 3), (65, 41, 64, 3), (96, 40, 64, 3), (97, 40, 64, 3)])
+def test_statistics_of_few_tokens(nb, d, n, k):
+    import torch
+    from paper_2608_03020_amd import loca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + n)
+    buf = torch.full((2, nb, n, -(-d // 8) * 8), float("nan"), dtype=torch.bfloat16, device="cuda")
+    buf[..., :d] = torch.randn((2, nb, n, d), generator=g, device="cuda")
+    y, a = torch.randn((2, nb, n, k), generator=g, device="cuda"), torch.rand(n, generator=g, device="cuda")
+    kw = dict(dtype=torch.float32, device="cuda")
+    S, K = torch.full((nb, d, d), float("nan"), **kw), torch.full((nb, d, k), float("nan"), **kw)
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_ACCUMULATE_STATS, nb, n, d, k))
+    ws.fill_(255)
+    info = torch.zeros(nb, dtype=torch.int32, device="cuda")
+    log("statistics of few tokens", nb, d, n, k)
+    for w in (None, a):
+        refS, refK = 0, 0
+        for m in range(2):
+            mb = loca.new_mb(nb)
+            mb[:, 0] = 7.0
+            loca.loca_accumulate_stats(buf[m][..., :d], y[m], 0.5, mb, S, K, ws, a_w=w, dev_info=info, overwrite=m == 0)
+            X, Y = buf[m][..., :d].double(), y[m].double()
+            aX = X if w is None else X * w.double()[None, :, None]
+            refS = refS + aX.transpose(1, 2).contiguous() @ X
+            eta = 0.5 * ((aX * X).sum((1, 2)) / 7.0).sqrt()[:, None, None]
+            refK = refK - eta * (aX.transpose(1, 2).contiguous() @ Y)
+        assert rel(torch.triu(S).cpu().numpy(), torch.triu(refS).cpu().numpy()) < 1e-5
+        assert rel(K.cpu().numpy(), refK.cpu().numpy()) < 1e-5 and info.eq(0).all()
+
+
 # split targets past 2 GB beside an X below it: their byte offsets leave 31 bits first when 2k >
 # ldx, and 2^32 bytes at n = 2^23, k = 128.  The n / 16 additions into a float32 sum round by at most
 # 2^-24 of the running sum each, and the entries that make up the norm grow steadily to their
