@@ -412,8 +412,12 @@ LOCA_DEV void tridiag64(const double* A, int n, int K, double* W, double* dT, do
 // reciprocals of its diagonal into dinv.  False for every thread when a pivot is not above 1e-10
 // of the largest diagonal entry (Ld then holds no factor).  K = 64: 29 us (44 with the matrix in
 // LDS, sixteen waves updating it there).
+// The waves without columns run meanwhile(thread among them) before the first barrier, beside the
+// loads of Gb.
 constexpr int kLd = 65;  // odd: a column's entries lie in different banks
-LOCA_DEV bool chol64(const double* part, int nsplit, int K, double* raw, double* Ld, double* dinv, double* red) {
+template <typename F>
+LOCA_DEV bool chol64(const double* part, int nsplit, int K, double* raw, double* Ld, double* dinv, double* red,
+                     const F& meanwhile) {
   __shared__ double s_col[2][128];
   __shared__ int s_fail;
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -436,6 +440,8 @@ LOCA_DEV bool chol64(const double* part, int nsplit, int K, double* raw, double*
     if (lane == 0) red[wid] = mx;
     if (wid == 0) s_col[0][lane] = a[0];
     if (wid == 1) s_col[0][64 + lane] = s_col[1][64 + lane] = 0.0;
+  } else {
+    meanwhile(tid - 64 * kRW);
   }
   __syncthreads();
   if (wid >= kRW) {
@@ -526,6 +532,19 @@ LOCA_DEV bool eig_top(const double* A, int n, int K, int r, double* W, OutT* Vou
   int* cut = &s_cut;
   if (tid == 0) red[kRedEig] = 0.0;
   __syncthreads();
+  if constexpr (!PACKED)
+    if (K == 1) {  // its one entry is the eigenvalue (the steps below: 31 us per call, now 24)
+      const double a = A[0];
+      if (!(fabs(a) < 1.7e308)) return false;  // as below
+      const int live = r >= 1 && a > 0.0 ? 1 : 0;
+      if (tid < n * n) Vout[tid] = (OutT)(tid == 0 ? live : 0);
+      if (tid == 0) {
+        eig[0] = a;
+        red[kRedLive] = (double)live;
+      }
+      __syncthreads();
+      return true;
+    }
   // 1. reduction to tridiagonal form
   if constexpr (!PACKED) {
     tridiag64(A, n, K, W, dT, eT, tauH);
@@ -1259,16 +1278,28 @@ __global__ __launch_bounds__(kTC) void k_trunc_core(int64_t kp, int64_t r_a, con
   const int n = K + (K & 1);  // even size for the tournament ordering
   const double* GmP = Gpart + (mi * 2) * nsplit * kp * kp;
   const double* GbP = Gpart + (mi * 2 + 1) * nsplit * kp * kp;
-  // 1. Gm into sG (n x n, zero padded), summed over the row ranges in order
-  for (int e = tid; e < n * n; e += kTC) {
-    const int i = e / n, j = e % n;
-    double gm = 0.0;
-    if (i < K && j < K)
-      for (int z = 0; z < nsplit; ++z) gm += GmP[z * kp * kp + i * kp + j];
-    sG[e] = gm;
-  }
+  // 1. Gm into sG (n x n, zero padded), summed over the row ranges in order, by the waves that hold
+  // no column of Gb, beside its loads (one after the other, d = 3813: 1 us more up to kp = 16, 10 at kp = 64)
+  auto sum_gm = [&](int t) {
+    constexpr int kGT = kTC - 64 * kRW, kGE = KB2 / kGT;  // threads, entries per thread at most
+    int at[kGE];
+    double gm[kGE];
+#pragma unroll
+    for (int u = 0; u < kGE; ++u) {
+      const int e = t + kGT * u, i = e / n, j = e % n;
+      at[u] = i < K && j < K ? i * K + j : -1;
+      gm[u] = 0.0;
+    }
+    for (int z = 0; z < nsplit; ++z)
+#pragma unroll
+      for (int u = 0; u < kGE; ++u)
+        if (at[u] >= 0) gm[u] += GmP[z * kp * kp + at[u]];
+#pragma unroll
+    for (int u = 0; u < kGE; ++u)
+      if (t + kGT * u < n * n) sG[t + kGT * u] = gm[u];
+  };
   // 2. Gb = L L^T (L in the lower triangle of sVb), or a failed pivot
-  const bool chol = chol64(GbP, nsplit, K, sV, sVb, sHi, red);
+  const bool chol = chol64(GbP, nsplit, K, sV, sVb, sHi, red, sum_gm);
   if (chol) {
     // 3. T = Gm L (into sV), P^T P = L^T T (upper triangle, packed; zero padding): a wave per
     // 16 x 16 block on the fp64 matrix cores (one thread per entry took two LDS reads per

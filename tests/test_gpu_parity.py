@@ -335,7 +335,7 @@ def test_truncation_matches_explicit_svd(d, kp, r):
     np.testing.assert_allclose(A.T @ b[0].cpu().numpy().T, W[0].cpu().numpy(), atol=1e-4 * np.abs(Wr_o).max())
 
 
-@pytest.mark.parametrize("kp,r,rank", [(64, 32, 5), (96, 40, 5), (64, 32, 0), (32, 16, 15)])
+@pytest.mark.parametrize("kp,r,rank", [(64, 32, 5), (96, 40, 5), (64, 32, 0), (32, 16, 15), (2, 2, 1), (1, 1, 0)])
 def test_truncation_low_rank_product(kp, r, rank):
     """W = M B~ of rank below r_a (a label set of six classes makes Y, hence K and M, of rank
     5; M = 0 gives W = 0): the directions with weight from the tridiagonal path, the others
