@@ -116,7 +116,9 @@ typedef void* loca_stream_t; /* hipStream_t */
  *   mb[b].sum_q2 = ||Y B~_b||_F^2 = sum_t Y_t (B~ B~^T) Y_t^T, the denominator of
  *   Eq. 10 (the displacement itself is never materialised; see
  *   loca_dense_targets).
- * logits : n x C (ld_logits >= C), F32 or BF16, shared by all blocks.
+ * logits : n x C (ld_logits >= C), F32 or BF16, shared by all blocks.  A large vocabulary
+ *       whose rows are multiples of 16 bytes is read in such units: the padding that shares
+ *       one with a row's last logits may be read, in the last row too; its values are not used.
  * labels : n int32 in [0, C).       w : n float loss weights, or NULL (= 1).
  * a_w : n float statistic weights a_t >= 0 (the weighted statistics of Section S7),
  *       or NULL (= 1); the same array is passed to loca_accumulate_stats.  Then
@@ -192,7 +194,11 @@ size_t loca_error_targets_noalloc_max_bytes(void);
  * call of the step has written them.  Each mini-batch uses its own eta_bar (Section S8).
  * x : per block n x d, ldx >= d, x_bstride; BF16 (then acc = F32) or F32
  *     (then acc = F64).  BF16 requires ldx % 8 == 0 and a 16-byte aligned
- *     base; F32 requires ldx % 4 == 0 and 16-byte alignment.
+ *     base; F32 requires ldx % 4 == 0 and 16-byte alignment.  Rows are read in
+ *     aligned units of 16 bytes: with d % 8 != 0 (F32: d % 4 != 0) the elements
+ *     d .. d + 7 (d + 3) that share a unit with the row's last ones may be read, in
+ *     the last row too, so they must be readable; their values, NaN included, are
+ *     not used.
  * y : per block n x k float (from loca_error_targets), y_bstride.
  * a_w : n float weights a_t >= 0 shared by the blocks, or NULL; it must be the
  *       array given to loca_error_targets for this micro-batch.  In bf16 mode each
@@ -420,7 +426,10 @@ loca_status loca_feedback_fit_large(loca_stream_t stream, int64_t nb, int64_t d,
  * matrix-core flops once (the softmax weights enter as two bf16 parts) instead of
  * 2 n V k per block, so it pays when L k > d.
  * logits : n x V (ld_logits >= V), F32 or BF16, 16-byte aligned, ld_logits a multiple
- *          of 8 (BF16) or 4 (F32).   labels : n int32 in [0, V).   w : n floats or NULL.
+ *          of 8 (BF16) or 4 (F32).  Rows are read in aligned units of 16 bytes: the
+ *          padding that shares a unit with a row's last logits may be read, in the last
+ *          row too; its values, NaN included, are not used.
+ * labels : n int32 in [0, V).   w : n floats or NULL.
  * wu : V x d, BF16 only (LOCA_E_UNSUPPORTED otherwise), 16-byte aligned.
  * e_out : n x d float, row stride ld_e >= d.
  * dev_info : one int32; 0, or 1 + the smallest row whose label is out of range.

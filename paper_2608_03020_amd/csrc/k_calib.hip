@@ -590,8 +590,8 @@ static hipError_t fit_tail(const CalibArgs& a, const float* R, char* p) {
 // 28 blocks of d = 3584 from 64 probes, k = 32, five classes: 1413 us while the tall products
 // were LDS-bound (4 x 107 us), the Cholesky of Gamma took three barriers per column in one
 // workgroup (133 us), R one thread per column (14 workgroups, 120 us) and the head fold one
-// workgroup per block (163 us); now 655 us, of which the tall products take 4 x 24, the fold
-// 29, Gamma's factor 15, R 21 and the truncation core 355.
+// workgroup per block (163 us); now 564 us, of which the tall products take 5 x 23, the fold
+// 29, Gamma's factor 15, R 21 and the truncation core about 230.
 hipError_t launch_feedback_fit(const CalibArgs& a) {
   const int64_t d = a.d, np_ = a.np_, nb = a.nb;
   const int ns = calib_splits(d);

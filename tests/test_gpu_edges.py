@@ -33,8 +33,9 @@ def test_dense_truncation_product_edges(d, kp, r):
     assert np.max(np.abs(W.double().cpu().numpy() - ref) - 2.0 ** -23 * np.abs(ref)) <= 1e-30
 
 
-# every width takes the direct-to-LDS kernel: below one tile, its edges, ragged last chunks with
-# NaN in the rows' padding (read, never used), fused (2k <= 64) and cross-tile targets, weights.
+# the direct-to-LDS kernel at every width, but for the calls of few tokens (64 by 260 alone among
+# these by their k): below one tile, its edges, ragged last chunks with NaN in the rows' padding
+# (read, never used), fused (2k <= 64) and cross-tile targets, weights.
 # S: float32 sums of exact products, error at most n 2^-24 sum|x_i x_j| and far below 1e-5 of S
 # in practice; K: two bf16 parts of Y (2^-16) on top
 @pytest.mark.parametrize("d,n,k,w", [(1, 40, 4, 0), (7, 33, 3, 1), (64, 500, 8, 0), (255, 100, 40, 0), (256, 257, 32, 1),
