@@ -29,15 +29,16 @@ HBM_PEAK_GBS = 8000.0
 # HBM traffic of the statistics kernel (k_gram_bf16_dl) per launch, from two rocprofv3
 # --pmc passes (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch) of
 #   bench.py --config <cfg> --steps 1 --warmup 0 --no-cpu-baseline,
-# each scaled by the factor the same counter gives for a plain device copy in the same run
-# (the bf16 stack of the inputs, 2 * N * d bytes read and written per block): 1.0 for both.
+# each scaled by the factor the same counter gives for a kernel of known traffic in the same
+# run (the inputs' conversion from float32 to bf16, 4 * N * d bytes read and 2 * N * d written
+# per block): FETCH_SIZE counts half of the bytes read, WRITE_SIZE all that are written.
 # Valid only for the kernel source it was taken on (digest of k_gram.hip + loca_common.h, the
 # kernel file and the device helpers it includes).
 TRAFFIC = {
-    "c3": {"fetch_kib": 3388361.0, "write_kib": 778898.2, "fetch_scale": 1.0, "write_scale": 1.0,
-           "src_digest": "8e73809de34918f3"},
-    "c5": {"fetch_kib": 15697122.3, "write_kib": 2700420.1, "fetch_scale": 1.0, "write_scale": 1.0,
-           "src_digest": "8e73809de34918f3"},
+    "c3": {"fetch_kib": 3415552.4, "write_kib": 752646.0, "fetch_scale": 2.0, "write_scale": 1.0,
+           "src_digest": "ee998c9036c0e1c8"},
+    "c5": {"fetch_kib": 16577396.0, "write_kib": 2677520.2, "fetch_scale": 2.0, "write_scale": 1.0,
+           "src_digest": "ee998c9036c0e1c8"},
 }
 
 

@@ -62,9 +62,10 @@ LOCA_DEV int fz_swz(int r) { return (r >> 1) & 7; }
 // share a token's running maximum, exchanged once per chunk; each keeps the sum of its own
 // exponentials, and the sums meet at the end.
 //
-// Bound by the matrix cores and the stream of W_u and h from L2: a stage's copies are (256 + TR)
-// rows for 256 TR products per unit of d, so 256 tokens a tile stream a third less per product
-// than 128.  n = 4096, V = 151936, d = 2048, 64 columns: 5.35 ms with 128 tokens, slices of 32
+// Bound by the matrix cores and the stream of W_u and h from L2 together: counters at the size below
+// put the matrix cores at 52% of the cycles (1.76 GHz under this load), the L1 waiting for L2 at 34%
+// and the waves in some wait at 43%.  A stage's copies are (256 + TR) rows for 256 TR products per
+// unit of d, so 256 tokens a tile stream a third less per product than 128.  n = 4096, V = 151936, d = 2048, 64 columns: 5.35 ms with 128 tokens, slices of 32
 // (half lines, each line fetched twice), run-time stage arithmetic and every exponential taken
 // twice; 2.56 ms now (1.03 PFLOP/s).
 template <int TR>
