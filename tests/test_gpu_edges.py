@@ -538,7 +538,7 @@ def test_label_set_head_edges(n, C, k, nb, wt):
 # each entry of W is off by about 2^-23 of its products, and so are the singular values; 1e-6
 # leaves a factor of eight
 @pytest.mark.parametrize("scale", [1.0, 1e-16, 1e14])
-@pytest.mark.parametrize("kp,r", [(1, 1), (2, 1), (3, 3), (4, 4), (7, 5), (8, 8), (9, 2), (15, 15), (16, 8), (17, 17), (31, 16),
+@pytest.mark.parametrize("kp,r", [(1, 1), (2, 1), (2, 2), (3, 3), (4, 4), (7, 5), (8, 8), (9, 2), (15, 15), (16, 8), (17, 17), (31, 16),
                                   (32, 32), (33, 12), (48, 32), (63, 63), (64, 64), (65, 20), (128, 64)])
 def test_truncation_core_edges(kp, r, scale):
     import torch
@@ -561,6 +561,31 @@ def test_truncation_core_edges(kp, r, scale):
         e_w, e_s = rel(W[i], ref), rel(sig[i].double().cpu().numpy(), s[:kp])
         log(f"  W_r {e_w:.1e} sigma {e_s:.1e}")
         assert e_w < 1e-6 and e_s < 1e-6
+    assert not info.any()
+
+
+# two equal singular values: W itself at rank 2, and at rank 1 any unit direction of its column space.
+# Factors rounded to float as above
+@pytest.mark.parametrize("r", [1, 2])
+def test_truncation_of_two_equal_values(r):
+    import torch
+    from paper_2608_03020_amd import loca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(r)
+    d = 150
+    orth = lambda: torch.linalg.qr(torch.randn((d, 2), generator=g, device="cuda").double())[0].float()
+    m, b = orth().contiguous()[None], orth().T.contiguous()[None]
+    kw = dict(dtype=torch.float32, device="cuda")
+    a_o, b_o = torch.full((1, r, d), float("nan"), **kw), torch.full((1, d, r), float("nan"), **kw)
+    sig, info = torch.full((1, 2), float("nan"), **kw), torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = loca.alloc_workspace(loca.workspace_size(loca.LOCA_OP_LOWRANK_TRUNCATE, 1, 0, d, 2, r_a=r))
+    log("truncation of two equal values", r)
+    loca.loca_lowrank_truncate(m.contiguous(), b.contiguous(), r, a_o, b_o, sig, info, ws)
+    A, B = a_o[0].double().cpu().numpy(), b_o[0].double().cpu().numpy()
+    W = m[0].double().cpu().numpy() @ b[0].double().cpu().numpy()
+    assert np.abs(A @ A.T - np.eye(r)).max() < 1e-6 and np.abs(sig.cpu().numpy() - 1.0).max() < 1e-6
+    Wr = (B @ A).T  # A's rows lie in W's column space, B = W^T A^T
+    assert np.linalg.norm(B - W.T @ A.T) < 1e-6 and (r == 1 or np.linalg.norm(Wr - W) < 1e-6)
     assert not info.any()
 
 
